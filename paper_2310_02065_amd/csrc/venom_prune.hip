@@ -34,6 +34,39 @@ __device__ __forceinline__ unsigned magnitude_key(uint16_t bits) {
   return a > 0x7c00u ? 0x7c00u : a;
 }
 
+// The two largest magnitudes among a row's four selected entries `w` (smaller position on ties) and
+// where they sit.
+__device__ __forceinline__ void pick_two(const uint16_t (&w)[kSelCols], int& p0, int& p1) {
+  unsigned key[kSelCols];
+#pragma unroll
+  for (int p = 0; p < kSelCols; ++p) key[p] = magnitude_key(w[p]);
+  p0 = 0;
+  unsigned k0 = key[0];
+#pragma unroll
+  for (int p = 1; p < kSelCols; ++p) if (key[p] > k0) { p0 = p; k0 = key[p]; }
+  p1 = p0 == 0 ? 1 : 0;
+  unsigned k1 = p0 == 0 ? key[1] : key[0];
+#pragma unroll
+  for (int p = 1; p < kSelCols; ++p) if (p != p0 && key[p] > k1) { p1 = p; k1 = key[p]; }
+}
+
+// Mask bytes of one row and group: 1 at columns c0 and c1, 0 elsewhere, with words of `mask_word` bytes.
+__device__ __forceinline__ void write_mask(uint8_t* mrow, int M, int mask_word, int c0, int c1) {
+  auto word4 = [&](int j) {   // mask bytes of columns j .. j+3
+    return ((unsigned)(c0 - j) < 4u ? 1u << (8 * (c0 - j)) : 0u) | ((unsigned)(c1 - j) < 4u ? 1u << (8 * (c1 - j)) : 0u);
+  };
+  if (mask_word == 16) {
+    for (int j = 0; j < M; j += 16)
+      *reinterpret_cast<uint4*>(mrow + j) = make_uint4(word4(j), word4(j + 4), word4(j + 8), word4(j + 12));
+  } else if (mask_word == 8) {
+    for (int j = 0; j < M; j += 8) *reinterpret_cast<uint2*>(mrow + j) = make_uint2(word4(j), word4(j + 4));
+  } else if (mask_word == 4) {
+    for (int j = 0; j < M; j += 4) *reinterpret_cast<unsigned*>(mrow + j) = word4(j);
+  } else {
+    for (int c = 0; c < M; ++c) mrow[c] = (c == c0 || c == c1) ? 1 : 0;
+  }
+}
+
 // One workgroup per (block row b, chunk of `gpw` groups): V rows x gpw*M columns.
 //   phase 1: column masses into LDS (64-bit integer adds), the block's total mass.  A thread owns
 //            8 neighbouring columns (one 16-byte load) and a slice of the rows, sums in registers
@@ -118,35 +151,10 @@ __global__ void __launch_bounds__(256) prune_kernel(const uint16_t* __restrict__
     const int v = i / ng, t = i % ng;
     const int64_t base = (b * V + v) * lda + (g0 + t) * M;
     uint16_t w[kSelCols];
-    unsigned key[kSelCols];
-    for (int p = 0; p < kSelCols; ++p) { w[p] = A[base + sel[t][p]]; key[p] = magnitude_key(w[p]); }
-    int p0 = 0;
-    for (int p = 1; p < kSelCols; ++p) if (key[p] > key[p0]) p0 = p;
-    int p1 = p0 == 0 ? 1 : 0;
-    for (int p = 0; p < kSelCols; ++p) if (p != p0 && key[p] > key[p1]) p1 = p;
-    uint8_t* mrow = mask + (b * V + v) * ldm + (g0 + t) * M;
-    const int c0 = sel[t][p0], c1 = sel[t][p1];
-    auto word8 = [&](int j) {   // mask bytes of columns j .. j+7
-      return ((unsigned)(c0 - j) < 8u ? 1ull << (8 * (c0 - j)) : 0ull) | ((unsigned)(c1 - j) < 8u ? 1ull << (8 * (c1 - j)) : 0ull);
-    };
-    if (mask_word == 16) {
-      for (int j = 0; j < M; j += 16) {
-        const unsigned long long lo = word8(j), hi = word8(j + 8);
-        *reinterpret_cast<uint4*>(mrow + j) = make_uint4((unsigned)lo, (unsigned)(lo >> 32), (unsigned)hi, (unsigned)(hi >> 32));
-      }
-    } else if (mask_word == 8) {
-      for (int j = 0; j < M; j += 8) {
-        *reinterpret_cast<unsigned long long*>(mrow + j) = word8(j);
-      }
-    } else if (mask_word == 4) {
-      for (int j = 0; j < M; j += 4) {
-        const unsigned word = ((unsigned)(c0 - j) < 4u ? 1u << (8 * (c0 - j)) : 0u) |
-                              ((unsigned)(c1 - j) < 4u ? 1u << (8 * (c1 - j)) : 0u);
-        *reinterpret_cast<unsigned*>(mrow + j) = word;
-      }
-    } else {
-      for (int c = 0; c < M; ++c) mrow[c] = (c == c0 || c == c1) ? 1 : 0;
-    }
+    for (int p = 0; p < kSelCols; ++p) w[p] = A[base + sel[t][p]];
+    int p0, p1;
+    pick_two(w, p0, p1);
+    write_mask(mask + (b * V + v) * ldm + (g0 + t) * M, M, mask_word, sel[t][p0], sel[t][p1]);
     my_kept += magnitude_units(w[p0]) + magnitude_units(w[p1]);
   }
   if (my_kept) atomicAdd(&wg_kept, my_kept);
@@ -157,14 +165,198 @@ __global__ void __launch_bounds__(256) prune_kernel(const uint16_t* __restrict__
   }
 }
 
+// Sums of magnitudes in a double that starts at 2^28: every magnitude is a multiple of 2^-24 and a
+// sum stays below 2^28 (at most kTileMaxV of at most 2^16), so the sum's unit in the last place is 2^-24, no
+// addition rounds, and the bits above those of 2^28 are the sum in units of 2^-24.  Three full-rate
+// instructions per element (convert, clamp, widen) and an addition, where the integer form
+// (decompose, 64-bit shift, 64-bit add) takes a dozen.
+constexpr double kMassBias = 268435456.0;        // 2^28
+constexpr int kTileMaxV = 2048;
+__device__ __forceinline__ double magnitude(uint16_t bits) {
+  const float x = (float)__builtin_bit_cast(_Float16, bits);
+  return (double)fminf(fabsf(x), 65536.f);        // Inf and NaN: 2^16 = 2^40 units
+}
+__device__ __forceinline__ unsigned long long mass_units(double biased) {
+  return __builtin_bit_cast(unsigned long long, biased) - __builtin_bit_cast(unsigned long long, kMassBias);
+}
+
+// The same pruning with the block's tile (V rows x `gpw` groups) held in LDS, so that the matrix is
+// read once, in 16-byte pieces, and the second pass (4 scattered 2-byte reads per row and group)
+// stays on chip.  Column choice: for M up to 64 a thread per column counts the columns that beat
+// its own (all threads of a group read the same masses: broadcasts), above that a wave per group
+// takes the maximum four times.
+// Bound by memory: 49152 x 12288 at V = 128, M = 32 takes 0.37 ms, 4.9 TB/s of the 1.8 GB read and written (a
+// copy reaches 5.1); prune_kernel takes 0.55 ms there.  Tiles of 128 columns x 128 rows (35 KB), so that
+// four workgroups share a compute unit and one's loads run under the others' second passes.
+// Needs V <= kTileMaxV and the tile within kTileLds; prune_kernel above takes the rest.
+constexpr int kTileLds = 64 * 1024;
+constexpr int kTileMaxGroups = 64;
+__host__ __device__ constexpr int tile_pitch(int cols) { return (cols * 2 + 15) / 16 * 16 + 16; }
+constexpr int64_t tile_lds(int V, int cols) { return (int64_t)V * tile_pitch(cols) + 8 * cols; }
+
+__global__ void __launch_bounds__(256) prune_tile_kernel(const uint16_t* __restrict__ A, int64_t lda, int V, int M,
+                                                         int64_t G, int gpw, int vec_ok, int mask_word,
+                                                         uint8_t* __restrict__ mask, int64_t ldm,
+                                                         unsigned long long* __restrict__ kept_mass,
+                                                         unsigned long long* __restrict__ total_mass) {
+  extern __shared__ __attribute__((aligned(16))) char tile[];      // [row][pitch], then the column masses
+  __shared__ int sel[kTileMaxGroups][kSelCols];                     // by rank, then ascending
+  __shared__ unsigned long long wg_total, wg_kept;
+  const int64_t b = blockIdx.y, g0 = (int64_t)blockIdx.x * gpw;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int ng = (int)((G - g0) < gpw ? (G - g0) : gpw);
+  const int span = ng * M;
+  const int pitch = tile_pitch(gpw * M);
+  unsigned long long* mass = reinterpret_cast<unsigned long long*>(tile + V * pitch);
+  const uint16_t* blk = A + b * V * lda + g0 * M;
+
+  for (int i = tid; i < span; i += 256) mass[i] = 0;
+  if (tid == 0) { wg_total = 0; wg_kept = 0; }
+  __syncthreads();
+  unsigned long long my_total = 0;
+  const int units = vec_ok ? span / 8 : 0;         // 8-column units: at most 128
+  if (units > 0) {
+    const int slices = 256 / units, u = tid % units, slice = tid / units;   // row slices working side by side
+    if (slice < slices) {
+      double m8[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) m8[e] = kMassBias;
+      constexpr int NL = 8;                        // loads in flight per thread
+      for (int v0 = slice; v0 < V; v0 += NL * slices) {
+        uint4 w[NL];
+#pragma unroll
+        for (int j = 0; j < NL; ++j) {
+          const int v = v0 + j * slices;
+          w[j] = v < V ? *reinterpret_cast<const uint4*>(blk + (int64_t)v * lda + 8 * u) : make_uint4(0, 0, 0, 0);
+        }
+#pragma unroll
+        for (int j = 0; j < NL; ++j) {
+          const int v = v0 + j * slices;
+          if (v < V) *reinterpret_cast<uint4*>(tile + v * pitch + u * 16) = w[j];
+          const uint32_t ws[4] = {w[j].x, w[j].y, w[j].z, w[j].w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            m8[2 * e] += magnitude((uint16_t)ws[e]);
+            m8[2 * e + 1] += magnitude((uint16_t)(ws[e] >> 16));
+          }
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const unsigned long long m = mass_units(m8[e]);
+        if (m) atomicAdd(&mass[8 * u + e], m);
+        my_total += m;
+      }
+    }
+  }
+  const int tail0 = units * 8, tail = span - tail0;  // columns not covered above
+  for (int i = tid; i < V * tail; i += 256) {
+    const int v = i / tail, c = tail0 + i % tail;
+    const uint16_t w = blk[(int64_t)v * lda + c];
+    *reinterpret_cast<uint16_t*>(tile + v * pitch + c * 2) = w;
+    const unsigned long long m = magnitude_units(w);
+    if (m) atomicAdd(&mass[c], m);
+    my_total += m;
+  }
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) my_total += __shfl_xor(my_total, s);
+  if (lane == 0 && my_total) atomicAdd(&wg_total, my_total);
+  __syncthreads();
+  // largest mass first, smaller index on ties
+  if (M <= 64) {
+    for (int c = tid; c < span; c += 256) {
+      const int t = c / M, own = c - t * M;
+      const unsigned long long* mg = mass + t * M;
+      const unsigned long long mine = mg[own];
+      int rank = 0;
+#pragma unroll 4
+      for (int j = 0; j < M; ++j) rank += mg[j] > mine || (mg[j] == mine && j < own);
+      if (rank < kSelCols) sel[t][rank] = own;
+    }
+  } else {
+    for (int t = tid >> 6; t < ng; t += 4) {
+      int s[kSelCols] = {-1, -1, -1, -1};
+#pragma unroll
+      for (int k = 0; k < kSelCols; ++k) {
+        unsigned long long best = 0;
+        int at = M;                                // M: nothing seen yet
+        for (int c = lane; c < M; c += 64) {
+          const unsigned long long m = mass[t * M + c];
+          const bool taken = c == s[0] || c == s[1] || c == s[2];
+          if (!taken && (at == M || m > best)) { best = m; at = c; }
+        }
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) {
+          const unsigned long long om = __shfl_xor(best, d);
+          const int oa = __shfl_xor(at, d);
+          if (oa < M && (at == M || om > best || (om == best && oa < at))) { best = om; at = oa; }
+        }
+        s[k] = at;
+        if (lane == 0) sel[t][k] = at;
+      }
+    }
+  }
+  __syncthreads();
+  if (tid < ng) {                                  // ascending order
+    int s0 = sel[tid][0], s1 = sel[tid][1], s2 = sel[tid][2], s3 = sel[tid][3];
+    auto order = [](int& x, int& y) { const int lo = x < y ? x : y, hi = x < y ? y : x; x = lo; y = hi; };
+    order(s0, s1); order(s2, s3); order(s0, s2); order(s1, s3); order(s1, s2);
+    sel[tid][0] = s0; sel[tid][1] = s1; sel[tid][2] = s2; sel[tid][3] = s3;
+  }
+  __syncthreads();
+  double my_kept = kMassBias;
+  for (int i = tid; i < V * ng; i += 256) {
+    const int v = i / ng, t = i - v * ng;
+    uint16_t w[kSelCols];
+    int c[kSelCols];
+#pragma unroll
+    for (int p = 0; p < kSelCols; ++p) {
+      c[p] = sel[t][p];
+      w[p] = *reinterpret_cast<const uint16_t*>(tile + v * pitch + (t * M + c[p]) * 2);
+    }
+    int p0, p1;
+    pick_two(w, p0, p1);
+    int c0 = c[0], c1 = c[0];
+    uint16_t w0 = w[0], w1 = w[0];
+#pragma unroll
+    for (int p = 1; p < kSelCols; ++p) {
+      if (p == p0) { c0 = c[p]; w0 = w[p]; }
+      if (p == p1) { c1 = c[p]; w1 = w[p]; }
+    }
+    write_mask(mask + (b * V + v) * ldm + (g0 + t) * M, M, mask_word, c0, c1);
+    my_kept += magnitude(w0) + magnitude(w1);
+  }
+  unsigned long long kept = mass_units(my_kept);
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) kept += __shfl_xor(kept, s);
+  if (lane == 0 && kept) atomicAdd(&wg_kept, kept);
+  __syncthreads();
+  if (tid == 0) {
+    if (total_mass && wg_total) atomicAdd(&total_mass[b], wg_total);
+    if (kept_mass && wg_kept) atomicAdd(&kept_mass[b], wg_kept);
+  }
+}
+
+// Groups per workgroup of prune_tile_kernel, 0 if the shape is not its: rows of 256 bytes, in whole
+// 16-byte pieces (which at odd M takes several groups); fewer where four tiles would not share a compute unit.
+static int tile_groups(int V, int M) {
+  if (V > kTileMaxV) return 0;
+  const int whole = M % 8 == 0 ? 1 : M % 4 == 0 ? 2 : M % 2 == 0 ? 4 : 8;
+  int n = (128 + M * whole - 1) / (M * whole);     // in units of `whole` groups
+  while (n > 1 && tile_lds(V, n * whole * M) > 38 * 1024) --n;
+  const int gpw = n * whole;
+  return tile_lds(V, gpw * M) <= kTileLds - 2048 && gpw * M <= kPruneMaxCols && gpw <= kTileMaxGroups ? gpw : 0;
+}
+
 hipError_t launch_prune(const uint16_t* A, int64_t lda, int64_t R, int64_t K, int V, int M, uint8_t* mask, int64_t ldm,
                         unsigned long long* kept_mass, unsigned long long* total_mass, hipStream_t st) {
   const int64_t Rb = R / V, G = K / M;
   if (kept_mass || total_mass)
     hipLaunchKernelGGL(zero_u64_kernel, dim3((unsigned)((Rb + 255) / 256)), dim3(256), 0, st, kept_mass, total_mass, Rb);
   if (Rb == 0 || G == 0) return hipGetLastError();
-  int gpw = kPruneMaxCols / M;
-  if (gpw > kStepGroups) gpw = kStepGroups;
+  const int tiled = tile_groups(V, M);
+  int gpw = tiled > 0 ? tiled : kPruneMaxCols / M;
+  if (tiled == 0 && gpw > kStepGroups) gpw = kStepGroups;
   if (gpw < 1) gpw = 1;
   const int64_t chunks = (G + gpw - 1) / gpw;
   // wide loads need every chunk of every row of A to start on a 16-byte boundary
@@ -173,8 +365,12 @@ hipError_t launch_prune(const uint16_t* A, int64_t lda, int64_t R, int64_t K, in
   const uintptr_t ma = reinterpret_cast<uintptr_t>(mask);
   const int mask_word = (M % 16 == 0 && ldm % 16 == 0 && ma % 16 == 0) ? 16 : (M % 8 == 0 && ldm % 8 == 0 && ma % 8 == 0) ? 8
                         : (M % 4 == 0 && ldm % 4 == 0 && ma % 4 == 0) ? 4 : 1;
-  hipLaunchKernelGGL(prune_kernel, dim3((unsigned)chunks, (unsigned)Rb), dim3(256), 0, st, A, lda, V, M, G, gpw, vec_ok,
-                     mask_word, mask, ldm, kept_mass, total_mass);
+  if (tiled > 0)
+    hipLaunchKernelGGL(prune_tile_kernel, dim3((unsigned)chunks, (unsigned)Rb), dim3(256), (size_t)tile_lds(V, gpw * M), st,
+                       A, lda, V, M, G, gpw, vec_ok, mask_word, mask, ldm, kept_mass, total_mass);
+  else
+    hipLaunchKernelGGL(prune_kernel, dim3((unsigned)chunks, (unsigned)Rb), dim3(256), 0, st, A, lda, V, M, G, gpw, vec_ok,
+                       mask_word, mask, ldm, kept_mass, total_mass);
   return hipGetLastError();
 }
 
