@@ -107,9 +107,9 @@ venom_status_t venom_compress(const void* A_f16_dev, int64_t lda, const uint8_t*
   hipStream_t st = static_cast<hipStream_t>(stream);
   hipError_t e = venom::launch_compress(static_cast<const uint16_t*>(A_f16_dev), lda, mask_dev, ldm, *h, st);
   unsigned long long key = ~0ull;
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(&key, h->ws + h->lay.off_status, sizeof(key), hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  if (e == hipSuccess)   // returns when the word is here: one wait, where an asynchronous copy into this frame and a
+                         // synchronisation are two
+    e = hipMemcpyWithStream(&key, h->ws + h->lay.off_status, sizeof(key), hipMemcpyDeviceToHost, st);
   if (e != hipSuccess) { delete h; return VENOM_ERR_HIP; }
   if (key != ~0ull) {
     const int64_t G = h->lay.G;
@@ -123,8 +123,6 @@ venom_status_t venom_compress(const void* A_f16_dev, int64_t lda, const uint8_t*
     delete h;
     return row_rule ? VENOM_ERR_MASK_ROW : VENOM_ERR_MASK_COLS;
   }
-  e = venom::launch_pack(*h, st);
-  if (e != hipSuccess) { delete h; return VENOM_ERR_HIP; }
   *out = h;
   return VENOM_OK;
 }
@@ -144,18 +142,11 @@ venom_status_t venom_import(const uint16_t* values_dev, const uint16_t* columns_
   hipStream_t st = static_cast<hipStream_t>(stream);
   hipError_t e = hipSuccess;
   if (R > 0 && K > 0) {
-    e = hipMemcpyAsync(h->ws + L.off_values, values_dev, (size_t)R * L.G * 4, hipMemcpyDeviceToDevice, st);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(h->ws + L.off_columns, columns_dev, (size_t)L.Rb * L.G * 8, hipMemcpyDeviceToDevice, st);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(h->ws + L.off_meta, meta_dev, (size_t)R * L.W * 4, hipMemcpyDeviceToDevice, st);
-    // the arrays come from outside: nothing is packed (or later gathered) from malformed ones
+    // the arrays come from outside: no handle to malformed ones leaves this function
     unsigned long long word = 0;
-    if (e == hipSuccess) e = venom::launch_validate(*h, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(&word, h->ws + L.off_status, sizeof(word), hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    e = venom::launch_import(values_dev, columns_dev, meta_dev, *h, st);
+    if (e == hipSuccess) e = hipMemcpyWithStream(&word, h->ws + L.off_status, sizeof(word), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess && word != ~0ull) { delete h; return VENOM_ERR_INVALID_ARG; }
-    if (e == hipSuccess) e = venom::launch_pack(*h, st);
   }
   if (e != hipSuccess) { delete h; return VENOM_ERR_HIP; }
   *out = h;

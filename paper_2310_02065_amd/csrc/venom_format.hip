@@ -38,214 +38,438 @@ constexpr unsigned long long kNoViolation = ~0ull;
 
 __global__ void init_status_kernel(unsigned long long* status) { *status = kNoViolation; }
 
-// One workgroup per (block row b, metadata word w) = V rows x 8 groups x M columns.
-//   phase 1: which columns of each group are used by any row of the block (coalesced mask read)
-//   phase 2: eight threads pick the 4 columns of their group: the used ones ascending, padded with
-//            the smallest unused ids, sorted
-//   phase 3: one thread per row: positions kept inside the 4 selected columns, padded with the
-//            smallest unused positions, sorted -> nibble; values copied as bits
-constexpr int kMaxM = 1024;
-
-__global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restrict__ A, int64_t lda,
-                                                       const uint8_t* __restrict__ mask, int64_t ldm, int V, int M,
-                                                       int64_t G, int64_t W, int vec_ok,
-                                                       uint32_t* __restrict__ values, uint16_t* __restrict__ columns,
-                                                       uint32_t* __restrict__ meta, unsigned long long* status) {
-  __shared__ uint8_t used[kStepGroups][kMaxM];
-  __shared__ int sel[kStepGroups][kSelCols];
-  __shared__ int cols_ok[kStepGroups];
-  const int64_t w = blockIdx.x, b = blockIdx.y;
-  const int tid = threadIdx.x;
-  const int64_t g0 = w * 8;
-  const int ng = (int)((G - g0) < 8 ? (G - g0) : 8);  // groups of this word that exist
-  const int span = ng * M;
-
-  for (int i = tid; i < kStepGroups * M; i += blockDim.x) used[i / M][i % M] = 0;
-  __syncthreads();
-  // a thread owns 8 neighbouring columns (one 8-byte mask load per row) and a slice of the rows;
-  // columns past the last multiple of 8 and unaligned masks take the byte loop
-  const int units = vec_ok ? span / 8 : 0;
-  if (units > 0) {
-    const int slices = blockDim.x / units > 0 ? blockDim.x / units : 1;
-    for (int u0 = 0; u0 < units; u0 += blockDim.x) {
-      const int u = u0 + (slices > 1 ? tid % units : tid);
-      const int slice = slices > 1 ? tid / units : 0;
-      if (u < units && slice < slices) {
-        unsigned long long seen = 0;               // OR of the 8 mask bytes over this thread's rows
-        for (int v = slice; v < V; v += slices)
-          seen |= *reinterpret_cast<const unsigned long long*>(mask + (b * V + v) * ldm + g0 * M + 8 * u);
-        for (int e = 0; e < 8; ++e)
-          if ((seen >> (8 * e)) & 0xffull) { const int c = 8 * u + e; used[c / M][c % M] = 1; }
-      }
-    }
-  }
-  const int tail0 = units * 8, tail = span - tail0;
-  for (int64_t i = tid; i < (int64_t)V * tail; i += blockDim.x) {
-    const int v = (int)(i / tail), c = tail0 + (int)(i % tail);
-    if (mask[(b * V + v) * ldm + g0 * M + c]) used[c / M][c % M] = 1;  // benign: every writer stores 1
-  }
-  __syncthreads();
-  if (tid < ng) {
-    int cnt = 0, s[kSelCols];
-    for (int c = 0; c < M; ++c)
-      if (used[tid][c]) { if (cnt < kSelCols) s[cnt] = c; ++cnt; }
-    const bool ok = cnt <= kSelCols;
-    if (!ok) atomicMin(status, ((unsigned long long)(b * G + g0 + tid) << 24));
-    // pad with the smallest unused ids, keeping the list sorted
-    for (int c = 0; cnt < kSelCols && c < M; ++c) {
-      if (used[tid][c]) continue;
-      int pos = cnt;
-      while (pos > 0 && s[pos - 1] > c) { s[pos] = s[pos - 1]; --pos; }
-      s[pos] = c; ++cnt;
-    }
-    cols_ok[tid] = ok;
-    for (int p = 0; p < kSelCols; ++p) {
-      sel[tid][p] = s[p];
-      columns[((b * G) + g0 + tid) * kSelCols + p] = (uint16_t)s[p];
-    }
-  }
-  __syncthreads();
-  // one thread per (row, group): eight neighbouring lanes hold the eight nibbles of a metadata word
-  // and combine them with three lane exchanges
-  for (int i = tid; i < ((V * 8 + 255) / 256) * 256; i += blockDim.x) {
-    const int v = i >> 3, t = i & 7;
-    uint32_t nib = 0;
-    if (v < V && t < ng) {
-      const int64_t r = b * V + v;
-      const int64_t base = g0 + t;
-      const uint8_t* mrow = mask + r * ldm + base * M;
-      int kept[kSelCols], nk = 0;
-      for (int p = 0; p < kSelCols; ++p) { kept[p] = mrow[sel[t][p]] != 0; nk += kept[p]; }
-      if (cols_ok[t] && nk > 2)
-        atomicMin(status, ((unsigned long long)(b * G + base) << 24) | (1ull << 23) | (unsigned long long)v);
-      // first two kept positions, then the smallest unused ones, sorted
-      int p0 = -1, p1 = -1;
-      for (int p = 0; p < kSelCols; ++p)
-        if (kept[p]) { if (p0 < 0) p0 = p; else if (p1 < 0) p1 = p; }
-      bool k0 = p0 >= 0, k1 = p1 >= 0;
-      if (!k0) { p0 = 0; p1 = 1; }                     // nothing kept: positions (0, 1)
-      else if (!k1) {                                   // one kept: add the smallest other position
-        if (p0 == 0) { p1 = 1; }
-        else { p1 = p0; p0 = 0; k1 = true; k0 = false; }
-      }
-      const uint16_t* arow = A + r * lda + base * M;
-      const uint32_t v0 = k0 ? arow[sel[t][p0]] : 0u;
-      const uint32_t v1 = k1 ? arow[sel[t][p1]] : 0u;
-      values[r * G + base] = v0 | (v1 << 16);
-      nib = (uint32_t)(p0 | (p1 << 2)) << (4 * t);
-    }
-    nib |= __shfl_xor(nib, 1);
-    nib |= __shfl_xor(nib, 2);
-    nib |= __shfl_xor(nib, 4);
-    if (v < V && t == 0) meta[(b * V + v) * W + w] = nib;
-  }
-}
-
-// Absolute row of B for every gathered row: [R/V][steps][32], entry 4*t + p of a step is
-// (8*step + t)*M + column_loc[p]; groups past the end point at row 0 (their values are zero).
-// (Vp, V: block heights of the packed copy and of the canonical arrays; they differ only at M = 4,
-// where all canonical block rows hold the same column ids.)
-__global__ void __launch_bounds__(256) pack_rowidx_kernel(const uint16_t* __restrict__ columns, int64_t G, int M,
-                                                          int64_t steps, int64_t total, int Vp, int V,
-                                                          int32_t* __restrict__ rowidx) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  const int rho = (int)(idx % kStepRows);
-  const int64_t s = (idx / kStepRows) % steps, b = idx / kStepRows / steps;
-  const int64_t g = s * 8 + rho / 4;
-  const int64_t cb = b * Vp / V;                   // canonical block row that holds the packed block's first row
-  rowidx[idx] = (g < G) ? (int32_t)(g * M + columns[(cb * G + g) * kSelCols + (rho % 4)]) : 0;
-}
-
-// canonical -> the kernel's packed A stream.  One record per (block row, k-step):
+// ---------------------------------------------------------------------------------------------
+// Where one (row, group) entry goes: the canonical arrays and, if the product kernel serves this
+// shape, its packed copies.  A packed record of one (block row, k-step):
 //   [V/32 tiles x 1024 B of values][512 B tail]
 // values of a tile: 64 lanes x 8 halfs; lane = 32*h + i holds row 32*tile + i and the two kept
 // values of groups 8*step + 4*h .. +3 -- the A operand of v_smfmac_f32_32x32x32_f16.
 // tail: 64 lanes x 4 x uint16, entry [lane][tile] = the lane's four canonical nibbles for that tile
 //       (a lane reads its 8 bytes with one LDS load; the matrix instruction picks the 16-bit field
-//       with its ABID operand).
-// One thread per lane-slot: (block row, step, tile, lane) for tile < vt; tile == vt clears the
-// index words of the tiles that do not exist.
-__global__ void __launch_bounds__(256) pack_arec_kernel(const uint32_t* __restrict__ values,
-                                                        const uint32_t* __restrict__ meta, int64_t G, int64_t W,
-                                                        int64_t steps, int vt, int V, int64_t total,
-                                                        char* __restrict__ arec) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  const int lane = (int)(idx % 64);
-  const int tile = (int)((idx / 64) % (vt + 1));
-  const int64_t s = (idx / 64 / (vt + 1)) % steps, b = idx / 64 / (vt + 1) / steps;
-  char* rec = arec + (b * steps + s) * ((int64_t)vt * kTileValBytes + kTailBytes);
-  char* tail = rec + vt * kTileValBytes;
-  if (tile == vt) {
-    for (int t = vt; t < kMaxTiles; ++t) reinterpret_cast<uint16_t*>(tail)[lane * kMaxTiles + t] = 0;
-    return;
-  }
-  const int64_t r = b * V + tile * kTileRows + (lane % 32);
-  const int h = lane / 32;
-  const int64_t g = s * 8 + 4 * h;
-  uint32_t v[4];
-  for (int e = 0; e < 4; ++e) v[e] = (g + e < G) ? values[r * G + g + e] : 0u;
-  reinterpret_cast<uint4*>(rec + tile * kTileValBytes)[lane] = make_uint4(v[0], v[1], v[2], v[3]);
-  const uint32_t word = (s < W) ? (meta[r * W + s] >> (16 * h)) & 0xffffu : 0u;
-  reinterpret_cast<uint16_t*>(tail)[lane * kMaxTiles + tile] = (uint16_t)word;
+//       with its ABID operand); the entries of tiles that do not exist are zero.
+// rowidx: absolute row of B of every gathered row, [block row][k-step][32], entry 4*t + p of a step
+// is (8*step + t)*M + column_loc[p]; groups past the end point at row 0 (their values are zero).
+// The block height Vp of the packed copy differs from V only at M = 4, where all canonical block
+// rows hold the same column ids.
+struct FormatDst {
+  uint32_t* values;
+  uint16_t* columns;
+  uint32_t* meta;
+  char* arec;              // null: no packed copies
+  int32_t* rowidx;
+  int64_t G, W;            // groups per row, metadata words per row = k-steps
+  int V, Vp, vt, M;
+};
+
+// Row `v` of canonical block row `cb` in the packed copy: its block row and the row inside it.
+__device__ __forceinline__ void packed_row(const FormatDst& d, int64_t cb, int v, int64_t& rb, int& rr) {
+  if (d.Vp == d.V) { rb = cb; rr = v; return; }
+  const int64_t r = cb * d.V + v;                // M = 4: blocks of 128 rows
+  rb = r / (kMaxTiles * kTileRows);
+  rr = (int)(r % (kMaxTiles * kTileRows));
 }
 
-// packed -> dense: one thread per output element.
-__global__ void __launch_bounds__(256) decompress_kernel(const char* __restrict__ arec,
-                                                         const int32_t* __restrict__ rowidx, int64_t R, int64_t K, int V,
-                                                         int M, int64_t steps, int vt, uint16_t* __restrict__ A,
-                                                         int64_t lda) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= R * K) return;
-  const int64_t r = idx / K, k = idx % K;
-  const int64_t g = k / M, s = g / 8, b = r / V;
-  const int t = (int)(g % 8), h = t / 4, ge = t % 4;
-  const int tile = (int)((r % V) / kTileRows);
-  const int lane = 32 * h + (int)(r % kTileRows);
-  const char* rec = arec + (b * steps + s) * ((int64_t)vt * kTileValBytes + kTailBytes);
-  const uint32_t word = reinterpret_cast<const uint16_t*>(rec + vt * kTileValBytes)[lane * kMaxTiles + tile];
-  const uint32_t nib = (word >> (4 * ge)) & 0xfu;
-  const int32_t* ri = rowidx + (b * steps + s) * kStepRows + 4 * t;
-  const uint16_t* pv = reinterpret_cast<const uint16_t*>(rec + tile * kTileValBytes) + lane * 8 + 2 * ge;
-  uint16_t out = 0;
-  if (ri[nib & 3] == k) out = pv[0];
-  if (ri[nib >> 2] == k) out = pv[1];
-  A[r * lda + k] = out;
+// Column ids of group g of block row cb, and the rows of B of group t of k-step w of packed block row rb.
+__device__ __forceinline__ void emit_columns(const FormatDst& d, int64_t cb, int64_t g, ushort4 c) {
+  *reinterpret_cast<ushort4*>(d.columns + (cb * d.G + g) * kSelCols) = c;
+}
+__device__ __forceinline__ void emit_rowidx(const FormatDst& d, int64_t rb, int64_t w, int t, ushort4 c) {
+  const int64_t g = w * 8 + t;
+  const int k0 = (int)(g * d.M);
+  *reinterpret_cast<int4*>(d.rowidx + (rb * d.W + w) * kStepRows + 4 * t) =
+      g < d.G ? make_int4(k0 + c.x, k0 + c.y, k0 + c.z, k0 + c.w) : make_int4(0, 0, 0, 0);
+}
+// The index word of row rr in the record `rec`: half h of the row's metadata word, one 2-byte store (a row
+// of the first tile clears the fields of the tiles that do not exist).
+__device__ __forceinline__ void emit_index_field(const FormatDst& d, char* rec, int rr, int h, uint32_t word) {
+  const int tile = rr / kTileRows, i = rr % kTileRows;
+  uint16_t* tail = reinterpret_cast<uint16_t*>(rec + d.vt * kTileValBytes) + (32 * h + i) * kMaxTiles;
+  tail[tile] = (uint16_t)(word >> (16 * h));
+  if (tile == 0)
+    for (int e = d.vt; e < kMaxTiles; ++e) tail[e] = 0;
+}
+// The same for a whole lane 32*h + i at once, from the words of rows i, i+32, ...: one 8-byte store, where those
+// words are at hand (in LDS: compression gains 2 %; fetching them again, in the import, loses 10 %).
+__device__ __forceinline__ void emit_index(const FormatDst& d, char* rec, int i, int h, const uint32_t (&word)[kMaxTiles]) {
+  uint32_t o[2] = {0, 0};
+#pragma unroll
+  for (int e = 0; e < kMaxTiles; ++e) o[e / 2] |= ((word[e] >> (16 * h)) & 0xffffu) << (16 * (e % 2));
+  *reinterpret_cast<uint2*>(rec + d.vt * kTileValBytes + (32 * h + i) * 8) = make_uint2(o[0], o[1]);
 }
 
-// Imported canonical arrays are data from outside: one thread per (row, group) checks what the
-// gather and the matrix instruction rely on -- column ids strictly increasing and below M (rows of
-// the block's first row only), the two m-indices of a nibble ordered idx0 < idx1, unused nibbles of
-// the last metadata word zero.  Any offence sets the flag; nothing is gathered from such arrays.
-__global__ void __launch_bounds__(256) validate_kernel(const uint16_t* __restrict__ columns,
-                                                       const uint32_t* __restrict__ meta, int64_t R, int64_t G,
-                                                       int64_t W, int V, int M, unsigned long long* status) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= R * W * 8) return;
-  const int64_t r = idx / (W * 8), g = idx % (W * 8);
-  const uint32_t nib = (meta[r * W + g / 8] >> (4 * (g % 8))) & 0xfu;
-  bool bad = false;
-  if (g < G) {
-    bad = (nib & 3u) >= (nib >> 2);
-    if (r % V == 0) {
-      const uint16_t* c = columns + ((r / V) * G + g) * kSelCols;
-      bad = bad || !(c[0] < c[1] && c[1] < c[2] && c[2] < c[3] && c[3] < M);
+// The non-zero bytes of a word as four bits.
+__device__ __forceinline__ uint32_t nonzero_bits(uint32_t x) {
+  const uint32_t top = (((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) & 0x80808080u;   // bit 7 of every non-zero byte
+  return ((top >> 7) * 0x10204080u) >> 28;       // byte e's flag to bit e
+}
+
+constexpr int kMaxM = 1024;
+constexpr int kCompressWords = 4;                // most metadata words (8 groups each) one workgroup takes
+constexpr int kCompressBits = 32 * 1024;         // most LDS for the mask bits of a workgroup's rows
+
+// bytes per row of mask bits in LDS, with a word of padding
+__host__ __device__ constexpr int bits_pitch(int wpw, int M) { return (wpw * M + 3) / 4 * 4 + 4; }
+
+// Dense + mask -> canonical arrays and packed copies.  One workgroup per (block row b, `wpw` metadata
+// words) = V rows x 8*wpw groups x M columns.
+//   phase 1: the mask is read once, UB bytes at a time (16, 8 or, unaligned, 1), and kept in LDS as one bit
+//            per column and row; the bits of all rows together say which columns the block uses
+//   phase 2: one thread per group picks the 4 columns: the used ones ascending, padded with the
+//            smallest unused ids, sorted
+//   phase 3: one thread per (row, group): positions kept inside the 4 selected columns, padded with
+//            the smallest unused positions, sorted -> nibble; values copied as bits; canonical and
+//            packed entries written together.  Four entries per thread are in flight at a time.
+// Bound by memory: 49152 x 12288 at M = 32 (0.6 GB of mask, 1.2 GB of A -- the two kept values of 32
+// touch every 64-byte sector -- and 0.17 GB written) takes 0.42 ms, 4.7 TB/s; it was 0.45 ms, and another
+// 0.08 ms to pack in a second pass, when phase 3 fetched the mask bytes again one by one.
+// bits_ok: the bits of V rows fit; otherwise (very tall blocks) phase 3 reads the mask again.
+template <int UB>
+__global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restrict__ A, int64_t lda,
+                                                       const uint8_t* __restrict__ mask, int64_t ldm, int wpw, int bits_ok,
+                                                       FormatDst d, unsigned long long* status) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t bits[];   // [row][pitch]
+  __shared__ uint32_t used[kCompressWords * 8 * kMaxM / 32 + 1];
+  __shared__ ushort4 sel[kCompressWords * 8];
+  __shared__ int cols_ok[kCompressWords * 8];
+  __shared__ uint32_t words[kCompressWords][kMaxTiles * kTileRows];   // metadata words, if the packed copy has blocks of V rows
+  const int V = d.V, M = d.M;
+  const int64_t b = blockIdx.y, w0 = (int64_t)blockIdx.x * wpw, g0 = w0 * 8;
+  const int tid = threadIdx.x;
+  const int nw = (int)((d.W - w0) < wpw ? (d.W - w0) : wpw);              // words of this workgroup that exist
+  const int ng = (int)((d.G - g0) < 8 * nw ? (d.G - g0) : 8 * nw);        // groups that exist
+  const int span = ng * M;
+  const int pitch = bits_pitch(wpw, M);
+  const uint8_t* mblk = mask + b * V * ldm + g0 * M;
+
+  const int units = UB > 1 ? span / UB : 0, tail0 = units * (UB > 1 ? UB : 0), tail = span - tail0;
+  for (int i = tid; i < (span + 31) / 32 + 1; i += 256) used[i] = 0;
+  if (bits_ok && tail > 0)                       // the columns of the byte loop are set bit by bit
+    for (int i = tid; i < V * pitch / 4; i += 256) reinterpret_cast<uint32_t*>(bits)[i] = 0;
+  __syncthreads();
+  if constexpr (UB > 1) {
+    const int slices = 256 / units > 0 ? 256 / units : 1;                 // row slices working side by side
+    for (int u0 = 0; u0 < units; u0 += 256) {                             // (more than 256 units: several sweeps)
+      const int u = u0 + (slices > 1 ? tid % units : tid);
+      const int slice = slices > 1 ? tid / units : 0;
+      if (u < units && slice < slices) {
+        uint32_t seen = 0;
+        const uint8_t* p = mblk + UB * u;
+        constexpr int NL = 8;                    // loads in flight per thread
+        for (int v0 = slice; v0 < V; v0 += NL * slices) {
+          uint32_t x[NL][UB / 4];
+#pragma unroll
+          for (int j = 0; j < NL; ++j) {
+            const int v = v0 + j * slices;
+#pragma unroll
+            for (int e = 0; e < UB / 4; ++e) x[j][e] = 0;
+            if (v < V) {
+              if constexpr (UB == 16) {
+                const uint4 q = *reinterpret_cast<const uint4*>(p + (int64_t)v * ldm);
+                x[j][0] = q.x; x[j][1] = q.y; x[j][2] = q.z; x[j][3] = q.w;
+              } else {
+                const uint2 q = *reinterpret_cast<const uint2*>(p + (int64_t)v * ldm);
+                x[j][0] = q.x; x[j][1] = q.y;
+              }
+            }
+          }
+#pragma unroll
+          for (int j = 0; j < NL; ++j) {
+            const int v = v0 + j * slices;
+            uint32_t m = 0;
+#pragma unroll
+            for (int e = 0; e < UB / 4; ++e) m |= nonzero_bits(x[j][e]) << (4 * e);
+            seen |= m;
+            if (bits_ok && v < V) {
+              if constexpr (UB == 16) *reinterpret_cast<uint16_t*>(bits + v * pitch + 2 * u) = (uint16_t)m;
+              else bits[v * pitch + u] = (uint8_t)m;
+            }
+          }
+        }
+        if (seen) atomicOr(&used[u * UB / 32], seen << (u * UB % 32));
+      }
     }
-  } else bad = nib != 0;
+  }
+  for (int64_t i = tid; i < (int64_t)V * tail; i += 256) {
+    const int v = (int)(i / tail), c = tail0 + (int)(i % tail);
+    if (mblk[(int64_t)v * ldm + c]) {
+      atomicOr(&used[c / 32], 1u << (c % 32));
+      if (bits_ok) atomicOr(reinterpret_cast<uint32_t*>(bits + v * pitch + c / 32 * 4), 1u << (c % 32));
+    }
+  }
+  __syncthreads();
+  if (tid < ng) {
+    int cnt = 0;
+    int s[kSelCols] = {0, 0, 0, 0};
+    auto bits32 = [&](int c) {                   // used flags of columns c .. c+31 of this group, zero past its end
+      const int o = tid * M + c;
+      const uint32_t x = (uint32_t)(((((unsigned long long)used[o / 32 + 1]) << 32) | used[o / 32]) >> (o % 32));
+      return M - c >= 32 ? x : x & ((1u << (M - c)) - 1u);
+    };
+    for (int c = 0; c < M; c += 32) {
+      uint32_t x = bits32(c);
+      int n = cnt;
+      cnt += __popc(x);
+      for (; x != 0 && n < kSelCols; ++n, x &= x - 1) {
+        const int id = c + __ffs(x) - 1;
+#pragma unroll
+        for (int p = 0; p < kSelCols; ++p) s[p] = p == n ? id : s[p];
+      }
+    }
+    const bool ok = cnt <= kSelCols;
+    if (!ok) atomicMin(status, ((unsigned long long)(b * d.G + g0 + tid) << 24));
+    // pad with the smallest unused ids, keeping the list sorted
+    for (int c = 0; cnt < kSelCols && c < M; ++c) {
+      if ((bits32(c) & 1u) != 0) continue;
+      int id = c;                                // bubble it into place
+#pragma unroll
+      for (int p = 0; p < kSelCols; ++p) {
+        if (p < cnt && s[p] > id) { const int x = s[p]; s[p] = id; id = x; }
+        else if (p == cnt) s[p] = id;
+      }
+      ++cnt;
+    }
+    cols_ok[tid] = ok;
+    sel[tid] = make_ushort4((uint16_t)s[0], (uint16_t)s[1], (uint16_t)s[2], (uint16_t)s[3]);
+  }
+  __syncthreads();
+  // one thread per (row, group): eight neighbouring lanes hold the eight nibbles of a metadata word
+  // and combine them with three lane exchanges
+  constexpr int NE = 4;                          // entries in flight per thread
+  const int64_t rec_bytes = (int64_t)d.vt * kTileValBytes + kTailBytes;
+  const int NG = 8 * nw;                         // lanes of a row (a multiple of 8)
+  const int total = V * NG;
+  for (int base = 0; base < total; base += 256 * NE) {
+    uint32_t v01[NE], nib[NE];
+#pragma unroll
+    for (int j = 0; j < NE; ++j) {
+      const int i = base + 256 * j + tid, v = i / NG, tg = i - v * NG;
+      nib[j] = 0; v01[j] = 0;
+      if (i < total && tg < ng) {
+        const ushort4 c4 = sel[tg];
+        const int c[kSelCols] = {c4.x, c4.y, c4.z, c4.w};
+        int kept = 0;                            // bit p: the row keeps selected column p
+#pragma unroll
+        for (int p = 0; p < kSelCols; ++p) {
+          const int col = tg * M + c[p];
+          const int k = bits_ok ? (bits[v * pitch + col / 8] >> (col % 8)) & 1 : mblk[(int64_t)v * ldm + col] != 0;
+          kept |= k << p;
+        }
+        if (cols_ok[tg] && __popc(kept) > 2)
+          atomicMin(status, ((unsigned long long)(b * d.G + g0 + tg) << 24) | (1ull << 23) | (unsigned long long)v);
+        // first two kept positions, then the smallest unused ones, sorted
+        int p0, p1;
+        bool k0 = true, k1 = true;
+        const int lo = __ffs(kept) - 1, rest = kept & (kept - 1);
+        if (kept == 0) { p0 = 0; p1 = 1; k0 = k1 = false; }     // nothing kept: positions (0, 1)
+        else if (rest != 0) { p0 = lo; p1 = __ffs(rest) - 1; }
+        else if (lo == 0) { p0 = 0; p1 = 1; k1 = false; }       // one kept: add the smallest other position
+        else { p0 = 0; p1 = lo; k0 = false; }
+        const uint16_t* arow = A + (b * V + v) * lda + (g0 + tg) * M;
+        const int c0 = p0 == 0 ? c[0] : p0 == 1 ? c[1] : c[2];
+        const int c1 = p1 == 1 ? c[1] : p1 == 2 ? c[2] : c[3];
+        const uint32_t a0 = k0 ? arow[c0] : 0u;
+        const uint32_t a1 = k1 ? arow[c1] : 0u;
+        v01[j] = a0 | (a1 << 16);
+        nib[j] = (uint32_t)(p0 | (p1 << 2)) << (4 * (tg & 7));
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < NE; ++j) {
+      const int i = base + 256 * j + tid, v = i / NG, tg = i - v * NG;
+      uint32_t word = nib[j];
+      word |= __shfl_xor(word, 1);
+      word |= __shfl_xor(word, 2);
+      word |= __shfl_xor(word, 4);
+      if (i < total) {
+        const int64_t w = w0 + (tg >> 3), g = g0 + tg, r = b * V + v;
+        const int t = tg & 7;
+        if (tg < ng) d.values[r * d.G + g] = v01[j];
+        if (t == 0) d.meta[r * d.W + w] = word;
+        if (v == 0 && tg < ng) emit_columns(d, b, g, sel[tg]);
+        if (d.arec != nullptr) {
+          int64_t rb;
+          int rr;
+          packed_row(d, b, v, rb, rr);
+          char* rec = d.arec + (rb * d.W + w) * rec_bytes;
+          const int h = t >> 2;
+          *reinterpret_cast<uint32_t*>(rec + (rr / kTileRows) * kTileValBytes + (32 * h + rr % kTileRows) * 16 + (t & 3) * 4) = v01[j];
+          if (t == 0 && d.Vp == d.V) words[tg >> 3][v] = word;
+          else if ((t & 3) == 0 && d.Vp != d.V) emit_index_field(d, rec, rr, h, word);   // (the packed block's other rows are elsewhere)
+          if (rr == 0) emit_rowidx(d, rb, w, t, tg < ng ? sel[tg] : make_ushort4(0, 0, 0, 0));
+        }
+      }
+    }
+  }
+  if (d.arec == nullptr || d.Vp != d.V) return;
+  __syncthreads();
+  for (int i = tid; i < nw * 64; i += 256) {
+    const int k = i / 64, l = i % 64;
+    uint32_t word[kMaxTiles];
+#pragma unroll
+    for (int e = 0; e < kMaxTiles; ++e) word[e] = e < d.vt ? words[k][32 * e + l % 32] : 0u;
+    emit_index(d, d.arec + (b * d.W + w0 + k) * rec_bytes, l % 32, l / 32, word);
+  }
+}
+
+// Canonical arrays from outside -> the workspace: checked, copied and packed in one pass (the handle
+// is only handed out if the check found nothing).  One thread per row and half metadata word = 4 groups: 16 bytes
+// of values, one 16-byte slot of the packed record.  A workgroup takes 32 rows x 4 words, so that it
+// reads rows of 128 bytes and completes the 128-byte lines of the packed records.
+// Checked is what the gather and the matrix instruction rely on -- column ids strictly increasing
+// and below M (once per block), the two m-indices of a nibble ordered idx0 < idx1, unused nibbles of
+// the last metadata word zero.
+// 8192 x 8192 at M = 8 (120 MB in and out): 28 us, 4.2 TB/s; three copies, the check and the packing by
+// themselves took 90 us.
+// aligned: rows of `values` and of its copy start on 16-byte boundaries.
+__global__ void __launch_bounds__(256) import_kernel(const uint32_t* __restrict__ values, const uint16_t* __restrict__ columns,
+                                                     const uint32_t* __restrict__ meta, int64_t R, int aligned, FormatDst d,
+                                                     unsigned long long* status) {
+  const int64_t wq = (d.W + 3) / 4;
+  const int64_t rblk = blockIdx.x / wq, wblk = blockIdx.x - rblk * wq;
+  const int u = threadIdx.x & 7, h = u & 1;        // eight lanes read 128 bytes of a row
+  const int64_t w = wblk * 4 + (u >> 1), r = rblk * 32 + (threadIdx.x >> 3);
+  if (w >= d.W || r >= R) return;
+  const int64_t cb0 = rblk * 32 / d.V;             // of the workgroup's first row: a scalar division
+  const int v0 = (int)(rblk * 32 - cb0 * d.V) + (int)(threadIdx.x >> 3);
+  const int down = v0 >= d.V ? v0 / d.V : 0;
+  const int64_t cb = cb0 + down;
+  const int v = v0 - down * d.V;
+  const int64_t g = w * 8 + 4 * h;
+  const int ng = g >= d.G ? 0 : d.G - g < 4 ? (int)(d.G - g) : 4;         // groups of the half word that exist
+  const uint32_t word = meta[r * d.W + w];
+  uint32_t x[4] = {0, 0, 0, 0};
+  const uint32_t* src = values + r * d.G + g;
+  uint32_t* dst = d.values + r * d.G + g;
+  if (aligned && ng == 4) {
+    const uint4 q = *reinterpret_cast<const uint4*>(src);
+    x[0] = q.x; x[1] = q.y; x[2] = q.z; x[3] = q.w;
+    *reinterpret_cast<uint4*>(dst) = q;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (e < ng) { x[e] = src[e]; dst[e] = x[e]; }
+  }
+  if (h == 0) d.meta[r * d.W + w] = word;
+  bool bad = false;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const uint32_t nib = (word >> (16 * h + 4 * e)) & 0xfu;
+    bad = bad || (e < ng ? (nib & 3u) >= (nib >> 2) : nib != 0);
+  }
+  int64_t rb = 0;
+  int rr = 1;
+  if (d.arec != nullptr) {
+    packed_row(d, cb, v, rb, rr);
+    char* rec = d.arec + (rb * d.W + w) * ((int64_t)d.vt * kTileValBytes + kTailBytes);
+    *reinterpret_cast<uint4*>(rec + (rr / kTileRows) * kTileValBytes + (32 * h + rr % kTileRows) * 16) =
+        make_uint4(x[0], x[1], x[2], x[3]);
+    emit_index_field(d, rec, rr, h, word);
+  }
+  if (v == 0 || rr == 0) {
+    for (int e = 0; e < 4; ++e) {
+      ushort4 c = make_ushort4(0, 0, 0, 0);
+      if (e < ng) {
+        const uint16_t* cp = columns + (cb * d.G + g + e) * kSelCols;
+        c = make_ushort4(cp[0], cp[1], cp[2], cp[3]);
+        bad = bad || !(c.x < c.y && c.y < c.z && c.z < c.w && c.w < d.M);
+        if (v == 0) emit_columns(d, cb, g + e, c);
+      }
+      if (rr == 0) emit_rowidx(d, rb, w, 4 * h + e, c);
+    }
+  }
   if (bad) *status = 0;
 }
 
-static inline unsigned blocks_for(int64_t total) { return (unsigned)((total + 255) / 256); }
+// Exact quotients of values below 2^31 by a divisor of at least 2: n / divisor = n * mul >> (31 + shift).
+struct Divisor { uint32_t mul; int shift; };
+static Divisor make_divisor(uint32_t d) {
+  int l = 1;
+  while ((1ull << l) < d) ++l;
+  return {(uint32_t)(((1ull << (31 + l)) + d - 1) / d), l};
+}
+__device__ __forceinline__ uint32_t divide(uint32_t n, Divisor d) { return __umulhi(n, d.mul) >> (d.shift - 1); }
 
-hipError_t launch_validate(const venom_handle& h, hipStream_t st) {
+// packed -> dense.  A workgroup expands 32 rows (one tile of a block row) x 256 columns, a thread 8
+// neighbouring columns of a row at a time (one 16-byte store where the output allows it): for every
+// group they touch -- one where M is a multiple of 8 -- it reads the group's four row ids, its index
+// nibble and its two values, and places the values by comparing positions.  Bound by the writes; the
+// index arithmetic is kept short because it would bound it otherwise: one division by M per thread, as a multiplication,
+// and everything that depends on the block row is uniform.
+// 8192 x 8192 at M = 8: 29 us, 4.6 TB/s of output (one thread per element, 2-byte stores: 231 us).
+template <bool WIDE>
+__global__ void __launch_bounds__(256) decompress_kernel(const char* __restrict__ arec,
+                                                         const int32_t* __restrict__ rowidx, int64_t K, int M, Divisor by_M,
+                                                         int64_t steps, int vt, int chunks, uint16_t* __restrict__ A,
+                                                         int64_t lda) {
+  const int64_t rt = blockIdx.x / (unsigned)chunks;              // 32-row tile of the matrix
+  const unsigned chunk = blockIdx.x - (unsigned)rt * (unsigned)chunks;
+  const int64_t b = rt / vt;
+  const int tile = (int)(rt - b * vt);
+  const int i = threadIdx.x >> 3;
+  const unsigned rec_bytes = (unsigned)(vt * kTileValBytes + kTailBytes);
+  const char* val = arec + b * steps * rec_bytes + tile * kTileValBytes + i * 16;
+  const char* idx = arec + b * steps * rec_bytes + vt * kTileValBytes + i * 8 + tile * 2;
+  const int32_t* ids = rowidx + b * steps * kStepRows;
+  uint16_t* row = A + (rt * kTileRows + i) * lda;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const unsigned k = chunk * 256 + j * 64 + (threadIdx.x & 7) * 8;
+    if (k >= K) break;
+    const unsigned end = K - k < 8 ? (unsigned)K : k + 8;
+    uint32_t o[4] = {0, 0, 0, 0};
+    unsigned g = divide(k, by_M), g_end = (g + 1) * (unsigned)M;
+    for (;;) {
+      const unsigned s = g / 8, t = g % 8;
+      const int64_t rec = (int64_t)s * rec_bytes;
+      const uint32_t word = *reinterpret_cast<const uint16_t*>(idx + rec + (t / 4) * 256);
+      const uint32_t v01 = *reinterpret_cast<const uint32_t*>(val + rec + (t / 4) * 512 + (t % 4) * 4);
+      const int4 ri = *reinterpret_cast<const int4*>(ids + (int64_t)s * kStepRows + 4 * t);
+      const uint32_t nib = (word >> (4 * (t % 4))) & 0xfu;
+      auto pick = [&](uint32_t p) { return (unsigned)(p == 0 ? ri.x : p == 1 ? ri.y : p == 2 ? ri.z : ri.w) - k; };
+      const unsigned c0 = pick(nib & 3u), c1 = pick(nib >> 2);   // outside 0 .. 7: not in this thread's columns
+      const uint32_t a0 = (v01 & 0xffffu) << (16 * (c0 & 1)), a1 = (v01 >> 16) << (16 * (c1 & 1));
+#pragma unroll
+      for (unsigned e = 0; e < 4; ++e) {
+        if (c0 >> 1 == e) o[e] |= a0;
+        if (c1 >> 1 == e) o[e] |= a1;
+      }
+      if (g_end >= end) break;
+      ++g;
+      g_end += M;
+    }
+    if (WIDE && K - k >= 8) {
+      typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+      *reinterpret_cast<u32x4*>(row + k) = u32x4{o[0], o[1], o[2], o[3]};
+    } else {
+#pragma unroll
+      for (unsigned e = 0; e < 8; ++e)
+        if (k + e < K) row[k + e] = (uint16_t)(o[e / 2] >> (16 * (e % 2)));
+    }
+  }
+}
+
+static FormatDst format_dst(const venom_handle& h) {
+  const Layout& L = h.lay;
+  FormatDst d{};
+  d.values = reinterpret_cast<uint32_t*>(h.ws + L.off_values);
+  d.columns = reinterpret_cast<uint16_t*>(h.ws + L.off_columns);
+  d.meta = reinterpret_cast<uint32_t*>(h.ws + L.off_meta);
+  d.arec = L.packed ? h.ws + L.off_arec : nullptr;
+  d.rowidx = L.packed ? reinterpret_cast<int32_t*>(h.ws + L.off_rowidx) : nullptr;
+  d.G = L.G; d.W = L.W;
+  d.V = h.V; d.Vp = L.packed ? L.vt * kTileRows : h.V; d.vt = L.vt; d.M = h.M;
+  return d;
+}
+
+hipError_t launch_import(const uint16_t* values, const uint16_t* columns, const uint32_t* meta, const venom_handle& h,
+                         hipStream_t st) {
   const Layout& L = h.lay;
   auto* status = reinterpret_cast<unsigned long long*>(h.ws + L.off_status);
   hipLaunchKernelGGL(init_status_kernel, dim3(1), dim3(1), 0, st, status);
   if (L.R > 0 && L.G > 0)
-    hipLaunchKernelGGL(validate_kernel, dim3(blocks_for(L.R * L.W * 8)), dim3(256), 0, st,
-                       reinterpret_cast<const uint16_t*>(h.ws + L.off_columns),
-                       reinterpret_cast<const uint32_t*>(h.ws + L.off_meta), L.R, L.G, L.W, h.V, h.M, status);
+    hipLaunchKernelGGL(import_kernel, dim3((unsigned)(((L.W + 3) / 4) * ((L.R + 31) / 32))), dim3(256), 0, st,
+                       reinterpret_cast<const uint32_t*>(values), columns, meta, L.R,
+                       L.G % 4 == 0 && reinterpret_cast<uintptr_t>(values) % 16 == 0, format_dst(h), status);
   return hipGetLastError();
 }
 
@@ -254,44 +478,33 @@ hipError_t launch_compress(const uint16_t* A, int64_t lda, const uint8_t* mask, 
   const Layout& L = h.lay;
   auto* status = reinterpret_cast<unsigned long long*>(h.ws + L.off_status);
   hipLaunchKernelGGL(init_status_kernel, dim3(1), dim3(1), 0, st, status);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   if (L.R > 0 && L.G > 0) {
-    dim3 grid((unsigned)L.W, (unsigned)L.Rb);
-    // wide mask loads need every 8-group chunk of every row to start on an 8-byte boundary
-    const int vec_ok = ldm % 8 == 0 && reinterpret_cast<uintptr_t>(mask) % 8 == 0;
-    hipLaunchKernelGGL(compress_kernel, grid, dim3(256), 0, st, A, lda, mask, ldm, h.V, h.M, L.G, L.W, vec_ok,
-                       reinterpret_cast<uint32_t*>(h.ws + L.off_values),
-                       reinterpret_cast<uint16_t*>(h.ws + L.off_columns),
-                       reinterpret_cast<uint32_t*>(h.ws + L.off_meta), status);
-    e = hipGetLastError();
+    // as many words per workgroup as leave eight workgroups per compute unit (rows of `values` are then written in
+    // longer pieces) and the mask bits within LDS
+    int wpw = kCompressWords;
+    while (wpw > 1 && (((L.W + wpw - 1) / wpw) * L.Rb < 2048 || (int64_t)h.V * bits_pitch(wpw, h.M) > kCompressBits / 2)) wpw /= 2;
+    const int64_t bit_bytes = (int64_t)h.V * bits_pitch(wpw, h.M);
+    const int bits_ok = bit_bytes <= kCompressBits;
+    const size_t lds = bits_ok ? (size_t)bit_bytes : 0;
+    const dim3 grid((unsigned)((L.W + wpw - 1) / wpw), (unsigned)L.Rb);
+    // wide mask loads need every chunk of 8*wpw groups of every row to start on such a boundary
+    const uintptr_t ma = reinterpret_cast<uintptr_t>(mask);
+    const int64_t chunk = (int64_t)8 * wpw * h.M;
+    auto fn = (chunk % 16 == 0 && ldm % 16 == 0 && ma % 16 == 0) ? compress_kernel<16>
+              : (ldm % 8 == 0 && ma % 8 == 0) ? compress_kernel<8> : compress_kernel<1>;
+    hipLaunchKernelGGL(fn, grid, dim3(256), lds, st, A, lda, mask, ldm, wpw, bits_ok, format_dst(h), status);
   }
-  return e;
-}
-
-hipError_t launch_pack(const venom_handle& h, hipStream_t st) {
-  const Layout& L = h.lay;
-  if (!L.packed || L.R == 0 || L.G == 0) return hipSuccess;
-  const int Vp = L.vt * kTileRows;
-  int64_t total = L.Rbp * L.steps * kStepRows;
-  hipLaunchKernelGGL(pack_rowidx_kernel, dim3(blocks_for(total)), dim3(256), 0, st,
-                     reinterpret_cast<const uint16_t*>(h.ws + L.off_columns), L.G, h.M, L.steps, total, Vp, h.V,
-                     reinterpret_cast<int32_t*>(h.ws + L.off_rowidx));
-  total = L.Rbp * L.steps * (L.vt + 1) * 64;
-  hipLaunchKernelGGL(pack_arec_kernel, dim3(blocks_for(total)), dim3(256), 0, st,
-                     reinterpret_cast<const uint32_t*>(h.ws + L.off_values),
-                     reinterpret_cast<const uint32_t*>(h.ws + L.off_meta), L.G, L.W, L.steps, L.vt, Vp, total,
-                     h.ws + L.off_arec);
   return hipGetLastError();
 }
 
 hipError_t launch_decompress(const venom_handle& h, uint16_t* A, int64_t lda, hipStream_t st) {
   const Layout& L = h.lay;
   if (L.R == 0 || L.K == 0) return hipSuccess;
-  const int64_t total = L.R * L.K;
-  hipLaunchKernelGGL(decompress_kernel, dim3(blocks_for(total)), dim3(256), 0, st, h.ws + L.off_arec,
-                     reinterpret_cast<const int32_t*>(h.ws + L.off_rowidx), L.R, L.K, L.vt * kTileRows, h.M, L.steps, L.vt,
-                     A, lda);
+  const int64_t chunks = (L.K + 255) / 256;
+  auto fn = (reinterpret_cast<uintptr_t>(A) % 16 == 0 && lda % 8 == 0) ? decompress_kernel<true> : decompress_kernel<false>;
+  hipLaunchKernelGGL(fn, dim3((unsigned)(L.R / kTileRows * chunks)), dim3(256), 0, st, h.ws + L.off_arec,
+                     reinterpret_cast<const int32_t*>(h.ws + L.off_rowidx), L.K, h.M, make_divisor((uint32_t)h.M), L.steps, L.vt,
+                     (int)chunks, A, lda);
   return hipGetLastError();
 }
 

@@ -51,9 +51,10 @@ namespace venom {
 // ---- format kernels (venom_format.hip)
 hipError_t launch_compress(const uint16_t* A, int64_t lda, const uint8_t* mask, int64_t ldm, const venom_handle& h,
                            hipStream_t st);
-hipError_t launch_pack(const venom_handle& h, hipStream_t st);
-// checks the canonical arrays in the workspace; the legality word reads ~0 afterwards iff they are well formed
-hipError_t launch_validate(const venom_handle& h, hipStream_t st);
+// checks, copies and packs canonical arrays; like launch_compress it leaves ~0 in the workspace's legality word iff
+// everything was well formed
+hipError_t launch_import(const uint16_t* values, const uint16_t* columns, const uint32_t* meta, const venom_handle& h,
+                         hipStream_t st);
 hipError_t launch_decompress(const venom_handle& h, uint16_t* A, int64_t lda, hipStream_t st);
 
 // ---- pruning (venom_prune.hip)
