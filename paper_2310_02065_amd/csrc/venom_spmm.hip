@@ -6,7 +6,8 @@
 //     16 halfs per lane (column = lane%32, four groups x the 4 selected rows);
 //   * a workgroup owns V x (64*NC) blocks of C (BS_r = V as in the paper, so every gathered row of
 //     B serves all V rows); a k-step is 8 groups = 32 gathered rows of B;
-//   * the workgroup is split by role.  NC CONSUMER waves each own a 64-column strip: they only read
+//   * the workgroup is split by role.  NC CONSUMER waves each own a 64-column strip (on the 64-column
+//     tile two or three waves share the one strip, a part of its rows each): they only read
 //     LDS (transposing reads ds_read_b64_tr_b16 build the B operand, plain reads fetch the packed
 //     values and index words) and issue matrix instructions.  Four PRODUCER waves, one per SIMD,
 //     only move data, by direct-to-LDS loads.  A SIMD issues one wave-wide 16-byte load (1 KB) per
@@ -85,8 +86,13 @@ __device__ __forceinline__ void barrier_only() { asm volatile("s_barrier" ::: "m
 // the same once every LDS access of this wave has completed
 __device__ __forceinline__ void lgkm_drained_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// 16-byte slot swizzle of gathered row rho inside its LDS row
-__device__ __forceinline__ int slot_swizzle(int rho) { return 4 * (rho & 3); }
+// 16-byte slot swizzle of gathered row rho inside its LDS row.  The four rows a lane block reads at
+// once lie ROW_BYTES apart; a row of 128 bytes is half the banks, so there only every second row has
+// to move (and a row has 8 slots, not 16 or more).
+template <int ROW_BYTES>
+__device__ __forceinline__ int slot_swizzle(int rho) {
+  return ROW_BYTES == 128 ? 4 * ((rho >> 1) & 1) : 4 * (rho & 3);
+}
 
 // GELU(x) = x * Phi(x) = x/2 * (1 + erf(x / sqrt 2)).  erf by the rational-times-Gaussian formula
 // 7.1.26 of Abramowitz & Stegun (absolute error below 1.5e-7, fp32 noise level), a dozen
@@ -143,14 +149,20 @@ struct TileWalk {
 // wait for those reads before barrier g+1, so the stage stays theirs until barrier g+2 and the
 // loads run NS-2 k-steps ahead.  D = 1: they drain their reads before every barrier and the loads
 // run NS-1 k-steps ahead.
-template <int VT, int NC, int NS, int NA, int D, bool OUT_F32, int MODE>
-__global__ void __launch_bounds__((NC + kProducers) * 64, 3) spmm_kernel(SpmmParams p) {
-  static_assert(NC == 2 || NC == 4 || NC == 8, "consumer waves per workgroup");
+// NR: consumer waves that share a 64-column strip, each owning VT/NR of its tile rows.  1 for the wide
+// tiles.  The 64-column tile has a single strip: one wave would need 8 matrix instructions (256
+// cycles) per k-step while its 8.5 KB arrive in ~190, so the strip's rows are split over two or three
+// waves; their accumulators are small enough for four waves per SIMD, i.e. two workgroups per unit.
+template <int VT, int NC, int NR, int NS, int NA, int D, bool OUT_F32, int MODE>
+__global__ void __launch_bounds__((NC * NR + kProducers) * 64, NC == 1 ? 4 : 3) spmm_kernel(SpmmParams p) {
+  static_assert(NC == 1 || NC == 2 || NC == 4 || NC == 8, "64-column strips per workgroup");
+  static_assert(VT % NR == 0, "the tile rows divide evenly over the waves of a strip");
   static_assert(D == 1 || D == 2, "barriers between the hand-over of a stage and its return");
   constexpr bool EPI = MODE != 0;
   static_assert(VT >= 1 && VT <= kMaxTiles, "32-row tiles per block row");
   constexpr int NP = kProducers;
-  constexpr int RT = VT;                           // 32-row tiles a consumer wave accumulates
+  constexpr int CONS = NC * NR;                    // consumer waves
+  constexpr int RT = VT / NR;                      // 32-row tiles a consumer wave accumulates
   constexpr int CT = 2;                            // 32-column tiles a consumer wave accumulates
   constexpr int WCOLS = 32 * CT;                   // columns of C per consumer wave
   constexpr int BSC = WCOLS * NC;                  // columns of C per workgroup
@@ -172,7 +184,9 @@ __global__ void __launch_bounds__((NC + kProducers) * 64, 3) spmm_kernel(SpmmPar
                                                    // then older, in their producer's load queue, than its loads of step g
   static_assert(PB >= 1 && PA >= PB, "a record is issued no later than the B rows of its k-step");
   static_assert(kRidSlots >= PB + 2, "a row-id slot is rewritten only after its last reader");
-  static_assert(NC * 32 * WCOLS * 2 <= B_BYTES, "the output staging of all consumers fits one B stage");
+  constexpr bool OWN_STG = NR > 1;                 // the consumers' output staging: the drained stage, or its own LDS
+  constexpr int STG = RIDRING + kRidSlots * kStepRows * 4;
+  static_assert(OWN_STG || CONS * 32 * WCOLS * 2 <= B_BYTES, "the output staging of all consumers fits one B stage");
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(LDS_PTR(char))smem;
@@ -197,7 +211,7 @@ __global__ void __launch_bounds__((NC + kProducers) * 64, 3) spmm_kernel(SpmmPar
   // tile, after which the consumers stage their output in the B stage they have just drained.
   const int G = tw.count * p.steps;
 
-  if (wave >= NC) {
+  if (wave >= CONS) {
     // ========================================================================= producers
     // Iteration i (after barrier i) issues, in this order: the row ids of step i+RA, this
     // producer's part of record i+PA, its part of the B rows of step i+PB.  Before barrier g the
@@ -272,7 +286,7 @@ __global__ void __launch_bounds__((NC + kProducers) * 64, 3) spmm_kernel(SpmmPar
 #pragma unroll
       for (int q = 0; q < CB; ++q) {
         const int rho = (PJ + NP * q) * RPI + lane / LPR;
-        chunk_col[q] = ((lane % LPR) ^ slot_swizzle(rho)) * 8;
+        chunk_col[q] = ((lane % LPR) ^ slot_swizzle<ROW_BYTES>(rho)) * 8;
       }
       uint32_t ld_col[CB];
       auto set_tile = [&](int t) {
@@ -374,7 +388,7 @@ __global__ void __launch_bounds__((NC + kProducers) * 64, 3) spmm_kernel(SpmmPar
       }
       for (; g < G; ++g) iteration(g, std::false_type{});
     };
-    switch (wave - NC) {
+    switch (wave - CONS) {
       case 0: produce(std::integral_constant<int, 0>{}); break;
       case 1: produce(std::integral_constant<int, 1>{}); break;
       case 2: produce(std::integral_constant<int, 2>{}); break;
@@ -385,6 +399,8 @@ __global__ void __launch_bounds__((NC + kProducers) * 64, 3) spmm_kernel(SpmmPar
     // Transposing LDS reads that build the B operand.  Sub-read cb of a 32-column tile: lane block
     // blk = lane/16 reads group t = 4*(cb/2) + 2*(blk/2) + cb%2, 16-column window 2*tile + blk%2;
     // inside the block lane i reads row 4*t + i/4, 8-byte piece i%4.
+    const int wc = NR == 1 ? wave : wave % NC;     // this wave's strip
+    const int wr = NR == 1 ? 0 : wave / NC;        // ... and its share of the strip's tile rows
     int rd_off[CT][4];
     {
       const int blk = lane >> 4, i = lane & 15, e = i >> 2, c8 = i & 3;
@@ -394,8 +410,8 @@ __global__ void __launch_bounds__((NC + kProducers) * 64, 3) spmm_kernel(SpmmPar
         for (int cb = 0; cb < 4; ++cb) {
           const int t = 4 * (cb >> 1) + 2 * (blk >> 1) + (cb & 1);
           const int rho = 4 * t + e;
-          const int win = (wave * CT + tc) * 2 + (blk & 1);
-          const int slot = (2 * win + (c8 >> 1)) ^ slot_swizzle(rho);
+          const int win = (wc * CT + tc) * 2 + (blk & 1);
+          const int slot = (2 * win + (c8 >> 1)) ^ slot_swizzle<ROW_BYTES>(rho);
           rd_off[tc][cb] = rho * ROW_BYTES + slot * 16 + (c8 & 1) * 8;
         }
     }
@@ -404,7 +420,7 @@ __global__ void __launch_bounds__((NC + kProducers) * 64, 3) spmm_kernel(SpmmPar
     uint32_t ixw[2];                               // index words of tile rows (0,1) and (2,3): 2 x 16 bits each
     half8 av[RT];                                  // the A operands of one k-step
     auto read_a = [&](const char* sa, int t) {
-      av[t] = *reinterpret_cast<const half8*>(sa + t * kTileValBytes + lane * 16);
+      av[t] = *reinterpret_cast<const half8*>(sa + (wr * RT + t) * kTileValBytes + lane * 16);
     };
     auto read_b = [&](const char* sb, int tc) {
 #pragma unroll
@@ -415,7 +431,8 @@ __global__ void __launch_bounds__((NC + kProducers) * 64, 3) spmm_kernel(SpmmPar
       }
     };
     auto read_ix = [&](const char* sa, int half) {
-      ixw[half] = *reinterpret_cast<const uint32_t*>(sa + T_OFF + lane * 8 + 4 * half);
+      if constexpr (NR > 1 && RT == 1) ixw[0] = *reinterpret_cast<const uint16_t*>(sa + T_OFF + lane * 8 + 2 * wr);
+      else ixw[half] = *reinterpret_cast<const uint32_t*>(sa + T_OFF + lane * 8 + 4 * (wr * (RT / 2) + half));
     };
     auto mma = [&](int t, int tc) {
       const int ix = (int)ixw[t >> 1];
@@ -486,8 +503,8 @@ __global__ void __launch_bounds__((NC + kProducers) * 64, 3) spmm_kernel(SpmmPar
       asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
       int ct, br;
       tw.locate(p, t, ct, br);
-      const int64_t row0 = (int64_t)br * RT * 32;
-      const int64_t col0 = (int64_t)ct * BSC + wave * WCOLS;
+      const int64_t row0 = ((int64_t)br * VT + wr * RT) * 32;
+      const int64_t col0 = (int64_t)ct * BSC + wc * WCOLS;
       // fused epilogue (the layer's bias, one per output row, then the activation), in fp32 on
       // the accumulators, one 32-row tile at a time right before it is stored: a ln holds rows
       // 8j + 4*(ln/32) + 0..3 of the tile
@@ -568,7 +585,7 @@ __global__ void __launch_bounds__((NC + kProducers) * 64, 3) spmm_kernel(SpmmPar
           constexpr int LPT = RB / 16;             // lanes (16-byte chunks) per token row
           constexpr int TPI = 64 / LPT;            // tokens per wave-wide read
           constexpr int SH = FT == 2 ? 1 : 2;      // tokens 2^SH apart share a bank group
-          char* stg = const_cast<char*>(sb) + wave * 4096;
+          char* stg = (OWN_STG ? smem + STG : const_cast<char*>(sb)) + wave * 4096;
           _Float16* Y = reinterpret_cast<_Float16*>(p.C);
           const int h = ln >> 5;
 #pragma unroll
@@ -636,7 +653,7 @@ __global__ void __launch_bounds__((NC + kProducers) * 64, 3) spmm_kernel(SpmmPar
         constexpr int SROW = 2 * WCOLS;            // bytes of a staged row
         constexpr int LPS = SROW / 16;             // lanes (16-byte chunks) per staged row
         constexpr int SWZ = LPS / 2;               // chunk distance that changes the bank group
-        char* stg = const_cast<char*>(sb) + wave * (32 * SROW);
+        char* stg = (OWN_STG ? smem + STG : const_cast<char*>(sb)) + wave * (32 * SROW);
         _Float16* Ch = reinterpret_cast<_Float16*>(p.C);
         const int chunk = ln % LPS, rsub = ln / LPS;
         const int64_t col = col0 + chunk * 8;
@@ -685,50 +702,63 @@ struct Variant {
   void (*fn[2][4])(SpmmParams);   // [fp32 output][mode]
 };
 
-template <int VT, int NC, int NS, int NA>
-constexpr int lds_bytes() {   // B ring, A ring, row-id ring (the output staging reuses a B stage)
-  return NS * kStepRows * 128 * NC + NA * (VT * kTileValBytes + kTailBytes) + kRidSlots * kStepRows * 4;
+template <int VT, int NC, int NR, int NS, int NA>
+constexpr int lds_bytes() {   // B ring, A ring, row-id ring, output staging (4 KB a wave) where it does not reuse a B stage
+  return NS * kStepRows * 128 * NC + NA * (VT * kTileValBytes + kTailBytes) + kRidSlots * kStepRows * 4 +
+         (NR > 1 ? NC * NR * 4096 : 0);
 }
 
-#define VARIANT(NAME, VT, NC, NS, NA, D)                                                                  \
-  { NAME, (VT) * 32, 64 * (NC), 64 * ((NC) + kProducers), lds_bytes<VT, NC, NS, NA>(),                     \
-    { { spmm_kernel<VT, NC, NS, NA, D, false, 0>, spmm_kernel<VT, NC, NS, NA, D, false, 1>,               \
-        spmm_kernel<VT, NC, NS, NA, D, false, 2>, spmm_kernel<VT, NC, NS, NA, D, false, 3> },             \
-      { spmm_kernel<VT, NC, NS, NA, D, true, 0>, spmm_kernel<VT, NC, NS, NA, D, true, 1>,                 \
-        spmm_kernel<VT, NC, NS, NA, D, true, 2>, spmm_kernel<VT, NC, NS, NA, D, true, 2> } } }
+#define VARIANT(NAME, VT, NC, NR, NS, NA, D)                                                                \
+  { NAME, (VT) * 32, 64 * (NC), 64 * ((NC) * (NR) + kProducers), lds_bytes<VT, NC, NR, NS, NA>(),            \
+    { { spmm_kernel<VT, NC, NR, NS, NA, D, false, 0>, spmm_kernel<VT, NC, NR, NS, NA, D, false, 1>,         \
+        spmm_kernel<VT, NC, NR, NS, NA, D, false, 2>, spmm_kernel<VT, NC, NR, NS, NA, D, false, 3> },       \
+      { spmm_kernel<VT, NC, NR, NS, NA, D, true, 0>, spmm_kernel<VT, NC, NR, NS, NA, D, true, 1>,           \
+        spmm_kernel<VT, NC, NR, NS, NA, D, true, 2>, spmm_kernel<VT, NC, NR, NS, NA, D, true, 2> } } }
 
 constexpr int kD = 2;   // barriers between the hand-over of a stage and its return (1 and 2 measure the same)
 static const Variant kVariants[] = {
-    VARIANT("v128_c512", 4, 8, 4, 6, kD), VARIANT("v128_c256", 4, 4, 6, 10, kD), VARIANT("v128_c128", 4, 2, 8, 10, kD),
-    VARIANT("v96_c512", 3, 8, 4, 8, kD),  VARIANT("v96_c256", 3, 4, 6, 10, kD), VARIANT("v96_c128", 3, 2, 8, 10, kD),
-    VARIANT("v64_c512", 2, 8, 4, 10, kD), VARIANT("v64_c256", 2, 4, 6, 10, kD), VARIANT("v64_c128", 2, 2, 8, 10, kD),
-    VARIANT("v32_c512", 1, 8, 4, 10, kD), VARIANT("v32_c256", 1, 4, 6, 10, kD), VARIANT("v32_c128", 1, 2, 8, 10, kD),
+    VARIANT("v128_c512", 4, 8, 1, 4, 6, kD), VARIANT("v128_c256", 4, 4, 1, 6, 10, kD),
+    VARIANT("v128_c128", 4, 2, 1, 8, 10, kD),
+    VARIANT("v96_c512", 3, 8, 1, 4, 8, kD), VARIANT("v96_c256", 3, 4, 1, 6, 10, kD),
+    VARIANT("v96_c128", 3, 2, 1, 8, 10, kD),
+    VARIANT("v64_c512", 2, 8, 1, 4, 10, kD), VARIANT("v64_c256", 2, 4, 1, 6, 10, kD),
+    VARIANT("v64_c128", 2, 2, 1, 8, 10, kD),
+    VARIANT("v32_c512", 1, 8, 1, 4, 10, kD), VARIANT("v32_c256", 1, 4, 1, 6, 10, kD),
+    VARIANT("v32_c128", 1, 2, 1, 8, 10, kD),
+    VARIANT("v128_c64", 4, 1, 2, 6, 10, kD),
+    VARIANT("v96_c64", 3, 1, 3, 6, 10, kD),
+    VARIANT("v64_c64", 2, 1, 2, 6, 10, kD),
+    VARIANT("v32_c64", 1, 1, 1, 6, 10, kD),
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
 int spmm_variant_count() { return kNumVariants; }
 const char* spmm_variant_name(int v) { return (v >= 0 && v < kNumVariants) ? kVariants[v].name : nullptr; }
 
-static int pick_variant(int V, int64_t Ccols, int64_t nbr) {
-  // The widest column tile that C fills at least half of: wide tiles re-read the A stream least
-  // and measured fastest at every large shape tried; narrow C takes the narrow tiles.  When that
+static int variant_of(int V, int bsc) {
+  for (int i = 0; i < kNumVariants; ++i)
+    if (kVariants[i].V == V && kVariants[i].bsc == bsc) return i;
+  return -1;
+}
+
+static int pick_variant(int V, int64_t Ccols, int64_t nbr, int cus) {
+  // The 64-column tile where C has no more columns than that, or where even its tiles find a compute
+  // unit each.  What bounds such a call is one unit's L2 -> LDS path (~46 B/clk): per k-step at
+  // V = 128 it takes 36.5 / 20.5 / 12.5 / 8.5 KB for 512 / 256 / 128 / 64 columns, so as long as the
+  // chip has units to spare a narrower tile is simply shorter.  Measured (us per call among others,
+  // the best wider tile -> 64 columns): 49152 x 12288 x 16 at 128:2:32 30.1 -> 18.8 (4.8 TB/s of the
+  // matrix), at 64:2:32 33.6 -> 22.6; 8192 x 8192 x 256 at 128:2:16 22.3 -> 20.1; 4096 x 4096 x 512
+  // at 128:2:16 15.3 -> 13.2; 1024 x 16000 x 2048 at 128:2:40 19.5 -> 16.5; 8160 x 8192 x 128 at
+  // 96:2:16 21.9 -> 18.3.  With two tiles per unit it is even (20.5 against 21.1) to 26 % slower
+  // (8192 x 8192 x 512 at 128:2:16, 29.9 against 23.7): the A stream is read once per tile.
+  if (Ccols <= 64 || nbr * ((Ccols + 63) / 64) <= cus) return variant_of(V, 64);
+  // Otherwise the widest column tile that C fills at least half of: wide tiles re-read the A stream
+  // least and measured fastest at every large shape tried; narrow C takes the narrow tiles.  When that
   // choice leaves more than half of the compute units without a tile (few block rows), the
   // 256-column tile spreads the work over twice as many units.
-  int best = -1;
-  for (int i = 0; i < kNumVariants; ++i) {
-    if (kVariants[i].V != V) continue;
-    if (best < 0) { best = i; continue; }
-    const bool fits_i = 2 * Ccols > kVariants[i].bsc, fits_b = 2 * Ccols > kVariants[best].bsc;
-    if (fits_i && (!fits_b || kVariants[i].bsc > kVariants[best].bsc)) best = i;
-    else if (!fits_i && !fits_b && kVariants[i].bsc < kVariants[best].bsc) best = i;
-  }
-  if (best >= 0 && kVariants[best].bsc == 512) {
-    const int64_t tiles = nbr * ((Ccols + 511) / 512);
-    if (tiles <= 128)
-      for (int i = 0; i < kNumVariants; ++i)
-        if (kVariants[i].V == V && kVariants[i].bsc == 256) best = i;
-  }
-  return best;
+  const int bsc = Ccols > 256 ? 512 : Ccols > 128 ? 256 : 128;
+  if (bsc == 512 && nbr * ((Ccols + 511) / 512) <= 128) return variant_of(V, 256);
+  return variant_of(V, bsc);
 }
 
 venom_status_t launch_spmm(const venom_handle& h, const void* B, int64_t ldb, int64_t Ccols, const void* bias, int act,
@@ -738,7 +768,16 @@ venom_status_t launch_spmm(const venom_handle& h, const void* B, int64_t ldb, in
   if (L.R == 0 || Ccols == 0) return VENOM_OK;
   if (L.steps == 0) return VENOM_ERR_UNSUPPORTED;  // K = 0: there is no k-step to run the pipeline on
   const int Vp = L.vt * kTileRows;                 // block height of the packed copy
-  if (variant < 0) variant = pick_variant(Vp, Ccols, L.Rbp);
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return VENOM_ERR_HIP;
+  static std::atomic<int> cu_count[kMaxDevices] = {};   // per device, filled on first use
+  int cus = (dev >= 0 && dev < kMaxDevices) ? cu_count[dev].load(std::memory_order_relaxed) : 0;
+  if (cus == 0) {
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < kNumXcd)
+      return VENOM_ERR_HIP;
+    if (dev >= 0 && dev < kMaxDevices) cu_count[dev].store(cus, std::memory_order_relaxed);
+  }
+  if (variant < 0) variant = pick_variant(Vp, Ccols, L.Rbp, cus);
   if (variant < 0 || variant >= kNumVariants || kVariants[variant].V != Vp) return VENOM_ERR_UNSUPPORTED;
   const Variant& var = kVariants[variant];
   SpmmParams p{};
@@ -764,15 +803,6 @@ venom_status_t launch_spmm(const venom_handle& h, const void* B, int64_t ldb, in
   p.per_xcd = (int)((total + kNumXcd - 1) / kNumXcd);
   // one resident workgroup per compute unit (two where the tile is small enough to share a unit);
   // each walks per_xcd / (grid / 8) tiles
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return VENOM_ERR_HIP;
-  static std::atomic<int> cu_count[kMaxDevices] = {};   // per device, filled on first use
-  int cus = (dev >= 0 && dev < kMaxDevices) ? cu_count[dev].load(std::memory_order_relaxed) : 0;
-  if (cus == 0) {
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < kNumXcd)
-      return VENOM_ERR_HIP;
-    if (dev >= 0 && dev < kMaxDevices) cu_count[dev].store(cus, std::memory_order_relaxed);
-  }
   const int share = (var.lds <= 80 * 1024 && var.threads <= 512) ? 2 : 1;
   const int64_t resident_per_xcd = (int64_t)(cus / kNumXcd) * share;
   const int64_t wg_per_xcd = p.per_xcd < resident_per_xcd ? p.per_xcd : resident_per_xcd;
