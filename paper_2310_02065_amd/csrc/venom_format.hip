@@ -147,7 +147,8 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
     for (int i = tid; i < V * pitch / 4; i += 256) reinterpret_cast<uint32_t*>(bits)[i] = 0;
   __syncthreads();
   if constexpr (UB > 1) {
-    const int slices = 256 / units > 0 ? 256 / units : 1;                 // row slices working side by side
+    // row slices working side by side; no unit at all where a padded mask's last columns are fewer than a load takes
+    const int slices = units > 0 && units < 256 ? 256 / units : 1;
     for (int u0 = 0; u0 < units; u0 += 256) {                             // (more than 256 units: several sweeps)
       const int u = u0 + (slices > 1 ? tid % units : tid);
       const int slice = slices > 1 ? tid / units : 0;

@@ -1,0 +1,99 @@
+"""The format and pruning kernels on the CPU: the device code itself, compiled as plain C++ with the compiler's
+undefined-behaviour checks (a violation traps), against the oracle bit for bit, and the launch code against
+the runtime's limits.  Each call runs in a process of its own, so that a trap fails one test."""
+import ctypes
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import vnm_oracle as o
+from paper_2310_02065_amd import build, inputs
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+c, p64 = ctypes, ctypes.c_int64
+
+
+def clang():
+    return os.path.join(os.path.dirname(os.path.realpath(build.hipcc())), "..", "lib", "llvm", "bin", "clang++")
+
+
+@pytest.fixture(scope="module")
+def library(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("host_kernels") / "libhost.so")
+    subprocess.run([clang(), "-x", "c++", "-std=c++20", "-O1", "-fPIC", "-shared",
+                    "-fsanitize=undefined", "-fsanitize-trap=all", "-Wno-everything",
+                    "-I", os.path.join(HERE, "host_kernels"), "-I", build.CSRC, "-I", os.path.join(build.ROOT, "include"),
+                    os.path.join(HERE, "host_kernels", "driver.cpp"), "-o", out], check=True)
+    return out
+
+
+def in_child(library, function, *args):
+    code = (f"import sys; sys.path[:0] = [{build.ROOT!r}, {HERE!r}]; import test_format_kernels_host as t; "
+            f"t.{function}(t.load({library!r}), *{args!r})")
+    res = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, f"exit status {res.returncode}\n{res.stdout[-2000:]}{res.stderr[-2000:]}"
+
+
+def load(path):
+    L = c.CDLL(path)
+    vp, i = c.c_void_p, c.c_int
+    L.host_workspace_bytes.argtypes, L.host_workspace_bytes.restype = [p64, p64, i, i], c.c_size_t
+    L.host_launches.restype = L.host_blocks.restype = c.c_uint64
+    L.host_compress.argtypes = [vp, p64, vp, p64, p64, p64, i, i, vp, vp]
+    L.host_import.argtypes = [vp, vp, vp, p64, p64, i, i, vp, vp]
+    L.host_export.argtypes = [p64, p64, i, i, vp, vp, vp, vp]
+    L.host_decompress.argtypes = [p64, p64, i, i, vp, vp, p64]
+    L.host_prune.argtypes = [vp, p64, p64, p64, i, i, vp, p64, vp, vp]
+    return L
+
+
+def aligned(nbytes, offset=0, fill=0xA5):
+    """nbytes of memory `offset` bytes past a 256-byte boundary."""
+    raw = np.full(nbytes + 512, fill, dtype=np.uint8)
+    start = (-raw.ctypes.data) % 256 + offset
+    return raw[start:start + nbytes]
+
+
+def pitched(a, pitch, offset=0):
+    """`a` in rows of `pitch` elements, the first one `offset` bytes past a 256-byte boundary."""
+    mem = aligned(a.shape[0] * pitch * a.itemsize, offset).view(a.dtype).reshape(a.shape[0], pitch)
+    mem[:, :a.shape[1]] = a
+    return mem
+
+
+def problem(R, K, V, M):
+    rng = np.random.default_rng(R + K + V)
+    A = (rng.standard_normal((R, K)) * 0.05).astype(np.float16).view(np.uint16)
+    mask = np.where(rng.random((R, K)) < 0.2, 0, inputs.gen_mask(R, K, V, M, rng)).astype(np.uint8)
+    return A, mask * rng.integers(1, 256, (R, K)).astype(np.uint8)
+
+
+def exported(L, R, K, V, M, ws):
+    G = K // M
+    out = (np.zeros((R, G, 2), np.uint16), np.zeros((R // V, G, 4), np.uint16), np.zeros((R, (G + 7) // 8), np.uint32))
+    L.host_export(R, K, V, M, ws.ctypes.data, *(x.ctypes.data for x in out))
+    return out
+
+
+def check_compress(L, R, K, V, M, ldm, offset):
+    A, mask = problem(R, K, V, M)
+    m = pitched(mask, ldm, offset)
+    ws, legal = aligned(L.host_workspace_bytes(R, K, V, M)), np.zeros(1, np.uint64)
+    assert L.host_compress(A.ctypes.data, K, m.ctypes.data, ldm, R, K, V, M, ws.ctypes.data, legal.ctypes.data) == 0
+    assert legal[0] == np.uint64(2**64 - 1)
+    for got, want in zip(exported(L, R, K, V, M, ws), o.compress(A, (mask != 0).astype(np.uint8), V, M)):
+        assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("R,K,V,M,ldm,offset", [
+    (64, 36, 32, 4, 48, 0),          # 16-byte mask loads, and a last word narrower than one of them
+    (64, 45, 32, 5, 48, 8),          # 8-byte loads, likewise
+    (64, 60, 32, 4, 64, 0),          # a last word that is a whole load and a remainder
+    (64, 92, 32, 4, 96, 8),          # the same with 8-byte loads
+    (64, 45, 32, 5, 45, 1),          # rows at every alignment
+])
+def test_compress(library, R, K, V, M, ldm, offset):
+    in_child(library, "check_compress", R, K, V, M, ldm, offset)
