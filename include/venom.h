@@ -79,10 +79,11 @@ venom_status_t venom_compress(const void* A_f16_dev, int64_t lda, const uint8_t*
                               venom_violation_t* viol);
 
 /* Section 3, the three arrays of the format as the persistent form of a compressed matrix: build
- * a handle from canonical arrays already on the device (layout above).  The arrays are copied into
- * the workspace and CHECKED there: column ids strictly increasing and below M, idx0 < idx1 in every
- * nibble, unused nibbles zero; anything else returns VENOM_ERR_INVALID_ARG, no handle, and nothing
- * is ever gathered from such arrays (value bits are free).  Synchronises `stream` once. */
+ * a handle from canonical arrays already on the device (layout above; they may start at any
+ * address).  While they are copied into the workspace they are CHECKED: column ids strictly
+ * increasing and below M, idx0 < idx1 in every nibble, unused nibbles zero; anything else returns
+ * VENOM_ERR_INVALID_ARG, no handle, and nothing is ever gathered from such arrays (value bits are
+ * free).  Synchronises `stream` once. */
 venom_status_t venom_import(const uint16_t* values_dev, const uint16_t* columns_dev, const uint32_t* meta_dev,
                             int64_t R, int64_t K, int V, int N, int M, void* workspace_dev,
                             size_t workspace_bytes, void* stream, venom_handle_t** out);

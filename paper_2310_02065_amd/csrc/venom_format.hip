@@ -103,6 +103,11 @@ __device__ __forceinline__ uint32_t nonzero_bits(uint32_t x) {
   return ((top >> 7) * 0x10204080u) >> 28;       // byte e's flag to bit e
 }
 
+// Words of arrays that come from outside at any address: global accesses need no alignment on this target, and the
+// compiler emits the same single loads for these types as for the aligned ones.
+typedef uint32_t u32_any __attribute__((aligned(1)));
+typedef uint16_t u16_any __attribute__((aligned(1)));
+
 constexpr int kMaxM = 1024;
 constexpr int kCompressWords = 4;                // most metadata words (8 groups each) one workgroup takes
 constexpr int kCompressBits = 32 * 1024;         // most LDS for the mask bits of a workgroup's rows
@@ -322,8 +327,8 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
 // 8192 x 8192 at M = 8 (120 MB in and out): 28 us, 4.2 TB/s; three copies, the check and the packing by
 // themselves took 90 us.
 // aligned: rows of `values` and of its copy start on 16-byte boundaries.
-__global__ void __launch_bounds__(256) import_kernel(const uint32_t* __restrict__ values, const uint16_t* __restrict__ columns,
-                                                     const uint32_t* __restrict__ meta, int64_t R, int aligned, FormatDst d,
+__global__ void __launch_bounds__(256) import_kernel(const u32_any* __restrict__ values, const u16_any* __restrict__ columns,
+                                                     const u32_any* __restrict__ meta, int64_t R, int aligned, FormatDst d,
                                                      unsigned long long* status) {
   const int64_t wq = (d.W + 3) / 4;
   const int64_t rblk = blockIdx.x / wq, wblk = blockIdx.x - rblk * wq;
@@ -339,7 +344,7 @@ __global__ void __launch_bounds__(256) import_kernel(const uint32_t* __restrict_
   const int ng = g >= d.G ? 0 : d.G - g < 4 ? (int)(d.G - g) : 4;         // groups of the half word that exist
   const uint32_t word = meta[r * d.W + w];
   uint32_t x[4] = {0, 0, 0, 0};
-  const uint32_t* src = values + r * d.G + g;
+  const u32_any* src = values + r * d.G + g;
   uint32_t* dst = d.values + r * d.G + g;
   if (aligned && ng == 4) {
     const uint4 q = *reinterpret_cast<const uint4*>(src);
@@ -370,7 +375,7 @@ __global__ void __launch_bounds__(256) import_kernel(const uint32_t* __restrict_
     for (int e = 0; e < 4; ++e) {
       ushort4 c = make_ushort4(0, 0, 0, 0);
       if (e < ng) {
-        const uint16_t* cp = columns + (cb * d.G + g + e) * kSelCols;
+        const u16_any* cp = columns + (cb * d.G + g + e) * kSelCols;
         c = make_ushort4(cp[0], cp[1], cp[2], cp[3]);
         bad = bad || !(c.x < c.y && c.y < c.z && c.z < c.w && c.w < d.M);
         if (v == 0) emit_columns(d, cb, g + e, c);
@@ -469,7 +474,7 @@ hipError_t launch_import(const uint16_t* values, const uint16_t* columns, const 
   hipLaunchKernelGGL(init_status_kernel, dim3(1), dim3(1), 0, st, status);
   if (L.R > 0 && L.G > 0)
     hipLaunchKernelGGL(import_kernel, dim3((unsigned)(((L.W + 3) / 4) * ((L.R + 31) / 32))), dim3(256), 0, st,
-                       reinterpret_cast<const uint32_t*>(values), columns, meta, L.R,
+                       reinterpret_cast<const u32_any*>(values), columns, meta, L.R,
                        L.G % 4 == 0 && reinterpret_cast<uintptr_t>(values) % 16 == 0, format_dst(h), status);
   return hipGetLastError();
 }

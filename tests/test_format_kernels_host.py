@@ -97,3 +97,35 @@ def check_compress(L, R, K, V, M, ldm, offset):
 ])
 def test_compress(library, R, K, V, M, ldm, offset):
     in_child(library, "check_compress", R, K, V, M, ldm, offset)
+
+
+def at(a, offset):
+    """The bytes of `a`, `offset` bytes past a 256-byte boundary."""
+    mem = aligned(a.nbytes, offset)
+    mem[:] = np.frombuffer(a.tobytes(), np.uint8)
+    return mem
+
+
+def check_import(L, R, K, V, M, *offsets):
+    A, mask = problem(R, K, V, M)
+    arrays = o.compress(A, (mask != 0).astype(np.uint8), V, M)
+    moved = [at(a, off) for a, off in zip(arrays, offsets)]
+    ws, legal = aligned(L.host_workspace_bytes(R, K, V, M)), np.zeros(1, np.uint64)
+    assert L.host_import(*(m.ctypes.data for m in moved), R, K, V, M, ws.ctypes.data, legal.ctypes.data) == 0
+    assert legal[0] == np.uint64(2**64 - 1)
+    for got, want in zip(exported(L, R, K, V, M, ws), arrays):
+        assert np.array_equal(got, want)
+    if V % 32 == 0:
+        dense = aligned(R * K * 2).view(np.uint16).reshape(R, K)
+        assert L.host_decompress(R, K, V, M, ws.ctypes.data, dense.ctypes.data, K) == 0
+        assert np.array_equal(dense, np.where(mask != 0, A, 0))
+
+
+@pytest.mark.parametrize("R,K,V,M,offsets", [
+    (64, 12 * 8, 32, 8, (0, 0, 0)),
+    (64, 12 * 8, 32, 8, (2, 2, 4)),  # arrays sliced out of larger ones
+    (64, 11 * 7, 32, 7, (6, 6, 8)),  # ... and groups per row that are no multiple of 4
+    (9, 11 * 5, 1, 5, (1, 3, 5)),    # any byte
+])
+def test_import(library, R, K, V, M, offsets):
+    in_child(library, "check_import", R, K, V, M, *offsets)

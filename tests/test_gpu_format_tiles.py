@@ -55,3 +55,20 @@ def test_format_path_bit_exact(R, K, V, M, shift):
             binding.venom_decompress(x, out=big[:, 3:3 + K])
             assert torch.equal(big[:, 3:3 + K].contiguous().view(torch.int16), dense.view(torch.int16))
             assert bool((big[:, :3] == -7.0).all()) and bool((big[:, 3 + K:] == -7.0).all())
+
+
+@pytest.mark.parametrize("R,K,V,M,offset", [
+    (256, 72 * 8, 64, 8, 2), (256, 71 * 7, 32, 7, 6),     # arrays that begin in the middle of a word
+    (256, 71 * 7, 32, 7, 0), (1024, 71 * 7, 1, 7, 4),     # groups per row that are no multiple of 4; single-row blocks
+])
+def test_import_of_arrays_at_any_address(R, K, V, M, offset):
+    rng = np.random.default_rng(R + K)
+    bits = (rng.standard_normal((R, K)) * 0.05).astype(np.float16).view(np.uint16)
+    want = o.compress(bits, inputs.gen_mask(R, K, V, M, rng), V, M)
+    moved = []
+    for w in want:
+        buf = torch.zeros(w.nbytes + 16, dtype=torch.uint8, device=DEV)
+        buf[offset:offset + w.nbytes] = torch.from_numpy(np.frombuffer(w.tobytes(), np.uint8).copy()).to(DEV)
+        moved.append(buf[offset:])
+    for got, w in zip(binding.venom_export(binding.venom_import(*moved, R, K, V, 2, M)), want):
+        assert np.array_equal(got.cpu().numpy().view(w.dtype), w)
