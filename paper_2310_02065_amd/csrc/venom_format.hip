@@ -107,6 +107,8 @@ __device__ __forceinline__ uint32_t nonzero_bits(uint32_t x) {
 // compiler emits the same single loads for these types as for the aligned ones.
 typedef uint32_t u32_any __attribute__((aligned(1)));
 typedef uint16_t u16_any __attribute__((aligned(1)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+typedef uint32_t u32x4_word __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int kMaxM = 1024;
 constexpr int kCompressWords = 4;                // most metadata words (8 groups each) one workgroup takes
@@ -319,24 +321,26 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
 
 // Canonical arrays from outside -> the workspace: checked, copied and packed in one pass (the handle
 // is only handed out if the check found nothing).  One thread per row and half metadata word = 4 groups: 16 bytes
-// of values, one 16-byte slot of the packed record.  A workgroup takes 32 rows x 4 words, so that it
-// reads rows of 128 bytes and completes the 128-byte lines of the packed records.
+// of values, one 16-byte slot of the packed record.  A workgroup takes 2^wbits words of 128 >> wbits rows.  Where
+// there are packed records, 4 words x 32 rows: it reads rows of 128 bytes and completes the 128-byte lines of the
+// records.  Without them, 32 words x 4 rows: a row that starts inside a line then shares far fewer lines with
+// workgroups of other XCDs (4096 x 8190 at 1:2:7, us per call: 81 with 4 words, 60 with 32, three copies and a check 72).
 // Checked is what the gather and the matrix instruction rely on -- column ids strictly increasing
 // and below M (once per block), the two m-indices of a nibble ordered idx0 < idx1, unused nibbles of
 // the last metadata word zero.
 // 8192 x 8192 at M = 8 (120 MB in and out): 28 us, 4.2 TB/s; three copies, the check and the packing by
 // themselves took 90 us.
-// aligned: rows of `values` and of its copy start on 16-byte boundaries.
 __global__ void __launch_bounds__(256) import_kernel(const u32_any* __restrict__ values, const u16_any* __restrict__ columns,
-                                                     const u32_any* __restrict__ meta, int64_t R, int aligned, FormatDst d,
+                                                     const u32_any* __restrict__ meta, int64_t R, int wbits, FormatDst d,
                                                      unsigned long long* status) {
-  const int64_t wq = (d.W + 3) / 4;
+  const int64_t wq = (d.W + (1 << wbits) - 1) >> wbits;
+  const int rows = 128 >> wbits;                   // of the workgroup
   const int64_t rblk = blockIdx.x / wq, wblk = blockIdx.x - rblk * wq;
-  const int u = threadIdx.x & 7, h = u & 1;        // eight lanes read 128 bytes of a row
-  const int64_t w = wblk * 4 + (u >> 1), r = rblk * 32 + (threadIdx.x >> 3);
+  const int u = threadIdx.x & ((2 << wbits) - 1), h = u & 1, i = threadIdx.x >> (wbits + 1);
+  const int64_t w = (wblk << wbits) + (u >> 1), r = rblk * rows + i;
   if (w >= d.W || r >= R) return;
-  const int64_t cb0 = rblk * 32 / d.V;             // of the workgroup's first row: a scalar division
-  const int v0 = (int)(rblk * 32 - cb0 * d.V) + (int)(threadIdx.x >> 3);
+  const int64_t cb0 = rblk * rows / d.V;           // of the workgroup's first row: a scalar division
+  const int v0 = (int)(rblk * rows - cb0 * d.V) + i;
   const int down = v0 >= d.V ? v0 / d.V : 0;
   const int64_t cb = cb0 + down;
   const int v = v0 - down * d.V;
@@ -346,10 +350,10 @@ __global__ void __launch_bounds__(256) import_kernel(const u32_any* __restrict__
   uint32_t x[4] = {0, 0, 0, 0};
   const u32_any* src = values + r * d.G + g;
   uint32_t* dst = d.values + r * d.G + g;
-  if (aligned && ng == 4) {
-    const uint4 q = *reinterpret_cast<const uint4*>(src);
+  if (ng == 4) {                                   // wide also where G is no multiple of 4 (rows start at any word)
+    const u32x4_any q = *reinterpret_cast<const u32x4_any*>(src);
     x[0] = q.x; x[1] = q.y; x[2] = q.z; x[3] = q.w;
-    *reinterpret_cast<uint4*>(dst) = q;
+    *reinterpret_cast<u32x4_word*>(dst) = q;
   } else {
 #pragma unroll
     for (int e = 0; e < 4; ++e)
@@ -472,10 +476,14 @@ hipError_t launch_import(const uint16_t* values, const uint16_t* columns, const 
   const Layout& L = h.lay;
   auto* status = reinterpret_cast<unsigned long long*>(h.ws + L.off_status);
   hipLaunchKernelGGL(init_status_kernel, dim3(1), dim3(1), 0, st, status);
-  if (L.R > 0 && L.G > 0)
-    hipLaunchKernelGGL(import_kernel, dim3((unsigned)(((L.W + 3) / 4) * ((L.R + 31) / 32))), dim3(256), 0, st,
-                       reinterpret_cast<const u32_any*>(values), columns, meta, L.R,
-                       L.G % 4 == 0 && reinterpret_cast<uintptr_t>(values) % 16 == 0, format_dst(h), status);
+  if (L.R > 0 && L.G > 0) {
+    // 32 rows x 4 words where there are packed records; otherwise longer pieces of fewer rows, as the rows are
+    int wbits = 2;
+    while (!L.packed && wbits < 5 && (1 << wbits) < L.W) ++wbits;
+    const int64_t words = (L.W + (1 << wbits) - 1) >> wbits, rows = 128 >> wbits;
+    hipLaunchKernelGGL(import_kernel, dim3((unsigned)(words * ((L.R + rows - 1) / rows))), dim3(256), 0, st,
+                       reinterpret_cast<const u32_any*>(values), columns, meta, L.R, wbits, format_dst(h), status);
+  }
   return hipGetLastError();
 }
 
