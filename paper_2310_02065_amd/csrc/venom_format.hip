@@ -409,10 +409,11 @@ __device__ __forceinline__ uint32_t divide(uint32_t n, Divisor d) { return __umu
 template <bool WIDE>
 __global__ void __launch_bounds__(256) decompress_kernel(const char* __restrict__ arec,
                                                          const int32_t* __restrict__ rowidx, int64_t K, int M, Divisor by_M,
-                                                         int64_t steps, int vt, int chunks, uint16_t* __restrict__ A,
-                                                         int64_t lda) {
-  const int64_t rt = blockIdx.x / (unsigned)chunks;              // 32-row tile of the matrix
-  const unsigned chunk = blockIdx.x - (unsigned)rt * (unsigned)chunks;
+                                                         int64_t steps, int vt, int chunks, int64_t rt0,
+                                                         uint16_t* __restrict__ A, int64_t lda) {
+  const unsigned rtl = blockIdx.x / (unsigned)chunks;
+  const unsigned chunk = blockIdx.x - rtl * (unsigned)chunks;
+  const int64_t rt = rt0 + rtl;                                  // 32-row tile of the matrix
   const int64_t b = rt / vt;
   const int tile = (int)(rt - b * vt);
   const int i = threadIdx.x >> 3;
@@ -516,10 +517,18 @@ hipError_t launch_decompress(const venom_handle& h, uint16_t* A, int64_t lda, hi
   if (L.R == 0 || L.K == 0) return hipSuccess;
   const int64_t chunks = (L.K + 255) / 256;
   auto fn = (reinterpret_cast<uintptr_t>(A) % 16 == 0 && lda % 8 == 0) ? decompress_kernel<true> : decompress_kernel<false>;
-  hipLaunchKernelGGL(fn, dim3((unsigned)(L.R / kTileRows * chunks)), dim3(256), 0, st, h.ws + L.off_arec,
-                     reinterpret_cast<const int32_t*>(h.ws + L.off_rowidx), L.K, h.M, make_divisor((uint32_t)h.M), L.steps, L.vt,
-                     (int)chunks, A, lda);
-  return hipGetLastError();
+  // a launch holds fewer than 2^32 threads, 256 per workgroup however few columns there are: tall narrow matrices
+  // take several
+  const int64_t tiles = L.R / kTileRows, most = kMaxBlocks / chunks;
+  for (int64_t rt0 = 0; rt0 < tiles; rt0 += most) {
+    const int64_t n = tiles - rt0 < most ? tiles - rt0 : most;
+    hipLaunchKernelGGL(fn, dim3((unsigned)(n * chunks)), dim3(256), 0, st, h.ws + L.off_arec,
+                       reinterpret_cast<const int32_t*>(h.ws + L.off_rowidx), L.K, h.M, make_divisor((uint32_t)h.M), L.steps,
+                       L.vt, (int)chunks, rt0, A, lda);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace venom

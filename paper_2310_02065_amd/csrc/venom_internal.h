@@ -16,6 +16,8 @@ constexpr int kStepRows = kStepGroups * kSelCols;  // gathered rows of B per k-s
 constexpr int kTileValBytes = 1024;                // packed values of one 32-row tile for one k-step
 constexpr int kMaxTiles = 4;                       // the product kernel serves V = 32, 64, 96, 128
 constexpr int kTailBytes = 512;                    // record tail: the index words, 64 lanes x 4 tiles x 16 bits
+constexpr int64_t kMaxBlocks = (1 << 24) - 1;      // most workgroups of 256 threads along x: a launch holds fewer than
+                                                   // 2^32 threads there
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 

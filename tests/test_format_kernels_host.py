@@ -129,3 +129,21 @@ def check_import(L, R, K, V, M, *offsets):
 ])
 def test_import(library, R, K, V, M, offsets):
     in_child(library, "check_import", R, K, V, M, *offsets)
+
+
+def check_decompress_launch(L, R, K, V, M):
+    L.host_dry_run(1)
+    assert L.host_decompress(R, K, V, M, 0, 0, K) == 0
+    assert L.host_blocks() == R // 32 * ((K + 255) // 256)
+    if R * K < 2**31:
+        assert L.host_launches() == 1
+
+
+@pytest.mark.parametrize("R,K,V,M", [
+    (2**29, 4, 2**14, 4),            # one column chunk per row: as many workgroups as the launch limit and one more
+    (2**30 - 2**15, 4, 2**14, 4),    # the tallest such matrix
+    (128, 2**31 - 32, 128, 32),      # 2^23 column chunks per row
+    (8192, 8192, 64, 8),
+])
+def test_decompress_launches_within_limits(library, R, K, V, M):
+    in_child(library, "check_decompress_launch", R, K, V, M)
