@@ -354,7 +354,8 @@ hipError_t launch_prune(const uint16_t* A, int64_t lda, int64_t R, int64_t K, in
   if (kept_mass || total_mass)
     hipLaunchKernelGGL(zero_u64_kernel, dim3((unsigned)((Rb + 255) / 256)), dim3(256), 0, st, kept_mass, total_mass, Rb);
   if (Rb == 0 || G == 0) return hipGetLastError();
-  const int tiled = tile_groups(V, M);
+  int tiled = tile_groups(V, M);
+  if (tiled > 0 && (G + tiled - 1) / tiled > kMaxBlocks) tiled = 0;   // too many workgroups for a launch (K near 2^31)
   int gpw = tiled > 0 ? tiled : kPruneMaxCols / M;
   if (tiled == 0 && gpw > kStepGroups) gpw = kStepGroups;
   if (gpw < 1) gpw = 1;

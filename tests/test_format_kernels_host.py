@@ -147,3 +147,18 @@ def check_decompress_launch(L, R, K, V, M):
 ])
 def test_decompress_launches_within_limits(library, R, K, V, M):
     in_child(library, "check_decompress_launch", R, K, V, M)
+
+
+def check_prune_launch(L, R, K, V, M):
+    L.host_dry_run(1)
+    assert L.host_prune(0, K, R, K, V, M, 0, K, 0, 0) == 0
+    assert L.host_launches() == 1
+
+
+@pytest.mark.parametrize("R,K,V,M", [
+    (1, 2**31 - 32, 1, 32),          # 128 columns per workgroup would be 2^24 workgroups
+    (32, 2**31 - 64, 32, 64),
+    (1, 2**31 - 128, 1, 128),        # 2^24 - 1
+])
+def test_prune_launches_within_limits(library, R, K, V, M):
+    in_child(library, "check_prune_launch", R, K, V, M)
