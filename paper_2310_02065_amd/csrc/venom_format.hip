@@ -107,6 +107,7 @@ __device__ __forceinline__ uint32_t nonzero_bits(uint32_t x) {
 // compiler emits the same single loads for these types as for the aligned ones.
 typedef uint32_t u32_any __attribute__((aligned(1)));
 typedef uint16_t u16_any __attribute__((aligned(1)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(1)));
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
 typedef uint32_t u32x4_word __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -119,7 +120,7 @@ __host__ __device__ constexpr int bits_pitch(int wpw, int M) { return (wpw * M +
 
 // Dense + mask -> canonical arrays and packed copies.  One workgroup per (block row b, `wpw` metadata
 // words) = V rows x 8*wpw groups x M columns.
-//   phase 1: the mask is read once, UB bytes at a time (16, 8 or, unaligned, 1), and kept in LDS as one bit
+//   phase 1: the mask is read once, UB bytes at a time (16 or 8, at any alignment), and kept in LDS as one bit
 //            per column and row; the bits of all rows together say which columns the block uses
 //   phase 2: one thread per group picks the 4 columns: the used ones ascending, padded with the
 //            smallest unused ids, sorted
@@ -148,53 +149,51 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
   const int pitch = bits_pitch(wpw, M);
   const uint8_t* mblk = mask + b * V * ldm + g0 * M;
 
-  const int units = UB > 1 ? span / UB : 0, tail0 = units * (UB > 1 ? UB : 0), tail = span - tail0;
+  const int units = span / UB, tail0 = units * UB, tail = span - tail0;
   for (int i = tid; i < (span + 31) / 32 + 1; i += 256) used[i] = 0;
   if (bits_ok && tail > 0)                       // the columns of the byte loop are set bit by bit
     for (int i = tid; i < V * pitch / 4; i += 256) reinterpret_cast<uint32_t*>(bits)[i] = 0;
   __syncthreads();
-  if constexpr (UB > 1) {
-    // row slices working side by side; no unit at all where a padded mask's last columns are fewer than a load takes
-    const int slices = units > 0 && units < 256 ? 256 / units : 1;
-    for (int u0 = 0; u0 < units; u0 += 256) {                             // (more than 256 units: several sweeps)
-      const int u = u0 + (slices > 1 ? tid % units : tid);
-      const int slice = slices > 1 ? tid / units : 0;
-      if (u < units && slice < slices) {
-        uint32_t seen = 0;
-        const uint8_t* p = mblk + UB * u;
-        constexpr int NL = 8;                    // loads in flight per thread
-        for (int v0 = slice; v0 < V; v0 += NL * slices) {
-          uint32_t x[NL][UB / 4];
+  // row slices working side by side; no unit at all where a padded mask's last columns are fewer than a load takes
+  const int slices = units > 0 && units < 256 ? 256 / units : 1;
+  for (int u0 = 0; u0 < units; u0 += 256) {                               // (more than 256 units: several sweeps)
+    const int u = u0 + (slices > 1 ? tid % units : tid);
+    const int slice = slices > 1 ? tid / units : 0;
+    if (u < units && slice < slices) {
+      uint32_t seen = 0;
+      const uint8_t* p = mblk + UB * u;
+      constexpr int NL = 8;                      // loads in flight per thread
+      for (int v0 = slice; v0 < V; v0 += NL * slices) {
+        uint32_t x[NL][UB / 4];
 #pragma unroll
-          for (int j = 0; j < NL; ++j) {
-            const int v = v0 + j * slices;
+        for (int j = 0; j < NL; ++j) {
+          const int v = v0 + j * slices;
 #pragma unroll
-            for (int e = 0; e < UB / 4; ++e) x[j][e] = 0;
-            if (v < V) {
-              if constexpr (UB == 16) {
-                const uint4 q = *reinterpret_cast<const uint4*>(p + (int64_t)v * ldm);
-                x[j][0] = q.x; x[j][1] = q.y; x[j][2] = q.z; x[j][3] = q.w;
-              } else {
-                const uint2 q = *reinterpret_cast<const uint2*>(p + (int64_t)v * ldm);
-                x[j][0] = q.x; x[j][1] = q.y;
-              }
-            }
-          }
-#pragma unroll
-          for (int j = 0; j < NL; ++j) {
-            const int v = v0 + j * slices;
-            uint32_t m = 0;
-#pragma unroll
-            for (int e = 0; e < UB / 4; ++e) m |= nonzero_bits(x[j][e]) << (4 * e);
-            seen |= m;
-            if (bits_ok && v < V) {
-              if constexpr (UB == 16) *reinterpret_cast<uint16_t*>(bits + v * pitch + 2 * u) = (uint16_t)m;
-              else bits[v * pitch + u] = (uint8_t)m;
+          for (int e = 0; e < UB / 4; ++e) x[j][e] = 0;
+          if (v < V) {
+            if constexpr (UB == 16) {
+              const u32x4_any q = *reinterpret_cast<const u32x4_any*>(p + (int64_t)v * ldm);
+              x[j][0] = q.x; x[j][1] = q.y; x[j][2] = q.z; x[j][3] = q.w;
+            } else {
+              const u32x2_any q = *reinterpret_cast<const u32x2_any*>(p + (int64_t)v * ldm);
+              x[j][0] = q.x; x[j][1] = q.y;
             }
           }
         }
-        if (seen) atomicOr(&used[u * UB / 32], seen << (u * UB % 32));
+#pragma unroll
+        for (int j = 0; j < NL; ++j) {
+          const int v = v0 + j * slices;
+          uint32_t m = 0;
+#pragma unroll
+          for (int e = 0; e < UB / 4; ++e) m |= nonzero_bits(x[j][e]) << (4 * e);
+          seen |= m;
+          if (bits_ok && v < V) {
+            if constexpr (UB == 16) *reinterpret_cast<uint16_t*>(bits + v * pitch + 2 * u) = (uint16_t)m;
+            else bits[v * pitch + u] = (uint8_t)m;
+          }
+        }
       }
+      if (seen) atomicOr(&used[u * UB / 32], seen << (u * UB % 32));
     }
   }
   for (int64_t i = tid; i < (int64_t)V * tail; i += 256) {
@@ -502,11 +501,7 @@ hipError_t launch_compress(const uint16_t* A, int64_t lda, const uint8_t* mask, 
     const int bits_ok = bit_bytes <= kCompressBits;
     const size_t lds = bits_ok ? (size_t)bit_bytes : 0;
     const dim3 grid((unsigned)((L.W + wpw - 1) / wpw), (unsigned)L.Rb);
-    // wide mask loads need every chunk of 8*wpw groups of every row to start on such a boundary
-    const uintptr_t ma = reinterpret_cast<uintptr_t>(mask);
-    const int64_t chunk = (int64_t)8 * wpw * h.M;
-    auto fn = (chunk % 16 == 0 && ldm % 16 == 0 && ma % 16 == 0) ? compress_kernel<16>
-              : (ldm % 8 == 0 && ma % 8 == 0) ? compress_kernel<8> : compress_kernel<1>;
+    auto fn = (int64_t)8 * wpw * h.M % 16 == 0 ? compress_kernel<16> : compress_kernel<8>;   // every chunk of columns in whole loads
     hipLaunchKernelGGL(fn, grid, dim3(256), lds, st, A, lda, mask, ldm, wpw, bits_ok, format_dst(h), status);
   }
   return hipGetLastError();

@@ -93,7 +93,8 @@ def check_compress(L, R, K, V, M, ldm, offset):
     (64, 45, 32, 5, 48, 8),          # 8-byte loads, likewise
     (64, 60, 32, 4, 64, 0),          # a last word that is a whole load and a remainder
     (64, 92, 32, 4, 96, 8),          # the same with 8-byte loads
-    (64, 45, 32, 5, 45, 1),          # rows at every alignment
+    (64, 45, 32, 5, 45, 1), (64, 60, 32, 4, 61, 3),   # rows at every alignment, both load widths
+    (8192, 45, 8192, 5, 45, 2),      # ... and a block too tall for bits on chip
 ])
 def test_compress(library, R, K, V, M, ldm, offset):
     in_child(library, "check_compress", R, K, V, M, ldm, offset)
