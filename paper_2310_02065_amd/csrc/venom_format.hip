@@ -1,6 +1,8 @@
 // Format kernels: dense + mask -> canonical V:N:M arrays (section 3 of the paper), canonical ->
 // the product kernel's packed copies, and packed -> dense (the format read backwards).
 // Pure data movement: fp16 payloads are handled as 16-bit patterns and never interpreted.
+#include <type_traits>
+
 #include "venom_internal.h"
 
 namespace venom {
@@ -113,7 +115,7 @@ typedef uint32_t u32x4_word __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int kMaxM = 1024;
 constexpr int kCompressWords = 4;                // most metadata words (8 groups each) one workgroup takes
-constexpr int kCompressBits = 32 * 1024;         // most LDS for the mask bits of a workgroup's rows
+constexpr int kCompressBits = 48 * 1024;         // most LDS for the mask bits of a workgroup's rows
 
 // bytes per row of mask bits in LDS, with a word of padding
 __host__ __device__ constexpr int bits_pitch(int wpw, int M) { return (wpw * M + 3) / 4 * 4 + 4; }
@@ -130,10 +132,14 @@ __host__ __device__ constexpr int bits_pitch(int wpw, int M) { return (wpw * M +
 // Bound by memory: 49152 x 12288 at M = 32 (0.6 GB of mask, 1.2 GB of A -- the two kept values of 32
 // touch every 64-byte sector -- and 0.17 GB written) takes 0.42 ms, 4.7 TB/s; it was 0.45 ms, and another
 // 0.08 ms to pack in a second pass, when phase 3 fetched the mask bytes again one by one.
-// bits_ok: the bits of V rows fit; otherwise (very tall blocks) phase 3 reads the mask again.
+// by_full, by_last: n / units = n * by >> 16 for n, units <= 256, for the loads of a row in all chunks of columns but the
+// last, and in the last (a division in the kernel is 5 % of a workgroup with one row).
+// bits_ok: the bits of V rows fit (48 KB of LDS: 49152 x 12288 at 1024:2:32 takes 464 us a call, 653 if phase 3 reads the
+// mask again); otherwise (very tall blocks) it does.
 template <int UB>
 __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                        const uint8_t* __restrict__ mask, int64_t ldm, int wpw, int bits_ok,
+                                                       unsigned by_full, unsigned by_last,
                                                        FormatDst d, unsigned long long* status) {
   extern __shared__ __attribute__((aligned(16))) uint8_t bits[];   // [row][pitch]
   __shared__ uint32_t used[kCompressWords * 8 * kMaxM / 32 + 1];
@@ -155,15 +161,16 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
     for (int i = tid; i < V * pitch / 4; i += 256) reinterpret_cast<uint32_t*>(bits)[i] = 0;
   __syncthreads();
   // row slices working side by side; no unit at all where a padded mask's last columns are fewer than a load takes
-  const int slices = units > 0 && units < 256 ? 256 / units : 1;
+  const unsigned by_units = (int)blockIdx.x + 1 < (int)gridDim.x ? by_full : by_last;
+  const int slices = units > 0 && units < 256 ? (int)(256 * by_units >> 16) : 1;
   for (int u0 = 0; u0 < units; u0 += 256) {                               // (more than 256 units: several sweeps)
-    const int u = u0 + (slices > 1 ? tid % units : tid);
-    const int slice = slices > 1 ? tid / units : 0;
+    const int slice = slices > 1 ? (int)(tid * by_units >> 16) : 0;
+    const int u = u0 + tid - slice * units;
     if (u < units && slice < slices) {
       uint32_t seen = 0;
       const uint8_t* p = mblk + UB * u;
-      constexpr int NL = 8;                      // loads in flight per thread
-      for (int v0 = slice; v0 < V; v0 += NL * slices) {
+      auto rows = [&](int v0, auto in_flight) {  // rows v0, v0 + slices, ..., their loads in flight together
+        constexpr int NL = decltype(in_flight)::value;
         uint32_t x[NL][UB / 4];
 #pragma unroll
         for (int j = 0; j < NL; ++j) {
@@ -192,7 +199,11 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
             else bits[v * pitch + u] = (uint8_t)m;
           }
         }
-      }
+      };
+      // short rows or few of them: one load each (1048576 x 32 at 128:2:8: 90 us a call with eight slots, 82 with one)
+      if (V <= slices) rows(slice, std::integral_constant<int, 1>{});
+      else
+        for (int v0 = slice; v0 < V; v0 += 8 * slices) rows(v0, std::integral_constant<int, 8>{});
       if (seen) atomicOr(&used[u * UB / 32], seen << (u * UB % 32));
     }
   }
@@ -245,11 +256,15 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
   const int64_t rec_bytes = (int64_t)d.vt * kTileValBytes + kTailBytes;
   const int NG = 8 * nw;                         // lanes of a row (a multiple of 8)
   const int total = V * NG;
+  auto row_of = [&](int i) {                     // i / NG, nw <= 4: no division
+    const int q = i >> 3;
+    return nw == 1 ? q : nw == 2 ? q >> 1 : nw == 4 ? q >> 2 : q / 3;
+  };
   for (int base = 0; base < total; base += 256 * NE) {
     uint32_t v01[NE], nib[NE];
 #pragma unroll
     for (int j = 0; j < NE; ++j) {
-      const int i = base + 256 * j + tid, v = i / NG, tg = i - v * NG;
+      const int i = base + 256 * j + tid, v = row_of(i), tg = i - v * NG;
       nib[j] = 0; v01[j] = 0;
       if (i < total && tg < ng) {
         const ushort4 c4 = sel[tg];
@@ -282,7 +297,7 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
     }
 #pragma unroll
     for (int j = 0; j < NE; ++j) {
-      const int i = base + 256 * j + tid, v = i / NG, tg = i - v * NG;
+      const int i = base + 256 * j + tid, v = row_of(i), tg = i - v * NG;
       uint32_t word = nib[j];
       word |= __shfl_xor(word, 1);
       word |= __shfl_xor(word, 2);
@@ -496,13 +511,18 @@ hipError_t launch_compress(const uint16_t* A, int64_t lda, const uint8_t* mask, 
     // as many words per workgroup as leave eight workgroups per compute unit (rows of `values` are then written in
     // longer pieces) and the mask bits within LDS
     int wpw = kCompressWords;
-    while (wpw > 1 && (((L.W + wpw - 1) / wpw) * L.Rb < 2048 || (int64_t)h.V * bits_pitch(wpw, h.M) > kCompressBits / 2)) wpw /= 2;
+    while (wpw > 1 && (((L.W + wpw - 1) / wpw) * L.Rb < 2048 || (int64_t)h.V * bits_pitch(wpw, h.M) > 16 * 1024)) wpw /= 2;
     const int64_t bit_bytes = (int64_t)h.V * bits_pitch(wpw, h.M);
     const int bits_ok = bit_bytes <= kCompressBits;
     const size_t lds = bits_ok ? (size_t)bit_bytes : 0;
     const dim3 grid((unsigned)((L.W + wpw - 1) / wpw), (unsigned)L.Rb);
-    auto fn = (int64_t)8 * wpw * h.M % 16 == 0 ? compress_kernel<16> : compress_kernel<8>;   // every chunk of columns in whole loads
-    hipLaunchKernelGGL(fn, grid, dim3(256), lds, st, A, lda, mask, ldm, wpw, bits_ok, format_dst(h), status);
+    auto by = [](int64_t n) { return n > 0 ? (unsigned)((65535 + n) / n) : 0u; };
+    // every chunk of columns in whole loads, fewer than 8 columns left over at the end of a row
+    const int64_t chunk = (int64_t)8 * wpw * h.M, last = L.K - (grid.x - 1) * chunk;
+    const int ub = chunk % 16 == 0 && L.K % 16 < 8 ? 16 : 8;
+    auto fn = ub == 16 ? compress_kernel<16> : compress_kernel<8>;
+    hipLaunchKernelGGL(fn, grid, dim3(256), lds, st, A, lda, mask, ldm, wpw, bits_ok, by(chunk / ub), by(last / ub), format_dst(h),
+                       status);
   }
   return hipGetLastError();
 }
