@@ -105,14 +105,6 @@ __device__ __forceinline__ uint32_t nonzero_bits(uint32_t x) {
   return ((top >> 7) * 0x10204080u) >> 28;       // byte e's flag to bit e
 }
 
-// Words of arrays that come from outside at any address: global accesses need no alignment on this target, and the
-// compiler emits the same single loads for these types as for the aligned ones.
-typedef uint32_t u32_any __attribute__((aligned(1)));
-typedef uint16_t u16_any __attribute__((aligned(1)));
-typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(1)));
-typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
-typedef uint32_t u32x4_word __attribute__((ext_vector_type(4), aligned(4)));
-
 constexpr int kMaxM = 1024;
 constexpr int kCompressWords = 4;                // most metadata words (8 groups each) one workgroup takes
 constexpr int kCompressBits = 48 * 1024;         // most LDS for the mask bits of a workgroup's rows

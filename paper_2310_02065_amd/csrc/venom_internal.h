@@ -19,6 +19,14 @@ constexpr int kTailBytes = 512;                    // record tail: the index wor
 constexpr int64_t kMaxBlocks = (1 << 24) - 1;      // most workgroups of 256 threads along x: a launch holds fewer than
                                                    // 2^32 threads there
 
+// Words of arrays that come from outside at any address: global accesses need no alignment on this target, and the
+// compiler emits the same single loads for these types as for the aligned ones.
+typedef uint32_t u32_any __attribute__((aligned(1)));
+typedef uint16_t u16_any __attribute__((aligned(1)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(1)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+typedef uint32_t u32x4_word __attribute__((ext_vector_type(4), aligned(4)));
+
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Where each array lives inside the caller's workspace (byte offsets, all 256-byte aligned).

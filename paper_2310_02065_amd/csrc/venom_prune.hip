@@ -181,7 +181,8 @@ __device__ __forceinline__ unsigned long long mass_units(double biased) {
 }
 
 // The same pruning with the block's tile (V rows x `gpw` groups) held in LDS, so that the matrix is
-// read once, in 16-byte pieces, and the second pass (4 scattered 2-byte reads per row and group)
+// read once, in 16-byte pieces at any alignment (12288 x 8190 at 128:2:10: 114 us; 299 when rows off the 16-byte
+// boundaries went element by element, 256 in prune_kernel), and the second pass (4 scattered 2-byte reads per row and group)
 // stays on chip.  Column choice: for M up to 64 a thread per column counts the columns that beat
 // its own (all threads of a group read the same masses: broadcasts), above that a wave per group
 // takes the maximum four times.
@@ -195,7 +196,7 @@ __host__ __device__ constexpr int tile_pitch(int cols) { return (cols * 2 + 15) 
 constexpr int64_t tile_lds(int V, int cols) { return (int64_t)V * tile_pitch(cols) + 8 * cols; }
 
 __global__ void __launch_bounds__(256) prune_tile_kernel(const uint16_t* __restrict__ A, int64_t lda, int V, int M,
-                                                         int64_t G, int gpw, int vec_ok, int mask_word,
+                                                         int64_t G, int gpw, int mask_word,
                                                          uint8_t* __restrict__ mask, int64_t ldm,
                                                          unsigned long long* __restrict__ kept_mass,
                                                          unsigned long long* __restrict__ total_mass) {
@@ -214,7 +215,7 @@ __global__ void __launch_bounds__(256) prune_tile_kernel(const uint16_t* __restr
   if (tid == 0) { wg_total = 0; wg_kept = 0; }
   __syncthreads();
   unsigned long long my_total = 0;
-  const int units = vec_ok ? span / 8 : 0;         // 8-column units: at most 128
+  const int units = span / 8;                      // 8-column units: at most 128
   if (units > 0) {
     const int slices = 256 / units, u = tid % units, slice = tid / units;   // row slices working side by side
     if (slice < slices) {
@@ -223,16 +224,16 @@ __global__ void __launch_bounds__(256) prune_tile_kernel(const uint16_t* __restr
       for (int e = 0; e < 8; ++e) m8[e] = kMassBias;
       constexpr int NL = 8;                        // loads in flight per thread
       for (int v0 = slice; v0 < V; v0 += NL * slices) {
-        uint4 w[NL];
+        u32x4_any w[NL];
 #pragma unroll
         for (int j = 0; j < NL; ++j) {
           const int v = v0 + j * slices;
-          w[j] = v < V ? *reinterpret_cast<const uint4*>(blk + (int64_t)v * lda + 8 * u) : make_uint4(0, 0, 0, 0);
+          w[j] = v < V ? *reinterpret_cast<const u32x4_any*>(blk + (int64_t)v * lda + 8 * u) : u32x4_any{0, 0, 0, 0};
         }
 #pragma unroll
         for (int j = 0; j < NL; ++j) {
           const int v = v0 + j * slices;
-          if (v < V) *reinterpret_cast<uint4*>(tile + v * pitch + u * 16) = w[j];
+          if (v < V) *reinterpret_cast<uint4*>(tile + v * pitch + u * 16) = make_uint4(w[j].x, w[j].y, w[j].z, w[j].w);
           const uint32_t ws[4] = {w[j].x, w[j].y, w[j].z, w[j].w};
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
@@ -368,7 +369,7 @@ hipError_t launch_prune(const uint16_t* A, int64_t lda, int64_t R, int64_t K, in
                         : (M % 4 == 0 && ldm % 4 == 0 && ma % 4 == 0) ? 4 : 1;
   if (tiled > 0)
     hipLaunchKernelGGL(prune_tile_kernel, dim3((unsigned)chunks, (unsigned)Rb), dim3(256), (size_t)tile_lds(V, gpw * M), st,
-                       A, lda, V, M, G, gpw, vec_ok, mask_word, mask, ldm, kept_mass, total_mass);
+                       A, lda, V, M, G, gpw, mask_word, mask, ldm, kept_mass, total_mass);
   else
     hipLaunchKernelGGL(prune_kernel, dim3((unsigned)chunks, (unsigned)Rb), dim3(256), 0, st, A, lda, V, M, G, gpw, vec_ok,
                        mask_word, mask, ldm, kept_mass, total_mass);

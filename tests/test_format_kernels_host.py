@@ -163,3 +163,24 @@ def check_prune_launch(L, R, K, V, M):
 ])
 def test_prune_launches_within_limits(library, R, K, V, M):
     in_child(library, "check_prune_launch", R, K, V, M)
+
+
+def check_prune(L, R, K, V, M, lda, offset):
+    A, _ = problem(R, K, V, M)
+    a = pitched(A, lda, offset)
+    mask = pitched(np.full((R, K), 7, np.uint8), K + 3)
+    kept, total = np.zeros(R // V, np.uint64), np.zeros(R // V, np.uint64)
+    assert L.host_prune(a.ctypes.data, lda, R, K, V, M, mask.ctypes.data, K + 3, kept.ctypes.data, total.ctypes.data) == 0
+    want, want_kept, want_total = o.prune(A, V, M)
+    assert np.array_equal(mask[:, :K], want) and (mask[:, K:] == 0xA5).all()
+    assert int(kept.sum()) == want_kept and int(total.sum()) == want_total
+
+
+@pytest.mark.parametrize("R,K,V,M,lda,offset", [
+    (64, 160, 32, 10, 160, 0),
+    (64, 170, 32, 10, 171, 2),       # rows at every 2-byte boundary, two columns left over
+    (64, 4, 32, 4, 5, 6),            # rows narrower than one load
+    (6, 210, 3, 7, 213, 14),
+])
+def test_prune(library, R, K, V, M, lda, offset):
+    in_child(library, "check_prune", R, K, V, M, lda, offset)
