@@ -339,12 +339,16 @@ __global__ void __launch_bounds__(256) prune_tile_kernel(const uint16_t* __restr
 }
 
 // Groups per workgroup of prune_tile_kernel, 0 if the shape is not its: rows of 256 bytes, in whole
-// 16-byte pieces (which at odd M takes several groups); fewer where four tiles would not share a compute unit.
+// 16-byte pieces (which at odd M takes several groups); more where a block has fewer than 32 rows, so that a
+// workgroup still holds 8 KB (4096 x 8192, us per call with 128 columns -> now, prune_kernel: 1:2:128 1227 -> 312, 960;
+// 16:2:64 104 -> 65, 101; 8:2:8 143 -> 63, 421), fewer where four tiles would not share a compute unit.
 static int tile_groups(int V, int M) {
   if (V > kTileMaxV) return 0;
   const int whole = M % 8 == 0 ? 1 : M % 4 == 0 ? 2 : M % 2 == 0 ? 4 : 8;
-  int n = (128 + M * whole - 1) / (M * whole);     // in units of `whole` groups
-  while (n > 1 && tile_lds(V, n * whole * M) > 38 * 1024) --n;
+  int cols = 128;
+  while (cols < kPruneMaxCols && V * cols < 4096) cols *= 2;
+  int n = (cols + M * whole - 1) / (M * whole);    // in units of `whole` groups
+  while (n > 1 && (tile_lds(V, n * whole * M) > 38 * 1024 || n * whole * M > kPruneMaxCols || n * whole > kTileMaxGroups)) --n;
   const int gpw = n * whole;
   return tile_lds(V, gpw * M) <= kTileLds - 2048 && gpw * M <= kPruneMaxCols && gpw <= kTileMaxGroups ? gpw : 0;
 }
