@@ -338,11 +338,17 @@ __global__ void __launch_bounds__(256) prune_tile_kernel(const uint16_t* __restr
   }
 }
 
+// Groups per workgroup of prune_kernel.
+static int general_groups(int M) {
+  const int gpw = kPruneMaxCols / M;
+  return gpw > kStepGroups ? kStepGroups : gpw < 1 ? 1 : gpw;
+}
+
 // Groups per workgroup of prune_tile_kernel, 0 if the shape is not its: rows of 256 bytes, in whole
 // 16-byte pieces (which at odd M takes several groups); more where a block has fewer than 32 rows, so that a
 // workgroup still holds 8 KB (4096 x 8192, us per call with 128 columns -> now, prune_kernel: 1:2:128 1227 -> 312, 960;
 // 16:2:64 104 -> 65, 101; 8:2:8 143 -> 63, 421), fewer where four tiles would not share a compute unit.
-static int tile_groups(int V, int M) {
+static int tile_groups(int V, int M, bool general_wide) {
   if (V > kTileMaxV) return 0;
   const int whole = M % 8 == 0 ? 1 : M % 4 == 0 ? 2 : M % 2 == 0 ? 4 : 8;
   int cols = 128;
@@ -350,6 +356,15 @@ static int tile_groups(int V, int M) {
   int n = (cols + M * whole - 1) / (M * whole);    // in units of `whole` groups
   while (n > 1 && (tile_lds(V, n * whole * M) > 38 * 1024 || n * whole * M > kPruneMaxCols || n * whole > kTileMaxGroups)) --n;
   const int gpw = n * whole;
+  // A tall block leaves the tile few columns, pieces of rows too short to read well.  prune_kernel, which takes
+  // `general` columns but reads the matrix twice, is then the better one where it reads in wide loads, unless the
+  // blocks are too large for its second pass to find them in the cache.  12288 x 8192, us per call, tile / prune_kernel,
+  // with the tile's columns: 320:2:8 48 105 / 122; 384:2:8 40 119 / 115; 384:2:4 40 130 / 185 (general = 32);
+  // 640:2:4 16 193 / 179; 512:2:16 16 192 / 92; 1024:2:8 8 384 / 110; 384:2:32 32 118 / 107; 512:2:32 32 111 / 123;
+  // 640:2:24 24 162 / 143.  At 12288 x 8190 (prune_kernel by single elements) 640:2:10 40 166 / 241;
+  // 896:2:6 24 202 / 296.
+  const int general = general_groups(M) * M, enough = general * 3 / 4 < 48 ? general * 3 / 4 : 48;
+  if (general_wide && gpw * M < enough && !(M >= 32 && M * V >= 14336)) return 0;
   return tile_lds(V, gpw * M) <= kTileLds - 2048 && gpw * M <= kPruneMaxCols && gpw <= kTileMaxGroups ? gpw : 0;
 }
 
@@ -359,14 +374,12 @@ hipError_t launch_prune(const uint16_t* A, int64_t lda, int64_t R, int64_t K, in
   if (kept_mass || total_mass)
     hipLaunchKernelGGL(zero_u64_kernel, dim3((unsigned)((Rb + 255) / 256)), dim3(256), 0, st, kept_mass, total_mass, Rb);
   if (Rb == 0 || G == 0) return hipGetLastError();
-  int tiled = tile_groups(V, M);
+  // prune_kernel's wide loads need every chunk of every row of A to start on a 16-byte boundary
+  const int vec_ok = ((int64_t)general_groups(M) * M) % 8 == 0 && lda % 8 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0;
+  int tiled = tile_groups(V, M, vec_ok);
   if (tiled > 0 && (G + tiled - 1) / tiled > kMaxBlocks) tiled = 0;   // too many workgroups for a launch (K near 2^31)
-  int gpw = tiled > 0 ? tiled : kPruneMaxCols / M;
-  if (tiled == 0 && gpw > kStepGroups) gpw = kStepGroups;
-  if (gpw < 1) gpw = 1;
+  const int gpw = tiled > 0 ? tiled : general_groups(M);
   const int64_t chunks = (G + gpw - 1) / gpw;
-  // wide loads need every chunk of every row of A to start on a 16-byte boundary
-  const int vec_ok = ((int64_t)gpw * M) % 8 == 0 && lda % 8 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0;
   // every (row, group) of the mask starts at row * ldm + group * M: the widest word that always divides that
   const uintptr_t ma = reinterpret_cast<uintptr_t>(mask);
   const int mask_word = (M % 16 == 0 && ldm % 16 == 0 && ma % 16 == 0) ? 16 : (M % 8 == 0 && ldm % 8 == 0 && ma % 8 == 0) ? 8

@@ -181,6 +181,9 @@ def check_prune(L, R, K, V, M, lda, offset):
     (64, 170, 32, 10, 171, 2),       # rows at every 2-byte boundary, two columns left over
     (64, 4, 32, 4, 5, 6),            # rows narrower than one load
     (6, 210, 3, 7, 213, 14),
+    (4, 1100, 2, 100, 1104, 0),      # few rows: a tile of 1000 columns, and one group
+    (640, 54, 640, 6, 55, 2),        # a tile of few columns where the general kernel would go by single elements
+    (896, 24, 896, 8, 24, 0),        # ... and where it would not: the general kernel
 ])
 def test_prune(library, R, K, V, M, lda, offset):
     in_child(library, "check_prune", R, K, V, M, lda, offset)
