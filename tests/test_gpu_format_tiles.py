@@ -1,6 +1,7 @@
 """Edges of the format kernels' tilings against the oracle, bit for bit: several metadata words per workgroup with a
-ragged last one, mask loads of every width, blocks too tall for on-chip mask bits or for the pruning
-tile, odd M, groups per row that are no multiple of 4, block heights that differ from the packed ones."""
+ragged last one, mask loads of both widths with columns left over, rows at every alignment, blocks too tall
+for on-chip mask bits or for the pruning tile, odd M, groups per row that are no multiple of 4, block heights
+that differ from the packed ones."""
 import numpy as np
 import pytest
 
@@ -14,10 +15,12 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("R,K,V,M,shift", [
-    (16384, 33 * 8, 64, 8, 0),       # 256 block rows x 5 words: several words per workgroup, the last with one group
+    (16384, 33 * 8, 64, 8, 0),       # 256 block rows x 5 words of which the last has one group: one word per workgroup
+    (65536, 17 * 8, 32, 8, 0),       # 2048 x 3: one workgroup takes all three words, the last with one group
+    (16384, 45 * 8, 8, 8, 0),        # 2048 x 6: four words per workgroup, then two, the last with five groups
     (4096, 130 * 32, 32, 32, 0),     # 128 block rows x 17 words, two groups in the last one
-    (192, 23 * 7, 96, 7, 0),         # odd M: 8-byte mask loads on rows of 161 bytes are not allowed
-    (128, 27 * 12, 64, 12, 8),       # mask rows on 8-byte boundaries only
+    (192, 23 * 7, 96, 7, 0),         # odd M: 8-byte mask loads on rows of 161 bytes
+    (128, 27 * 12, 64, 12, 8),       # 16-byte loads and four columns left over; mask rows on 4-byte boundaries
     (128, 27 * 12, 64, 12, 3),       # ... on none
     (1024, 8 * 64, 1024, 64, 0),     # the mask bits of a block do not fit LDS
     (2304, 64, 2304, 8, 0),          # taller than the pruning tile serves
@@ -55,6 +58,52 @@ def test_format_path_bit_exact(R, K, V, M, shift):
             binding.venom_decompress(x, out=big[:, 3:3 + K])
             assert torch.equal(big[:, 3:3 + K].contiguous().view(torch.int16), dense.view(torch.int16))
             assert bool((big[:, :3] == -7.0).all()) and bool((big[:, 3 + K:] == -7.0).all())
+
+
+@pytest.mark.parametrize("R,K,V,M,lda,ldm", [
+    (128, 9 * 4, 64, 4, 40, 48),     # the last word is narrower than a 16-byte load
+    (128, 15 * 4, 64, 4, 64, 64),    # ... is one load and 12 columns
+    (128, 9 * 5, 64, 5, 48, 56),     # ... narrower than the 8-byte loads of an odd chunk
+    (96, 13 * 10, 32, 10, 136, 130), # two columns left over, of A too
+    (96, 21 * 40, 32, 40, 840, 843), # K % 16 == 8
+    (640, 9 * 6, 640, 6, 55, 55),    # a tall block, rows at any boundary: a pruning tile of 24 columns
+    (1024, 9 * 16, 1024, 16, 144, 144),   # ... at 16-byte boundaries: the general kernel
+    (48, 11 * 100, 2, 100, 1104, 1100),   # blocks of few rows: tiles of ten groups, and one
+])
+def test_padded_rows_bit_exact(R, K, V, M, lda, ldm):
+    rng = np.random.default_rng(R + K)
+    bits = (rng.standard_normal((R, K)) * 0.05).astype(np.float16).view(np.uint16)
+    A = torch.full((R, lda), 9.0, dtype=torch.float16, device=DEV)
+    A[:, :K] = torch.from_numpy(bits.view(np.float16)).to(DEV)
+    pmask, kept, total = binding.venom_prune(A[:, :K], V, 2, M)
+    omask, okept, ototal = o.prune(bits, V, M)
+    assert np.array_equal(pmask.cpu().numpy(), omask)
+    assert sum(int(x) for x in kept.cpu().tolist()) == okept and sum(int(x) for x in total.cpu().tolist()) == ototal
+    mask = np.where(rng.random((R, K)) < 0.2, 0, inputs.gen_mask(R, K, V, M, rng)).astype(np.uint8)
+    wide = torch.full((R, ldm), 7, dtype=torch.uint8, device=DEV)
+    wide[:, :K] = torch.from_numpy(mask * rng.integers(1, 256, (R, K)).astype(np.uint8)).to(DEV)
+    h = binding.venom_compress(A[:, :K], wide[:, :K], V, 2, M)
+    for got, w in zip(binding.venom_export(h), o.compress(bits, mask, V, M)):
+        assert np.array_equal(got.cpu().numpy().view(w.dtype), w)
+
+
+def test_two_words_per_workgroup():
+    """The chunk of columns in between (2 words: mask bits of 4 would not fit) needs 107 million entries; the same block
+    rows compressed by themselves take one word at a time."""
+    V, M, G = 96, 64, 17
+    R, K = 1024 * V, G * M
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(7)
+    A = torch.randn(R, K, dtype=torch.float16, device=DEV, generator=gen)
+    mask, _, _ = binding.venom_prune(A, V, 2, M)
+    h = binding.venom_compress(A, mask, V, 2, M)
+    whole = binding.venom_export(h)
+    assert torch.equal(binding.venom_decompress(h), torch.where(mask != 0, A, 0))
+    for b in (0, 511, 1023):
+        rows = slice(b * V, (b + 1) * V)
+        values, columns, meta = binding.venom_export(binding.venom_compress(A[rows], mask[rows], V, 2, M))
+        assert torch.equal(whole[0][rows], values) and torch.equal(whole[1][b:b + 1], columns)
+        assert torch.equal(whole[2][rows], meta)
 
 
 @pytest.mark.parametrize("R,K,V,M,offset", [
