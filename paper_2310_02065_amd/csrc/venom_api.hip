@@ -42,8 +42,9 @@ venom_status_t check_shape(int64_t R, int64_t K, int V, int N, int M) {
   if (R % V != 0 || K % M != 0) return VENOM_ERR_SHAPE;
   if (M > 1024 || V >= (1 << 23)) return VENOM_ERR_UNSUPPORTED;
   if (K >= ((int64_t)1 << 31)) return VENOM_ERR_UNSUPPORTED;  // gathered row ids are 32-bit
-  // block rows ride on the y dimension of the compression grid; the element-wise format kernels
-  // number their threads with 32-bit block ids
+  // block rows ride on the y dimension of the compression and pruning grids; with R * K <= 2^38 the other grids
+  // (import: R/32 x K/(32 M) workgroups, decompression: R/32 x K/256, in several launches) have 32-bit block ids.
+  // What the runtime still refuses to launch comes back as VENOM_ERR_HIP.
   if (R / V > 65535 || R > ((int64_t)1 << 38) / (K > 0 ? K : 1)) return VENOM_ERR_UNSUPPORTED;
   return VENOM_OK;
 }

@@ -171,7 +171,7 @@ __global__ void __launch_bounds__(256) prune_kernel(const uint16_t* __restrict__
 // instructions per element (convert, clamp, widen) and an addition, where the integer form
 // (decompose, 64-bit shift, 64-bit add) takes a dozen.
 constexpr double kMassBias = 268435456.0;        // 2^28
-constexpr int kTileMaxV = 2048;
+constexpr int kTileMaxV = 2048;                  // (the LDS stops tiles earlier, at 1982 rows)
 __device__ __forceinline__ double magnitude(uint16_t bits) {
   const float x = (float)__builtin_bit_cast(_Float16, bits);
   return (double)fminf(fabsf(x), 65536.f);        // Inf and NaN: 2^16 = 2^40 units

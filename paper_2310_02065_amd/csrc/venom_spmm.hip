@@ -743,19 +743,22 @@ static int variant_of(int V, int bsc) {
 
 static int pick_variant(int V, int64_t Ccols, int64_t nbr, int cus) {
   // The 64-column tile where C has no more columns than that, or where even its tiles find a compute
-  // unit each.  What bounds such a call is one unit's L2 -> LDS path (~46 B/clk): per k-step at
-  // V = 128 it takes 36.5 / 20.5 / 12.5 / 8.5 KB for 512 / 256 / 128 / 64 columns, so as long as the
-  // chip has units to spare a narrower tile is simply shorter.  Measured (us per call among others,
-  // the best wider tile -> 64 columns): 49152 x 12288 x 16 at 128:2:32 30.1 -> 18.8 (4.8 TB/s of the
-  // matrix), at 64:2:32 33.6 -> 22.6; 8192 x 8192 x 256 at 128:2:16 22.3 -> 20.1; 4096 x 4096 x 512
+  // unit each.  What bounds such a call is one unit's L2 -> LDS path and the producers' chain of loads: per
+  // k-step at V = 128 a tile takes 36.5 / 20.5 / 12.5 / 8.5 KB for 512 / 256 / 128 / 64 columns, so as
+  // long as the chip has units to spare a narrower tile is simply shorter.  Measured (us per call among others,
+  // the best wider tile -> 64 columns): 49152 x 12288 x 16 at 128:2:32 30 -> 19 (4.8 TB/s of the
+  // matrix), at 64:2:32 34 -> 23; 8192 x 8192 x 256 at 128:2:16 22.4 -> 19.6; 4096 x 4096 x 512
   // at 128:2:16 15.3 -> 13.2; 1024 x 16000 x 2048 at 128:2:40 19.5 -> 16.5; 8160 x 8192 x 128 at
-  // 96:2:16 21.9 -> 18.3.  With two tiles per unit it is even (20.5 against 21.1) to 26 % slower
-  // (8192 x 8192 x 512 at 128:2:16, 29.9 against 23.7): the A stream is read once per tile.
+  // 96:2:16 21.9 -> 18.3; of 182 shapes that take it here, none slower.  With 257 to 512 tiles neither side wins
+  // throughout: of 35 shapes 19 are over 3 % faster on it (4096 x 4096 x 1024 at 128:2:32 12.2 -> 10.8), 8
+  // over 3 % slower, the more k-steps the worse (8192 x 8192 x 512 at 128:2:32, 16 and 8: 16.9 -> 18.8,
+  // 23.4 -> 29.9, 36.3 -> 52.2), because the A stream is read once per tile.
   if (Ccols <= 64 || nbr * ((Ccols + 63) / 64) <= cus) return variant_of(V, 64);
   // Otherwise the widest column tile that C fills at least half of: wide tiles re-read the A stream
-  // least and measured fastest at every large shape tried; narrow C takes the narrow tiles.  When that
-  // choice leaves more than half of the compute units without a tile (few block rows), the
-  // 256-column tile spreads the work over twice as many units.
+  // least; narrow C takes the narrow tiles.  When that choice leaves more than half of the compute units
+  // without a tile (few block rows), the 256-column tile spreads the work over twice as many units.  Of 254
+  // shapes 242 are within 3 % of the best of these three; the others, with few block rows and many k-steps,
+  // would be 4 to 14 % faster with 128 columns (1024 x 16000 x 2048 at 64:2:10 48 against 42).
   const int bsc = Ccols > 256 ? 512 : Ccols > 128 ? 256 : 128;
   if (bsc == 512 && nbr * ((Ccols + 511) / 512) <= 128) return variant_of(V, 256);
   return variant_of(V, bsc);
