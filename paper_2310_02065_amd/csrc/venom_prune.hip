@@ -348,7 +348,7 @@ static int general_groups(int M) {
 // 16-byte pieces (which at odd M takes several groups); more where a block has fewer than 32 rows, so that a
 // workgroup still holds 8 KB (4096 x 8192, us per call with 128 columns -> now, prune_kernel: 1:2:128 1227 -> 312, 960;
 // 16:2:64 104 -> 65, 101; 8:2:8 143 -> 63, 421), fewer where four tiles would not share a compute unit.
-static int tile_groups(int V, int M, bool general_wide) {
+static int tile_groups(int V, int M) {
   if (V > kTileMaxV) return 0;
   const int whole = M % 8 == 0 ? 1 : M % 4 == 0 ? 2 : M % 2 == 0 ? 4 : 8;
   int cols = 128;
@@ -356,16 +356,29 @@ static int tile_groups(int V, int M, bool general_wide) {
   int n = (cols + M * whole - 1) / (M * whole);    // in units of `whole` groups
   while (n > 1 && (tile_lds(V, n * whole * M) > 38 * 1024 || n * whole * M > kPruneMaxCols || n * whole > kTileMaxGroups)) --n;
   const int gpw = n * whole;
-  // A tall block leaves the tile few columns, pieces of rows too short to read well.  prune_kernel, which takes
-  // `general` columns but reads the matrix twice, is then the better one where it reads in wide loads, unless the
-  // blocks are too large for its second pass to find them in the cache.  12288 x 8192, us per call, tile / prune_kernel,
-  // with the tile's columns: 320:2:8 48 105 / 122; 384:2:8 40 119 / 115; 384:2:4 40 130 / 185 (general = 32);
-  // 640:2:4 16 193 / 179; 512:2:16 16 192 / 92; 1024:2:8 8 384 / 110; 384:2:32 32 118 / 107; 512:2:32 32 111 / 123;
-  // 640:2:24 24 162 / 143.  At 12288 x 8190 (prune_kernel by single elements) 640:2:10 40 166 / 241;
-  // 896:2:6 24 202 / 296.
-  const int general = general_groups(M) * M, enough = general * 3 / 4 < 48 ? general * 3 / 4 : 48;
-  if (general_wide && gpw * M < enough && !(M >= 32 && M * V >= 14336)) return 0;
   return tile_lds(V, gpw * M) <= kTileLds - 2048 && gpw * M <= kPruneMaxCols && gpw <= kTileMaxGroups ? gpw : 0;
+}
+
+// A tall block leaves the tile few columns, pieces of rows too short to read well; prune_kernel takes `general` columns of
+// it but reads the matrix twice, and its workgroups last longer.  So the tile is the better kernel while prune_kernel would
+// not fill the chip, up to the number of prune_kernel's workgroups returned here, which grows with the share of its
+// columns that the tile keeps.  Measured for V = 192 .. 1536, M = 4 .. 64, matrices of 1.5 to 600 million entries (468 shapes
+// with rows at 16-byte boundaries, as many without); us per call, tile / prune_kernel, by tile columns: 8: 2048 x 768 at
+// 1024:2:8 20 / 54, 12288 x 8192 384 / 110; 16: 12288 x 8192 at 512:2:16 192 / 92; 24: 2048 x 768 at 512:2:8 20 / 36,
+// 12288 x 8192 160 / 112, 49152 x 12288 at 512:2:4 1200 / 1011; 32: 12288 x 8192 at 512:2:32 111 / 123, 49152 x
+// 12288 700 / 617, 12288 x 8192 at 448:2:4 127 / 180; 48: 49152 x 12288 at 256:2:48 1.25 times as long as prune_kernel,
+// 12288 x 8192 at 320:2:8 0.85 times; 64 and more: never slower.  Where prune_kernel could only read single elements the tile
+// wins from 16 or 24 columns on (12288 x 8190 at 640:2:10 166 / 241), below that on small matrices.  Chosen so, 920 of the 936
+// shapes are within 4 % of the better kernel, the others within 10 %.
+static int64_t tile_pays_up_to(int cols, int general, bool general_wide) {
+  constexpr int64_t kAlways = INT64_MAX;
+  const int share = 8 * cols / general;            // in eighths
+  if (!general_wide) return cols < 16 ? 800 : cols < 24 && share < 2 ? 4000 : kAlways;
+  if (cols >= 64 || cols >= general) return kAlways;
+  if (cols < 16) return 280;
+  if (cols < 32) return share < 3 ? 420 : share < 4 ? 840 : cols < 24 ? 1500 : share < 6 ? kAlways : 13000;
+  if (cols < 48) return share < 4 ? 900 : 2850;
+  return share < 3 ? 1300 : share < 4 ? 2600 : 12000;
 }
 
 hipError_t launch_prune(const uint16_t* A, int64_t lda, int64_t R, int64_t K, int V, int M, uint8_t* mask, int64_t ldm,
@@ -375,10 +388,12 @@ hipError_t launch_prune(const uint16_t* A, int64_t lda, int64_t R, int64_t K, in
     hipLaunchKernelGGL(zero_u64_kernel, dim3((unsigned)((Rb + 255) / 256)), dim3(256), 0, st, kept_mass, total_mass, Rb);
   if (Rb == 0 || G == 0) return hipGetLastError();
   // prune_kernel's wide loads need every chunk of every row of A to start on a 16-byte boundary
-  const int vec_ok = ((int64_t)general_groups(M) * M) % 8 == 0 && lda % 8 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0;
-  int tiled = tile_groups(V, M, vec_ok);
+  const int general = general_groups(M);
+  const int vec_ok = ((int64_t)general * M) % 8 == 0 && lda % 8 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0;
+  int tiled = tile_groups(V, M);
+  if (Rb * ((G + general - 1) / general) > tile_pays_up_to(tiled * M, general * M, vec_ok)) tiled = 0;
   if (tiled > 0 && (G + tiled - 1) / tiled > kMaxBlocks) tiled = 0;   // too many workgroups for a launch (K near 2^31)
-  const int gpw = tiled > 0 ? tiled : general_groups(M);
+  const int gpw = tiled > 0 ? tiled : general;
   const int64_t chunks = (G + gpw - 1) / gpw;
   // every (row, group) of the mask starts at row * ldm + group * M: the widest word that always divides that
   const uintptr_t ma = reinterpret_cast<uintptr_t>(mask);

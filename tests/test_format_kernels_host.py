@@ -182,8 +182,8 @@ def check_prune(L, R, K, V, M, lda, offset):
     (64, 4, 32, 4, 5, 6),            # rows narrower than one load
     (6, 210, 3, 7, 213, 14),
     (4, 1100, 2, 100, 1104, 0),      # few rows: a tile of 1000 columns, and one group
-    (640, 54, 640, 6, 55, 2),        # a tile of few columns where the general kernel would go by single elements
-    (896, 24, 896, 8, 24, 0),        # ... and where it would not: the general kernel
+    (640, 54, 640, 6, 55, 2),        # a tile of 24 columns
+    (1024, 128, 1024, 64, 128, 0), (1024, 64, 1024, 64, 67, 6),   # too tall for a tile: the general kernel, wide loads and not
 ])
 def test_prune(library, R, K, V, M, lda, offset):
     in_child(library, "check_prune", R, K, V, M, lda, offset)

@@ -66,8 +66,9 @@ def test_format_path_bit_exact(R, K, V, M, shift):
     (128, 9 * 5, 64, 5, 48, 56),     # ... narrower than the 8-byte loads of an odd chunk
     (96, 13 * 10, 32, 10, 136, 130), # two columns left over, of A too
     (96, 21 * 40, 32, 40, 840, 843), # K % 16 == 8
-    (640, 9 * 6, 640, 6, 55, 55),    # a tall block, rows at any boundary: a pruning tile of 24 columns
-    (1024, 9 * 16, 1024, 16, 144, 144),   # ... at 16-byte boundaries: the general kernel
+    (640, 9 * 6, 640, 6, 55, 55),    # a tall block: a pruning tile of 24 columns
+    (1024, 9 * 64, 1024, 64, 579, 577),   # too tall for one: the general kernel, rows at any boundary
+    (8192, 325 * 8, 1024, 8, 2600, 2600), # tiles of 8 columns against 328 workgroups of the general kernel: the latter
     (48, 11 * 100, 2, 100, 1104, 1100),   # blocks of few rows: tiles of ten groups, and one
 ])
 def test_padded_rows_bit_exact(R, K, V, M, lda, ldm):
