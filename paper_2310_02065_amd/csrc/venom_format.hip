@@ -126,7 +126,7 @@ __host__ __device__ constexpr int bits_pitch(int wpw, int M) { return (wpw * M +
 // 0.08 ms to pack in a second pass, when phase 3 fetched the mask bytes again one by one.
 // by_full, by_last: n / units = n * by >> 16 for n, units <= 256, for the loads of a row in all chunks of columns but the
 // last, and in the last (a division in the kernel is 5 % of a workgroup with one row).
-// bits_ok: the bits of V rows fit (48 KB of LDS: 49152 x 12288 at 1024:2:32 takes 464 us a call, 653 if phase 3 reads the
+// bits_ok: the bits of V rows fit (48 KB of LDS: 49152 x 12288 at 1024:2:32 takes 464 us a call, more if phase 3 reads the
 // mask again); otherwise (very tall blocks) it does.
 template <int UB>
 __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restrict__ A, int64_t lda,
@@ -262,11 +262,16 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
         const ushort4 c4 = sel[tg];
         const int c[kSelCols] = {c4.x, c4.y, c4.z, c4.w};
         int kept = 0;                            // bit p: the row keeps selected column p
+        if (bits_ok) {
 #pragma unroll
-        for (int p = 0; p < kSelCols; ++p) {
-          const int col = tg * M + c[p];
-          const int k = bits_ok ? (bits[v * pitch + col / 8] >> (col % 8)) & 1 : mblk[(int64_t)v * ldm + col] != 0;
-          kept |= k << p;
+          for (int p = 0; p < kSelCols; ++p) {
+            const int col = tg * M + c[p];
+            kept |= ((bits[v * pitch + col / 8] >> (col % 8)) & 1) << p;
+          }
+        } else {                                 // four loads in flight (one after the other: 1351 instead of 1029 us
+          const uint8_t* mrow = mblk + (int64_t)v * ldm + tg * M;   // for 49152 x 12288 at 8192:2:8)
+          const uint8_t m0 = mrow[c[0]], m1 = mrow[c[1]], m2 = mrow[c[2]], m3 = mrow[c[3]];
+          kept = (m0 != 0) | (m1 != 0) << 1 | (m2 != 0) << 2 | (m3 != 0) << 3;
         }
         if (cols_ok[tg] && __popc(kept) > 2)
           atomicMin(status, ((unsigned long long)(b * d.G + g0 + tg) << 24) | (1ull << 23) | (unsigned long long)v);
