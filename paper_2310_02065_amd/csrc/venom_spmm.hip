@@ -74,8 +74,8 @@ __device__ __forceinline__ void dma4(const char* base, uint32_t lane_off, uint32
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(lane_off), "s"(base), "s"(lds_addr)
                : "memory");
 }
-// wait until at most n of this wave's loads are outstanding, 0 <= n <= MAXN; the steady state
-// (n == MAXN) is the first case tested.  The count is an immediate of the instruction, hence the cascade.
+// wait until at most n of this wave's loads are outstanding, 0 <= n <= MAXN.  The count is an immediate
+// of the instruction, hence the cascade.
 template <int MAXN>
 __device__ __forceinline__ void wait_loads(int n) {
   static_assert(MAXN <= 63, "vmcnt is a 6-bit counter");
@@ -180,10 +180,12 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, NC == 1 ? 4 : 3) 
   constexpr int NJ = VT + 1;                       // A loads per k-step: VT value blocks + the tail
   constexpr int PB = NS - D;                       // k-steps the B stream runs ahead
   constexpr int PA = NA - D;                       // k-steps the A stream runs ahead
-  constexpr int RA = 2 * PB + 2;                   // k-steps the row-id stream runs ahead: the ids of step g+PB+1 are
-                                                   // then older, in their producer's load queue, than its loads of step g
+  constexpr int RA = 2 * PB + 2 > PA ? 2 * PB + 2 : PA;   // k-steps the row-id stream runs ahead: the ids of step g+PB+1
+                                                   // are then older, in their producer's load queue, than its loads
+                                                   // of step g, and the stream ends no later than the records
   static_assert(PB >= 1 && PA >= PB, "a record is issued no later than the B rows of its k-step");
   static_assert(kRidSlots >= PB + 2, "a row-id slot is rewritten only after its last reader");
+  static_assert(RA <= kRidSlots, "the row ids of the start-up fit the ring");
   constexpr bool OWN_STG = NR > 1;                 // the consumers' output staging: the drained stage, or its own LDS
   constexpr int STG = RIDRING + kRidSlots * kStepRows * 4;
   static_assert(OWN_STG || CONS * 32 * WCOLS * 2 <= B_BYTES, "the output staging of all consumers fits one B stage");
@@ -230,7 +232,13 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, NC == 1 ? 4 : 3) 
       // its loads, ~70 cycles, and instructions between two loads are not hidden behind them:
       // measured).  So the streams advance by plain increments, ring positions wrap by compare and
       // select, and everything that depends on the tile is recomputed in a branch taken once per tile.
+      // For the same reason the loop that runs most k-steps (`runs` below) is taken without a branch between its
+      // loads: it covers the iterations in which no stream comes to the end of its tile.  A k-step of a 64-column
+      // tile takes 0.12 us in it (one tile alone on the chip, operands in L2) and 0.20 us in a loop that tests
+      // the four streams each time round.
       const uint32_t lane_off = lane * 16;
+      using checked = std::false_type;             // tags of the streams' steps: the tile may end with it / it does not
+      using inside = std::true_type;
       int ct, br;
       // ---- record stream: record pointer, LDS slot address, k-steps left in its tile
       tw.locate(p, 0, ct, br);
@@ -238,7 +246,7 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, NC == 1 ? 4 : 3) 
       int64_t a_inc = p.rec_bytes;
       uint32_t a_lds = lds0 + ARING;
       int a_left = p.steps, a_t = 0;
-      auto next_record = [&]() {
+      auto next_record = [&](auto inside_tile) {
 #pragma unroll
         for (int a = PJ; a < NJ; a += NP) {
           if (a < VT) dma16(a_ptr + a * 1024, lane_off, a_lds + a * 1024);
@@ -246,6 +254,7 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, NC == 1 ? 4 : 3) 
         }
         a_ptr += a_inc;
         a_lds = a_lds + REC == lds0 + ARING + NA * REC ? lds0 + ARING : a_lds + REC;
+        if constexpr (decltype(inside_tile)::value) return;
         if (--a_left == 0) {
           a_left = p.steps;
           if (++a_t < tw.count) {
@@ -261,21 +270,26 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, NC == 1 ? 4 : 3) 
       int r_inc = kStepRows * 4;
       uint32_t r_lds = lds0 + RIDRING;
       int r_left = p.steps, r_t = 0;
-      auto next_rowids = [&]() {
+      auto end_of_rowids = [&]() {                 // the stream has come to the end of its tile
+        r_left = p.steps;
+        if (++r_t < tw.count) {
+          int ct2, br2;
+          tw.locate(p, r_t, ct2, br2);
+          const bool back = p.serpentine && (r_t & 1);
+          r_inc = back ? -(kStepRows * 4) : kStepRows * 4;
+          r_ptr = reinterpret_cast<const char*>(p.rowidx) +
+                  ((int64_t)br2 * p.steps + (back ? p.steps - 1 : 0)) * (kStepRows * 4);
+        } else {                                   // past the last one it stays on its last k-step: ids nobody reads,
+          r_ptr -= r_inc;                          // so that an iteration has the same loads while records are left
+          r_inc = 0;
+        }
+      };
+      auto next_rowids = [&](auto inside_tile) {
         if (lane < kStepRows) dma4(r_ptr, lane * 4, r_lds);
         r_ptr += r_inc;
         r_lds = r_lds + kStepRows * 4 == lds0 + RIDRING + kRidSlots * kStepRows * 4 ? lds0 + RIDRING : r_lds + kStepRows * 4;
-        if (--r_left == 0) {
-          r_left = p.steps;
-          if (++r_t < tw.count) {
-            int ct2, br2;
-            tw.locate(p, r_t, ct2, br2);
-            const bool back = p.serpentine && (r_t & 1);
-            r_inc = back ? -(kStepRows * 4) : kStepRows * 4;
-            r_ptr = reinterpret_cast<const char*>(p.rowidx) +
-                    ((int64_t)br2 * p.steps + (back ? p.steps - 1 : 0)) * (kStepRows * 4);
-          }
-        }
+        if constexpr (decltype(inside_tile)::value) return;
+        if (--r_left == 0) end_of_rowids();
       };
       // ---- B stream.  Load q of this producer is load number PJ + NP*q of the k-step; it covers
       // rows (that number)*RPI .. +RPI-1; lane l writes 16-byte slot l%LPR of row l/LPR and fetches
@@ -312,7 +326,7 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, NC == 1 ? 4 : 3) 
         rid_rd = rid_rd + kStepRows * 4 == smem + RIDRING + rowsel * 4 + kRidSlots * kStepRows * 4
                      ? smem + RIDRING + rowsel * 4 : rid_rd + kStepRows * 4;
       };
-      auto next_rows = [&]() {
+      auto next_rows = [&](auto inside_tile) {
         uint32_t off[CB];
 #pragma unroll
         for (int q = 0; q < CB; ++q)   // row id x bytes per row + this lane's column bytes, one instruction
@@ -320,42 +334,44 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, NC == 1 ? 4 : 3) 
 #pragma unroll
         for (int q = 0; q < CB; ++q) dma16(p.B, off[q], b_lds + q * (NP * 1024));
         b_lds = b_lds + B_BYTES == lds0 + PJ * 1024 + NS * B_BYTES ? lds0 + PJ * 1024 : b_lds + B_BYTES;
+        if constexpr (decltype(inside_tile)::value) return;
         if (--b_left == 0) {
           b_left = p.steps;
           if (++b_t < tw.count) set_tile(b_t);
         }
       };
-      // loads this producer issued in each of the last PB-1 iterations (oldest first)
-      int issued[PB > 1 ? PB - 1 : 1] = {};
-      auto remember = [&](int n) {
-#pragma unroll
-        for (int k = 0; k + 1 < PB - 1; ++k) issued[k] = issued[k + 1];
-        if (PB > 1) issued[PB - 2] = n;
-      };
-      auto outstanding_after_step = [&]() {
-        int n = 0;
-#pragma unroll
-        for (int k = 0; k < PB - 1; ++k) n += issued[k];
-        return n;
-      };
       // start-up: the row ids of the first RA steps, then what iterations -PA .. -1 would have issued
-      if constexpr (CR != 0)
-        for (int j = 0; j < RA && j < G; ++j) next_rowids();
-      asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");   // the first row ids are on chip
-      for (int i = -PA; i < 0; ++i) {
-        int n = 0;
-        if (i + PA < G) { next_record(); n += CA; }
-        if (i + PB >= 0 && i + PB < G) { read_rowids(); next_rows(); n += CB; }
-        remember(n);
+      // (the records that run ahead of the rows do not wait for the ids)
+      auto first_records = [&]() {
+        for (int i = -PA; i < -PB; ++i)
+          if (i + PA < G) next_record(checked{});
+      };
+      if constexpr (CR != 0) {
+        const int n0 = p.steps < RA ? p.steps : RA;  // those of the first tile: eight k-steps a load
+#pragma unroll
+        for (int q = 0; 8 * q < RA; ++q) {
+          const int s = 8 * q + lane / 8;
+          if (s < n0) dma16(r_ptr, s * (kStepRows * 4) + lane % 8 * 16, r_lds + q * 1024);
+        }
+        r_ptr += n0 * (kStepRows * 4);
+        r_lds = n0 == kRidSlots ? r_lds : r_lds + n0 * (kStepRows * 4);
+        r_left -= n0;
+        if (r_left == 0) end_of_rowids();
+        for (int j = n0; j < RA && j < G; ++j) next_rowids(checked{});
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      } else first_records();
+      barrier_only();                              // the first row ids are on chip
+      if constexpr (CR != 0) first_records();
+      for (int i = -PB; i < 0; ++i) {
+        if (i + PA < G) next_record(checked{});
+        if (i + PB < G) { read_rowids(); next_rows(checked{}); }
       }
       const bool ragged = p.pad_row0 < kStepRows;  // K/M is not a multiple of 8
       int c_left = p.steps, c_t = 0;               // k-steps left in the tile the consumers are on / that tile
-      // One iteration.  STEADY: all three streams are inside the sequence and have been for PB
-      // iterations, so the loads outstanding after those of step g are a compile-time count.
-      auto iteration = [&](int g, auto steady_const) {
-        constexpr bool STEADY = decltype(steady_const)::value;
-        if constexpr (STEADY) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((PB - 1) * L) : "memory");
-        else wait_loads<(PB - 1) * L>(outstanding_after_step());
+      // One iteration: the loads of step g have landed, barrier, the next loads.  RECORDS, ROWS: these
+      // streams are still inside the sequence.  `waited` waits for the loads of step g.
+      auto iteration = [&](int g, auto records, auto rows, auto waited) {
+        waited();
         if (ragged && c_left == ((p.serpentine && (c_t & 1)) ? p.steps : 1)) {
           // The last k-step of a tile when K/M is not a multiple of 8: its trailing groups do not
           // exist.  Their values are zero, but 0 x Inf is not, so the rows gathered for them (row 0
@@ -369,24 +385,65 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, NC == 1 ? 4 : 3) 
           lgkm_drained_barrier();
         } else barrier_only();
         // after barrier g the consumers are done with stage g-D and record g-D
-        int n = 0;
-        const bool rows = STEADY || g + PB < G;
-        if (rows) read_rowids();
-        if constexpr (CR != 0)
-          if (STEADY || g + RA < G) { next_rowids(); n += 1; }
-        if (STEADY || g + PA < G) { next_record(); n += CA; }
-        if (rows) { next_rows(); n += CB; }
-        if constexpr (!STEADY) remember(n);
+        if constexpr (decltype(rows)::value) read_rowids();
+        if constexpr (decltype(records)::value) {
+          if constexpr (CR != 0) next_rowids(checked{});
+          next_record(checked{});
+        }
+        if constexpr (decltype(rows)::value) next_rows(checked{});
         if (--c_left == 0) { c_left = p.steps; ++c_t; barrier_only(); }
       };
+      // How many iterations from the next on, at most n, do not end a tile of any of the streams
+      // (the first k-step of a tile, where the ragged end of a backward tile lies, is left to the checked one).
+      const bool any_runs = p.steps > 4;           // (shorter tiles end a stream in all of them)
+      auto runs = [&](int n, bool records) {
+        if (!any_runs) return 0;
+        n = n < b_left - 1 ? n : b_left - 1;
+        n = n < c_left - 1 ? n : c_left - 1;
+        if (records) {
+          n = n < a_left - 1 ? n : a_left - 1;
+          if constexpr (CR != 0) n = n < r_left - 1 ? n : r_left - 1;
+        }
+        return ragged && c_left == p.steps ? 0 : n;
+      };
+      // The loads of step g are those of iteration g-PB: step g is there when only those of the PB-1
+      // iterations since are outstanding.  While records are left these are L each (the start-up
+      // issued no row ids beside the first records and rows), after that at least CB.
       int g = 0;
-      for (; g < G && g < PB; ++g) iteration(g, std::false_type{});
-      if (g + RA < G) {
-        for (; g + RA < G; ++g) iteration(g, std::true_type{});
-#pragma unroll
-        for (int k = 0; k < PB - 1; ++k) issued[k] = L;   // what the steady iterations issued
+      while (g + PA < G) {
+        iteration(g, std::true_type{}, std::true_type{}, [&]() {
+          if (CR != 0 && g < PB - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((PB - 1) * (CA + CB)) : "memory");
+          else asm volatile("s_waitcnt vmcnt(%0)" ::"n"((PB - 1) * L) : "memory");
+        });
+        ++g;
+        if (g < PB - 1) continue;
+        int n = runs(G - PA - g, true);
+        if (n <= 0) continue;
+        g += n; a_left -= n; b_left -= n; c_left -= n;
+        if constexpr (CR != 0) r_left -= n;
+        do {
+          asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((PB - 1) * L) : "memory");
+          read_rowids();
+          if constexpr (CR != 0) next_rowids(inside{});
+          next_record(inside{});
+          next_rows(inside{});
+        } while (--n > 0);
       }
-      for (; g < G; ++g) iteration(g, std::false_type{});
+      while (g + PB < G) {
+        iteration(g, std::false_type{}, std::true_type{},
+                  []() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"((PB - 1) * CB) : "memory"); });
+        ++g;
+        int n = runs(G - PB - g, false);
+        if (n <= 0) continue;
+        g += n; b_left -= n; c_left -= n;
+        do {
+          asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((PB - 1) * CB) : "memory");
+          read_rowids();
+          next_rows(inside{});
+        } while (--n > 0);
+      }
+      for (; g < G; ++g)
+        iteration(g, std::false_type{}, std::false_type{}, [&]() { wait_loads<(PB - 1) * CB>((G - 1 - g) * CB); });
     };
     switch (wave - CONS) {
       case 0: produce(std::integral_constant<int, 0>{}); break;
@@ -476,6 +533,9 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, NC == 1 ? 4 : 3) 
       for (int s = 1; s < p.steps; ++s) {
         if constexpr (D == 1) lgkm_drained_barrier();   // my reads of the last stage are over; this one is complete
         else barrier_only();                            // stage s and record s are complete
+        // (the next matrix instruction may wait for this wave's reads, and the narrow tiles' k-steps are short: they
+        // arrive at the barrier first.  On the wide ones it is issued while the wave waits there)
+        if constexpr (NC <= 2) __builtin_amdgcn_sched_barrier(0);
         advance();
 #pragma unroll
         for (int tc = 0; tc < CT; ++tc) {
