@@ -151,10 +151,17 @@ struct TileWalk {
 // run NS-1 k-steps ahead.
 // NR: consumer waves that share a 64-column strip, each owning VT/NR of its tile rows.  1 for the wide
 // tiles.  The 64-column tile has a single strip: one wave would need 8 matrix instructions (256
-// cycles) per k-step while its 8.5 KB arrive in ~190, so the strip's rows are split over two or three
-// waves; their accumulators are small enough for four waves per SIMD, i.e. two workgroups per unit.
+// cycles) per k-step while its 8.5 KB arrive in ~190, so the strip's rows are split over two or three waves.
+//
+// Waves per SIMD that the registers are kept low enough for: four where a workgroup has at most eight waves with at most 64
+// accumulators each (two 32-row tiles), five for ten waves of 32, so that two workgroups share a unit if their LDS
+// allows it; three for the others.
+constexpr int simd_waves(int VT, int NC, int NR) {
+  return VT / NR == 1 && NC * NR == 6 ? 5 : VT / NR <= 2 && NC * NR <= 4 ? 4 : 3;
+}
+
 template <int VT, int NC, int NR, int NS, int NA, int D, bool OUT_F32, int MODE>
-__global__ void __launch_bounds__((NC * NR + kProducers) * 64, NC == 1 ? 4 : 3) spmm_kernel(SpmmParams p) {
+__global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC, NR)) spmm_kernel(SpmmParams p) {
   static_assert(NC == 1 || NC == 2 || NC == 4 || NC == 8, "64-column strips per workgroup");
   static_assert(VT % NR == 0, "the tile rows divide evenly over the waves of a strip");
   static_assert(D == 1 || D == 2, "barriers between the hand-over of a stage and its return");
@@ -753,12 +760,19 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, NC == 1 ? 4 : 3) 
 }
 
 // ---------------------------------------------------------------------------------------------
+// What a call takes with a variant, in us: `launch`; for each tile that the busiest unit walks `tile`, and `k_step` for each
+// of its k-steps; and as the units compete for the L2s and the memory behind them, `chip_tile` and `chip_step` for each tile
+// and k-step that a unit has on average, and `fill_step` for each k-step of a tile by the share of the units in use.
+struct TileCost { float launch, k_step, tile, chip_step, chip_tile, fill_step; };
+
 struct Variant {
   const char* name;
   int V;       // block height it serves
   int bsc;     // columns per workgroup
   int threads;
   int lds;     // dynamic LDS bytes
+  int share;   // workgroups that share a compute unit
+  TileCost cost;
   void (*fn[2][4])(SpmmParams);   // [fp32 output][mode]
 };
 
@@ -768,60 +782,72 @@ constexpr int lds_bytes() {   // B ring, A ring, row-id ring, output staging (4 
          (NR > 1 ? NC * NR * 4096 : 0);
 }
 
-#define VARIANT(NAME, VT, NC, NR, NS, NA, D)                                                                \
+#define VARIANT(NAME, VT, NC, NR, NS, NA, ...)                                                              \
   { NAME, (VT) * 32, 64 * (NC), 64 * ((NC) * (NR) + kProducers), lds_bytes<VT, NC, NR, NS, NA>(),            \
-    { { spmm_kernel<VT, NC, NR, NS, NA, D, false, 0>, spmm_kernel<VT, NC, NR, NS, NA, D, false, 1>,         \
-        spmm_kernel<VT, NC, NR, NS, NA, D, false, 2>, spmm_kernel<VT, NC, NR, NS, NA, D, false, 3> },       \
-      { spmm_kernel<VT, NC, NR, NS, NA, D, true, 0>, spmm_kernel<VT, NC, NR, NS, NA, D, true, 1>,           \
-        spmm_kernel<VT, NC, NR, NS, NA, D, true, 2>, spmm_kernel<VT, NC, NR, NS, NA, D, true, 2> } } }
+    simd_waves(VT, NC, NR) >= 4 && lds_bytes<VT, NC, NR, NS, NA>() <= 80 * 1024 ? 2 : 1, { __VA_ARGS__ },    \
+    { { spmm_kernel<VT, NC, NR, NS, NA, kD, false, 0>, spmm_kernel<VT, NC, NR, NS, NA, kD, false, 1>,       \
+        spmm_kernel<VT, NC, NR, NS, NA, kD, false, 2>, spmm_kernel<VT, NC, NR, NS, NA, kD, false, 3> },     \
+      { spmm_kernel<VT, NC, NR, NS, NA, kD, true, 0>, spmm_kernel<VT, NC, NR, NS, NA, kD, true, 1>,         \
+        spmm_kernel<VT, NC, NR, NS, NA, kD, true, 2>, spmm_kernel<VT, NC, NR, NS, NA, kD, true, 2> } } }
 
 constexpr int kD = 2;   // barriers between the hand-over of a stage and its return (1 and 2 measure the same)
+// Rows per wave and ring depths, as measured (us per call).  V = 128: two waves per strip up to 256 columns
+// (2048 x 1520 x 7896 at 128:2:20 with 256 columns 17.5, one wave 19.9).  "d" has rings shallow enough for a second
+// workgroup on the unit, whose k-loop runs while the first one stores: better with few k-steps a tile, worse with many
+// (16384 x 1024 x 512 at 128:2:8 13.9 against 14.5, 1024 x 16000 x 4096 at 128:2:40 20.4 against 17.8).  At V = 64 and 32
+// the accumulators allow that with 256 columns (3072 x 768 x 4096 at 64:2:8 14.6, one workgroup with deeper rings 15.3).
+// More stages than these cost start-up and gain nothing, except on the 64-column tile (V = 128: 5 stages
+// are 3 % faster below 20 k-steps, 6 stages 5 to 20 % above).
 static const Variant kVariants[] = {
-    VARIANT("v128_c512", 4, 8, 1, 4, 6, kD), VARIANT("v128_c256", 4, 4, 1, 6, 10, kD),
-    VARIANT("v128_c128", 4, 2, 1, 8, 10, kD),
-    VARIANT("v96_c512", 3, 8, 1, 4, 8, kD), VARIANT("v96_c256", 3, 4, 1, 6, 10, kD),
-    VARIANT("v96_c128", 3, 2, 1, 8, 10, kD),
-    VARIANT("v64_c512", 2, 8, 1, 4, 10, kD), VARIANT("v64_c256", 2, 4, 1, 6, 10, kD),
-    VARIANT("v64_c128", 2, 2, 1, 8, 10, kD),
-    VARIANT("v32_c512", 1, 8, 1, 4, 10, kD), VARIANT("v32_c256", 1, 4, 1, 6, 10, kD),
-    VARIANT("v32_c128", 1, 2, 1, 8, 10, kD),
-    VARIANT("v128_c64", 4, 1, 2, 6, 10, kD),
-    VARIANT("v96_c64", 3, 1, 3, 6, 10, kD),
-    VARIANT("v64_c64", 2, 1, 2, 6, 10, kD),
-    VARIANT("v32_c64", 1, 1, 1, 6, 10, kD),
+    VARIANT("v128_c512", 4, 8, 1, 4, 6, 1.23f, .315f, 3.87f, .252f, 3.48f, 0.f),
+    VARIANT("v128_c256", 4, 4, 2, 5, 6, 2.69f, .215f, 1.24f, .125f, 2.34f, 0.f),
+    VARIANT("v128_c128", 4, 2, 2, 5, 6, 1.97f, .138f, 1.58f, .082f, .73f, 0.f),
+    VARIANT("v128_c128d", 4, 2, 2, 4, 6, 2.87f, .149f, .47f, .050f, 1.07f, .021f),
+    VARIANT("v128_c64", 4, 1, 2, 6, 6, 2.98f, .122f, .52f, .004f, .49f, .035f),
+    VARIANT("v96_c512", 3, 8, 1, 4, 6, 2.53f, .279f, 1.92f, .230f, 2.53f, 0.f),
+    VARIANT("v96_c256", 3, 4, 1, 5, 6, 3.27f, .174f, .88f, .122f, 1.60f, 0.f),
+    VARIANT("v96_c128", 3, 2, 3, 5, 6, 2.48f, .165f, .84f, .041f, .81f, .030f),
+    VARIANT("v96_c128d", 3, 2, 3, 4, 4, 2.99f, .160f, .17f, .011f, 1.09f, .028f),
+    VARIANT("v96_c64", 3, 1, 3, 5, 6, 3.07f, .128f, .04f, 0.f, .66f, .021f),
+    VARIANT("v64_c512", 2, 8, 1, 4, 10, 2.22f, .285f, 1.98f, .158f, 1.08f, .014f),
+    VARIANT("v64_c256", 2, 4, 1, 5, 6, 2.75f, .164f, .73f, .087f, 1.13f, .016f),
+    VARIANT("v64_c256d", 2, 4, 1, 4, 4, 2.88f, .163f, .35f, .075f, 1.11f, .045f),
+    VARIANT("v64_c128", 2, 2, 2, 5, 6, 2.77f, .133f, .33f, .017f, .54f, .034f),
+    VARIANT("v64_c64", 2, 1, 2, 6, 10, 3.02f, .112f, .15f, 0.f, .42f, .014f),
+    VARIANT("v32_c512", 1, 8, 1, 4, 10, 3.43f, .260f, 0.f, .100f, 1.79f, .044f),
+    VARIANT("v32_c256", 1, 4, 1, 6, 10, 2.19f, .157f, .90f, .041f, .39f, .059f),
+    VARIANT("v32_c256d", 1, 4, 1, 4, 6, 2.36f, .136f, .74f, .060f, .17f, .048f),
+    VARIANT("v32_c128", 1, 2, 1, 6, 6, 2.71f, .111f, .59f, 0.f, .05f, .021f),
+    VARIANT("v32_c64", 1, 1, 1, 6, 10, 2.94f, .093f, .42f, 0.f, 0.f, .015f),
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
 int spmm_variant_count() { return kNumVariants; }
 const char* spmm_variant_name(int v) { return (v >= 0 && v < kNumVariants) ? kVariants[v].name : nullptr; }
 
-static int variant_of(int V, int bsc) {
-  for (int i = 0; i < kNumVariants; ++i)
-    if (kVariants[i].V == V && kVariants[i].bsc == bsc) return i;
-  return -1;
-}
-
-static int pick_variant(int V, int64_t Ccols, int64_t nbr, int cus) {
-  // The 64-column tile where C has no more columns than that, or where even its tiles find a compute
-  // unit each.  What bounds such a call is one unit's L2 -> LDS path and the producers' chain of loads: per
-  // k-step at V = 128 a tile takes 36.5 / 20.5 / 12.5 / 8.5 KB for 512 / 256 / 128 / 64 columns, so as
-  // long as the chip has units to spare a narrower tile is simply shorter.  Measured (us per call among others,
-  // the best wider tile -> 64 columns): 49152 x 12288 x 16 at 128:2:32 30 -> 19 (4.8 TB/s of the
-  // matrix), at 64:2:32 34 -> 23; 8192 x 8192 x 256 at 128:2:16 22.4 -> 19.6; 4096 x 4096 x 512
-  // at 128:2:16 15.3 -> 13.2; 1024 x 16000 x 2048 at 128:2:40 19.5 -> 16.5; 8160 x 8192 x 128 at
-  // 96:2:16 21.9 -> 18.3; of 182 shapes that take it here, none slower.  With 257 to 512 tiles neither side wins
-  // throughout: of 35 shapes 19 are over 3 % faster on it (4096 x 4096 x 1024 at 128:2:32 12.2 -> 10.8), 8
-  // over 3 % slower, the more k-steps the worse (8192 x 8192 x 512 at 128:2:32, 16 and 8: 16.9 -> 18.8,
-  // 23.4 -> 29.9, 36.3 -> 52.2), because the A stream is read once per tile.
-  if (Ccols <= 64 || nbr * ((Ccols + 63) / 64) <= cus) return variant_of(V, 64);
-  // Otherwise the widest column tile that C fills at least half of: wide tiles re-read the A stream
-  // least; narrow C takes the narrow tiles.  When that choice leaves more than half of the compute units
-  // without a tile (few block rows), the 256-column tile spreads the work over twice as many units.  Of 254
-  // shapes 242 are within 3 % of the best of these three; the others, with few block rows and many k-steps,
-  // would be 4 to 14 % faster with 128 columns (1024 x 16000 x 2048 at 64:2:10 48 against 42).
-  const int bsc = Ccols > 256 ? 512 : Ccols > 128 ? 256 : 128;
-  if (bsc == 512 && nbr * ((Ccols + 511) / 512) <= 128) return variant_of(V, 256);
-  return variant_of(V, bsc);
+// The variant of block height V with the smallest expected time.  Narrow tiles spread a small product over more units and
+// have shorter k-steps (us alone on the chip, V = 128: 0.31 / 0.21 / 0.14 / 0.12 for 512 / 256 / 128 / 64 columns: 36.5 /
+// 20.5 / 12.5 / 8.5 KB); wide ones read the records of A less often and load the chip's fabric less; the columns that
+// pad C to whole tiles and a last round with few tiles cost as much as full ones.  The constants of TileCost are least
+// squares fits (relative error, shapes where the variant is near the best counting three times) to the times of all
+// variants over 676 shapes (R 64-49152, K 256-16000, C 8-16384, M 4-128, plain fp16 product): the chosen one is on
+// average 0.7 % slower than the best of the table, at most 15 %.  Against tiles chosen by columns and counts of tiles alone,
+// in us: 256 x 15890 x 6944 at 64:2:10 75 -> 51, 13056 x 2624 x 336 at 96:2:64 11.6 -> 7.6, 3968 x 11324 x 688 at 64:2:4
+// 84 -> 66.
+static int pick_variant(int V, int64_t Ccols, int64_t nbr, int64_t steps, int cus) {
+  int best = -1;
+  float best_time = 0.f;
+  for (int i = 0; i < kNumVariants; ++i) {
+    const Variant& v = kVariants[i];
+    if (v.V != V) continue;
+    const TileCost& c = v.cost;
+    const int64_t tiles = nbr * ((Ccols + v.bsc - 1) / v.bsc);
+    const float s = (float)steps, most = (float)((tiles + cus - 1) / cus), mean = (float)tiles / (float)cus;
+    const float time = c.launch + most * (c.k_step * s + c.tile) + mean * (c.chip_step * s + c.chip_tile) +
+                       (mean < 1.f ? mean : 1.f) * c.fill_step * s;
+    if (best < 0 || time < best_time) { best = i; best_time = time; }
+  }
+  return best;
 }
 
 venom_status_t launch_spmm(const venom_handle& h, const void* B, int64_t ldb, int64_t Ccols, const void* bias, int act,
@@ -840,7 +866,7 @@ venom_status_t launch_spmm(const venom_handle& h, const void* B, int64_t ldb, in
       return VENOM_ERR_HIP;
     if (dev >= 0 && dev < kMaxDevices) cu_count[dev].store(cus, std::memory_order_relaxed);
   }
-  if (variant < 0) variant = pick_variant(Vp, Ccols, L.Rbp, cus);
+  if (variant < 0) variant = pick_variant(Vp, Ccols, L.Rbp, L.steps, cus);
   if (variant < 0 || variant >= kNumVariants || kVariants[variant].V != Vp) return VENOM_ERR_UNSUPPORTED;
   const Variant& var = kVariants[variant];
   SpmmParams p{};
@@ -866,8 +892,7 @@ venom_status_t launch_spmm(const venom_handle& h, const void* B, int64_t ldb, in
   p.per_xcd = (int)((total + kNumXcd - 1) / kNumXcd);
   // one resident workgroup per compute unit (two where the tile is small enough to share a unit);
   // each walks per_xcd / (grid / 8) tiles
-  const int share = (var.lds <= 80 * 1024 && var.threads <= 512) ? 2 : 1;
-  const int64_t resident_per_xcd = (int64_t)(cus / kNumXcd) * share;
+  const int64_t resident_per_xcd = (int64_t)(cus / kNumXcd) * var.share;
   const int64_t wg_per_xcd = p.per_xcd < resident_per_xcd ? p.per_xcd : resident_per_xcd;
   const unsigned grid = (unsigned)(wg_per_xcd * kNumXcd);
   // a workgroup numbers the k-steps of all its tiles with one 32-bit counter

@@ -1,5 +1,5 @@
 """The 64-column tile against the oracle, chosen explicitly and by default: its edges in the columns (64 / 72), sizes on
-both sides of the dispatch rule (256 tiles / 260), one to three waves per strip, ragged last k-steps, several tiles per
+both sides of one tile per unit (256 tiles / 260), one to three waves per strip, ragged last k-steps, several tiles per
 workgroup (every second one runs its k-steps backwards), every output form."""
 import numpy as np
 import pytest
@@ -19,7 +19,7 @@ DEV = "cuda:0"
     (256, 640, 72, 128, 16),          # ... and a second one with 8 columns
     (576, 330, 200, 96, 10),          # three waves per strip, 33 groups
     (512, 56, 4096, 128, 7),          # one k-step, 4 x 64 = 256 tiles
-    (512, 56, 4104, 128, 7),          # 260: the wide tiles again
+    (512, 56, 4104, 128, 7),          # 260
     (64, 136, 56, 64, 8), (32, 4000, 16, 32, 100),
     (1100 * 64, 17 * 8, 16, 64, 8),   # 1100 tiles: two or three per workgroup; three k-steps, one group in the last
     (700 * 96, 9 * 10, 40, 96, 10),   # 700 tiles; two k-steps
