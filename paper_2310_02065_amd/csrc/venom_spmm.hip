@@ -47,6 +47,7 @@ struct SpmmParams {
   int64_t ldb_bytes, ldc, Ccols, rec_bytes;
   int steps;
   int nbr, nct;            // block rows, column tiles
+  int cgroup;              // the tile list goes through groups of this many column tiles, block row by block row
   int per_xcd;             // ceil(nbr*nct / 8)
   int stream_out;          // nonzero: non-temporal stores of C
   int serpentine;          // nonzero: a workgroup's odd tiles run their k-steps backwards, so the end of the
@@ -132,8 +133,11 @@ struct TileWalk {
   int base, first, stride, count;
   __device__ __forceinline__ void locate(const SpmmParams& p, int t, int& ct, int& br) const {
     const int work = base + first + t * stride;
-    ct = work / p.nbr;
-    br = work - ct * p.nbr;
+    const int group = work / (p.nbr * p.cgroup), rest = work - group * (p.nbr * p.cgroup);
+    if (p.cgroup == 1) { ct = group; br = rest; return; }
+    const int left = p.nct - group * p.cgroup, width = left < p.cgroup ? left : p.cgroup;   // (the last group may be narrower)
+    br = rest / width;
+    ct = group * p.cgroup + rest - br * width;
   }
 };
 
@@ -850,6 +854,26 @@ static int pick_variant(int V, int64_t Ccols, int64_t nbr, int64_t steps, int cu
   return best;
 }
 
+// How many column tiles the workgroups of an XCD take side by side.  `resident` tiles are in work there together: one
+// column of them shares the rows of one slab of B but needs as many block rows of A; `c` columns need a c-th of the
+// records and c slabs.  With a 64-column slab the records are most of what the XCD fetches: 8192 x 8192 x 256 at 128:2:16
+// (64 x 4 tiles, 32 per XCD: 10.5 MB with one column, 6.8 with two) 15.4 -> 13.4 us, 16384 x 1024 x 512 at 128:2:8 on
+// this tile 16.8 -> 14.6.  Where the fetch shrinks by less than a quarter nothing is gained (4096 x 4096 x 1024 at
+// 128:2:16 12.3 -> 12.6), nor where the XCD's L2 holds the records (3072 x 768 x 4096 at 64:2:8 23 -> 25), nor on
+// the wider tiles (49152 x 12288 x 2048 at 128:2:32 228 -> 230).
+static int column_group(const Layout& L, int bsc, int64_t nbr, int64_t nct, int64_t resident) {
+  if (bsc != 64) return 1;
+  auto records = [&](int c) {
+    const int64_t rows = (resident + c - 1) / c;
+    return (double)(rows < nbr ? rows : nbr) * (double)L.steps * (double)L.rec_bytes;
+  };
+  auto fetched = [&](int c) { return records(c) + (double)c * 2.0 * bsc * (double)L.K; };
+  int best = 1;
+  for (int c = 2; c <= 4 && c <= nct; c *= 2)
+    if (records(best) > 3e6 && fetched(c) < 0.75 * fetched(best)) best = c;
+  return best;
+}
+
 venom_status_t launch_spmm(const venom_handle& h, const void* B, int64_t ldb, int64_t Ccols, const void* bias, int act,
                            void* C, int64_t ldc, int c_dtype, int tokens_major, int variant, hipStream_t st) {
   const Layout& L = h.lay;
@@ -894,6 +918,7 @@ venom_status_t launch_spmm(const venom_handle& h, const void* B, int64_t ldb, in
   // each walks per_xcd / (grid / 8) tiles
   const int64_t resident_per_xcd = (int64_t)(cus / kNumXcd) * var.share;
   const int64_t wg_per_xcd = p.per_xcd < resident_per_xcd ? p.per_xcd : resident_per_xcd;
+  p.cgroup = column_group(L, var.bsc, p.nbr, p.nct, wg_per_xcd);
   const unsigned grid = (unsigned)(wg_per_xcd * kNumXcd);
   // a workgroup numbers the k-steps of all its tiles with one 32-bit counter
   if ((p.per_xcd + wg_per_xcd - 1) / wg_per_xcd * L.steps >= ((int64_t)1 << 30)) return VENOM_ERR_UNSUPPORTED;
