@@ -410,14 +410,18 @@ static Divisor make_divisor(uint32_t d) {
 }
 __device__ __forceinline__ uint32_t divide(uint32_t n, Divisor d) { return __umulhi(n, d.mul) >> (d.shift - 1); }
 
-// packed -> dense.  A workgroup expands 32 rows (one tile of a block row) x 256 columns, a thread 8
-// neighbouring columns of a row at a time (one 16-byte store where the output allows it): for every
-// group they touch -- one where M is a multiple of 8 -- it reads the group's four row ids, its index
-// nibble and its two values, and places the values by comparing positions.  Bound by the writes; the
-// index arithmetic is kept short because it would bound it otherwise: one division by M per thread, as a multiplication,
-// and everything that depends on the block row is uniform.
-// 8192 x 8192 at M = 8: 29 us, 4.6 TB/s of output (one thread per element, 2-byte stores: 231 us).
-template <bool WIDE>
+// packed -> dense.  A workgroup expands 32 rows (one tile of a block row) x 256 columns; a thread owns 8 neighbouring
+// columns of four rows.  The NG groups that its columns can touch -- one where M is a multiple of 8, three below M = 7 -- are
+// the same in every row, so their row ids are read once and turned into positions among the 8 columns; then
+// each row and group takes an index word and the two values, placed by comparing positions, and each row one
+// 16-byte store at any alignment, past the caches: nothing reads the lines again here, and streamed they leave at the rate
+// of a linear fill.  ALL: M = 4, where every column is kept and a thread's two groups share an index word and
+// an 8-byte pair of values.  Bound by the writes, and before that by the latency of the reads: the loads of all four
+// rows are in flight together.
+// us per call, before (one row and group at a time, cached stores, unaligned rows by elements) and now: 49152 x 12288 at
+// 128:2:32 309 -> 207 (6.2 TB/s; 276 with cached stores), 8192 x 8192 at 64:2:8 35 -> 32, 16384 x 4096 at 128:2:4 60 ->
+// 32, 8192 x 8190 at 64:2:5 156 -> 73.
+template <int NG, bool ALL>
 __global__ void __launch_bounds__(256) decompress_kernel(const char* __restrict__ arec,
                                                          const int32_t* __restrict__ rowidx, int64_t K, int M, Divisor by_M,
                                                          int64_t steps, int vt, int chunks, int64_t rt0,
@@ -427,45 +431,65 @@ __global__ void __launch_bounds__(256) decompress_kernel(const char* __restrict_
   const int64_t rt = rt0 + rtl;                                  // 32-row tile of the matrix
   const int64_t b = rt / vt;
   const int tile = (int)(rt - b * vt);
-  const int i = threadIdx.x >> 3;
+  const unsigned k = chunk * 256 + (threadIdx.x & 31) * 8;
+  if (k >= K) return;
+  const int i0 = threadIdx.x >> 5;                               // rows i0, i0 + 8, ...
   const unsigned rec_bytes = (unsigned)(vt * kTileValBytes + kTailBytes);
-  const char* val = arec + b * steps * rec_bytes + tile * kTileValBytes + i * 16;
-  const char* idx = arec + b * steps * rec_bytes + vt * kTileValBytes + i * 8 + tile * 2;
-  const int32_t* ids = rowidx + b * steps * kStepRows;
-  uint16_t* row = A + (rt * kTileRows + i) * lda;
+  const char* recs = arec + b * steps * rec_bytes;
+  const unsigned end = K - k < 8 ? (unsigned)K : k + 8;
+  const unsigned g0 = divide(k, by_M);
+  constexpr int NI = 4;                                          // rows per thread
+  int4 ids[NG];
+  uint32_t word[NG][NI], v01[NG][NI];
+  bool in[NG];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const unsigned k = chunk * 256 + j * 64 + (threadIdx.x & 7) * 8;
-    if (k >= K) break;
-    const unsigned end = K - k < 8 ? (unsigned)K : k + 8;
+  for (int q = 0; q < NG; ++q) {
+    const unsigned g = g0 + q, s = g / 8, t = g % 8;
+    in[q] = q == 0 || g * (unsigned)M < end;                     // (a group that starts past the columns may not exist)
+    if (!in[q]) continue;
+    if constexpr (ALL) ids[q] = make_int4((int)(4 * g), (int)(4 * g + 1), (int)(4 * g + 2), (int)(4 * g + 3));
+    else ids[q] = *reinterpret_cast<const int4*>(rowidx + (b * steps + s) * kStepRows + 4 * t);
+    const char* rec = recs + (int64_t)s * rec_bytes;
+    const char* val = rec + tile * kTileValBytes + (32 * (t / 4) + i0) * 16 + (t % 4) * 4;
+    const char* idx = rec + vt * kTileValBytes + (32 * (t / 4) + i0) * 8 + tile * 2;
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      if constexpr (ALL) {
+        if (q > 0) continue;
+        word[0][j] = word[NG - 1][j] = *reinterpret_cast<const uint16_t*>(idx + j * 64);
+        const uint2 pair = *reinterpret_cast<const uint2*>(val + j * 128);   // (the record has room for a group past the end)
+        v01[0][j] = pair.x;
+        v01[NG - 1][j] = pair.y;
+      } else {
+        word[q][j] = *reinterpret_cast<const uint16_t*>(idx + j * 64);
+        v01[q][j] = *reinterpret_cast<const uint32_t*>(val + j * 128);
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NI; ++j) {
     uint32_t o[4] = {0, 0, 0, 0};
-    unsigned g = divide(k, by_M), g_end = (g + 1) * (unsigned)M;
-    for (;;) {
-      const unsigned s = g / 8, t = g % 8;
-      const int64_t rec = (int64_t)s * rec_bytes;
-      const uint32_t word = *reinterpret_cast<const uint16_t*>(idx + rec + (t / 4) * 256);
-      const uint32_t v01 = *reinterpret_cast<const uint32_t*>(val + rec + (t / 4) * 512 + (t % 4) * 4);
-      const int4 ri = *reinterpret_cast<const int4*>(ids + (int64_t)s * kStepRows + 4 * t);
-      const uint32_t nib = (word >> (4 * (t % 4))) & 0xfu;
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+      if (!in[q]) continue;
+      const int4 ri = ids[q];
+      const uint32_t nib = word[q][j] >> (4 * ((g0 + q) % 4));
       auto pick = [&](uint32_t p) { return (unsigned)(p == 0 ? ri.x : p == 1 ? ri.y : p == 2 ? ri.z : ri.w) - k; };
-      const unsigned c0 = pick(nib & 3u), c1 = pick(nib >> 2);   // outside 0 .. 7: not in this thread's columns
-      const uint32_t a0 = (v01 & 0xffffu) << (16 * (c0 & 1)), a1 = (v01 >> 16) << (16 * (c1 & 1));
+      const unsigned c0 = pick(nib & 3u), c1 = pick((nib >> 2) & 3u);   // outside 0 .. 7: not in this thread's columns
+      const uint32_t a0 = (v01[q][j] & 0xffffu) << (16 * (c0 & 1)), a1 = (v01[q][j] >> 16) << (16 * (c1 & 1));
 #pragma unroll
       for (unsigned e = 0; e < 4; ++e) {
         if (c0 >> 1 == e) o[e] |= a0;
         if (c1 >> 1 == e) o[e] |= a1;
       }
-      if (g_end >= end) break;
-      ++g;
-      g_end += M;
     }
-    if (WIDE && K - k >= 8) {
-      typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-      *reinterpret_cast<u32x4*>(row + k) = u32x4{o[0], o[1], o[2], o[3]};
+    uint16_t* row = A + (rt * kTileRows + i0 + 8 * j) * lda + k;
+    if (end - k == 8) {
+      __builtin_nontemporal_store(u32x4_any{o[0], o[1], o[2], o[3]}, reinterpret_cast<u32x4_any*>(row));
     } else {
 #pragma unroll
       for (unsigned e = 0; e < 8; ++e)
-        if (k + e < K) row[k + e] = (uint16_t)(o[e / 2] >> (16 * (e % 2)));
+        if (k + e < K) row[e] = (uint16_t)(o[e / 2] >> (16 * (e % 2)));
     }
   }
 }
@@ -528,7 +552,8 @@ hipError_t launch_decompress(const venom_handle& h, uint16_t* A, int64_t lda, hi
   const Layout& L = h.lay;
   if (L.R == 0 || L.K == 0) return hipSuccess;
   const int64_t chunks = (L.K + 255) / 256;
-  auto fn = (reinterpret_cast<uintptr_t>(A) % 16 == 0 && lda % 8 == 0) ? decompress_kernel<true> : decompress_kernel<false>;
+  auto fn = h.M % 8 == 0 ? decompress_kernel<1, false> : h.M == 4 ? decompress_kernel<2, true>
+            : h.M == 5 || h.M == 6 ? decompress_kernel<3, false> : decompress_kernel<2, false>;
   // a launch holds fewer than 2^32 threads, 256 per workgroup however few columns there are: tall narrow matrices
   // take several
   const int64_t tiles = L.R / kTileRows, most = kMaxBlocks / chunks;

@@ -132,6 +132,27 @@ def test_import(library, R, K, V, M, offsets):
     in_child(library, "check_import", R, K, V, M, *offsets)
 
 
+def check_decompress(L, R, K, V, M, lda, offset):
+    A, mask = problem(R, K, V, M)
+    ws, legal = aligned(L.host_workspace_bytes(R, K, V, M)), np.zeros(1, np.uint64)
+    assert L.host_compress(A.ctypes.data, K, mask.ctypes.data, K, R, K, V, M, ws.ctypes.data, legal.ctypes.data) == 0
+    dense = pitched(np.full((R, K), 7, np.uint16), lda, offset)
+    assert L.host_decompress(R, K, V, M, ws.ctypes.data, dense.ctypes.data, lda) == 0
+    assert np.array_equal(dense[:, :K], np.where(mask != 0, A, 0)) and (dense[:, K:] == 0xA5A5).all()
+
+
+@pytest.mark.parametrize("R,K,V,M,lda,offset", [
+    (128, 4, 32, 4, 4, 0), (128, 20, 64, 4, 21, 2),   # one group; five, the last one without its pair
+    (128, 268, 128, 4, 272, 0),      # a second chunk of columns, its last piece four wide
+    (64, 35, 32, 5, 37, 6),          # three groups under eight columns
+    (96, 330, 96, 6, 331, 4), (64, 63, 64, 7, 64, 0),
+    (64, 27, 32, 9, 27, 2), (64, 300, 64, 10, 301, 14),
+    (64, 520, 32, 8, 520, 0), (128, 96, 128, 32, 97, 2),   # one group
+])
+def test_decompress(library, R, K, V, M, lda, offset):
+    in_child(library, "check_decompress", R, K, V, M, lda, offset)
+
+
 def check_decompress_launch(L, R, K, V, M):
     L.host_dry_run(1)
     assert L.host_decompress(R, K, V, M, 0, 0, K) == 0
