@@ -345,16 +345,24 @@ static int general_groups(int M) {
 }
 
 // Groups per workgroup of prune_tile_kernel, 0 if the shape is not its: rows of 256 bytes, in whole
-// 16-byte pieces (which at odd M takes several groups); more where a block has fewer than 32 rows, so that a
-// workgroup still holds 8 KB (4096 x 8192, us per call with 128 columns -> now, prune_kernel: 1:2:128 1227 -> 312, 960;
-// 16:2:64 104 -> 65, 101; 8:2:8 143 -> 63, 421), fewer where four tiles would not share a compute unit.
+// 16-byte pieces (which at odd M takes several groups), doubled while four tiles still share a compute unit: a workgroup's
+// second passes then cost less per byte (8192 x 8192, us per call with 128 columns -> now: 64:2:16 62 -> 51, 48:2:8 78 -> 60,
+// 32:2:16 94 -> 53, 40:2:32 83 -> 56; with 256: 16:2:16 95 -> 63; 4096 x 8192 at 1:2:128, prune_kernel 960: 1227 ->
+// 312).  Widths between the doublings lose (80 rows, 176 columns: 63 -> 65).  Where the columns are no whole number of groups
+// the doubling pays in low blocks only (56:2:10, 280 columns: 97 -> 103; 12:2:40 with 1024 columns 139 -> 151), and less
+// where a wave picks the columns of a group (M > 64: 16:2:100 with 600 columns 114 -> 133).
 static int tile_groups(int V, int M) {
   if (V > kTileMaxV) return 0;
   const int whole = M % 8 == 0 ? 1 : M % 4 == 0 ? 2 : M % 2 == 0 ? 4 : 8;
+  constexpr int kShared = 38 * 1024;
+  int widest = V < 8 ? kPruneMaxCols : 512;
+  if (512 % M == 0) widest = V < 16 ? kPruneMaxCols : 512;
+  else if (M > 64) widest = V < 8 ? kPruneMaxCols : V < 16 ? 512 : V < 32 ? 256 : 128;
+  else if (V > 48) widest = 128;
   int cols = 128;
-  while (cols < kPruneMaxCols && V * cols < 4096) cols *= 2;
+  while (cols < widest && tile_lds(V, 2 * cols) <= kShared) cols *= 2;
   int n = (cols + M * whole - 1) / (M * whole);    // in units of `whole` groups
-  while (n > 1 && (tile_lds(V, n * whole * M) > 38 * 1024 || n * whole * M > kPruneMaxCols || n * whole > kTileMaxGroups)) --n;
+  while (n > 1 && (tile_lds(V, n * whole * M) > kShared || n * whole * M > kPruneMaxCols || n * whole > kTileMaxGroups)) --n;
   const int gpw = n * whole;
   return tile_lds(V, gpw * M) <= kTileLds - 2048 && gpw * M <= kPruneMaxCols && gpw <= kTileMaxGroups ? gpw : 0;
 }
