@@ -33,6 +33,16 @@ void* static_scratch_of_current_device() {
   return addr[dev];
 }
 
+// Whether p (null: nothing) is memory of the same GPU as q.
+bool same_device(const void* q, const void* p) {
+  if (p == nullptr) return true;
+  hipPointerAttribute_t aq{}, ap{};
+  if (hipPointerGetAttributes(&aq, q) == hipSuccess && hipPointerGetAttributes(&ap, p) == hipSuccess)
+    return aq.type == hipMemoryTypeDevice && ap.type == hipMemoryTypeDevice && aq.device == ap.device;
+  (void)hipGetLastError();                         // memory the runtime does not know
+  return false;
+}
+
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
 venom_status_t check_shape(int64_t R, int64_t K, int V, int N, int M) {
@@ -161,6 +171,11 @@ venom_status_t venom_export(const venom_handle_t* h, uint16_t* values_dev, uint1
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (h->R == 0 || h->K == 0) return VENOM_OK;
   hipError_t e = hipSuccess;
+  if (same_device(h->ws, values_dev) && same_device(h->ws, columns_dev) && same_device(h->ws, meta_dev)) {
+    e = venom::launch_export(*h, values_dev, columns_dev, meta_dev, st);
+    return e == hipSuccess ? VENOM_OK : VENOM_ERR_HIP;
+  }
+  // memory that a kernel on the handle's device may not reach: copies, which the runtime routes
   if (values_dev)
     e = hipMemcpyAsync(values_dev, h->ws + L.off_values, (size_t)h->R * L.G * 4, hipMemcpyDeviceToDevice, st);
   if (e == hipSuccess && columns_dev)

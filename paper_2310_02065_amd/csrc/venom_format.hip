@@ -548,6 +548,52 @@ hipError_t launch_compress(const uint16_t* A, int64_t lda, const uint8_t* mask, 
   return hipGetLastError();
 }
 
+// The canonical arrays out of the workspace, all three in one launch: each workgroup copies 16 KB of one of them, 16
+// bytes a thread and access, at any alignment of the destination, streamed.  Three asynchronous copies cost the host 5 us
+// each, and two of them move next to nothing.  us per call of the binding, copies -> now: 49152 x 12288 at
+// 128:2:32 (86 MB) 36 -> 29 (30 with cached stores), 16384 x 4096 at 128:2:4 32 -> 23, 512 x 1024 at 64:2:8 18 -> 13.5.
+struct CopyList { const char* src[3]; char* dst[3]; int64_t bytes[3]; unsigned first[3]; };   // first workgroup of each
+constexpr int kCopyUnits = 4;                        // 16-byte pieces per thread
+constexpr int64_t kCopyBytes = 256 * 16 * kCopyUnits;
+
+__global__ void __launch_bounds__(256) export_kernel(CopyList l) {
+  const int k = blockIdx.x >= l.first[2] ? 2 : blockIdx.x >= l.first[1] ? 1 : 0;
+  const char* src = k == 0 ? l.src[0] : k == 1 ? l.src[1] : l.src[2];
+  char* dst = k == 0 ? l.dst[0] : k == 1 ? l.dst[1] : l.dst[2];
+  const int64_t bytes = k == 0 ? l.bytes[0] : k == 1 ? l.bytes[1] : l.bytes[2];
+  const int64_t at = (int64_t)(blockIdx.x - (k == 0 ? l.first[0] : k == 1 ? l.first[1] : l.first[2])) * kCopyBytes + threadIdx.x * 16;
+  u32x4_any x[kCopyUnits];
+#pragma unroll
+  for (int j = 0; j < kCopyUnits; ++j) {
+    const int64_t o = at + j * 4096;
+    if (o + 16 <= bytes) x[j] = *reinterpret_cast<const u32x4_any*>(src + o);
+  }
+#pragma unroll
+  for (int j = 0; j < kCopyUnits; ++j) {
+    const int64_t o = at + j * 4096;
+    if (o + 16 <= bytes) __builtin_nontemporal_store(x[j], reinterpret_cast<u32x4_any*>(dst + o));
+    else
+      for (int64_t e = o; e < bytes; e += 4)         // (the arrays are whole words)
+        *reinterpret_cast<u32_any*>(dst + e) = *reinterpret_cast<const u32_any*>(src + e);
+  }
+}
+
+hipError_t launch_export(const venom_handle& h, void* values, void* columns, void* meta, hipStream_t st) {
+  const Layout& L = h.lay;
+  CopyList l{{h.ws + L.off_values, h.ws + L.off_columns, h.ws + L.off_meta},
+             {static_cast<char*>(values), static_cast<char*>(columns), static_cast<char*>(meta)},
+             {values ? L.R * L.G * 4 : 0, columns ? L.Rb * L.G * 8 : 0, meta ? L.R * L.W * 4 : 0},
+             {0, 0, 0}};
+  unsigned blocks = 0;
+  for (int k = 0; k < 3; ++k) {
+    l.first[k] = blocks;
+    blocks += (unsigned)((l.bytes[k] + kCopyBytes - 1) / kCopyBytes);
+  }
+  if (blocks == 0) return hipSuccess;
+  hipLaunchKernelGGL(export_kernel, dim3(blocks), dim3(256), 0, st, l);
+  return hipGetLastError();
+}
+
 hipError_t launch_decompress(const venom_handle& h, uint16_t* A, int64_t lda, hipStream_t st) {
   const Layout& L = h.lay;
   if (L.R == 0 || L.K == 0) return hipSuccess;

@@ -66,6 +66,8 @@ hipError_t launch_compress(const uint16_t* A, int64_t lda, const uint8_t* mask, 
 hipError_t launch_import(const uint16_t* values, const uint16_t* columns, const uint32_t* meta, const venom_handle& h,
                          hipStream_t st);
 hipError_t launch_decompress(const venom_handle& h, uint16_t* A, int64_t lda, hipStream_t st);
+// copies the canonical arrays (null: not that one) to memory of the handle's device, at any address
+hipError_t launch_export(const venom_handle& h, void* values, void* columns, void* meta, hipStream_t st);
 
 // ---- pruning (venom_prune.hip)
 hipError_t launch_prune(const uint16_t* A, int64_t lda, int64_t R, int64_t K, int V, int M, uint8_t* mask, int64_t ldm,

@@ -122,3 +122,23 @@ def test_import_of_arrays_at_any_address(R, K, V, M, offset):
         moved.append(buf[offset:])
     for got, w in zip(binding.venom_export(binding.venom_import(*moved, R, K, V, 2, M)), want):
         assert np.array_equal(got.cpu().numpy().view(w.dtype), w)
+
+
+@pytest.mark.parametrize("R,K,V,M", [(64, 5 * 8, 64, 8), (32, 1024 * 4, 32, 4), (96, 33 * 7, 96, 7), (9, 50 * 5, 1, 5)])
+def test_export_at_any_address_and_in_part(R, K, V, M):
+    rng = np.random.default_rng(R + K)
+    mask = inputs.gen_mask(R, K, V, M, rng)
+    A = rng.standard_normal((R, K)).astype(np.float16)
+    h = binding.venom_compress(torch.from_numpy(A).to(DEV), torch.from_numpy(mask).to(DEV), V, 2, M)
+    want = [torch.from_numpy(np.ascontiguousarray(x).view(np.uint8).reshape(-1)) for x in o.compress(A.view(np.uint16), mask, V, M)]
+    for shifts in ((0, 0, 0), (2, 6, 4), (1, 3, 5)):
+        for skip in (None, 0, 1, 2):
+            bufs = [torch.full((w.numel() + 16,), 0xA5, dtype=torch.uint8, device=DEV) for w in want]
+            ptrs = [None if k == skip else b.data_ptr() + s for k, (b, s) in enumerate(zip(bufs, shifts))]
+            assert binding.lib().venom_export(h.ptr, *ptrs, None) == binding.VENOM_OK
+            torch.cuda.synchronize()
+            for k, (b, s, w) in enumerate(zip(bufs, shifts, want)):
+                got = b.cpu()
+                inside = got[s:s + w.numel()]
+                assert bool((inside == 0xA5).all()) if k == skip else torch.equal(inside, w), (shifts, skip, k)
+                assert bool((got[:s] == 0xA5).all()) and bool((got[s + w.numel():] == 0xA5).all())
