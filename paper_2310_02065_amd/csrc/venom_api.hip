@@ -33,6 +33,45 @@ void* static_scratch_of_current_device() {
   return addr[dev];
 }
 
+// Words of pinned host memory that a kernel can write and the host reads after waiting for the stream: one per call in
+// flight, from a page that is allocated with the first call and kept.  A call that finds none left, or no page, does
+// without (get() is null).
+class HostWord {
+ public:
+  HostWord() {
+    std::lock_guard<std::mutex> lock(mutex());
+    Page& p = page();
+    if (!p.words && !p.tried) {
+      void* mem = nullptr;
+      p.tried = true;
+      if (hipHostMalloc(&mem, kWords * kStride, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) p.words = static_cast<char*>(mem);
+      else (void)hipGetLastError();
+    }
+    if (!p.words || !~p.used) return;
+    slot_ = __builtin_ctzll(~p.used);
+    p.used |= 1ull << slot_;
+    *get() = ~0ull;
+  }
+  ~HostWord() {
+    if (slot_ < 0) return;
+    std::lock_guard<std::mutex> lock(mutex());
+    page().used &= ~(1ull << slot_);
+  }
+  HostWord(const HostWord&) = delete;
+  HostWord& operator=(const HostWord&) = delete;
+  unsigned long long* get() const {
+    return slot_ < 0 ? nullptr : reinterpret_cast<unsigned long long*>(page().words + slot_ * kStride);
+  }
+  unsigned long long read() const { return *const_cast<volatile unsigned long long*>(get()); }
+
+ private:
+  static constexpr int kWords = 64, kStride = 64;  // a cache line each
+  struct Page { char* words; unsigned long long used; bool tried; };
+  static Page& page() { static Page p{}; return p; }
+  static std::mutex& mutex() { static std::mutex m; return m; }
+  int slot_ = -1;
+};
+
 // Whether p (null: nothing) is memory of the same GPU as q.
 bool same_device(const void* q, const void* p) {
   if (p == nullptr) return true;
@@ -116,11 +155,24 @@ venom_status_t venom_compress(const void* A_f16_dev, int64_t lda, const uint8_t*
   s = make_handle(R, K, V, N, M, workspace_dev, workspace_bytes, &h);
   if (s != VENOM_OK) return s;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  hipError_t e = venom::launch_compress(static_cast<const uint16_t*>(A_f16_dev), lda, mask_dev, ldm, *h, st);
+  const uint16_t* A = static_cast<const uint16_t*>(A_f16_dev);
+  hipError_t e = hipSuccess;
   unsigned long long key = ~0ull;
-  if (e == hipSuccess)   // returns when the word is here: one wait, where an asynchronous copy into this frame and a
-                         // synchronisation are two
-    e = hipMemcpyWithStream(&key, h->ws + h->lay.off_status, sizeof(key), hipMemcpyDeviceToHost, st);
+  bool legal = false;
+  {
+    const HostWord word;                           // first only: is the mask legal?
+    if (word.get()) {
+      e = venom::launch_compress(A, lda, mask_dev, ldm, *h, st, word.get());
+      if (e == hipSuccess) e = hipStreamSynchronize(st);
+      legal = e == hipSuccess && word.read() == ~0ull;
+    }
+  }
+  if (e == hipSuccess && !legal) {                 // no, or no such word: where is the first offender?
+    e = venom::launch_compress(A, lda, mask_dev, ldm, *h, st);
+    if (e == hipSuccess)   // returns when the word is here: one wait, where an asynchronous copy into this frame and a
+                           // synchronisation are two
+      e = hipMemcpyWithStream(&key, h->ws + h->lay.off_status, sizeof(key), hipMemcpyDeviceToHost, st);
+  }
   if (e != hipSuccess) { delete h; return VENOM_ERR_HIP; }
   if (key != ~0ull) {
     const int64_t G = h->lay.G;
@@ -154,10 +206,14 @@ venom_status_t venom_import(const uint16_t* values_dev, const uint16_t* columns_
   hipError_t e = hipSuccess;
   if (R > 0 && K > 0) {
     // the arrays come from outside: no handle to malformed ones leaves this function
-    unsigned long long word = 0;
-    e = venom::launch_import(values_dev, columns_dev, meta_dev, *h, st);
-    if (e == hipSuccess) e = hipMemcpyWithStream(&word, h->ws + L.off_status, sizeof(word), hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess && word != ~0ull) { delete h; return VENOM_ERR_INVALID_ARG; }
+    unsigned long long key = 0;
+    const HostWord word;
+    e = venom::launch_import(values_dev, columns_dev, meta_dev, *h, st, word.get());
+    if (e == hipSuccess) {
+      if (word.get()) { e = hipStreamSynchronize(st); key = word.read(); }
+      else e = hipMemcpyWithStream(&key, h->ws + L.off_status, sizeof(key), hipMemcpyDeviceToHost, st);
+    }
+    if (e == hipSuccess && key != ~0ull) { delete h; return VENOM_ERR_INVALID_ARG; }
   }
   if (e != hipSuccess) { delete h; return VENOM_ERR_HIP; }
   *out = h;

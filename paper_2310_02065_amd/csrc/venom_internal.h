@@ -59,12 +59,13 @@ struct venom_handle {
 namespace venom {
 
 // ---- format kernels (venom_format.hip)
+// ~0 in the workspace's legality word, or the smallest key of a violation; with `found`, a word of host memory that
+// holds ~0, only whether there is one: then that word becomes 0 and the workspace's is left alone
 hipError_t launch_compress(const uint16_t* A, int64_t lda, const uint8_t* mask, int64_t ldm, const venom_handle& h,
-                           hipStream_t st);
-// checks, copies and packs canonical arrays; like launch_compress it leaves ~0 in the workspace's legality word iff
-// everything was well formed
+                           hipStream_t st, unsigned long long* found = nullptr);
+// checks, copies and packs canonical arrays; the words as above, ~0 iff everything was well formed
 hipError_t launch_import(const uint16_t* values, const uint16_t* columns, const uint32_t* meta, const venom_handle& h,
-                         hipStream_t st);
+                         hipStream_t st, unsigned long long* found = nullptr);
 hipError_t launch_decompress(const venom_handle& h, uint16_t* A, int64_t lda, hipStream_t st);
 // copies the canonical arrays (null: not that one) to memory of the handle's device, at any address
 hipError_t launch_export(const venom_handle& h, void* values, void* columns, void* meta, hipStream_t st);
