@@ -10,6 +10,10 @@ import ctypes
 import os
 from ctypes import POINTER, byref, c_char_p, c_int, c_int64, c_size_t, c_void_p
 
+import torch
+
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libvenom.so")
 
@@ -94,13 +98,17 @@ def lib() -> ctypes.CDLL:
 
 
 def _stream_ptr(stream=None):
-    import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return c_void_p(s.cuda_stream)
+    """The stream's handle as an integer; the current device's current stream by default.  (Asked for by itself it takes
+    0.2 us; torch.cuda.current_stream() makes an object of it first, 1.5 us.)"""
+    if stream is not None:
+        return stream.cuda_stream
+    if _current_raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _current_raw_stream(torch.cuda.current_device())
 
 
 def _ptr(t):
-    return c_void_p(t.data_ptr()) if t is not None else c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def venom_workspace_bytes(R, K, V, N, M) -> int:
@@ -135,7 +143,6 @@ class Handle:
 
 
 def _workspace(R, K, V, N, M, device):
-    import torch
     nbytes = venom_workspace_bytes(R, K, V, N, M)
     ws = torch.empty(max(nbytes, 256) + 256, dtype=torch.uint8, device=device)
     off = (-ws.data_ptr()) % 256
@@ -144,7 +151,6 @@ def _workspace(R, K, V, N, M, device):
 
 def venom_compress(A, mask, V, N, M, stream=None) -> Handle:
     """A: R x K float16 CUDA tensor (row stride lda), mask: R x K uint8 CUDA tensor."""
-    import torch
     assert A.is_cuda and mask.is_cuda and A.dtype == torch.float16 and mask.dtype in (torch.uint8, torch.bool)
     assert A.dim() == 2 and mask.shape == A.shape and A.stride(1) == 1 and mask.stride(1) == 1
     R, K = A.shape
@@ -165,7 +171,6 @@ def venom_compress(A, mask, V, N, M, stream=None) -> Handle:
 def venom_prune(A, V, N, M, stream=None):
     """Magnitude pruning of A (R x K float16 CUDA tensor) to V:N:M.  Returns (mask uint8 R x K,
     kept_mass int64 [R/V], total_mass int64 [R/V]); the masses are exact integers in units of 2^-24."""
-    import torch
     assert A.is_cuda and A.dtype == torch.float16 and A.dim() == 2 and A.stride(1) == 1
     R, K = A.shape
     mask = torch.empty((R, K), dtype=torch.uint8, device=A.device)
@@ -210,7 +215,6 @@ def venom_import(values, columns, meta, R, K, V, N, M, stream=None) -> Handle:
 def venom_export(h: Handle, stream=None):
     """Returns (values int16 [R,G,2], columns int16 [R/V,G,4], meta int32 [R,ceil(G/8)]) CUDA tensors
     holding the canonical uint16 / uint32 bit patterns."""
-    import torch
     G = h.G
     dev = h.workspace.device
     values = torch.empty((h.R, G, 2), dtype=torch.int16, device=dev)
@@ -223,7 +227,6 @@ def venom_export(h: Handle, stream=None):
 
 
 def venom_decompress(h: Handle, out=None, stream=None):
-    import torch
     if out is None:
         out = torch.empty((h.R, h.K), dtype=torch.float16, device=h.workspace.device)
     st = lib().venom_decompress(h.ptr, _ptr(out), out.stride(0) if h.R > 1 else max(h.K, out.stride(0)),
@@ -234,25 +237,35 @@ def venom_decompress(h: Handle, out=None, stream=None):
 
 
 ACTIVATIONS = {"none": 0, "gelu": 1, "gelu_tanh": 2}
+_OUT_DTYPES = {torch.float16: 0, torch.float32: 1}
+
+
+def _scratch_bytes(h: Handle, tokens) -> int:
+    """Room for X transposed, its rows padded to whole 16-byte pieces (venom_linear_scratch_bytes, which the library
+    checks the scratch against)."""
+    return h.K * ((tokens + 7) // 8 * 8) * 2
 
 
 def venom_spmm(h: Handle, B, out=None, out_dtype=None, variant=-1, stream=None, bias=None, activation="none"):
     """C = act(A . B + bias[:, None]).  B: K x C float16 CUDA tensor (unit column stride);
     bias: float16 CUDA vector of R entries or None; returns/fills C (R x C)."""
-    import torch
-    assert B.is_cuda and B.dtype == torch.float16 and B.dim() == 2 and B.stride(1) == 1
-    Ccols = B.shape[1]
+    assert B.is_cuda and B.dtype == torch.float16 and B.dim() == 2
+    (rows, Ccols), (ldb, unit) = B.shape, B.stride()
+    assert unit == 1
     if out is None:
         out = torch.empty((h.R, Ccols), dtype=out_dtype or torch.float16, device=B.device)
-    assert out.dtype in (torch.float16, torch.float32) and out.stride(1) == 1
-    c_dtype = 1 if out.dtype == torch.float32 else 0
-    ldb = B.stride(0) if B.shape[0] > 1 else max(Ccols, B.stride(0))
-    ldc = out.stride(0) if out.shape[0] > 1 else max(Ccols, out.stride(0))
+    dtype, strides = out.dtype, out.stride()
+    assert dtype in _OUT_DTYPES and strides[1] == 1
+    ldc = strides[0]
+    if rows <= 1:
+        ldb = max(Ccols, ldb)
+    if out.shape[0] <= 1:
+        ldc = max(Ccols, ldc)
     if bias is not None:
         assert bias.is_cuda and bias.dtype == torch.float16 and bias.dim() == 1 and bias.shape[0] == h.R
         assert bias.stride(0) == 1
-    st = lib().venom_spmm_bias_act(h.ptr, _ptr(B), ldb, Ccols, _ptr(bias), ACTIVATIONS[activation], _ptr(out), ldc,
-                                   c_dtype, variant, _stream_ptr(stream))
+    st = lib().venom_spmm_bias_act(h.ptr, B.data_ptr(), ldb, Ccols, _ptr(bias), ACTIVATIONS[activation], out.data_ptr(), ldc,
+                                   _OUT_DTYPES[dtype], variant, _stream_ptr(stream))
     if st != VENOM_OK:
         raise VenomError(st, "venom_spmm")
     return out
@@ -261,24 +274,21 @@ def venom_spmm(h: Handle, B, out=None, out_dtype=None, variant=-1, stream=None, 
 def venom_linear(h: Handle, X, bias=None, activation="none", out=None, out_dtype=None, scratch=None, stream=None):
     """Y = act(X . A^T + bias): X tokens x K float16 CUDA tensor, Y tokens x R (token-major in and out).
     `scratch` (uint8 CUDA tensor) receives X transposed; allocated here when not given."""
-    import torch
-    assert X.is_cuda and X.dtype == torch.float16 and X.dim() == 2 and X.stride(1) == 1 and X.shape[1] == h.K
-    tokens = X.shape[0]
+    assert X.is_cuda and X.dtype == torch.float16 and X.dim() == 2
+    (tokens, K), (ldx, unit) = X.shape, X.stride()
+    assert unit == 1 and K == h.K
     if out is None:
         out = torch.empty((tokens, h.R), dtype=out_dtype or torch.float16, device=X.device)
-    assert out.dtype in (torch.float16, torch.float32) and out.stride(1) == 1 and out.shape == (tokens, h.R)
-    need = c_size_t(0)
-    st = lib().venom_linear_scratch_bytes(h.ptr, tokens, byref(need))
-    if st != VENOM_OK:
-        raise VenomError(st, "venom_linear_scratch_bytes")
+    dtype, (ldy, unit) = out.dtype, out.stride()
+    assert dtype in _OUT_DTYPES and unit == 1 and out.shape == (tokens, h.R)
     if scratch is None:
-        scratch = torch.empty(max(need.value, 16), dtype=torch.uint8, device=X.device)
+        scratch = torch.empty(max(_scratch_bytes(h, tokens), 16), dtype=torch.uint8, device=X.device)
     if bias is not None:
         assert bias.is_cuda and bias.dtype == torch.float16 and bias.dim() == 1 and bias.shape[0] == h.R
-    ldx = X.stride(0) if tokens > 1 else max(h.K, X.stride(0))
-    ldy = out.stride(0) if tokens > 1 else max(h.R, out.stride(0))
-    st = lib().venom_linear(h.ptr, _ptr(X), ldx, tokens, _ptr(bias), ACTIVATIONS[activation], _ptr(out), ldy,
-                            1 if out.dtype == torch.float32 else 0, _ptr(scratch), scratch.numel(), _stream_ptr(stream))
+    if tokens <= 1:
+        ldx, ldy = max(h.K, ldx), max(h.R, ldy)
+    st = lib().venom_linear(h.ptr, X.data_ptr(), ldx, tokens, _ptr(bias), ACTIVATIONS[activation], out.data_ptr(), ldy,
+                            _OUT_DTYPES[dtype], scratch.data_ptr(), scratch.numel(), _stream_ptr(stream))
     if st != VENOM_OK:
         raise VenomError(st, "venom_linear")
     return out
@@ -291,7 +301,6 @@ def venom_linear_static_max_bytes() -> int:
 def venom_linear_static(h: Handle, X, out, bias=None, activation="none", stream=None):
     """venom_linear with the library's own static scratch: the caller passes the input and the output,
     nothing is allocated here or in the library."""
-    import torch
     assert X.is_cuda and X.dtype == torch.float16 and X.dim() == 2 and X.stride(1) == 1 and X.shape[1] == h.K
     tokens = X.shape[0]
     assert out.dtype in (torch.float16, torch.float32) and out.stride(1) == 1 and out.shape == (tokens, h.R)
@@ -323,13 +332,9 @@ class Spmm:
         return cls(weight, mask, bias, V, N, M, activation)
 
     def __call__(self, x, out=None, out_dtype=None, stream=None):
-        import torch
-        need = c_size_t(0)
-        st = lib().venom_linear_scratch_bytes(self.handle.ptr, x.shape[0], byref(need))
-        if st != VENOM_OK:
-            raise VenomError(st, "venom_linear_scratch_bytes")
-        if self._scratch is None or self._scratch.numel() < need.value or self._scratch.device != x.device:
-            self._scratch = torch.empty(max(need.value, 16), dtype=torch.uint8, device=x.device)
+        need = max(_scratch_bytes(self.handle, x.shape[0]), 16)
+        if self._scratch is None or self._scratch.numel() < need or self._scratch.device != x.device:
+            self._scratch = torch.empty(need, dtype=torch.uint8, device=x.device)
         return venom_linear(self.handle, x, self.bias, self.activation, out, out_dtype, self._scratch, stream)
 
 
