@@ -95,25 +95,30 @@ __device__ __forceinline__ int slot_swizzle(int rho) {
   return ROW_BYTES == 128 ? 4 * ((rho >> 1) & 1) : 4 * (rho & 3);
 }
 
-// GELU(x) = x * Phi(x) = x/2 * (1 + erf(x / sqrt 2)).  erf by the rational-times-Gaussian formula
-// 7.1.26 of Abramowitz & Stegun (absolute error below 1.5e-7, fp32 noise level), a dozen
-// instructions with the hardware exp2 and reciprocal: the output stage evaluates it 128 times per
-// lane, fully unrolled, so a library erff would cost more code than the rest of the kernel.
+// GELU(x) = x * Phi(x) = x/2 + |x| (1/2 - Q(|x|)), Q the upper tail of the normal distribution, as 2^P(|x|): log2 Q is
+// smooth, so one exponential and no reciprocal.  P is the degree-8 polynomial with P(0) = -1 that minimises the largest
+// error |x| Q ln 2 |P - log2 Q| on 0 <= |x| <= 6 (a linear program; 1e-8), under the condition that its leading
+// coefficient is negative and it stays below -29 from there on, where Q |x| is no longer seen: no clamp is needed, and
+// infinities and NaN come out as from x * Phi(x).  In fp32 3e-7 of GELU at most, 4e-8 in norm on N(0, 1/4) .. N(0, 9): a
+// third of the rational-times-Gaussian formula it replaces (4e-7, 1e-7), in 11 full-rate instructions and one
+// transcendental where that took 15 and two.  The output stage evaluates it 128 times per lane on the waves that the
+// matrix instructions then wait for: 4096 x 1024 x 16384 at 128:2:16 with bias, us per call, 76 -> 69; as token-major layer 94 -> 87.
 __device__ __forceinline__ float gelu_by_definition(float x) {
-  const float z = fabsf(x) * 0.70710678118654752f;
-  const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, z, 1.f));
-  float poly = fmaf(1.061405429f, t, -1.453152027f);
-  poly = fmaf(poly, t, 1.421413741f);
-  poly = fmaf(poly, t, -0.284496736f);
-  poly = fmaf(poly, t, 0.254829592f);
-  const float tail = poly * t * __builtin_amdgcn_exp2f(-1.4426950408889634f * z * z);   // 1 - erf(z)
-  const float phi = x < 0.f ? 0.5f * tail : 1.f - 0.5f * tail;                           // Phi(x)
-  return x * phi;
+  const float a = fabsf(x);
+  float p = fmaf(-1.95304377e-06f, a, 2.87517058e-05f);
+  p = fmaf(p, a, -1.35294098e-04f);
+  p = fmaf(p, a, -2.61155932e-04f);
+  p = fmaf(p, a, 7.22804625e-03f);
+  p = fmaf(p, a, -5.2612373e-02f);
+  p = fmaf(p, a, -4.59168876e-01f);
+  p = fmaf(p, a, -1.15110991f);
+  p = fmaf(p, a, -1.f);
+  return fmaf(a, 0.5f - __builtin_amdgcn_exp2f(p), 0.5f * x);
 }
-// The tanh form x/2 * (1 + tanh u), u = sqrt(2/pi) (x + 0.044715 x^3), written as x / (1 + e^(-2u)).
+// The tanh form x/2 * (1 + tanh u), u = sqrt(2/pi) (x + 0.044715 x^3), written as x / (1 + e^(-2u)); the exponent of 2
+// is x (A + B x^2), A = -2 log2(e) sqrt(2/pi), B = 0.044715 A.
 __device__ __forceinline__ float gelu_tanh_form(float x) {
-  const float u = 0.79788456080286536f * x * fmaf(0.044715f * x, x, 1.f);
-  const float e = __builtin_amdgcn_exp2f(-2.f * 1.4426950408889634f * u);
+  const float e = __builtin_amdgcn_exp2f(x * fmaf(x * x, -0.10294324f, -2.30220818f));
   return x * __builtin_amdgcn_rcpf(1.f + e);
 }
 

@@ -287,3 +287,27 @@ def test_matrix_instruction_probe_runs():
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     tflops = 2000 * 8 * 32768 * 16 * cus / (a.elapsed_time(b) * 1e-3) / 1e12
     assert 500 < tflops < 2600, tflops      # useful FLOP/s of the instruction alone: below the 2.5 PFLOP/s spec peak
+
+
+@pytest.mark.parametrize("activation,limit", [
+    ("gelu", 5e-7),       # the polynomial 1e-8, its fp32 evaluation and the exponential 3e-7 (at |x| = 12 an ulp is 9.5e-7)
+    ("gelu_tanh", 8e-7),
+])
+def test_activation_over_all_fp16_arguments(activation, limit):
+    # a zero product: the output is the activation of the bias, for every fp16 number, infinities and NaN included
+    bits = np.arange(1 << 16, dtype=np.uint32).astype(np.uint16)
+    x = bits.view(np.float16)
+    R, K, C, V, M = 1 << 16, 64, 8, 128, 8
+    A, mask = np.zeros((R, K), np.uint16), np.zeros((R, K), np.uint8)
+    h = compress_dev(A, mask, V, M)
+    B0 = torch.zeros((K, C), dtype=torch.float16, device=DEV)
+    out = binding.venom_spmm(h, B0, out_dtype=torch.float32, bias=torch.from_numpy(x.copy()).to(DEV), activation=activation)
+    got = out.cpu().numpy().astype(np.float64)
+    assert np.array_equal(got, np.repeat(got[:, :1], C, axis=1), equal_nan=True)
+    got, wide = got[:, 0], x.astype(np.float64)
+    near = np.abs(wide) <= 12
+    want = (o.gelu_erf if activation == "gelu" else o.gelu_tanh)(wide[near])
+    assert (np.abs(got[near] - want) <= limit * np.maximum(1, np.abs(want) / 8)).all()
+    far = np.isfinite(wide) & ~near
+    assert np.array_equal(got[far], np.where(wide[far] > 0, wide[far], 0.0))
+    assert np.isnan(got[np.isnan(wide)]).all() and (got[np.isposinf(wide)] == np.inf).all() and np.isnan(got[np.isneginf(wide)]).all()
