@@ -299,7 +299,7 @@ venom_status_t venom_linear(const venom_handle_t* h, const void* X_f16_dev, int6
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int64_t ldbt = (tokens + 7) / 8 * 8;
   if (venom::launch_transpose_tokens(static_cast<const uint16_t*>(X_f16_dev), ldx, tokens, h->K,
-                                     static_cast<uint16_t*>(scratch_dev), ldbt, st) != hipSuccess)
+                                     static_cast<uint16_t*>(scratch_dev), ldbt, tokens * h->R * (int64_t)esz, st) != hipSuccess)
     return VENOM_ERR_HIP;
   return venom::launch_spmm(*h, scratch_dev, ldbt, tokens, bias_f16_dev, activation, Y_dev, ldy, y_dtype, 1, -1, st);
 }

@@ -84,7 +84,8 @@ venom_status_t launch_spmm(const venom_handle& h, const void* B, int64_t ldb, in
 // register-only loop of 2:4 matrix instructions, for the measured instruction peak (grid = one workgroup of 8 waves per
 // compute unit x 2)
 hipError_t launch_smfmac_probe(int iters, float* sink, hipStream_t st);
+// out_bytes: of the layer's output, which follows
 hipError_t launch_transpose_tokens(const uint16_t* X, int64_t ldx, int64_t tokens, int64_t K, uint16_t* BT, int64_t ldbt,
-                                   hipStream_t st);
+                                   int64_t out_bytes, hipStream_t st);
 
 }  // namespace venom

@@ -1019,6 +1019,9 @@ __global__ void __launch_bounds__(256) transpose_tokens_kernel(const uint16_t* _
 // aligned and K a multiple of 8: a thread loads 8 consecutive k of a token, the tile sits in LDS as
 // [token][k] with rows of 136 bytes (so that the column reads below spread over the banks), and a
 // thread gathers 8 consecutive tokens of one k for its store; 8 lanes write 128 contiguous bytes.
+// STREAM: X is read past the caches, which leaves them to BT.  (Tiles of 128 tokens, with four loads a thread, are slower:
+// layer of 4096 x 1024 x 16384 tokens 71.5 -> 73 us, with transposing LDS reads 75.)
+template <bool STREAM>
 __global__ void __launch_bounds__(256) transpose_tokens_wide_kernel(const uint16_t* __restrict__ X, int64_t ldx,
                                                                     int64_t tokens, int64_t K,
                                                                     uint16_t* __restrict__ BT, int64_t ldbt) {
@@ -1030,7 +1033,17 @@ __global__ void __launch_bounds__(256) transpose_tokens_wide_kernel(const uint16
   for (int j = 0; j < 2; ++j) {                    // token r + 32j, k chunk c
     const int64_t tok = tok0 + r + 32 * j, k = k0 + 8 * c;
     uint4 w = make_uint4(0, 0, 0, 0);
-    if (tok < tokens && k < K) w = *reinterpret_cast<const uint4*>(X + tok * ldx + k);
+    if (tok < tokens && k < K) {
+      typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+      const u32x4* src = reinterpret_cast<const u32x4*>(X + tok * ldx + k);
+      if constexpr (STREAM) {
+        const u32x4 q = __builtin_nontemporal_load(src);
+        w = make_uint4(q.x, q.y, q.z, q.w);
+      } else {
+        const u32x4 q = *src;
+        w = make_uint4(q.x, q.y, q.z, q.w);
+      }
+    }
     uint2* dst = reinterpret_cast<uint2*>(tile + (r + 32 * j) * kPitch + c * 16);
     dst[0] = make_uint2(w.x, w.y);
     dst[1] = make_uint2(w.z, w.w);
@@ -1052,11 +1065,17 @@ __global__ void __launch_bounds__(256) transpose_tokens_wide_kernel(const uint16
 }
 
 hipError_t launch_transpose_tokens(const uint16_t* X, int64_t ldx, int64_t tokens, int64_t K, uint16_t* BT, int64_t ldbt,
-                                   hipStream_t st) {
+                                   int64_t out_bytes, hipStream_t st) {
   if (tokens == 0 || K == 0) return hipSuccess;
   if (reinterpret_cast<uintptr_t>(X) % 16 == 0 && reinterpret_cast<uintptr_t>(BT) % 16 == 0 && ldx % 8 == 0 &&
       ldbt % 8 == 0 && K % 8 == 0) {
-    hipLaunchKernelGGL(transpose_tokens_wide_kernel, dim3((unsigned)((K + 63) / 64), (unsigned)((ldbt + 63) / 64)), dim3(256),
+    // A layer whose activations, their copy and output are more than half of the 256 MB memory-side cache does not find X
+    // there when it is called again, and needs the room for the copy; a smaller one may.  us per call of the layer,
+    // cached / streamed reads: 4096 x 1024 x 16384 tokens (201 MB) 70.2 / 66.2, 512 x 8192 x 8192 (277) 99 / 83, 512 x 4096 x
+    // 8192 (143) 59.0 / 57.2; 512 x 4096 x 6144 (107) 46.0 / 49.7, 2048 x 1024 x 12288 (101) 36.6 / 37.4.
+    const bool streamed = 2 * tokens * K * 2 + out_bytes > (int64_t)128 << 20;
+    auto fn = streamed ? transpose_tokens_wide_kernel<true> : transpose_tokens_wide_kernel<false>;
+    hipLaunchKernelGGL(fn, dim3((unsigned)((K + 63) / 64), (unsigned)((ldbt + 63) / 64)), dim3(256),
                        0, st, X, ldx, tokens, K, BT, ldbt);
     return hipGetLastError();
   }
