@@ -1,5 +1,6 @@
 // The C ABI: argument validation, workspace carving, handle lifetime.  All device work is in
 // venom_format.hip / venom_spmm.hip; nothing here allocates device memory.
+#include <initializer_list>
 #include <mutex>
 #include <new>
 
@@ -72,14 +73,22 @@ class HostWord {
   int slot_ = -1;
 };
 
-// Whether p (null: nothing) is memory of the same GPU as q.
-bool same_device(const void* q, const void* p) {
-  if (p == nullptr) return true;
-  hipPointerAttribute_t aq{}, ap{};
-  if (hipPointerGetAttributes(&aq, q) == hipSuccess && hipPointerGetAttributes(&ap, p) == hipSuccess)
-    return aq.type == hipMemoryTypeDevice && ap.type == hipMemoryTypeDevice && aq.device == ap.device;
-  (void)hipGetLastError();                         // memory the runtime does not know
-  return false;
+// Whether a kernel launched on st now runs on the GPU that holds q and all p (null: nothing).  A copy needs neither the
+// current device nor the stream's to be that one.
+bool on_device_of(const void* q, std::initializer_list<const void*> ps, hipStream_t st) {
+  hipPointerAttribute_t aq{};
+  int current = -1;
+  hipDevice_t of_stream = -1;
+  bool same = hipPointerGetAttributes(&aq, q) == hipSuccess && aq.type == hipMemoryTypeDevice &&
+              hipGetDevice(&current) == hipSuccess && aq.device == current &&
+              (st == nullptr || (hipStreamGetDevice(st, &of_stream) == hipSuccess && of_stream == current));
+  for (const void* p : ps) {
+    hipPointerAttribute_t ap{};
+    if (same && p != nullptr)
+      same = hipPointerGetAttributes(&ap, p) == hipSuccess && ap.type == hipMemoryTypeDevice && ap.device == current;
+  }
+  if (!same) (void)hipGetLastError();              // memory the runtime does not know
+  return same;
 }
 
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
@@ -227,7 +236,7 @@ venom_status_t venom_export(const venom_handle_t* h, uint16_t* values_dev, uint1
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (h->R == 0 || h->K == 0) return VENOM_OK;
   hipError_t e = hipSuccess;
-  if (same_device(h->ws, values_dev) && same_device(h->ws, columns_dev) && same_device(h->ws, meta_dev)) {
+  if (on_device_of(h->ws, {values_dev, columns_dev, meta_dev}, st)) {
     e = venom::launch_export(*h, values_dev, columns_dev, meta_dev, st);
     return e == hipSuccess ? VENOM_OK : VENOM_ERR_HIP;
   }

@@ -142,3 +142,31 @@ def test_export_at_any_address_and_in_part(R, K, V, M):
                 inside = got[s:s + w.numel()]
                 assert bool((inside == 0xA5).all()) if k == skip else torch.equal(inside, w), (shifts, skip, k)
                 assert bool((got[:s] == 0xA5).all()) and bool((got[s + w.numel():] == 0xA5).all())
+
+
+def test_export_on_another_stream_and_in_a_graph():
+    R, K, V, M = 64, 5 * 8, 64, 8
+    rng = np.random.default_rng(3)
+    mask = inputs.gen_mask(R, K, V, M, rng)
+    A = rng.standard_normal((R, K)).astype(np.float16)
+    h = binding.venom_compress(torch.from_numpy(A).to(DEV), torch.from_numpy(mask).to(DEV), V, 2, M)
+    want = [torch.from_numpy(np.ascontiguousarray(x).view(np.uint8).reshape(-1)) for x in o.compress(A.view(np.uint16), mask, V, M)]
+    bufs = [torch.zeros(w.numel(), dtype=torch.uint8, device=DEV) for w in want]
+    ptrs = [b.data_ptr() for b in bufs]
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    assert binding.lib().venom_export(h.ptr, *ptrs, side.cuda_stream) == binding.VENOM_OK
+    side.synchronize()
+    for b, w in zip(bufs, want):
+        assert torch.equal(b.cpu(), w)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        st = binding.lib().venom_export(h.ptr, *ptrs, torch.cuda.current_stream().cuda_stream)
+    assert st == binding.VENOM_OK
+    for _ in range(3):
+        for b in bufs:
+            b.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for b, w in zip(bufs, want):
+            assert torch.equal(b.cpu(), w)
