@@ -138,7 +138,13 @@ __host__ __device__ constexpr int bits_pitch(int wpw, int M) { return (wpw * M +
 // last, and in the last (a division in the kernel is 5 % of a workgroup with one row).
 // bits_ok: the bits of V rows fit (48 KB of LDS: 49152 x 12288 at 1024:2:32 takes 464 us a call, more if phase 3 reads the
 // mask again); otherwise (very tall blocks) it does.
-template <int UB>
+// The block rows are taken from the last to the first: what wrote the mask (and read the matrix) went the other way, and
+// left the ends of both in the memory-side cache.  ONCE (phase 1 is the mask's only reader, bits_ok): its loads
+// are streamed, so that they leave that room to the matrix and the outputs.  us of venom_prune and
+// venom_compress together, first to last and cached -> last to first -> streamed as well: 49152 x 12288 at 128:2:32 803 -> 784 ->
+// 765, 12288 x 12288 at 256:2:8 278 -> 267 -> 263, 49152 x 2048 at 32:2:16 168 -> 158 -> 154, 16384 x 4096 at 128:2:16
+// 116 -> 114 -> 113 (compression of one mask again and again, 66 instead of 65).
+template <int UB, bool ONCE>
 __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                        const uint8_t* __restrict__ mask, int64_t ldm, int wpw, int bits_ok,
                                                        unsigned by_full, unsigned by_last,
@@ -149,7 +155,7 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
   __shared__ int cols_ok[kCompressWords * 8];
   __shared__ uint32_t words[kCompressWords][kMaxTiles * kTileRows];   // metadata words, if the packed copy has blocks of V rows
   const int V = d.V, M = d.M;
-  const int64_t b = blockIdx.y, w0 = (int64_t)blockIdx.x * wpw, g0 = w0 * 8;
+  const int64_t b = gridDim.y - 1 - blockIdx.y, w0 = (int64_t)blockIdx.x * wpw, g0 = w0 * 8;
   const int tid = threadIdx.x;
   const int nw = (int)((d.W - w0) < wpw ? (d.W - w0) : wpw);              // words of this workgroup that exist
   const int ng = (int)((d.G - g0) < 8 * nw ? (d.G - g0) : 8 * nw);        // groups that exist
@@ -181,7 +187,8 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
           for (int e = 0; e < UB / 4; ++e) x[j][e] = 0;
           if (v < V) {
             if constexpr (UB == 16) {
-              const u32x4_any q = *reinterpret_cast<const u32x4_any*>(p + (int64_t)v * ldm);
+              const u32x4_any* src = reinterpret_cast<const u32x4_any*>(p + (int64_t)v * ldm);
+              const u32x4_any q = ONCE ? __builtin_nontemporal_load(src) : *src;
               x[j][0] = q.x; x[j][1] = q.y; x[j][2] = q.z; x[j][3] = q.w;
             } else {
               const u32x2_any q = *reinterpret_cast<const u32x2_any*>(p + (int64_t)v * ldm);
@@ -551,7 +558,7 @@ hipError_t launch_compress(const uint16_t* A, int64_t lda, const uint8_t* mask, 
     // every chunk of columns in whole loads, fewer than 8 columns left over at the end of a row
     const int64_t chunk = (int64_t)8 * wpw * h.M, last = L.K - (grid.x - 1) * chunk;
     const int ub = chunk % 16 == 0 && L.K % 16 < 8 ? 16 : 8;
-    auto fn = ub == 16 ? compress_kernel<16> : compress_kernel<8>;
+    auto fn = ub == 8 ? compress_kernel<8, false> : bits_ok ? compress_kernel<16, true> : compress_kernel<16, false>;
     hipLaunchKernelGGL(fn, grid, dim3(256), lds, st, A, lda, mask, ldm, wpw, bits_ok, by(chunk / ub), by(last / ub), format_dst(h),
                        found, status);
   }
