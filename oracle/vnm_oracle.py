@@ -240,11 +240,12 @@ GELU_LIPSCHITZ = 1.13          # sup |gelu'(x)| = 1.1289 (at x = sqrt(2)): GELU 
 
 
 def gelu_erf(x: np.ndarray) -> np.ndarray:
-    """GELU(x) = x * Phi(x) = x/2 * (1 + erf(x / sqrt 2)), the definition, in fp64."""
+    """GELU(x) = x * Phi(x) = x/2 * erfc(-x / sqrt 2), the definition, in fp64 (by erfc, as 1 + erf loses the tail of
+    negative x)."""
     import math
-    erf = np.vectorize(math.erf, otypes=[np.float64])
+    erfc = np.vectorize(math.erfc, otypes=[np.float64])
     x = np.asarray(x, dtype=np.float64)
-    return 0.5 * x * (1.0 + erf(x / math.sqrt(2.0)))
+    return 0.5 * x * erfc(-x / math.sqrt(2.0))
 
 
 def gelu_tanh(x: np.ndarray) -> np.ndarray:

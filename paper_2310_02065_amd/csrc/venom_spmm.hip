@@ -95,25 +95,51 @@ __device__ __forceinline__ int slot_swizzle(int rho) {
   return ROW_BYTES == 128 ? 4 * ((rho >> 1) & 1) : 4 * (rho & 3);
 }
 
-// GELU(x) = x * Phi(x) = x/2 + |x| (1/2 - Q(|x|)), Q the upper tail of the normal distribution, as 2^P(|x|): log2 Q is
-// smooth, so one exponential and no reciprocal.  P is the degree-8 polynomial with P(0) = -1 that minimises the largest
-// error |x| Q ln 2 |P - log2 Q| on 0 <= |x| <= 6 (a linear program; 1e-8), under the condition that its leading
-// coefficient is negative and it stays below -29 from there on, where Q |x| is no longer seen: no clamp is needed, and
-// infinities and NaN come out as from x * Phi(x).  In fp32 3e-7 of GELU at most, 4e-8 in norm on N(0, 1/4) .. N(0, 9): a
-// third of the rational-times-Gaussian formula it replaces (4e-7, 1e-7), in 11 full-rate instructions and one
-// transcendental where that took 15 and two.  The output stage evaluates it 128 times per lane on the waves that the
-// matrix instructions then wait for: 4096 x 1024 x 16384 at 128:2:16 with bias, us per call, 76 -> 69; as token-major layer 94 -> 87.
+// GELU(x) = x * Phi(x) = max(x, 0) - |x| Q(|x|), Q the upper tail of the normal distribution, as 2^P(|x|): log2 Q is
+// smooth, so one exponential and no reciprocal, and x < 0 gets its tail by a product, not as a difference.  P(0) = -1, and
+// each P is the polynomial of its degree with the smallest largest error (a linear program), counted in units of E as
+// error of |x| Q and, for |x| > 4, in units of 2e-4 (|x| - 2.5)^2 as relative error of Q (0.6 to 0.9 of that of the
+// rational-times-Gaussian formula 7.1.26 of Abramowitz & Stegun, which served here before):
+//   fp16 output: degree 8 on |x| <= 5.9, E = 2e-8; from there on P stays below -29 and falls, and the output is zero.
+//     Its leading coefficient is negative, so that no clamp is needed.  Of all fp16 x 54 round another way than
+//     the exact value, by one unit in the last place (256 with 7.1.26, 332 with x/2 + |x| (1/2 - Q)).
+//   fp32 output: degree 11 on |x| <= 13, E = 5e-9, as there the tail is seen down to x = -12.9, where 2^P underflows.  |x| is
+//     clamped where it is multiplied, too: no 0 x Inf.  3e-8 in norm on N(0, 1/4) .. N(0, 9) (7.1.26: 5e-8 to 1e-7), on no
+//     interval worse than 7.1.26 or x/2 + |x| (1/2 - Q).
+// `on` is 1 for x > 0 and 0 for x < 0 (in between it is multiplied by next to nothing), one multiplication with the
+// clamp of its result; infinities and NaN come out as from x * Phi(x).  11 and 15 full-rate instructions and one transcendental
+// (7.1.26: 15 and two).  The output stage evaluates it 128 times per lane on the waves that the matrix instructions
+// then wait for: 4096 x 1024 x 16384 at 128:2:16 with bias, us per call, 7.1.26 -> now, fp16 73 -> 65, fp32 91 -> 90; as
+// token-major layer 93 -> 90 and 117 -> 113.
+template <bool OUT_F32>
 __device__ __forceinline__ float gelu_by_definition(float x) {
-  const float a = fabsf(x);
-  float p = fmaf(-1.95304377e-06f, a, 2.87517058e-05f);
-  p = fmaf(p, a, -1.35294098e-04f);
-  p = fmaf(p, a, -2.61155932e-04f);
-  p = fmaf(p, a, 7.22804625e-03f);
-  p = fmaf(p, a, -5.2612373e-02f);
-  p = fmaf(p, a, -4.59168876e-01f);
-  p = fmaf(p, a, -1.15110991f);
-  p = fmaf(p, a, -1.f);
-  return fmaf(a, 0.5f - __builtin_amdgcn_exp2f(p), 0.5f * x);
+  const float on = __builtin_amdgcn_fmed3f(x * 0x1p126f, 0.f, 1.f);
+  if constexpr (OUT_F32) {
+    const float a = __builtin_amdgcn_fmed3f(fabsf(x), 0.f, 13.5f);
+    float p = fmaf(5.57935698e-10f, a, -3.05136716e-08f);
+    p = fmaf(p, a, 6.97282076e-07f);
+    p = fmaf(p, a, -8.63450987e-06f);
+    p = fmaf(p, a, 6.18117556e-05f);
+    p = fmaf(p, a, -2.28697128e-04f);
+    p = fmaf(p, a, -1.04886603e-04f);
+    p = fmaf(p, a, 7.07445014e-03f);
+    p = fmaf(p, a, -5.25283851e-02f);
+    p = fmaf(p, a, -4.59191263e-01f);
+    p = fmaf(p, a, -1.15110779f);
+    p = fmaf(p, a, -1.f);
+    return fmaf(-a, __builtin_amdgcn_exp2f(p), x * on);
+  } else {
+    const float a = fabsf(x);
+    float p = fmaf(-1.12579994e-06f, a, 1.83935899e-05f);
+    p = fmaf(p, a, -8.35712781e-05f);
+    p = fmaf(p, a, -3.9356359e-04f);
+    p = fmaf(p, a, 7.4137128e-03f);
+    p = fmaf(p, a, -5.27529866e-02f);
+    p = fmaf(p, a, -4.59116608e-01f);
+    p = fmaf(p, a, -1.15111709f);
+    p = fmaf(p, a, -1.f);
+    return x * fabsf(on - __builtin_amdgcn_exp2f(p));
+  }
 }
 // The tanh form x/2 * (1 + tanh u), u = sqrt(2/pi) (x + 0.044715 x^3), written as x / (1 + e^(-2u)); the exponent of 2
 // is x (A + B x^2), A = -2 log2(e) sqrt(2/pi), B = 0.044715 A.
@@ -604,7 +630,7 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
           for (int tc = tc_lo; tc < tc_hi; ++tc)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-              acc[tr][tc][v] = gelu_by_definition(acc[tr][tc][v]);
+              acc[tr][tc][v] = gelu_by_definition<OUT_F32>(acc[tr][tc][v]);
               if ((v & 1) == 1) __builtin_amdgcn_sched_barrier(0);
             }
         } else if (p.act == VENOM_ACT_GELU_TANH) {
