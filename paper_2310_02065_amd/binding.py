@@ -3,11 +3,16 @@
 Every step of the path (compression, packing, the product) runs in the library's HIP kernels;
 PyTorch supplies device memory and streams.  There is no CPU fallback: if the shared library has
 not been built, `lib()` raises.
+
+Every call takes a `stream` (default: the current one).  Tensors made for the caller -- results, a handle's workspace --
+belong to the current stream all the same: where another one is passed, it is the caller who has it wait for the current
+stream and keeps them until their work is done, as with any tensor that is used on a second stream.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import threading
 from ctypes import POINTER, byref, c_char_p, c_int, c_int64, c_size_t, c_void_p
 
 import torch
@@ -246,6 +251,48 @@ def _scratch_bytes(h: Handle, tokens) -> int:
     return h.K * ((tokens + 7) // 8 * 8) * 2
 
 
+def _new_scratch(nbytes, device, stream):
+    """Scratch of a call on `stream` (None: the current one), from that stream's share of the caching allocator: dropped
+    while the call's kernels are still to run, it is handed out again only to work that follows them on the stream."""
+    if stream is None:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+
+
+def _capturing(stream) -> bool:
+    if stream is None:
+        return torch.cuda.is_current_stream_capturing()
+    with torch.cuda.stream(stream):
+        return torch.cuda.is_current_stream_capturing()
+
+
+class _KeptScratch:
+    """The scratch buffers of one layer, one for each stream and thread that calls it (calls on different streams overlap, and
+    two threads on one stream may queue their kernels between each other's), at most LIMIT of them, the oldest dropped
+    first.  A call that is being captured gets one of its own from the graph's memory: the graph keeps using it."""
+
+    LIMIT = 8
+
+    def __init__(self):
+        self._buffers = {}
+        self._lock = threading.Lock()
+
+    def get(self, nbytes, x, stream, stream_ptr):
+        if _capturing(stream):
+            return _new_scratch(nbytes, x.device, stream)
+        key = (stream_ptr, x.get_device(), threading.get_ident())
+        buf = self._buffers.get(key)
+        if buf is None or buf.numel() < nbytes:
+            buf = _new_scratch(nbytes, x.device, stream)
+            with self._lock:
+                self._buffers.pop(key, None)
+                self._buffers[key] = buf
+                while len(self._buffers) > self.LIMIT:
+                    self._buffers.pop(next(iter(self._buffers)))
+        return buf
+
+
 def venom_spmm(h: Handle, B, out=None, out_dtype=None, variant=-1, stream=None, bias=None, activation="none"):
     """C = act(A . B + bias[:, None]).  B: K x C float16 CUDA tensor (unit column stride);
     bias: float16 CUDA vector of R entries or None; returns/fills C (R x C)."""
@@ -274,6 +321,13 @@ def venom_spmm(h: Handle, B, out=None, out_dtype=None, variant=-1, stream=None, 
 def venom_linear(h: Handle, X, bias=None, activation="none", out=None, out_dtype=None, scratch=None, stream=None):
     """Y = act(X . A^T + bias): X tokens x K float16 CUDA tensor, Y tokens x R (token-major in and out).
     `scratch` (uint8 CUDA tensor) receives X transposed; allocated here when not given."""
+    if scratch is None:
+        assert X.is_cuda and X.dim() == 2
+        scratch = _new_scratch(max(_scratch_bytes(h, X.shape[0]), 16), X.device, stream)
+    return _linear(h, X, bias, activation, out, out_dtype, scratch, _stream_ptr(stream))
+
+
+def _linear(h, X, bias, activation, out, out_dtype, scratch, stream_ptr):
     assert X.is_cuda and X.dtype == torch.float16 and X.dim() == 2
     (tokens, K), (ldx, unit) = X.shape, X.stride()
     assert unit == 1 and K == h.K
@@ -281,14 +335,12 @@ def venom_linear(h: Handle, X, bias=None, activation="none", out=None, out_dtype
         out = torch.empty((tokens, h.R), dtype=out_dtype or torch.float16, device=X.device)
     dtype, (ldy, unit) = out.dtype, out.stride()
     assert dtype in _OUT_DTYPES and unit == 1 and out.shape == (tokens, h.R)
-    if scratch is None:
-        scratch = torch.empty(max(_scratch_bytes(h, tokens), 16), dtype=torch.uint8, device=X.device)
     if bias is not None:
         assert bias.is_cuda and bias.dtype == torch.float16 and bias.dim() == 1 and bias.shape[0] == h.R
     if tokens <= 1:
         ldx, ldy = max(h.K, ldx), max(h.R, ldy)
     st = lib().venom_linear(h.ptr, X.data_ptr(), ldx, tokens, _ptr(bias), ACTIVATIONS[activation], out.data_ptr(), ldy,
-                            _OUT_DTYPES[dtype], scratch.data_ptr(), scratch.numel(), _stream_ptr(stream))
+                            _OUT_DTYPES[dtype], scratch.data_ptr(), scratch.numel(), stream_ptr)
     if st != VENOM_OK:
         raise VenomError(st, "venom_linear")
     return out
@@ -317,13 +369,14 @@ class Spmm:
     """The layer object of the paper's end-to-end section (its module listing): built once from a
     dense weight, a mask and a bias, it holds the compressed handle and is called like the linear
     layer it replaces, `y = layer(x)` with x tokens x K and y tokens x R.  Holds state only; every
-    call is one venom_linear (the scratch for the transposed activations is kept between calls)."""
+    call is one venom_linear (the scratch for the transposed activations is kept between calls, one for each
+    stream and thread that calls)."""
 
     def __init__(self, weight, mask, bias=None, V=128, N=2, M=8, activation="none"):
         self.handle = venom_compress(weight, mask, V, N, M)
         self.bias = bias
         self.activation = activation
-        self._scratch = None
+        self._scratch = _KeptScratch()
 
     @classmethod
     def from_dense(cls, weight, bias=None, V=128, N=2, M=8, activation="none"):
@@ -332,10 +385,9 @@ class Spmm:
         return cls(weight, mask, bias, V, N, M, activation)
 
     def __call__(self, x, out=None, out_dtype=None, stream=None):
-        need = max(_scratch_bytes(self.handle, x.shape[0]), 16)
-        if self._scratch is None or self._scratch.numel() < need or self._scratch.device != x.device:
-            self._scratch = torch.empty(need, dtype=torch.uint8, device=x.device)
-        return venom_linear(self.handle, x, self.bias, self.activation, out, out_dtype, self._scratch, stream)
+        ptr = _stream_ptr(stream)
+        scratch = self._scratch.get(max(_scratch_bytes(self.handle, x.shape[0]), 16), x, stream, ptr)
+        return _linear(self.handle, x, self.bias, self.activation, out, out_dtype, scratch, ptr)
 
 
 def venom_get_info(h: Handle):

@@ -89,3 +89,44 @@ def test_layer_object_prunes_compresses_and_matches_the_oracle():
         Ys, Ey = o.linear_fp64(ov, oc, om, R, K, V, M, X.view(np.uint16), bias.view(np.uint16), "gelu")
         ok, info = o.accept(Y.double().cpu().numpy(), Ys, Ey)
         assert ok, (T, info)
+
+
+def test_one_layer_on_two_streams_and_in_a_graph():
+    # Every stream transposes into a scratch of its own, which lives until the stream's work is done: the calls are queued
+    # behind a wait, and in the meantime memory of the same sizes is taken and filled on the current stream.
+    R, K, V, M = 256, 512, 128, 16
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(5)
+    W = torch.randn(R, K, dtype=torch.float16, device=DEV, generator=gen)
+    layer = binding.Spmm.from_dense(W, V=V, M=M)
+    xs = [torch.randn(T, K, dtype=torch.float16, device=DEV, generator=gen) for T in (264, 264, 520, 72)]
+    want = [layer(x) for x in xs]
+    ys = [torch.zeros_like(w) for w in want]
+    zs = [torch.zeros_like(w) for w in want]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for s in streams:
+        with torch.cuda.stream(s):
+            torch.cuda._sleep(20_000_000)
+    for i, (x, y, z) in enumerate(zip(xs, ys, zs)):
+        layer(x, out=y, stream=streams[i % 2])
+        binding.venom_linear(layer.handle, x, out=z, stream=streams[i % 2])      # a scratch that is dropped at once
+    for x in xs:
+        for _ in range(4):
+            torch.full((x.shape[1] * x.shape[0] * 2,), 0xFF, dtype=torch.uint8, device=DEV)
+    torch.cuda.synchronize()
+    for y, z, w in zip(ys, zs, want):
+        assert torch.equal(y, w) and torch.equal(z, w)
+    graph = torch.cuda.CUDAGraph()
+    for y in ys:
+        y.zero_()
+    with torch.cuda.graph(graph):
+        layer(xs[0], out=ys[0])
+        layer(xs[3], out=ys[3])
+    for _ in range(3):
+        ys[0].zero_()
+        ys[3].zero_()
+        graph.replay()
+        assert torch.equal(layer(xs[2]), want[2])
+        torch.cuda.synchronize()
+        assert torch.equal(ys[0], want[0]) and torch.equal(ys[3], want[3])
