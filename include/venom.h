@@ -7,7 +7,7 @@
  *
  * Conventions that hold for every entry point
  *   - every pointer named *_dev is DEVICE memory owned by the caller; the library never
- *     allocates or frees device memory.  Pointers without that suffix are HOST memory.
+ *     allocates or frees device memory (64 words and the array of venom_linear_static come with its code).  Pointers without that suffix are HOST memory.
  *   - matrices are row-major; leading dimensions (lda, ldm, ldb, ldc) are in ELEMENTS.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *   - every call returns a venom_status_t; nothing aborts or throws across the boundary.
@@ -72,7 +72,8 @@ venom_status_t venom_workspace_bytes(int64_t R, int64_t K, int V, int N, int M, 
  *   workspace_dev / workspace_bytes   >= venom_workspace_bytes(...), 256-byte aligned
  *   out         receives the handle on VENOM_OK, NULL otherwise
  *   viol        optional (may be NULL); filled on VENOM_ERR_MASK_*
- * Synchronises `stream` once (to read the legality word back). */
+ * Synchronises `stream` once (to read the legality word back), after a violation once more (for its place).  The
+ * first such call, or venom_import, of the process allocates a page of pinned host memory, which is kept. */
 venom_status_t venom_compress(const void* A_f16_dev, int64_t lda, const uint8_t* mask_dev, int64_t ldm,
                               int64_t R, int64_t K, int V, int N, int M, void* workspace_dev,
                               size_t workspace_bytes, void* stream, venom_handle_t** out,
@@ -83,7 +84,7 @@ venom_status_t venom_compress(const void* A_f16_dev, int64_t lda, const uint8_t*
  * address).  While they are copied into the workspace they are CHECKED: column ids strictly
  * increasing and below M, idx0 < idx1 in every nibble, unused nibbles zero; anything else returns
  * VENOM_ERR_INVALID_ARG, no handle, and nothing is ever gathered from such arrays (value bits are
- * free).  Synchronises `stream` once. */
+ * free).  Synchronises `stream` once, twice if the arrays are refused. */
 venom_status_t venom_import(const uint16_t* values_dev, const uint16_t* columns_dev, const uint32_t* meta_dev,
                             int64_t R, int64_t K, int V, int N, int M, void* workspace_dev,
                             size_t workspace_bytes, void* stream, venom_handle_t** out);

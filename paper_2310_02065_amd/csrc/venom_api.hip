@@ -34,44 +34,74 @@ void* static_scratch_of_current_device() {
   return addr[dev];
 }
 
-// Words of pinned host memory that a kernel can write and the host reads after waiting for the stream: one per call in
-// flight, from a page that is allocated with the first call and kept.  A call that finds none left, or no page, does
-// without (get() is null).
-class HostWord {
+// A legality slot of the kernels (venom_internal.h) and its word of pinned host memory, for one call: a kernel can write the
+// word and the host reads it after waiting for the stream.  The words are in a page that is allocated with the first call
+// and kept.  A call that finds no slot left, or no page, does without (slot() is -1, word() null).
+class LegalitySlot {
  public:
-  HostWord() {
+  LegalitySlot() {
     std::lock_guard<std::mutex> lock(mutex());
     Page& p = page();
-    if (!p.words && !p.tried) {
+    if (!p.words) {
       void* mem = nullptr;
-      p.tried = true;
-      if (hipHostMalloc(&mem, kWords * kStride, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) p.words = static_cast<char*>(mem);
+      if (hipHostMalloc(&mem, venom::kLegalitySlots * kStride, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) p.words = static_cast<char*>(mem);
       else (void)hipGetLastError();
     }
     if (!p.words || !~p.used) return;
     slot_ = __builtin_ctzll(~p.used);
     p.used |= 1ull << slot_;
-    *get() = ~0ull;
+    *word() = 0;
   }
-  ~HostWord() {
-    if (slot_ < 0) return;
+  // A slot whose kernels may still write (the wait failed) is not given back; those of a refused capture never run.
+  ~LegalitySlot() {
+    if (slot_ < 0 || in_flight_) return;
     std::lock_guard<std::mutex> lock(mutex());
     page().used &= ~(1ull << slot_);
   }
-  HostWord(const HostWord&) = delete;
-  HostWord& operator=(const HostWord&) = delete;
-  unsigned long long* get() const {
+  LegalitySlot(const LegalitySlot&) = delete;
+  LegalitySlot& operator=(const LegalitySlot&) = delete;
+  int slot() const { return slot_; }
+  unsigned long long* word() const {
     return slot_ < 0 ? nullptr : reinterpret_cast<unsigned long long*>(page().words + slot_ * kStride);
   }
-  unsigned long long read() const { return *const_cast<volatile unsigned long long*>(get()); }
+  // After the launch of the kernels that were given this slot: waits for them, and fetches ~key of the first violation, 0 if
+  // there is none.
+  hipError_t result(hipStream_t st, unsigned long long* violation) {
+    hipError_t e = hipStreamSynchronize(st);
+    in_flight_ = e != hipSuccess && e != hipErrorStreamCaptureUnsupported && e != hipErrorStreamCaptureInvalidated;
+    if (e != hipSuccess) return e;
+    if (read() != 0) {
+      in_flight_ = true;
+      e = venom::launch_take_violation(slot_, word(), st);
+      if (e == hipSuccess) e = hipStreamSynchronize(st);
+      if (e != hipSuccess) return e;
+      in_flight_ = false;
+    }
+    *violation = read();
+    return hipSuccess;
+  }
 
  private:
-  static constexpr int kWords = 64, kStride = 64;  // a cache line each
-  struct Page { char* words; unsigned long long used; bool tried; };
+  static constexpr int kStride = 64;               // a cache line each
+  static_assert(venom::kLegalitySlots == 64, "a bit of Page::used each");
+  struct Page { char* words; unsigned long long used; };
   static Page& page() { static Page p{}; return p; }
   static std::mutex& mutex() { static std::mutex m; return m; }
+  unsigned long long read() const { return *const_cast<volatile unsigned long long*>(word()); }
   int slot_ = -1;
+  bool in_flight_ = false;
 };
+
+// Waits for the kernels launched with `slot`, whatever their launch returned, and fetches the legality word, theirs or
+// the workspace's.
+hipError_t wait_for_legality(hipError_t launched, LegalitySlot& slot, const venom_handle& h, hipStream_t st,
+                             unsigned long long* violation) {
+  hipError_t e;
+  if (slot.slot() >= 0) e = slot.result(st, violation);
+  // returns when the word is here: one wait, where an asynchronous copy into this frame and a synchronisation are two
+  else e = hipMemcpyWithStream(violation, h.ws + h.lay.off_status, sizeof(*violation), hipMemcpyDeviceToHost, st);
+  return launched != hipSuccess ? launched : e;
+}
 
 // Whether a kernel launched on st now runs on the GPU that holds q and all p (null: nothing).  A copy needs neither the
 // current device nor the stream's to be that one.
@@ -164,26 +194,13 @@ venom_status_t venom_compress(const void* A_f16_dev, int64_t lda, const uint8_t*
   s = make_handle(R, K, V, N, M, workspace_dev, workspace_bytes, &h);
   if (s != VENOM_OK) return s;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const uint16_t* A = static_cast<const uint16_t*>(A_f16_dev);
-  hipError_t e = hipSuccess;
-  unsigned long long key = ~0ull;
-  bool legal = false;
-  {
-    const HostWord word;                           // first only: is the mask legal?
-    if (word.get()) {
-      e = venom::launch_compress(A, lda, mask_dev, ldm, *h, st, word.get());
-      if (e == hipSuccess) e = hipStreamSynchronize(st);
-      legal = e == hipSuccess && word.read() == ~0ull;
-    }
-  }
-  if (e == hipSuccess && !legal) {                 // no, or no such word: where is the first offender?
-    e = venom::launch_compress(A, lda, mask_dev, ldm, *h, st);
-    if (e == hipSuccess)   // returns when the word is here: one wait, where an asynchronous copy into this frame and a
-                           // synchronisation are two
-      e = hipMemcpyWithStream(&key, h->ws + h->lay.off_status, sizeof(key), hipMemcpyDeviceToHost, st);
-  }
+  LegalitySlot slot;
+  unsigned long long violation = 0;
+  hipError_t e = venom::launch_compress(static_cast<const uint16_t*>(A_f16_dev), lda, mask_dev, ldm, *h, st, slot.slot(), slot.word());
+  e = wait_for_legality(e, slot, *h, st, &violation);
   if (e != hipSuccess) { delete h; return VENOM_ERR_HIP; }
-  if (key != ~0ull) {
+  if (violation != 0) {
+    const unsigned long long key = ~violation;
     const int64_t G = h->lay.G;
     const int64_t blk = (int64_t)(key >> 24);
     const bool row_rule = (key >> 23) & 1;
@@ -210,19 +227,15 @@ venom_status_t venom_import(const uint16_t* values_dev, const uint16_t* columns_
   venom_handle_t* h = nullptr;
   s = make_handle(R, K, V, N, M, workspace_dev, workspace_bytes, &h);
   if (s != VENOM_OK) return s;
-  const Layout& L = h->lay;
   hipStream_t st = static_cast<hipStream_t>(stream);
   hipError_t e = hipSuccess;
   if (R > 0 && K > 0) {
     // the arrays come from outside: no handle to malformed ones leaves this function
-    unsigned long long key = 0;
-    const HostWord word;
-    e = venom::launch_import(values_dev, columns_dev, meta_dev, *h, st, word.get());
-    if (e == hipSuccess) {
-      if (word.get()) { e = hipStreamSynchronize(st); key = word.read(); }
-      else e = hipMemcpyWithStream(&key, h->ws + L.off_status, sizeof(key), hipMemcpyDeviceToHost, st);
-    }
-    if (e == hipSuccess && key != ~0ull) { delete h; return VENOM_ERR_INVALID_ARG; }
+    LegalitySlot slot;
+    unsigned long long violation = 0;
+    e = venom::launch_import(values_dev, columns_dev, meta_dev, *h, st, slot.slot(), slot.word());
+    e = wait_for_legality(e, slot, *h, st, &violation);
+    if (e == hipSuccess && violation != 0) { delete h; return VENOM_ERR_INVALID_ARG; }
   }
   if (e != hipSuccess) { delete h; return VENOM_ERR_HIP; }
   *out = h;

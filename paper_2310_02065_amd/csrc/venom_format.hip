@@ -35,19 +35,34 @@ Layout make_layout(int64_t R, int64_t K, int V, int M) {
 // ---------------------------------------------------------------------------------------------
 // Legality word: the smallest key wins, so the first offending block in row-major order is
 // reported, the column rule before the row rule inside one block, and the first row for the
-// row rule.  key = (block_linear << 24) | (kind << 23) | row_in_block.
-// A first run only has to say whether there is any: `found` is then a word of host memory that the host has set and
-// a violation clears with a plain store, so that neither a kernel that sets the word nor a copy that fetches it is needed.
+// row rule.  key = (block_linear << 24) | (kind << 23) | row_in_block; the word holds ~key, 0 if there is none.
+// With a slot the word is one of the library's own, which is 0 between calls, and `found` is a word of host memory that the host
+// has cleared and the first violation sets: a legal call then needs neither a kernel that clears the word nor a
+// copy that fetches it, and only after a violation take_violation_kernel does both.
 // us per call of the binding, without -> with it: venom_import of 512 x 1024 at 64:2:8 27.4 -> 23.3, of 8192 x 8192
 // 51 -> 47; venom_compress of 4096 x 1024 at 128:2:16 35 -> 31.
-// Without it the smallest key goes to the workspace's word.
-constexpr unsigned long long kNoViolation = ~0ull;
+// Without one (slot < 0) it is the workspace's.  A wave reports one violation, and none after the one that is known; the host
+// is told once, by the wave that finds the word empty.  8192 x 8192 at 64:2:8, us per call with every group wrong, against a
+// store to the host by each thread that finds a violation and a second run for its place: compression 602 -> 122,
+// import 3804 -> 98; with one group wrong 163 -> 94 and 47 -> 59.
+static __device__ unsigned long long violations[kLegalitySlots];
 
-__global__ void init_status_kernel(unsigned long long* status) { *status = kNoViolation; }
+struct Legality {
+  int slot;
+  unsigned long long *found, *own;               // own: the workspace's word, used without a slot
+};
 
-__device__ __forceinline__ void report(unsigned long long* found, unsigned long long* status, unsigned long long key) {
-  if (found != nullptr) *reinterpret_cast<volatile unsigned long long*>(found) = 0;
-  else atomicMin(status, key);
+__global__ void init_status_kernel(unsigned long long* status) { *status = 0; }
+
+__global__ void take_violation_kernel(int slot, unsigned long long* to) {
+  *reinterpret_cast<volatile unsigned long long*>(to) = violations[slot];
+  violations[slot] = 0;
+}
+
+__device__ __forceinline__ void report(const Legality& l, unsigned long long key) {
+  unsigned long long* word = l.slot >= 0 ? &violations[l.slot] : l.own;
+  if (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= ~key) return;
+  if (atomicMax(word, ~key) == 0 && l.slot >= 0) *reinterpret_cast<volatile unsigned long long*>(l.found) = 1;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -148,7 +163,7 @@ template <int UB, bool ONCE>
 __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                        const uint8_t* __restrict__ mask, int64_t ldm, int wpw, int bits_ok,
                                                        unsigned by_full, unsigned by_last,
-                                                       FormatDst d, unsigned long long* found, unsigned long long* status) {
+                                                       FormatDst d, Legality legality) {
   extern __shared__ __attribute__((aligned(16))) uint8_t bits[];   // [row][pitch]
   __shared__ uint32_t used[kCompressWords * 8 * kMaxM / 32 + 1];
   __shared__ ushort4 sel[kCompressWords * 8];
@@ -224,6 +239,7 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
     }
   }
   __syncthreads();
+  uint32_t first = ~0u;                          // key of this thread's first violation, groups counted from g0
   if (tid < ng) {
     int cnt = 0;
     int s[kSelCols] = {0, 0, 0, 0};
@@ -243,7 +259,7 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
       }
     }
     const bool ok = cnt <= kSelCols;
-    if (!ok) report(found, status, (unsigned long long)(b * d.G + g0 + tid) << 24);
+    if (!ok) first = (uint32_t)tid << 24;
     // pad with the smallest unused ids, keeping the list sorted
     for (int c = 0; cnt < kSelCols && c < M; ++c) {
       if ((bits32(c) & 1u) != 0) continue;
@@ -290,8 +306,10 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
           const uint8_t m0 = mrow[c[0]], m1 = mrow[c[1]], m2 = mrow[c[2]], m3 = mrow[c[3]];
           kept = (m0 != 0) | (m1 != 0) << 1 | (m2 != 0) << 2 | (m3 != 0) << 3;
         }
-        if (cols_ok[tg] && __popc(kept) > 2)
-          report(found, status, ((unsigned long long)(b * d.G + g0 + tg) << 24) | (1ull << 23) | (unsigned long long)v);
+        if (cols_ok[tg] && __popc(kept) > 2) {
+          const uint32_t key = (uint32_t)tg << 24 | 1u << 23 | (uint32_t)v;
+          first = first < key ? first : key;
+        }
         // first two kept positions, then the smallest unused ones, sorted
         int p0, p1;
         bool k0 = true, k1 = true;
@@ -336,6 +354,13 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
       }
     }
   }
+  if (__ballot(first != ~0u) != 0) {
+    for (int m = 1; m < 64; m *= 2) {
+      const uint32_t other = __shfl_xor(first, m);
+      first = first < other ? first : other;
+    }
+    if (tid % 64 == 0) report(legality, ((unsigned long long)(b * d.G + g0) << 24) + first);
+  }
   if (d.arec == nullptr || d.Vp != d.V) return;
   __syncthreads();
   for (int i = tid; i < nw * 64; i += 256) {
@@ -360,7 +385,7 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
 // themselves took 90 us.
 __global__ void __launch_bounds__(256) import_kernel(const u32_any* __restrict__ values, const u16_any* __restrict__ columns,
                                                      const u32_any* __restrict__ meta, int64_t R, int wbits, FormatDst d,
-                                                     unsigned long long* status) {
+                                                     Legality legality) {
   const int64_t wq = (d.W + (1 << wbits) - 1) >> wbits;
   const int rows = 128 >> wbits;                   // of the workgroup
   const int64_t rblk = blockIdx.x / wq, wblk = blockIdx.x - rblk * wq;
@@ -415,7 +440,8 @@ __global__ void __launch_bounds__(256) import_kernel(const u32_any* __restrict__
       if (rr == 0) emit_rowidx(d, rb, w, 4 * h + e, c);
     }
   }
-  if (bad) *reinterpret_cast<volatile unsigned long long*>(status) = 0;
+  const unsigned long long lanes = __ballot(bad);
+  if (bad && (lanes & ((1ull << threadIdx.x % 64) - 1)) == 0) report(legality, 0);   // (which one it is nobody asks)
 }
 
 // Exact quotients of values below 2^31 by a divisor of at least 2: n / divisor = n * mul >> (31 + shift).
@@ -525,26 +551,26 @@ static FormatDst format_dst(const venom_handle& h) {
 }
 
 hipError_t launch_import(const uint16_t* values, const uint16_t* columns, const uint32_t* meta, const venom_handle& h,
-                         hipStream_t st, unsigned long long* found) {
+                         hipStream_t st, int slot, unsigned long long* found) {
   const Layout& L = h.lay;
-  auto* status = found ? found : reinterpret_cast<unsigned long long*>(h.ws + L.off_status);
-  if (!found) hipLaunchKernelGGL(init_status_kernel, dim3(1), dim3(1), 0, st, status);
+  const Legality legality{slot, found, reinterpret_cast<unsigned long long*>(h.ws + L.off_status)};
+  if (slot < 0) hipLaunchKernelGGL(init_status_kernel, dim3(1), dim3(1), 0, st, legality.own);
   if (L.R > 0 && L.G > 0) {
     // 32 rows x 4 words where there are packed records; otherwise longer pieces of fewer rows, as the rows are
     int wbits = 2;
     while (!L.packed && wbits < 5 && (1 << wbits) < L.W) ++wbits;
     const int64_t words = (L.W + (1 << wbits) - 1) >> wbits, rows = 128 >> wbits;
     hipLaunchKernelGGL(import_kernel, dim3((unsigned)(words * ((L.R + rows - 1) / rows))), dim3(256), 0, st,
-                       reinterpret_cast<const u32_any*>(values), columns, meta, L.R, wbits, format_dst(h), status);
+                       reinterpret_cast<const u32_any*>(values), columns, meta, L.R, wbits, format_dst(h), legality);
   }
   return hipGetLastError();
 }
 
 hipError_t launch_compress(const uint16_t* A, int64_t lda, const uint8_t* mask, int64_t ldm, const venom_handle& h,
-                           hipStream_t st, unsigned long long* found) {
+                           hipStream_t st, int slot, unsigned long long* found) {
   const Layout& L = h.lay;
-  auto* status = reinterpret_cast<unsigned long long*>(h.ws + L.off_status);
-  if (!found) hipLaunchKernelGGL(init_status_kernel, dim3(1), dim3(1), 0, st, status);
+  const Legality legality{slot, found, reinterpret_cast<unsigned long long*>(h.ws + L.off_status)};
+  if (slot < 0) hipLaunchKernelGGL(init_status_kernel, dim3(1), dim3(1), 0, st, legality.own);
   if (L.R > 0 && L.G > 0) {
     // as many words per workgroup as leave eight workgroups per compute unit (rows of `values` are then written in
     // longer pieces) and the mask bits within LDS
@@ -560,8 +586,13 @@ hipError_t launch_compress(const uint16_t* A, int64_t lda, const uint8_t* mask, 
     const int ub = chunk % 16 == 0 && L.K % 16 < 8 ? 16 : 8;
     auto fn = ub == 8 ? compress_kernel<8, false> : bits_ok ? compress_kernel<16, true> : compress_kernel<16, false>;
     hipLaunchKernelGGL(fn, grid, dim3(256), lds, st, A, lda, mask, ldm, wpw, bits_ok, by(chunk / ub), by(last / ub), format_dst(h),
-                       found, status);
+                       legality);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_take_violation(int slot, unsigned long long* to, hipStream_t st) {
+  hipLaunchKernelGGL(take_violation_kernel, dim3(1), dim3(1), 0, st, slot, to);
   return hipGetLastError();
 }
 

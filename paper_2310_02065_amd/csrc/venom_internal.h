@@ -59,13 +59,16 @@ struct venom_handle {
 namespace venom {
 
 // ---- format kernels (venom_format.hip)
-// ~0 in the workspace's legality word, or the smallest key of a violation; with `found`, a word of host memory that
-// holds ~0, only whether there is one: then that word becomes 0 and the workspace's is left alone
+// The legality word: ~key of the first violation, 0 if there is none.  Without a slot it is the workspace's, for the host
+// to fetch.  With one (below kLegalitySlots, one call at a time) the library's: `found`, a word of host memory that holds 0,
+// is non-zero after a violation, and then launch_take_violation brings the word to the host and clears it.
+constexpr int kLegalitySlots = 64;
 hipError_t launch_compress(const uint16_t* A, int64_t lda, const uint8_t* mask, int64_t ldm, const venom_handle& h,
-                           hipStream_t st, unsigned long long* found = nullptr);
-// checks, copies and packs canonical arrays; the words as above, ~0 iff everything was well formed
+                           hipStream_t st, int slot = -1, unsigned long long* found = nullptr);
+// checks, copies and packs canonical arrays; the word says whether everything was well formed, not what was not
 hipError_t launch_import(const uint16_t* values, const uint16_t* columns, const uint32_t* meta, const venom_handle& h,
-                         hipStream_t st, unsigned long long* found = nullptr);
+                         hipStream_t st, int slot = -1, unsigned long long* found = nullptr);
+hipError_t launch_take_violation(int slot, unsigned long long* to, hipStream_t st);
 hipError_t launch_decompress(const venom_handle& h, uint16_t* A, int64_t lda, hipStream_t st);
 // copies the canonical arrays (null: not that one) to memory of the handle's device, at any address
 hipError_t launch_export(const venom_handle& h, void* values, void* columns, void* meta, hipStream_t st);

@@ -115,8 +115,21 @@ template <class T> T __shfl_xor(T v, int mask) {
   emu::yield();
   return other;
 }
+inline unsigned long long __ballot(bool x) {          // over the wave's threads that are still there
+  emu::slot[emu::current] = x;
+  emu::yield();
+  unsigned long long lanes = 0;
+  const unsigned wave = emu::current / 64 * 64;
+  for (unsigned l = 0; l < 64 && wave + l < blockDim.x; ++l)
+    if (!emu::finished[wave + l] && emu::slot[wave + l] != 0) lanes |= 1ull << l;
+  emu::yield();
+  return lanes;
+}
 template <class T> T atomicAdd(T* p, T v) { const T old = *p; *p = old + v; return old; }
 template <class T> T atomicMin(T* p, T v) { const T old = *p; *p = old < v ? old : v; return old; }
+#define __HIP_MEMORY_SCOPE_AGENT 0
+#define __hip_atomic_load(p, order, scope) (*(p))
+template <class T> T atomicMax(T* p, T v) { const T old = *p; *p = old > v ? old : v; return old; }
 inline unsigned atomicOr(unsigned* p, unsigned v) { const unsigned old = *p; *p = old | v; return old; }
 inline int __popc(unsigned x) { return __builtin_popcount(x); }
 inline int __ffs(int x) { return __builtin_ffs(x); }

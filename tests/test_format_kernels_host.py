@@ -44,6 +44,8 @@ def load(path):
     L.host_launches.restype = L.host_blocks.restype = c.c_uint64
     L.host_compress.argtypes = [vp, p64, vp, p64, p64, p64, i, i, vp, vp]
     L.host_import.argtypes = [vp, vp, vp, p64, p64, i, i, vp, vp]
+    L.host_compress_with_slot.argtypes = [vp, p64, vp, p64, p64, p64, i, i, vp, i, vp, vp]
+    L.host_import_with_slot.argtypes = [vp, vp, vp, p64, p64, i, i, vp, i, vp, vp]
     L.host_export.argtypes = [p64, p64, i, i, vp, vp, vp, vp]
     L.host_decompress.argtypes = [p64, p64, i, i, vp, vp, p64]
     L.host_prune.argtypes = [vp, p64, p64, p64, i, i, vp, p64, vp, vp]
@@ -151,6 +153,43 @@ def check_decompress(L, R, K, V, M, lda, offset):
 ])
 def test_decompress(library, R, K, V, M, lda, offset):
     in_child(library, "check_decompress", R, K, V, M, lda, offset)
+
+
+def check_violations(L, R, K, V, M, places):
+    """Legal, then with a whole group kept in each row of `places`, then legal again, in one slot."""
+    A, mask = problem(R, K, V, M)
+    bad = mask.copy()
+    for row, g in places:
+        bad[row, g * M:(g + 1) * M] = 1
+    status, where = o.check_mask(bad, V, M)
+    key = (where[0] * (K // M) + where[1]) << 24 | (status == o.ERR_MASK_ROW and 1 << 23 | where[2] % V)
+    ws, one = aligned(L.host_workspace_bytes(R, K, V, M)), np.zeros(1, np.uint64)
+    none = 2**64 - 1
+    for m, want in ((mask, none), (bad, key), (mask, none), (np.ones_like(mask), 0 if M > 4 else 1 << 23)):
+        found, legal = np.zeros(1, np.uint64), np.zeros(2, np.uint64)
+        assert L.host_compress_with_slot(A.ctypes.data, K, m.ctypes.data, K, R, K, V, M, ws.ctypes.data, 63, found.ctypes.data,
+                                         legal.ctypes.data) == 0
+        assert (found[0] != 0) == (want != none) and int(legal[0]) == want and int(legal[1]) == none
+        assert L.host_compress(A.ctypes.data, K, m.ctypes.data, K, R, K, V, M, ws.ctypes.data, one.ctypes.data) == 0
+        assert int(one[0]) == want
+    arrays = o.compress(A, mask, V, M)
+    for row, word in ((None, None), (R - 1, arrays[2].shape[1] - 1), (0, 0), (None, None)):
+        meta = arrays[2].copy()
+        if row is not None:
+            meta[row, word] = 0
+        found, legal = np.zeros(1, np.uint64), np.zeros(2, np.uint64)
+        assert L.host_import_with_slot(arrays[0].ctypes.data, arrays[1].ctypes.data, meta.ctypes.data, R, K, V, M, ws.ctypes.data,
+                                       0, found.ctypes.data, legal.ctypes.data) == 0
+        assert (found[0] != 0) == (row is not None) == (int(legal[0]) != none) and int(legal[1]) == none
+
+
+@pytest.mark.parametrize("R,K,V,M,places", [
+    (128, 264, 32, 8, ((97, 3), (70, 20), (66, 20), (40, 32))),      # packed copies; the last group of a ragged word
+    (64, 130, 1, 5, ((63, 25), (9, 7))),                             # a row to a block, no packed copies
+    (128, 64, 64, 4, ((100, 1), (3, 9), (2, 9))),                    # M = 4: only the row rule
+])
+def test_violations(library, R, K, V, M, places):
+    in_child(library, "check_violations", R, K, V, M, places)
 
 
 def check_decompress_launch(L, R, K, V, M):

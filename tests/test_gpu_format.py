@@ -190,3 +190,77 @@ def test_workspace_errors():
     assert L.venom_compress(*args(base + 8, need)) == binding.VENOM_ERR_WORKSPACE
     assert L.venom_compress(*args(base, need)) == binding.VENOM_OK and out.value
     L.venom_destroy(out)
+
+
+def test_violations_on_several_threads_and_streams():
+    # legal and illegal masks and arrays in turn on each of four threads, each on a stream of its own: every call gets its
+    # own verdict, and the place of its own first offender
+    import threading
+    R, K, V, M = 256, 512, 64, 8
+    G = K // M
+    A, mask, _ = inputs.gen_problem(R, K, 8, V, M, 1.0, seed=19)
+    Ad, good = to_dev_f16(A), torch.from_numpy(mask).to(DEV)
+    arrays = binding.venom_export(binding.venom_compress(Ad, good, V, 2, M))
+    wrong = torch.zeros_like(arrays[2])
+    torch.cuda.synchronize()
+    seen = []
+
+    def work(i):
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            for n in range(12):
+                g, b = (7 * i + 5 * n) % G, (i + n) % (R // V)
+                bad = good.clone()
+                bad[b * V:, g * M:(g + 1) * M] = 1
+                try:
+                    binding.venom_compress(Ad, bad, V, 2, M, stream=s)
+                    seen.append("legal")
+                except binding.VenomError as e:
+                    if (e.status, e.violation) != (binding.VENOM_ERR_MASK_COLS, (b, g, -1)):
+                        seen.append((e.violation, (b, g)))
+                binding.venom_compress(Ad, good, V, 2, M, stream=s)
+                try:
+                    binding.venom_import(arrays[0], arrays[1], wrong, R, K, V, 2, M, stream=s)
+                    seen.append("well formed")
+                except binding.VenomError as e:
+                    if e.status != binding.VENOM_ERR_INVALID_ARG:
+                        seen.append(str(e))
+                binding.venom_import(*arrays, R, K, V, 2, M, stream=s)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not seen, seen[:5]
+
+
+def test_input_that_is_wrong_throughout_takes_no_multiple_of_the_time():
+    # every wave finds a violation; each reports one, and most find it known.  (A store to host memory by each thread took
+    # 8 and 80 times as long as the legal call.)
+    import time
+    R, K, V, M = 8192, 8192, 64, 8
+    A = torch.randn(R, K, dtype=torch.float16, device=DEV)
+    good, _, _ = binding.venom_prune(A, V, 2, M)
+    bad = torch.ones_like(good)
+    arrays = binding.venom_export(binding.venom_compress(A, good, V, 2, M))
+    wrong = (arrays[0], arrays[1], torch.zeros_like(arrays[2]))
+
+    def fastest(call, legal):
+        best = 1.0
+        for _ in range(8):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            try:
+                call()
+                assert legal
+            except binding.VenomError:
+                assert not legal
+            best = min(best, time.perf_counter() - t)
+        return best
+
+    for name, right, wrong_call in (
+            ("compress", lambda: binding.venom_compress(A, good, V, 2, M), lambda: binding.venom_compress(A, bad, V, 2, M)),
+            ("import", lambda: binding.venom_import(*arrays, R, K, V, 2, M), lambda: binding.venom_import(*wrong, R, K, V, 2, M))):
+        t, u = fastest(right, True), fastest(wrong_call, False)
+        assert u < 3 * t + 50e-6, (name, t, u)
