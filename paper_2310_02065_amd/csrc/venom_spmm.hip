@@ -101,7 +101,7 @@ __device__ __forceinline__ int slot_swizzle(int rho) {
 // error of |x| Q and, for |x| > 4, in units of 2e-4 (|x| - 2.5)^2 as relative error of Q (0.6 to 0.9 of that of the
 // rational-times-Gaussian formula 7.1.26 of Abramowitz & Stegun, which served here before):
 //   fp16 output: degree 8 on |x| <= 5.9, E = 2e-8; from there on P stays below -29 and falls, and the output is zero.
-//     Its leading coefficient is negative, so that no clamp is needed.  Of all fp16 x 54 round another way than
+//     Its leading coefficient is negative, so that no clamp is needed.  Of all fp16 x 53 round another way than
 //     the exact value, by one unit in the last place (256 with 7.1.26, 332 with x/2 + |x| (1/2 - Q)).
 //   fp32 output: degree 11 on |x| <= 13, E = 5e-9, as there the tail is seen down to x = -12.9, where 2^P underflows.  |x| is
 //     clamped where it is multiplied, too: no 0 x Inf.  3e-8 in norm on N(0, 1/4) .. N(0, 9) (7.1.26: 5e-8 to 1e-7), on no

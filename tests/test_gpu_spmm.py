@@ -138,7 +138,7 @@ def test_argument_errors():
 @pytest.mark.parametrize("activation", ["none", "gelu", "gelu_tanh"])
 @pytest.mark.parametrize("out_dtype", [torch.float16, torch.float32])
 @pytest.mark.parametrize("R,K,C,V,M", [(256, 384, 264, 128, 8), (192, 896, 136, 64, 16), (128, 720, 72, 32, 10),
-                                       (256, 128, 264, 128, 4)])
+                                       (256, 128, 264, 128, 4), (288, 330, 584, 96, 10)])
 def test_fused_bias_and_activation(R, K, C, V, M, out_dtype, activation):
     A, mask, B = inputs.gen_problem(R, K, C, V, M, 1.0, seed=900 + R + M)
     rng = np.random.default_rng(77 + R)
@@ -341,7 +341,7 @@ def test_gelu_keeps_its_negative_tail_in_fp32():
 def test_gelu_rounds_to_fp16_within_a_unit():
     # The fit's error, 2e-8 absolute or 2e-4 (|x| - 2.5)^2 relative, and fp32 evaluation are well below half a unit in
     # the last place (6e-8 where they are smallest): the result is the exact value's rounding or its neighbour, and the
-    # neighbour for few (54 of the 63488 in an fp32 model of the kernel's operations).
+    # neighbour for few (53 of the 63488).
     x, got = gelu_of_every_fp16_number(torch.float16)
     want = o.gelu_erf(x).astype(np.float16)
     same = got == want
