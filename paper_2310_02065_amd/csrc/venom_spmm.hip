@@ -844,16 +844,16 @@ static const Variant kVariants[] = {
     VARIANT("v96_c128", 3, 2, 3, 5, 6, 2.48f, .165f, .84f, .041f, .81f, .030f),
     VARIANT("v96_c128d", 3, 2, 3, 4, 4, 2.99f, .160f, .17f, .011f, 1.09f, .028f),
     VARIANT("v96_c64", 3, 1, 3, 5, 6, 3.07f, .128f, .04f, 0.f, .66f, .021f),
-    VARIANT("v64_c512", 2, 8, 1, 4, 10, 2.22f, .285f, 1.98f, .158f, 1.08f, .014f),
-    VARIANT("v64_c256", 2, 4, 1, 5, 6, 2.75f, .164f, .73f, .087f, 1.13f, .016f),
-    VARIANT("v64_c256d", 2, 4, 1, 4, 4, 2.88f, .163f, .35f, .075f, 1.11f, .045f),
-    VARIANT("v64_c128", 2, 2, 2, 5, 6, 2.77f, .133f, .33f, .017f, .54f, .034f),
-    VARIANT("v64_c64", 2, 1, 2, 6, 10, 3.02f, .112f, .15f, 0.f, .42f, .014f),
-    VARIANT("v32_c512", 1, 8, 1, 4, 10, 3.43f, .260f, 0.f, .100f, 1.79f, .044f),
-    VARIANT("v32_c256", 1, 4, 1, 6, 10, 2.19f, .157f, .90f, .041f, .39f, .059f),
-    VARIANT("v32_c256d", 1, 4, 1, 4, 6, 2.36f, .136f, .74f, .060f, .17f, .048f),
-    VARIANT("v32_c128", 1, 2, 1, 6, 6, 2.71f, .111f, .59f, 0.f, .05f, .021f),
-    VARIANT("v32_c64", 1, 1, 1, 6, 10, 2.94f, .093f, .42f, 0.f, 0.f, .015f),
+    VARIANT("v64_c512", 2, 8, 1, 4, 10, 2.529f, .279f, 2.075f, .157f, 1.107f, .027f),
+    VARIANT("v64_c256", 2, 4, 1, 5, 6, 2.885f, .17f, .693f, .088f, 1.349f, .011f),
+    VARIANT("v64_c256d", 2, 4, 1, 4, 4, 3.263f, .163f, .316f, .07f, 1.176f, .049f),
+    VARIANT("v64_c128", 2, 2, 2, 5, 6, 2.608f, .146f, .317f, .024f, .544f, .024f),
+    VARIANT("v64_c64", 2, 1, 2, 6, 10, 2.314f, .101f, .026f, .015f, .74f, .032f),
+    VARIANT("v32_c512", 1, 8, 1, 4, 10, 3.21f, .242f, .031f, .117f, 1.984f, .034f),
+    VARIANT("v32_c256", 1, 4, 1, 6, 10, 1.9f, .142f, 1.182f, .073f, .464f, .009f),
+    VARIANT("v32_c256d", 1, 4, 1, 4, 6, 2.392f, .135f, .759f, .06f, .039f, .048f),
+    VARIANT("v32_c128", 1, 2, 1, 6, 6, 2.32f, .13f, .547f, 0.f, .137f, .001f),
+    VARIANT("v32_c64", 1, 1, 1, 6, 10, 1.95f, .065f, .595f, .033f, .084f, .005f),
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
@@ -863,12 +863,16 @@ const char* spmm_variant_name(int v) { return (v >= 0 && v < kNumVariants) ? kVa
 // The variant of block height V with the smallest expected time.  Narrow tiles spread a small product over more units and
 // have shorter k-steps (us alone on the chip, V = 128: 0.31 / 0.21 / 0.14 / 0.12 for 512 / 256 / 128 / 64 columns: 36.5 /
 // 20.5 / 12.5 / 8.5 KB); wide ones read the records of A less often and load the chip's fabric less; the columns that
-// pad C to whole tiles and a last round with few tiles cost as much as full ones.  The constants of TileCost are least
-// squares fits (relative error, shapes where the variant is near the best counting three times) to the times of all
-// variants over 676 shapes (R 64-49152, K 256-16000, C 8-16384, M 4-128, plain fp16 product): the chosen one is on
-// average 0.7 % slower than the best of the table, at most 15 %.  Against tiles chosen by columns and counts of tiles alone,
-// in us: 256 x 15890 x 6944 at 64:2:10 75 -> 51, 13056 x 2624 x 336 at 96:2:64 11.6 -> 7.6, 3968 x 11324 x 688 at 64:2:4
-// 84 -> 66.
+// pad C to whole tiles and a last round with few tiles cost as much as full ones.  The constants of TileCost are fits to the
+// times of all variants over random shapes (R 64-49152, K 256-16000, C 8-16384, M 4-128).  V = 128 and 96: least squares of the
+// relative error, 676 shapes, plain fp16 product, shapes where the variant is near the best counting three times.
+// V = 64 and 32: from such a fit on by random steps that make the chosen variant's time over the best one's smaller, on
+// average over 1530 shapes in seven output forms (so fitted, v32_c256 is taken where it is the best, for few tiles of many
+// k-steps: 416 x 14192 x 3616 at 32:2:8 56 -> 49 us).  In 3900 shapes the chosen variant is slower than the best by, on average and at most: plain
+// product 0.5 and 25 %, with bias and GELU 0.5 and 36 %, token-major 0.6 and 29 %, with both 0.7 and 32 %, fp32 1.0 and 29 %,
+// fp32 with GELU 0.6 and 31 %, token-major as well 1.3 and 42 %.  Against tiles chosen by columns and counts of tiles alone 0.76
+// to 0.81 of the time on average, 154 of 18769 calls over 8 us more than 3 % slower; in us: 256 x 15890 x 6944 at 64:2:10
+// 75 -> 51, 13056 x 2624 x 336 at 96:2:64 11.6 -> 7.6, 3968 x 11324 x 688 at 64:2:4 84 -> 66.
 static int pick_variant(int V, int64_t Ccols, int64_t nbr, int64_t steps, int cus) {
   int best = -1;
   float best_time = 0.f;
