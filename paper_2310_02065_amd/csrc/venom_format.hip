@@ -454,16 +454,16 @@ static Divisor make_divisor(uint32_t d) {
 __device__ __forceinline__ uint32_t divide(uint32_t n, Divisor d) { return __umulhi(n, d.mul) >> (d.shift - 1); }
 
 // packed -> dense.  A workgroup expands 32 rows (one tile of a block row) x 256 columns; a thread owns 8 neighbouring
-// columns of four rows.  The NG groups that its columns can touch -- one where M is a multiple of 8, three below M = 7 -- are
-// the same in every row, so their row ids are read once and turned into positions among the 8 columns; then
-// each row and group takes an index word and the two values, placed by comparing positions, and each row one
-// 16-byte store at any alignment, past the caches: nothing reads the lines again here, and streamed they leave at the rate
-// of a linear fill.  ALL: M = 4, where every column is kept and a thread's two groups share an index word and
-// an 8-byte pair of values.  Bound by the writes, and before that by the latency of the reads: the loads of all four
-// rows are in flight together.
+// columns of four rows.  The NG groups that its columns can touch -- one where M is a multiple of 8, three at M = 5, else two
+// (the first column is a multiple of 8, so at M = 6 at most the fifth of its group) -- are the same in every row, so
+// their row ids are read once and turned into positions among the 8 columns; then each row and group takes an index
+// word and the two values, placed by comparing positions, and each row one 16-byte store at any alignment, past the
+// caches: nothing reads the lines again here, and streamed they leave at the rate of a linear fill.  ALL: M = 4, where
+// every column is kept and a thread's two groups share an index word and an 8-byte pair of values.  Bound by the
+// writes, and before that by the latency of the reads: the loads of all four rows are in flight together.
 // us per call, before (one row and group at a time, cached stores, unaligned rows by elements) and now: 49152 x 12288 at
 // 128:2:32 309 -> 207 (6.2 TB/s; 276 with cached stores), 8192 x 8192 at 64:2:8 35 -> 32, 16384 x 4096 at 128:2:4 60 ->
-// 32, 8192 x 8190 at 64:2:5 156 -> 73.
+// 32, 8192 x 8190 at 64:2:5 156 -> 73, at 64:2:6 111 -> 61.
 template <int NG, bool ALL>
 __global__ void __launch_bounds__(256) decompress_kernel(const char* __restrict__ arec,
                                                          const int32_t* __restrict__ rowidx, int64_t K, int M, Divisor by_M,
@@ -647,7 +647,7 @@ hipError_t launch_decompress(const venom_handle& h, uint16_t* A, int64_t lda, hi
   if (L.R == 0 || L.K == 0) return hipSuccess;
   const int64_t chunks = (L.K + 255) / 256;
   auto fn = h.M % 8 == 0 ? decompress_kernel<1, false> : h.M == 4 ? decompress_kernel<2, true>
-            : h.M == 5 || h.M == 6 ? decompress_kernel<3, false> : decompress_kernel<2, false>;
+            : h.M == 5 ? decompress_kernel<3, false> : decompress_kernel<2, false>;
   // a launch holds fewer than 2^32 threads, 256 per workgroup however few columns there are: tall narrow matrices
   // take several
   const int64_t tiles = L.R / kTileRows, most = kMaxBlocks / chunks;

@@ -867,7 +867,7 @@ const char* spmm_variant_name(int v) { return (v >= 0 && v < kNumVariants) ? kVa
 // times of all variants over random shapes (R 64-49152, K 256-16000, C 8-16384, M 4-128).  V = 128 and 96: least squares of the
 // relative error, 676 shapes, plain fp16 product, shapes where the variant is near the best counting three times.
 // V = 64 and 32: from such a fit on by random steps that make the chosen variant's time over the best one's smaller, on
-// average over 1530 shapes in seven output forms (so fitted, v32_c256 is taken where it is the best, for few tiles of many
+// average over 1551 shapes in seven output forms (so fitted, v32_c256 is taken where it is the best, for few tiles of many
 // k-steps: 416 x 14192 x 3616 at 32:2:8 56 -> 49 us).  In 3900 shapes the chosen variant is slower than the best by, on average and at most: plain
 // product 0.5 and 25 %, with bias and GELU 0.5 and 36 %, token-major 0.6 and 29 %, with both 0.7 and 32 %, fp32 1.0 and 29 %,
 // fp32 with GELU 0.6 and 31 %, token-major as well 1.3 and 42 %.  Against tiles chosen by columns and counts of tiles alone 0.76

@@ -147,7 +147,7 @@ def check_decompress(L, R, K, V, M, lda, offset):
     (128, 4, 32, 4, 4, 0), (128, 20, 64, 4, 21, 2),   # one group; five, the last one without its pair
     (128, 268, 128, 4, 272, 0),      # a second chunk of columns, its last piece four wide
     (64, 35, 32, 5, 37, 6),          # three groups under eight columns
-    (96, 330, 96, 6, 331, 4), (64, 63, 64, 7, 64, 0),
+    (96, 330, 96, 6, 331, 4), (64, 534, 32, 6, 534, 2), (64, 63, 64, 7, 64, 0),   # two, at M = 6 each offset in the group
     (64, 27, 32, 9, 27, 2), (64, 300, 64, 10, 301, 14),
     (64, 520, 32, 8, 520, 0), (128, 96, 128, 32, 97, 2),   # one group
 ])
