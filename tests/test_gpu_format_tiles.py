@@ -170,3 +170,22 @@ def test_export_on_another_stream_and_in_a_graph():
         torch.cuda.synchronize()
         for b, w in zip(bufs, want):
             assert torch.equal(b.cpu(), w)
+
+
+@pytest.mark.parametrize("R,K,V,M", [(64, 5 * 8, 64, 8), (96, 33 * 7, 96, 7)])
+def test_export_to_pinned_host_memory(R, K, V, M):
+    # memory that is not on the handle's device, or only some of it: the runtime's copies
+    rng = np.random.default_rng(R + K)
+    mask = inputs.gen_mask(R, K, V, M, rng)
+    A = rng.standard_normal((R, K)).astype(np.float16)
+    h = binding.venom_compress(torch.from_numpy(A).to(DEV), torch.from_numpy(mask).to(DEV), V, 2, M)
+    want = [torch.from_numpy(np.ascontiguousarray(x).view(np.uint8).reshape(-1)) for x in o.compress(A.view(np.uint16), mask, V, M)]
+    for where in ((1, 1, 1), (0, 1, 0), (1, 0, 0), (0, 0, 1)):
+        bufs = [torch.empty(w.numel() + 16, dtype=torch.uint8, pin_memory=True).fill_(0xA5) if host else
+                torch.full((w.numel() + 16,), 0xA5, dtype=torch.uint8, device=DEV) for host, w in zip(where, want)]
+        torch.cuda.synchronize()
+        assert binding.lib().venom_export(h.ptr, *(b.data_ptr() for b in bufs), None) == binding.VENOM_OK
+        torch.cuda.synchronize()
+        for b, w in zip(bufs, want):
+            got = b.cpu()
+            assert torch.equal(got[:w.numel()], w) and bool((got[w.numel():] == 0xA5).all()), where
