@@ -1099,11 +1099,15 @@ hipError_t launch_transpose_tokens(const uint16_t* X, int64_t ldx, int64_t token
   if (tokens == 0 || K == 0) return hipSuccess;
   if (reinterpret_cast<uintptr_t>(X) % 16 == 0 && reinterpret_cast<uintptr_t>(BT) % 16 == 0 && ldx % 8 == 0 &&
       ldbt % 8 == 0 && K % 8 == 0) {
-    // A layer whose activations, their copy and output are more than half of the 256 MB memory-side cache does not find X
-    // there when it is called again, and needs the room for the copy; a smaller one may.  us per call of the layer,
-    // cached / streamed reads: 4096 x 1024 x 16384 tokens (201 MB) 70.2 / 66.2, 512 x 8192 x 8192 (277) 99 / 83, 512 x 4096 x
-    // 8192 (143) 59.0 / 57.2; 512 x 4096 x 6144 (107) 46.0 / 49.7, 2048 x 1024 x 12288 (101) 36.6 / 37.4.
-    const bool streamed = 2 * tokens * K * 2 + out_bytes > (int64_t)128 << 20;
+    // X, its copy and the output against the 256 MB memory-side cache.  Where they exceed it, X is not found there when
+    // the layer is called again, and its reads only take room from the copy.  Where they take more than half and the output is
+    // at least twice X, that holds as soon as other buffers come in between (activations and output of three
+    // layers in turn), and little is lost if they do not (the same buffers again and again); with a smaller output more is.
+    // us per call, cached / streamed, the same buffers and three in turn: 8192 x 8192 x 8192 tokens (403 MB) 223 / 205, 224 / 206;
+    // 4096 x 1024 x 16384 (201) 49.0 / 51.2, 54.9 / 51.1; 8192 x 1024 x 8192 (168) 45.8 / 46.1, 49.5 / 46.4; 2048 x 2048 x 16384 (201)
+    // 50.9 / 56.7, 59.3 / 56.9; 512 x 6144 x 8192 (210) 49.8 / 53.9, 53.2 / 53.8; 512 x 4096 x 8192 (143) 35.5 / 38.7, 38.5 / 38.7.
+    const int64_t x_bytes = tokens * K * 2, all = 2 * x_bytes + out_bytes;
+    const bool streamed = all > (int64_t)256 << 20 || (all > (int64_t)128 << 20 && out_bytes >= 2 * x_bytes);
     auto fn = streamed ? transpose_tokens_wide_kernel<true> : transpose_tokens_wide_kernel<false>;
     hipLaunchKernelGGL(fn, dim3((unsigned)((K + 63) / 64), (unsigned)((ldbt + 63) / 64)), dim3(256),
                        0, st, X, ldx, tokens, K, BT, ldbt);
