@@ -14,10 +14,14 @@ import ctypes
 import os
 import threading
 from ctypes import POINTER, byref, c_char_p, c_int, c_int64, c_size_t, c_void_p
+from threading import get_ident
 
 import torch
 
+# What torch.cuda's functions call, without their wrappers (each costs a few tenths of a microsecond per library call).
 _current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
+_is_current_stream_capturing = getattr(torch._C, "_cuda_isCurrentStreamCapturing", lambda: False)
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libvenom.so")
@@ -109,7 +113,7 @@ def _stream_ptr(stream=None):
         return stream.cuda_stream
     if _current_raw_stream is None:
         return torch.cuda.current_stream().cuda_stream
-    return _current_raw_stream(torch.cuda.current_device())
+    return _current_raw_stream(_current_device())            # (there are CUDA tensors, so CUDA is initialised)
 
 
 def _ptr(t):
@@ -262,9 +266,9 @@ def _new_scratch(nbytes, device, stream):
 
 def _capturing(stream) -> bool:
     if stream is None:
-        return torch.cuda.is_current_stream_capturing()
+        return _is_current_stream_capturing()
     with torch.cuda.stream(stream):
-        return torch.cuda.is_current_stream_capturing()
+        return _is_current_stream_capturing()
 
 
 class _KeptScratch:
@@ -279,18 +283,21 @@ class _KeptScratch:
         self._lock = threading.Lock()
 
     def get(self, nbytes, x, stream, stream_ptr):
-        if _capturing(stream):
-            return _new_scratch(nbytes, x.device, stream)
-        key = (stream_ptr, x.get_device(), threading.get_ident())
-        buf = self._buffers.get(key)
-        if buf is None or buf.numel() < nbytes:
-            buf = _new_scratch(nbytes, x.device, stream)
+        """(tensor, its address, its bytes), at least nbytes of them."""
+        key = (stream_ptr, x.get_device(), get_ident())
+        kept = self._buffers.get(key)
+        capturing = _capturing(stream)
+        if kept is not None and kept[2] >= nbytes and not capturing:
+            return kept
+        buf = _new_scratch(nbytes, x.device, stream)
+        kept = (buf, buf.data_ptr(), buf.numel())
+        if not capturing:
             with self._lock:
                 self._buffers.pop(key, None)
-                self._buffers[key] = buf
+                self._buffers[key] = kept
                 while len(self._buffers) > self.LIMIT:
                     self._buffers.pop(next(iter(self._buffers)))
-        return buf
+        return kept
 
 
 def venom_spmm(h: Handle, B, out=None, out_dtype=None, variant=-1, stream=None, bias=None, activation="none"):
@@ -324,10 +331,10 @@ def venom_linear(h: Handle, X, bias=None, activation="none", out=None, out_dtype
     if scratch is None:
         assert X.is_cuda and X.dim() == 2
         scratch = _new_scratch(max(_scratch_bytes(h, X.shape[0]), 16), X.device, stream)
-    return _linear(h, X, bias, activation, out, out_dtype, scratch, _stream_ptr(stream))
+    return _linear(h, X, bias, activation, out, out_dtype, scratch.data_ptr(), scratch.numel(), _stream_ptr(stream))
 
 
-def _linear(h, X, bias, activation, out, out_dtype, scratch, stream_ptr):
+def _linear(h, X, bias, activation, out, out_dtype, scratch_ptr, scratch_bytes, stream_ptr):
     assert X.is_cuda and X.dtype == torch.float16 and X.dim() == 2
     (tokens, K), (ldx, unit) = X.shape, X.stride()
     assert unit == 1 and K == h.K
@@ -340,7 +347,7 @@ def _linear(h, X, bias, activation, out, out_dtype, scratch, stream_ptr):
     if tokens <= 1:
         ldx, ldy = max(h.K, ldx), max(h.R, ldy)
     st = lib().venom_linear(h.ptr, X.data_ptr(), ldx, tokens, _ptr(bias), ACTIVATIONS[activation], out.data_ptr(), ldy,
-                            _OUT_DTYPES[dtype], scratch.data_ptr(), scratch.numel(), stream_ptr)
+                            _OUT_DTYPES[dtype], scratch_ptr, scratch_bytes, stream_ptr)
     if st != VENOM_OK:
         raise VenomError(st, "venom_linear")
     return out
@@ -386,8 +393,9 @@ class Spmm:
 
     def __call__(self, x, out=None, out_dtype=None, stream=None):
         ptr = _stream_ptr(stream)
-        scratch = self._scratch.get(max(_scratch_bytes(self.handle, x.shape[0]), 16), x, stream, ptr)
-        return _linear(self.handle, x, self.bias, self.activation, out, out_dtype, scratch, ptr)
+        h = self.handle
+        scratch = self._scratch.get(max(_scratch_bytes(h, x.shape[0]), 16), x, stream, ptr)   # held until the call is queued
+        return _linear(h, x, self.bias, self.activation, out, out_dtype, scratch[1], scratch[2], ptr)
 
 
 def venom_get_info(h: Handle):
