@@ -16,6 +16,7 @@ constexpr int kStepRows = kStepGroups * kSelCols;  // gathered rows of B per k-s
 constexpr int kTileValBytes = 1024;                // packed values of one 32-row tile for one k-step
 constexpr int kMaxTiles = 4;                       // the product kernel serves V = 32, 64, 96, 128
 constexpr int kTailBytes = 512;                    // record tail: the index words, 64 lanes x 4 tiles x 16 bits
+constexpr int kMaxDevices = 16;    // devices whose per-device launch state is cached
 constexpr int64_t kMaxBlocks = (1 << 24) - 1;      // most workgroups of 256 threads along x: a launch holds fewer than
                                                    // 2^32 threads there
 
@@ -84,6 +85,14 @@ const char* spmm_variant_name(int v);
 // tokens_major != 0: C is written transposed (C[column][row], leading dimension ldc counts rows of A)
 venom_status_t launch_spmm(const venom_handle& h, const void* B, int64_t ldb, int64_t Ccols, const void* bias, int act,
                            void* C, int64_t ldc, int c_dtype, int tokens_major, int variant, hipStream_t st);
+// Compute units of the current device, 0 if they cannot be found out.
+int compute_units();
+// The same for at most 32 columns (venom_skinny.hip), where skinny_product or skinny_layer says so.  in_place: src is X, tokens x K,
+// else B; token_major: as above.
+bool skinny_product(const venom_handle& h, int64_t ld, int64_t cols, int cus);
+bool skinny_layer(const venom_handle& h, int64_t ldx, int64_t tokens, int cus);
+venom_status_t launch_skinny(const venom_handle& h, const void* src, int64_t ld, int64_t cols, const void* bias, int act, void* out,
+                             int64_t ldo, int dtype, bool in_place, bool token_major, int cus, hipStream_t st);
 // register-only loop of 2:4 matrix instructions, for the measured instruction peak (grid = one workgroup of 8 waves per
 // compute unit x 2)
 hipError_t launch_smfmac_probe(int iters, float* sink, hipStream_t st);

@@ -27,17 +27,9 @@
 #include <atomic>
 #include <type_traits>
 
-#include "venom_internal.h"
+#include "venom_device.h"
 
 namespace venom {
-
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef _Float16 half16 __attribute__((ext_vector_type(16)));
-typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-typedef short short4v __attribute__((ext_vector_type(4)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-
-#define LDS_PTR(T) T __attribute__((address_space(3)))*
 
 struct SpmmParams {
   const char* arec;        // packed A stream, one record per (block row, k-step)
@@ -58,7 +50,6 @@ struct SpmmParams {
 };
 
 constexpr int kNumXcd = 8;
-constexpr int kMaxDevices = 16;      // devices whose per-device launch state is cached
 constexpr int kProducers = 4;        // producer waves per workgroup: one per SIMD
 constexpr int kRidSlots = 16;        // row-id ring: 128 bytes per k-step
 
@@ -93,64 +84,6 @@ __device__ __forceinline__ void lgkm_drained_barrier() { asm volatile("s_waitcnt
 template <int ROW_BYTES>
 __device__ __forceinline__ int slot_swizzle(int rho) {
   return ROW_BYTES == 128 ? 4 * ((rho >> 1) & 1) : 4 * (rho & 3);
-}
-
-// GELU(x) = x * Phi(x) = max(x, 0) - |x| Q(|x|), Q the upper tail of the normal distribution, as 2^P(|x|): log2 Q is
-// smooth, so one exponential and no reciprocal, and x < 0 gets its tail by a product, not as a difference.  P(0) = -1, and
-// each P is the polynomial of its degree with the smallest largest error (a linear program), counted in units of E as
-// error of |x| Q and, for |x| > 4, in units of 2e-4 (|x| - 2.5)^2 as relative error of Q (0.6 to 0.9 of that of the
-// rational-times-Gaussian formula 7.1.26 of Abramowitz & Stegun, which served here before):
-//   fp16 output: degree 8 on |x| <= 5.9, E = 2e-8; from there on P stays below -29 and falls, and the output is zero.
-//     Its leading coefficient is negative, so that no clamp is needed.  Of all fp16 x 53 round another way than
-//     the exact value, by one unit in the last place (256 with 7.1.26, 332 with x/2 + |x| (1/2 - Q)).
-//   fp32 output: degree 11 on |x| <= 13, E = 5e-9, as there the tail is seen down to x = -12.9, where 2^P underflows.  |x| is
-//     clamped where it is multiplied, too: no 0 x Inf.  3e-8 in norm on N(0, 1/4) .. N(0, 9) (7.1.26: 5e-8 to 1e-7), on no
-//     interval worse than 7.1.26 or x/2 + |x| (1/2 - Q).
-// `on` is 1 for x > 0 and 0 for x < 0 (in between it is multiplied by next to nothing), one multiplication with the
-// clamp of its result; infinities and NaN come out as from x * Phi(x).  11 and 15 full-rate instructions and one transcendental
-// (7.1.26: 15 and two).  The output stage evaluates it 128 times per lane on the waves that the matrix instructions
-// then wait for: 4096 x 1024 x 16384 at 128:2:16 with bias, us per call, 7.1.26 -> now, fp16 73 -> 65, fp32 91 -> 90; as
-// token-major layer 93 -> 90 and 117 -> 113.
-template <bool OUT_F32>
-__device__ __forceinline__ float gelu_by_definition(float x) {
-  const float on = __builtin_amdgcn_fmed3f(x * 0x1p126f, 0.f, 1.f);
-  if constexpr (OUT_F32) {
-    const float a = __builtin_amdgcn_fmed3f(fabsf(x), 0.f, 13.5f);
-    float p = fmaf(5.57935698e-10f, a, -3.05136716e-08f);
-    p = fmaf(p, a, 6.97282076e-07f);
-    p = fmaf(p, a, -8.63450987e-06f);
-    p = fmaf(p, a, 6.18117556e-05f);
-    p = fmaf(p, a, -2.28697128e-04f);
-    p = fmaf(p, a, -1.04886603e-04f);
-    p = fmaf(p, a, 7.07445014e-03f);
-    p = fmaf(p, a, -5.25283851e-02f);
-    p = fmaf(p, a, -4.59191263e-01f);
-    p = fmaf(p, a, -1.15110779f);
-    p = fmaf(p, a, -1.f);
-    return fmaf(-a, __builtin_amdgcn_exp2f(p), x * on);
-  } else {
-    const float a = fabsf(x);
-    float p = fmaf(-1.12579994e-06f, a, 1.83935899e-05f);
-    p = fmaf(p, a, -8.35712781e-05f);
-    p = fmaf(p, a, -3.9356359e-04f);
-    p = fmaf(p, a, 7.4137128e-03f);
-    p = fmaf(p, a, -5.27529866e-02f);
-    p = fmaf(p, a, -4.59116608e-01f);
-    p = fmaf(p, a, -1.15111709f);
-    p = fmaf(p, a, -1.f);
-    return x * fabsf(on - __builtin_amdgcn_exp2f(p));
-  }
-}
-// The tanh form x/2 * (1 + tanh u), u = sqrt(2/pi) (x + 0.044715 x^3), written as x / (1 + e^(-2u)); the exponent of 2
-// is x (A + B x^2), A = -2 log2(e) sqrt(2/pi), B = 0.044715 A.
-__device__ __forceinline__ float gelu_tanh_form(float x) {
-  const float e = __builtin_amdgcn_exp2f(x * fmaf(x * x, -0.10294324f, -2.30220818f));
-  return x * __builtin_amdgcn_rcpf(1.f + e);
-}
-
-template <int ABID>
-__device__ __forceinline__ floatx16 smfmac(half8 a, half16 b, floatx16 c, int idx) {
-  return __builtin_amdgcn_smfmac_f32_32x32x32_f16(a, b, c, idx, 0, ABID);
 }
 
 // This workgroup's share of the tile list.  The grid holds one workgroup per compute unit (the
@@ -909,6 +842,19 @@ static int column_group(const Layout& L, int bsc, int64_t nbr, int64_t nct, int6
   return best;
 }
 
+int compute_units() {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 0;
+  static std::atomic<int> cu_count[kMaxDevices] = {};   // per device, filled on first use
+  const bool cached = dev >= 0 && dev < kMaxDevices;
+  int cus = cached ? cu_count[dev].load(std::memory_order_relaxed) : 0;
+  if (cus == 0) {
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    if (cached) cu_count[dev].store(cus, std::memory_order_relaxed);
+  }
+  return cus;
+}
+
 venom_status_t launch_spmm(const venom_handle& h, const void* B, int64_t ldb, int64_t Ccols, const void* bias, int act,
                            void* C, int64_t ldc, int c_dtype, int tokens_major, int variant, hipStream_t st) {
   const Layout& L = h.lay;
@@ -916,15 +862,13 @@ venom_status_t launch_spmm(const venom_handle& h, const void* B, int64_t ldb, in
   if (L.R == 0 || Ccols == 0) return VENOM_OK;
   if (L.steps == 0) return VENOM_ERR_UNSUPPORTED;  // K = 0: there is no k-step to run the pipeline on
   const int Vp = L.vt * kTileRows;                 // block height of the packed copy
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return VENOM_ERR_HIP;
-  static std::atomic<int> cu_count[kMaxDevices] = {};   // per device, filled on first use
-  int cus = (dev >= 0 && dev < kMaxDevices) ? cu_count[dev].load(std::memory_order_relaxed) : 0;
-  if (cus == 0) {
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < kNumXcd)
-      return VENOM_ERR_HIP;
-    if (dev >= 0 && dev < kMaxDevices) cu_count[dev].store(cus, std::memory_order_relaxed);
-  }
+  const int cus = compute_units();
+  if (cus < kNumXcd) return VENOM_ERR_HIP;
+  // gather offsets are formed as row * ldb_bytes + column bytes in 32 bits with a 24-bit multiply
+  if (h.K >= ((int64_t)1 << 24) || ldb * 2 >= ((int64_t)1 << 24) || h.K * ldb * 2 >= ((int64_t)1 << 32))
+    return VENOM_ERR_UNSUPPORTED;
+  if (variant < 0 && skinny_product(h, ldb, Ccols, cus))
+    return launch_skinny(h, B, ldb, Ccols, bias, act, C, ldc, c_dtype, false, tokens_major != 0, cus, st);
   if (variant < 0) variant = pick_variant(Vp, Ccols, L.Rbp, L.steps, cus);
   if (variant < 0 || variant >= kNumVariants || kVariants[variant].V != Vp) return VENOM_ERR_UNSUPPORTED;
   const Variant& var = kVariants[variant];
@@ -944,9 +888,6 @@ venom_status_t launch_spmm(const venom_handle& h, const void* B, int64_t ldb, in
   const int64_t nbr = L.Rbp;
   const int64_t total = nct * nbr;
   if (total > (int64_t)1 << 30 || L.steps > (int64_t)1 << 24) return VENOM_ERR_UNSUPPORTED;
-  // gather offsets are formed as row * ldb_bytes + column bytes in 32 bits with a 24-bit multiply
-  if (h.K >= ((int64_t)1 << 24) || ldb * 2 >= ((int64_t)1 << 24) || h.K * ldb * 2 >= ((int64_t)1 << 32))
-    return VENOM_ERR_UNSUPPORTED;
   p.nbr = (int)nbr; p.nct = (int)nct;
   p.per_xcd = (int)((total + kNumXcd - 1) / kNumXcd);
   // one resident workgroup per compute unit (two where the tile is small enough to share a unit);
@@ -965,6 +906,8 @@ venom_status_t launch_spmm(const venom_handle& h, const void* B, int64_t ldb, in
     // opting in to more than 64 KB of dynamic LDS is a per-function attribute (set once per device)
     // (two threads racing here both set the same attribute: harmless)
     static std::atomic<bool> opted_in[kNumVariants][8][kMaxDevices] = {};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return VENOM_ERR_HIP;
     const bool cached = dev >= 0 && dev < kMaxDevices;
     if (!cached || !opted_in[variant][4 * c_dtype + epi][dev].load(std::memory_order_acquire)) {
       if (hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
