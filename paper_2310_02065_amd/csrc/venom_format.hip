@@ -455,27 +455,38 @@ __device__ __forceinline__ uint32_t divide(uint32_t n, Divisor d) { return __umu
 
 // packed -> dense.  A workgroup expands 32 rows (one tile of a block row) x 256 columns; a thread owns 8 neighbouring
 // columns of four rows.  The NG groups that its columns can touch -- one where M is a multiple of 8, three at M = 5, else two
-// (the first column is a multiple of 8, so at M = 6 at most the fifth of its group) -- are the same in every row, so
-// their row ids are read once and turned into positions among the 8 columns; then each row and group takes an index
-// word and the two values, placed by comparing positions, and each row one 16-byte store at any alignment, past the
-// caches: nothing reads the lines again here, and streamed they leave at the rate of a linear fill.  ALL: M = 4, where
-// every column is kept and a thread's two groups share an index word and an 8-byte pair of values.  Bound by the
-// writes, and before that by the latency of the reads: the loads of all four rows are in flight together.
-// us per call, before (one row and group at a time, cached stores, unaligned rows by elements) and now: 49152 x 12288 at
-// 128:2:32 309 -> 207 (6.2 TB/s; 276 with cached stores), 8192 x 8192 at 64:2:8 35 -> 32, 16384 x 4096 at 128:2:4 60 ->
-// 32, 8192 x 8190 at 64:2:5 156 -> 73, at 64:2:6 111 -> 61.
-template <int NG, bool ALL>
+// (the first column is a multiple of 8, so at M = 6 at most the fifth of its group) -- are the same in every row, and so is
+// what a nibble means there: of its two values, which bytes go to which of the four output words.  That is tabulated in LDS, as
+// byte selectors for each of the six nibbles, while the loads of all four rows are in flight; then each row and group takes an
+// index word, the two values, one LDS read and four byte permutations, and each row one 16-byte store at any alignment.
+// ALL: M = 4, where every column is kept and a thread's two groups share an index word and an 8-byte pair of values.  PAIRS: M
+// below 16, where most threads have two groups: neighbours, whose values lie side by side and whose index word is the same, unless
+// the second starts a new half of the k-step.  STREAM: rows on 16-byte boundaries: stores past the caches, as nothing reads the
+// lines again here and streamed they leave at the rate of a linear fill.  Other rows have their stores merged to whole lines in
+// the L2, so neighbouring workgroups run on the same XCD.  Bound by the writes, below M = 16 by the number of loads.
+// us per call, positions compared in every row (some 40 instructions a row and group), one group at a time, all streamed -> now: 8192
+// x 8192 at 64:2:8 35 -> 31, at 64:2:16 31.8 -> 27.6, 49152 x 12288 at 128:2:32 207 -> 207 (6.2 TB/s); rows on no 16-byte boundary:
+// 8192 x 8100 at 64:2:100 47 -> 24 (streamed 41), 8192 x 8180 at 64:2:20 50 -> 32, 8192 x 8190 at 64:2:10 50 -> 34 and at 64:2:7 67 -> 49
+// (one group at a time 60).  The entries of a chunk staged in LDS by wide loads: 64:2:8 39, 64:2:7 65.
+template <int NG, bool ALL, bool PAIRS, bool STREAM>
 __global__ void __launch_bounds__(256) decompress_kernel(const char* __restrict__ arec,
                                                          const int32_t* __restrict__ rowidx, int64_t K, int M, Divisor by_M,
                                                          int64_t steps, int vt, int chunks, int64_t rt0,
                                                          uint16_t* __restrict__ A, int64_t lda) {
-  const unsigned rtl = blockIdx.x / (unsigned)chunks;
-  const unsigned chunk = blockIdx.x - rtl * (unsigned)chunks;
+  __shared__ uint4 select[NG][16][32];                           // [group of the thread's columns][nibble][thread of a row]
+  unsigned work = blockIdx.x;
+  if constexpr (!STREAM) {
+    const unsigned per_xcd = gridDim.x / 8;
+    if (work < 8 * per_xcd) work = work % 8 * per_xcd + work / 8;
+  }
+  const unsigned rtl = work / (unsigned)chunks;
+  const unsigned chunk = work - rtl * (unsigned)chunks;
   const int64_t rt = rt0 + rtl;                                  // 32-row tile of the matrix
   const int64_t b = rt / vt;
   const int tile = (int)(rt - b * vt);
-  const unsigned k = chunk * 256 + (threadIdx.x & 31) * 8;
-  if (k >= K) return;
+  const unsigned cx = threadIdx.x & 31;
+  const unsigned k = chunk * 256 + cx * 8;
+  const bool inside = k < K;
   const int i0 = threadIdx.x >> 5;                               // rows i0, i0 + 8, ...
   const unsigned rec_bytes = (unsigned)(vt * kTileValBytes + kTailBytes);
   const char* recs = arec + b * steps * rec_bytes;
@@ -483,52 +494,70 @@ __global__ void __launch_bounds__(256) decompress_kernel(const char* __restrict_
   const unsigned g0 = divide(k, by_M);
   constexpr int NI = 4;                                          // rows per thread
   int4 ids[NG];
-  uint32_t word[NG][NI], v01[NG][NI];
+  uint32_t word[NG][NI] = {}, v01[NG][NI] = {};
   bool in[NG];
 #pragma unroll
   for (int q = 0; q < NG; ++q) {
     const unsigned g = g0 + q, s = g / 8, t = g % 8;
-    in[q] = q == 0 || g * (unsigned)M < end;                     // (a group that starts past the columns may not exist)
+    in[q] = inside && (q == 0 || g * (unsigned)M < end);         // (a group that starts past the columns may not exist)
+    ids[q] = make_int4(0, 0, 0, 0);
     if (!in[q]) continue;
     if constexpr (ALL) ids[q] = make_int4((int)(4 * g), (int)(4 * g + 1), (int)(4 * g + 2), (int)(4 * g + 3));
     else ids[q] = *reinterpret_cast<const int4*>(rowidx + (b * steps + s) * kStepRows + 4 * t);
+    if (PAIRS && q == 1 && t % 4 != 0) continue;                 // came with the group before
     const char* rec = recs + (int64_t)s * rec_bytes;
     const char* val = rec + tile * kTileValBytes + (32 * (t / 4) + i0) * 16 + (t % 4) * 4;
     const char* idx = rec + vt * kTileValBytes + (32 * (t / 4) + i0) * 8 + tile * 2;
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
-      if constexpr (ALL) {
-        if (q > 0) continue;
-        word[0][j] = word[NG - 1][j] = *reinterpret_cast<const uint16_t*>(idx + j * 64);
-        const uint2 pair = *reinterpret_cast<const uint2*>(val + j * 128);   // (the record has room for a group past the end)
-        v01[0][j] = pair.x;
-        v01[NG - 1][j] = pair.y;
+      if constexpr (ALL || PAIRS) {
+        if (ALL && q > 0) continue;
+        // (the word after a group's values is in the record also where no group follows: another row's, or the tail)
+        const u32x2_any pair = *reinterpret_cast<const u32x2_any*>(val + j * 128);
+        word[q][j] = *reinterpret_cast<const uint16_t*>(idx + j * 64);
+        v01[q][j] = pair.x;
+        if (q == 0) { v01[1 % NG][j] = pair.y; word[1 % NG][j] = word[0][j]; }
       } else {
         word[q][j] = *reinterpret_cast<const uint16_t*>(idx + j * 64);
         v01[q][j] = *reinterpret_cast<const uint32_t*>(val + j * 128);
       }
     }
   }
+  if (i0 < 6) {                                                  // the six nibbles p0 | p1 << 2 with p0 < p1
+    const int p1 = i0 == 0 ? 1 : i0 < 3 ? 2 : 3, p0 = i0 - p1 * (p1 - 1) / 2;
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+      const int4 ri = ids[q];
+      auto pick = [&](int p) { return (unsigned)(p == 0 ? ri.x : p == 1 ? ri.y : p == 2 ? ri.z : ri.w) - k; };
+      const unsigned c0 = pick(p0), c1 = pick(p1);               // outside 0 .. 7: not in this thread's columns
+      uint32_t o[4];
+#pragma unroll
+      for (unsigned e = 0; e < 4; ++e) {                         // selector 0x0c: a zero byte
+        const uint32_t lo = in[q] && c0 == 2 * e ? 0x0100u : in[q] && c1 == 2 * e ? 0x0302u : 0x0c0cu;
+        const uint32_t hi = in[q] && c0 == 2 * e + 1 ? 0x0100u : in[q] && c1 == 2 * e + 1 ? 0x0302u : 0x0c0cu;
+        o[e] = lo | hi << 16;
+      }
+      select[q][p0 | p1 << 2][cx] = make_uint4(o[0], o[1], o[2], o[3]);
+    }
+  }
+  __syncthreads();
+  if (!inside) return;
 #pragma unroll
   for (int j = 0; j < NI; ++j) {
     uint32_t o[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int q = 0; q < NG; ++q) {
-      if (!in[q]) continue;
-      const int4 ri = ids[q];
-      const uint32_t nib = word[q][j] >> (4 * ((g0 + q) % 4));
-      auto pick = [&](uint32_t p) { return (unsigned)(p == 0 ? ri.x : p == 1 ? ri.y : p == 2 ? ri.z : ri.w) - k; };
-      const unsigned c0 = pick(nib & 3u), c1 = pick((nib >> 2) & 3u);   // outside 0 .. 7: not in this thread's columns
-      const uint32_t a0 = (v01[q][j] & 0xffffu) << (16 * (c0 & 1)), a1 = (v01[q][j] >> 16) << (16 * (c1 & 1));
-#pragma unroll
-      for (unsigned e = 0; e < 4; ++e) {
-        if (c0 >> 1 == e) o[e] |= a0;
-        if (c1 >> 1 == e) o[e] |= a1;
-      }
+      const uint32_t nib = in[q] ? word[q][j] >> (4 * ((g0 + q) % 4)) & 15u : 4u;
+      const uint4 s = select[q][nib][cx];
+      o[0] |= __builtin_amdgcn_perm(0u, v01[q][j], s.x);
+      o[1] |= __builtin_amdgcn_perm(0u, v01[q][j], s.y);
+      o[2] |= __builtin_amdgcn_perm(0u, v01[q][j], s.z);
+      o[3] |= __builtin_amdgcn_perm(0u, v01[q][j], s.w);
     }
     uint16_t* row = A + (rt * kTileRows + i0 + 8 * j) * lda + k;
     if (end - k == 8) {
-      __builtin_nontemporal_store(u32x4_any{o[0], o[1], o[2], o[3]}, reinterpret_cast<u32x4_any*>(row));
+      if constexpr (STREAM) __builtin_nontemporal_store(u32x4_any{o[0], o[1], o[2], o[3]}, reinterpret_cast<u32x4_any*>(row));
+      else *reinterpret_cast<u32x4_any*>(row) = u32x4_any{o[0], o[1], o[2], o[3]};
     } else {
 #pragma unroll
       for (unsigned e = 0; e < 8; ++e)
@@ -642,12 +671,19 @@ hipError_t launch_export(const venom_handle& h, void* values, void* columns, voi
   return hipGetLastError();
 }
 
+template <bool STREAM>
+static auto decompress_of(int M) {
+  return M % 8 == 0 ? decompress_kernel<1, false, false, STREAM> : M == 4 ? decompress_kernel<2, true, false, STREAM>
+         : M == 5 ? decompress_kernel<3, false, true, STREAM> : M < 16 ? decompress_kernel<2, false, true, STREAM>
+         : decompress_kernel<2, false, false, STREAM>;
+}
+
 hipError_t launch_decompress(const venom_handle& h, uint16_t* A, int64_t lda, hipStream_t st) {
   const Layout& L = h.lay;
   if (L.R == 0 || L.K == 0) return hipSuccess;
   const int64_t chunks = (L.K + 255) / 256;
-  auto fn = h.M % 8 == 0 ? decompress_kernel<1, false> : h.M == 4 ? decompress_kernel<2, true>
-            : h.M == 5 ? decompress_kernel<3, false> : decompress_kernel<2, false>;
+  const bool aligned = reinterpret_cast<uintptr_t>(A) % 16 == 0 && lda % 8 == 0;
+  auto fn = aligned ? decompress_of<true>(h.M) : decompress_of<false>(h.M);
   // a launch holds fewer than 2^32 threads, 256 per workgroup however few columns there are: tall narrow matrices
   // take several
   const int64_t tiles = L.R / kTileRows, most = kMaxBlocks / chunks;

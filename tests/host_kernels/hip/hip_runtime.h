@@ -134,3 +134,14 @@ inline unsigned atomicOr(unsigned* p, unsigned v) { const unsigned old = *p; *p 
 inline int __popc(unsigned x) { return __builtin_popcount(x); }
 inline int __ffs(int x) { return __builtin_ffs(x); }
 inline unsigned __umulhi(unsigned a, unsigned b) { return (unsigned)(((unsigned long long)a * b) >> 32); }
+// bytes 0-3 are b's, 4-7 a's, 12 is zero
+inline unsigned __builtin_amdgcn_perm(unsigned a, unsigned b, unsigned select) {
+  const unsigned long long bytes = (unsigned long long)a << 32 | b;
+  unsigned r = 0;
+  for (int i = 0; i < 4; ++i) {
+    const unsigned s = select >> (8 * i) & 0xff;
+    if (s < 8) r |= (unsigned)(bytes >> (8 * s) & 0xff) << (8 * i);
+    else if (s != 12) __builtin_trap();
+  }
+  return r;
+}

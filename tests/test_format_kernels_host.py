@@ -150,6 +150,8 @@ def check_decompress(L, R, K, V, M, lda, offset):
     (96, 330, 96, 6, 331, 4), (64, 534, 32, 6, 534, 2), (64, 63, 64, 7, 64, 0),   # two, at M = 6 each offset in the group
     (64, 27, 32, 9, 27, 2), (64, 300, 64, 10, 301, 14),
     (64, 520, 32, 8, 520, 0), (128, 96, 128, 32, 97, 2),   # one group
+    (320, 700, 64, 7, 701, 2), (288, 600, 96, 20, 600, 0), (288, 600, 96, 20, 604, 0),   # 30 and 27 workgroups, over XCDs or not
+    (64, 160, 32, 10, 160, 0), (64, 75, 64, 5, 80, 0),   # pairs of groups and their ends, rows on 16-byte boundaries
 ])
 def test_decompress(library, R, K, V, M, lda, offset):
     in_child(library, "check_decompress", R, K, V, M, lda, offset)
