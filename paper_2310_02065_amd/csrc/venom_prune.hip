@@ -195,6 +195,12 @@ constexpr int kTileMaxGroups = 64;
 __host__ __device__ constexpr int tile_pitch(int cols) { return (cols * 2 + 15) / 16 * 16 + 16; }
 constexpr int64_t tile_lds(int V, int cols) { return (int64_t)V * tile_pitch(cols) + 8 * cols; }
 
+// PIECES: large groups whose mask bytes are no whole number of 16-byte words: written one group a thread, the words of a store lie
+// M bytes apart (a store for each 4 at M = 100).  Instead the picks go to LDS, over the group's first two entries, and each thread
+// then makes 16 bytes of a row, of all groups that meet there, stored at any alignment; neighbouring workgroups, which share
+// the lines at their edges, run on the same XCD.  8192 x 8100, us per call: 64:2:100 118 -> 73, 128:2:100 125 -> 96, 32:2:100 121 -> 91.
+// Groups of up to 64 gain nothing or lose by the second pass over LDS (64:2:40 66 -> 68, 64:2:7 76 -> 86).
+template <bool PIECES>
 __global__ void __launch_bounds__(256) prune_tile_kernel(const uint16_t* __restrict__ A, int64_t lda, int V, int M,
                                                          int64_t G, int gpw, int mask_word,
                                                          uint8_t* __restrict__ mask, int64_t ldm,
@@ -203,7 +209,16 @@ __global__ void __launch_bounds__(256) prune_tile_kernel(const uint16_t* __restr
   extern __shared__ __attribute__((aligned(16))) char tile[];      // [row][pitch], then the column masses
   __shared__ int sel[kTileMaxGroups][kSelCols];                     // by rank, then ascending
   __shared__ unsigned long long wg_total, wg_kept;
-  const int64_t b = blockIdx.y, g0 = (int64_t)blockIdx.x * gpw;
+  int64_t b = blockIdx.y, chunk = blockIdx.x;
+  if constexpr (PIECES) {
+    const uint64_t all = (uint64_t)gridDim.x * gridDim.y, per_xcd = all / 8, id = blockIdx.y * (uint64_t)gridDim.x + blockIdx.x;
+    if (id < 8 * per_xcd) {
+      const uint64_t work = id % 8 * per_xcd + id / 8;
+      b = (int64_t)(work / gridDim.x);
+      chunk = (int64_t)(work - b * gridDim.x);
+    }
+  }
+  const int64_t g0 = chunk * gpw;
   const int tid = threadIdx.x, lane = tid & 63;
   const int ng = (int)((G - g0) < gpw ? (G - g0) : gpw);
   const int span = ng * M;
@@ -324,8 +339,46 @@ __global__ void __launch_bounds__(256) prune_tile_kernel(const uint16_t* __restr
       if (p == p0) { c0 = c[p]; w0 = w[p]; }
       if (p == p1) { c1 = c[p]; w1 = w[p]; }
     }
-    write_mask(mask + (b * V + v) * ldm + (g0 + t) * M, M, mask_word, c0, c1);
+    if constexpr (PIECES) {
+      uint16_t* pick = reinterpret_cast<uint16_t*>(tile + v * pitch) + t * M;   // (this row and group is read by this thread only)
+      pick[0] = (uint16_t)(t * M + c0);
+      pick[1] = (uint16_t)(t * M + c1);
+    } else {
+      write_mask(mask + (b * V + v) * ldm + (g0 + t) * M, M, mask_word, c0, c1);
+    }
     my_kept += magnitude(w0) + magnitude(w1);
+  }
+  if constexpr (PIECES) {
+    __syncthreads();
+    const int pieces = (span + 15) / 16;
+    for (int i = tid; i < V * pieces; i += 256) {
+      const int v = i / pieces, j = 16 * (i - v * pieces), left = span - j;
+      const uint16_t* row = reinterpret_cast<const uint16_t*>(tile + v * pitch);
+      uint64_t lo = 0, hi = 0;
+      for (int at = j / M * M; at < j + 16 && at < span; at += M) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          const unsigned d = (unsigned)(row[at + p] - j);
+          if (d < 8) lo |= (uint64_t)1 << (8 * d);
+          else if (d < 16) hi |= (uint64_t)1 << (8 * d - 64);
+        }
+      }
+      uint8_t* out = mask + (b * V + v) * ldm + g0 * M + j;
+      if (left >= 16) {
+        *reinterpret_cast<u32x4_any*>(out) = u32x4_any{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+      } else {
+        int n = left;
+        if (n >= 8) {
+          *reinterpret_cast<u32x2_any*>(out) = u32x2_any{(uint32_t)lo, (uint32_t)(lo >> 32)};
+          lo = hi; out += 8; n -= 8;
+        }
+        if (n >= 4) {
+          *reinterpret_cast<u32_any*>(out) = (uint32_t)lo;
+          lo >>= 32; out += 4; n -= 4;
+        }
+        for (; n > 0; --n, lo >>= 8) *out++ = (uint8_t)lo;
+      }
+    }
   }
   unsigned long long kept = mass_units(my_kept);
 #pragma unroll
@@ -407,8 +460,11 @@ hipError_t launch_prune(const uint16_t* A, int64_t lda, int64_t R, int64_t K, in
   const uintptr_t ma = reinterpret_cast<uintptr_t>(mask);
   const int mask_word = (M % 16 == 0 && ldm % 16 == 0 && ma % 16 == 0) ? 16 : (M % 8 == 0 && ldm % 8 == 0 && ma % 8 == 0) ? 8
                         : (M % 4 == 0 && ldm % 4 == 0 && ma % 4 == 0) ? 4 : 1;
-  if (tiled > 0)
-    hipLaunchKernelGGL(prune_tile_kernel, dim3((unsigned)chunks, (unsigned)Rb), dim3(256), (size_t)tile_lds(V, gpw * M), st,
+  if (tiled > 0 && mask_word < 16 && M > 64)
+    hipLaunchKernelGGL(prune_tile_kernel<true>, dim3((unsigned)chunks, (unsigned)Rb), dim3(256), (size_t)tile_lds(V, gpw * M), st,
+                       A, lda, V, M, G, gpw, mask_word, mask, ldm, kept_mass, total_mass);
+  else if (tiled > 0)
+    hipLaunchKernelGGL(prune_tile_kernel<false>, dim3((unsigned)chunks, (unsigned)Rb), dim3(256), (size_t)tile_lds(V, gpw * M), st,
                        A, lda, V, M, G, gpw, mask_word, mask, ldm, kept_mass, total_mass);
   else
     hipLaunchKernelGGL(prune_kernel, dim3((unsigned)chunks, (unsigned)Rb), dim3(256), 0, st, A, lda, V, M, G, gpw, vec_ok,
