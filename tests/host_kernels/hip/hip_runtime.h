@@ -1,6 +1,7 @@
 // Just enough of the HIP device language, as plain C++, to run the format and pruning kernels on the
 // CPU under the compiler's undefined-behaviour checks.  A workgroup's threads are fibers on one OS
-// thread; a barrier or a lane exchange is a switch to the next fiber, so all fibers meet at every one of them.
+// thread; a lane exchange is a switch to the next fiber, at which all fibers of a wave meet, a barrier as many as it takes until all
+// fibers have come to it.
 #pragma once
 #include <math.h>
 #include <stddef.h>
@@ -41,6 +42,7 @@ inline std::vector<char> stacks(kMaxThreads * (size_t)(256 << 10));
 inline ucontext_t scheduler, fiber[kMaxThreads];
 inline bool finished[kMaxThreads];
 inline unsigned current;
+inline unsigned barriers[kMaxThreads];              // that each fiber has come to
 inline void* body;
 inline void (*call)(void*);
 inline unsigned long long slot[kMaxThreads];        // values of a lane exchange
@@ -68,6 +70,7 @@ template <class F> void run_block(unsigned threads, F& f) {
     fiber[t].uc_link = &scheduler;
     makecontext(&fiber[t], fiber_main, 0);
     finished[t] = false;
+    barriers[t] = 0;
   }
   for (bool any = true; any;) {
     any = false;
@@ -107,7 +110,14 @@ inline hipError_t hipGetLastError() {
   return e;
 }
 
-inline void __syncthreads() { emu::yield(); }
+inline void __syncthreads() {                          // (a wave may come to it many lane exchanges before another)
+  const unsigned mine = ++emu::barriers[emu::current];
+  for (bool wait = true; wait;) {
+    emu::yield();
+    wait = false;
+    for (unsigned t = 0; t < blockDim.x; ++t) wait |= !emu::finished[t] && emu::barriers[t] < mine;
+  }
+}
 template <class T> T __shfl_xor(T v, int mask) {
   emu::slot[emu::current] = v;
   emu::yield();
