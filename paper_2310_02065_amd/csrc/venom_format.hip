@@ -124,6 +124,14 @@ __device__ __forceinline__ void emit_index(const FormatDst& d, char* rec, int i,
   *reinterpret_cast<uint2*>(rec + d.vt * kTileValBytes + (32 * h + i) * 8) = make_uint2(o[0], o[1]);
 }
 
+// x of eight neighbouring lanes (0-7, 8-15, ...), combined; all lanes of the wave take part.
+__device__ __forceinline__ uint32_t or_of_eight_lanes(uint32_t x) {
+  x |= __builtin_amdgcn_mov_dpp(x, 0xb1, 0xf, 0xf, true);        // quads: 1 0 3 2
+  x |= __builtin_amdgcn_mov_dpp(x, 0x4e, 0xf, 0xf, true);        // 2 3 0 1
+  x |= __builtin_amdgcn_mov_dpp(x, 0x141, 0xf, 0xf, true);       // the mirrored half row: lane 7 - l
+  return x;
+}
+
 // The non-zero bytes of a word as four bits.
 __device__ __forceinline__ uint32_t nonzero_bits(uint32_t x) {
   const uint32_t top = (((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) & 0x80808080u;   // bit 7 of every non-zero byte
@@ -145,10 +153,14 @@ __host__ __device__ constexpr int bits_pitch(int wpw, int M) { return (wpw * M +
 //            smallest unused ids, sorted
 //   phase 3: one thread per (row, group): positions kept inside the 4 selected columns, padded with
 //            the smallest unused positions, sorted -> nibble; values copied as bits; canonical and
-//            packed entries written together.  Four entries per thread are in flight at a time.
-// Bound by memory: 49152 x 12288 at M = 32 (0.6 GB of mask, 1.2 GB of A -- the two kept values of 32
-// touch every 64-byte sector -- and 0.17 GB written) takes 0.42 ms, 4.7 TB/s; it was 0.45 ms, and another
-// 0.08 ms to pack in a second pass, when phase 3 fetched the mask bytes again one by one.
+//            packed entries written together.  A thread keeps its group, so that only what depends on the row is
+//            left in the loop, and the nibble comes from a table of the 16 sets of kept positions.
+// NE: rows of phase 3 in flight per thread.  Bound by memory from M = 32 on: 49152 x 12288 (0.6 GB of mask, 1.2 GB of A -- the two
+// kept values of 32 touch every 64-byte sector -- and 0.17 GB written) takes 0.39 ms, 5.0 TB/s; it was 0.40 ms with four rows in
+// flight, 0.45 ms, and another 0.08 ms to pack in a second pass, when phase 3 fetched the mask bytes again one by one.  For
+// smaller groups there are more entries than bytes to wait for, and eight rows in flight cost occupancy: 8192 x 8192 at 64:2:8,
+// us per call with 2 / 4 / 8 rows 80.6 / 84.5 / 87.1.  Against an index computation for each entry: 128:2:4 135 -> 115, 64:2:8 83 -> 75,
+// 64:2:16 71 -> 67, 128:2:40 68 -> 64.
 // by_full, by_last: n / units = n * by >> 16 for n, units <= 256, for the loads of a row in all chunks of columns but the
 // last, and in the last (a division in the kernel is 5 % of a workgroup with one row).
 // bits_ok: the bits of V rows fit (48 KB of LDS: 49152 x 12288 at 1024:2:32 takes 464 us a call, more if phase 3 reads the
@@ -159,7 +171,7 @@ __host__ __device__ constexpr int bits_pitch(int wpw, int M) { return (wpw * M +
 // venom_compress together, first to last and cached -> last to first -> streamed as well: 49152 x 12288 at 128:2:32 803 -> 784 ->
 // 765, 12288 x 12288 at 256:2:8 278 -> 267 -> 263, 49152 x 2048 at 32:2:16 168 -> 158 -> 154, 16384 x 4096 at 128:2:16
 // 116 -> 114 -> 113 (compression of one mask again and again, 66 instead of 65).
-template <int UB, bool ONCE>
+template <int UB, bool ONCE, int NE>
 __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                        const uint8_t* __restrict__ mask, int64_t ldm, int wpw, int bits_ok,
                                                        unsigned by_full, unsigned by_last,
@@ -275,81 +287,79 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
     sel[tid] = make_ushort4((uint16_t)s[0], (uint16_t)s[1], (uint16_t)s[2], (uint16_t)s[3]);
   }
   __syncthreads();
-  // one thread per (row, group): eight neighbouring lanes hold the eight nibbles of a metadata word
-  // and combine them with three lane exchanges
-  constexpr int NE = 4;                          // entries in flight per thread
+  // one thread per (row, group): eight neighbouring lanes hold the eight nibbles of a metadata word and combine them with three
+  // lane exchanges.  A thread keeps its group and goes from row to row, so all that depends on the group is done once.
   const int64_t rec_bytes = (int64_t)d.vt * kTileValBytes + kTailBytes;
-  const int NG = 8 * nw;                         // lanes of a row (a multiple of 8)
-  const int total = V * NG;
-  auto row_of = [&](int i) {                     // i / NG, nw <= 4: no division
-    const int q = i >> 3;
-    return nw == 1 ? q : nw == 2 ? q >> 1 : nw == 4 ? q >> 2 : q / 3;
-  };
-  for (int base = 0; base < total; base += 256 * NE) {
+  const int lanes = nw == 1 ? 3 : nw == 2 ? 4 : 5;                        // log2 of a row's lanes (of 32, three words leave eight idle)
+  const int tg = tid & ((1 << lanes) - 1), dv = 256 >> lanes;
+  const bool group_in = tg < ng, word_in = tg < 8 * nw;
+  const ushort4 c4 = group_in ? sel[tg] : make_ushort4(0, 0, 0, 0);
+  const uint64_t cols = (uint64_t)c4.x | (uint64_t)c4.y << 16 | (uint64_t)c4.z << 32 | (uint64_t)c4.w << 48;
+  const bool legal_cols = group_in && cols_ok[tg];
+  const int64_t w = w0 + (tg >> 3), g = g0 + tg;
+  const int t = tg & 7, h = t >> 2;
+  const uint16_t* acol = A + b * V * lda + g * M;
+  uint32_t* vals = d.values + b * V * d.G + g;
+  uint32_t* meta = d.meta + b * V * d.W + w;
+  char* rec0 = d.arec == nullptr ? nullptr : d.arec + (b * d.W + w) * rec_bytes;   // (of this block, if the packed one is the same)
+  const bool same_block = d.Vp == d.V;
+  for (int base = 0; base < V; base += NE * dv) {
     uint32_t v01[NE], nib[NE];
 #pragma unroll
     for (int j = 0; j < NE; ++j) {
-      const int i = base + 256 * j + tid, v = row_of(i), tg = i - v * NG;
+      const int v = base + (tid >> lanes) + j * dv;
       nib[j] = 0; v01[j] = 0;
-      if (i < total && tg < ng) {
-        const ushort4 c4 = sel[tg];
-        const int c[kSelCols] = {c4.x, c4.y, c4.z, c4.w};
+      if (v < V && group_in) {
         int kept = 0;                            // bit p: the row keeps selected column p
-        if (bits_ok) {
+        if (bits_ok && M <= 32) {                // the group's bits in one word
+          const uint32_t* row = reinterpret_cast<const uint32_t*>(bits + v * pitch) + tg * M / 32;
+          const uint32_t x = (uint32_t)((((uint64_t)row[1] << 32) | row[0]) >> (tg * M % 32));
+          kept = (x >> c4.x & 1) | (x >> c4.y & 1) << 1 | (x >> c4.z & 1) << 2 | (x >> c4.w & 1) << 3;
+        } else if (bits_ok) {
 #pragma unroll
           for (int p = 0; p < kSelCols; ++p) {
-            const int col = tg * M + c[p];
+            const int col = tg * M + (int)(cols >> (16 * p) & 0xffff);
             kept |= ((bits[v * pitch + col / 8] >> (col % 8)) & 1) << p;
           }
         } else {                                 // four loads in flight (one after the other: 1351 instead of 1029 us
           const uint8_t* mrow = mblk + (int64_t)v * ldm + tg * M;   // for 49152 x 12288 at 8192:2:8)
-          const uint8_t m0 = mrow[c[0]], m1 = mrow[c[1]], m2 = mrow[c[2]], m3 = mrow[c[3]];
+          const uint8_t m0 = mrow[c4.x], m1 = mrow[c4.y], m2 = mrow[c4.z], m3 = mrow[c4.w];
           kept = (m0 != 0) | (m1 != 0) << 1 | (m2 != 0) << 2 | (m3 != 0) << 3;
         }
-        if (cols_ok[tg] && __popc(kept) > 2) {
+        if (legal_cols && __popc(kept) > 2) {
           const uint32_t key = (uint32_t)tg << 24 | 1u << 23 | (uint32_t)v;
           first = first < key ? first : key;
         }
-        // first two kept positions, then the smallest unused ones, sorted
-        int p0, p1;
-        bool k0 = true, k1 = true;
-        const int lo = __ffs(kept) - 1, rest = kept & (kept - 1);
-        if (kept == 0) { p0 = 0; p1 = 1; k0 = k1 = false; }     // nothing kept: positions (0, 1)
-        else if (rest != 0) { p0 = lo; p1 = __ffs(rest) - 1; }
-        else if (lo == 0) { p0 = 0; p1 = 1; k1 = false; }       // one kept: add the smallest other position
-        else { p0 = 0; p1 = lo; k0 = false; }
-        const uint16_t* arow = A + (b * V + v) * lda + (g0 + tg) * M;
-        const int c0 = p0 == 0 ? c[0] : p0 == 1 ? c[1] : c[2];
-        const int c1 = p1 == 1 ? c[1] : p1 == 2 ? c[2] : c[3];
-        const uint32_t a0 = k0 ? arow[c0] : 0u;
-        const uint32_t a1 = k1 ? arow[c1] : 0u;
+        // the nibble p0 | p1 << 2: the first two kept positions, padded with the smallest unused ones, sorted; of `kept` = 0 .. 15
+        constexpr uint64_t kNibbles = 0x498e4dcc49884444ull;
+        const uint32_t n = (uint32_t)(kNibbles >> (4 * kept)) & 15u, p0 = n & 3u, p1 = n >> 2;
+        const uint16_t* arow = acol + (int64_t)v * lda;
+        const uint32_t a0 = kept >> p0 & 1 ? arow[cols >> (16 * p0) & 0xffff] : 0u;
+        const uint32_t a1 = kept >> p1 & 1 ? arow[cols >> (16 * p1) & 0xffff] : 0u;
         v01[j] = a0 | (a1 << 16);
-        nib[j] = (uint32_t)(p0 | (p1 << 2)) << (4 * (tg & 7));
+        nib[j] = n << (4 * t);
       }
     }
 #pragma unroll
     for (int j = 0; j < NE; ++j) {
-      const int i = base + 256 * j + tid, v = row_of(i), tg = i - v * NG;
-      uint32_t word = nib[j];
-      word |= __shfl_xor(word, 1);
-      word |= __shfl_xor(word, 2);
-      word |= __shfl_xor(word, 4);
-      if (i < total) {
-        const int64_t w = w0 + (tg >> 3), g = g0 + tg, r = b * V + v;
-        const int t = tg & 7;
-        if (tg < ng) d.values[r * d.G + g] = v01[j];
-        if (t == 0) d.meta[r * d.W + w] = word;
-        if (v == 0 && tg < ng) emit_columns(d, b, g, sel[tg]);
+      const int v = base + (tid >> lanes) + j * dv;
+      const uint32_t word = or_of_eight_lanes(nib[j]);
+      if (v < V && word_in) {
+        if (group_in) vals[v * d.G] = v01[j];
+        if (t == 0) meta[v * d.W] = word;
+        if (v == 0 && group_in) emit_columns(d, b, g, c4);
         if (d.arec != nullptr) {
-          int64_t rb;
-          int rr;
-          packed_row(d, b, v, rb, rr);
-          char* rec = d.arec + (rb * d.W + w) * rec_bytes;
-          const int h = t >> 2;
+          int64_t rb = b;
+          int rr = v;
+          char* rec = rec0;
+          if (!same_block) {
+            packed_row(d, b, v, rb, rr);
+            rec = d.arec + (rb * d.W + w) * rec_bytes;
+          }
           *reinterpret_cast<uint32_t*>(rec + (rr / kTileRows) * kTileValBytes + (32 * h + rr % kTileRows) * 16 + (t & 3) * 4) = v01[j];
-          if (t == 0 && d.Vp == d.V) words[tg >> 3][v] = word;
-          else if ((t & 3) == 0 && d.Vp != d.V) emit_index_field(d, rec, rr, h, word);   // (the packed block's other rows are elsewhere)
-          if (rr == 0) emit_rowidx(d, rb, w, t, tg < ng ? sel[tg] : make_ushort4(0, 0, 0, 0));
+          if (t == 0 && same_block) words[tg >> 3][v] = word;
+          else if ((t & 3) == 0 && !same_block) emit_index_field(d, rec, rr, h, word);   // (the packed block's other rows are elsewhere)
+          if (rr == 0) emit_rowidx(d, rb, w, t, c4);
         }
       }
     }
@@ -613,7 +623,11 @@ hipError_t launch_compress(const uint16_t* A, int64_t lda, const uint8_t* mask, 
     // every chunk of columns in whole loads, fewer than 8 columns left over at the end of a row
     const int64_t chunk = (int64_t)8 * wpw * h.M, last = L.K - (grid.x - 1) * chunk;
     const int ub = chunk % 16 == 0 && L.K % 16 < 8 ? 16 : 8;
-    auto fn = ub == 8 ? compress_kernel<8, false> : bits_ok ? compress_kernel<16, true> : compress_kernel<16, false>;
+    auto of = [&](auto ne) {
+      constexpr int NE = decltype(ne)::value;
+      return ub == 8 ? compress_kernel<8, false, NE> : bits_ok ? compress_kernel<16, true, NE> : compress_kernel<16, false, NE>;
+    };
+    auto fn = h.M >= 32 ? of(std::integral_constant<int, 8>{}) : of(std::integral_constant<int, 2>{});
     hipLaunchKernelGGL(fn, grid, dim3(256), lds, st, A, lda, mask, ldm, wpw, bits_ok, by(chunk / ub), by(last / ub), format_dst(h),
                        legality);
   }

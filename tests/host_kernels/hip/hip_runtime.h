@@ -155,3 +155,14 @@ inline unsigned __builtin_amdgcn_perm(unsigned a, unsigned b, unsigned select) {
   }
   return r;
 }
+// lane exchanges inside rows of 16 lanes: four lanes permuted, and the mirrored half row
+inline unsigned __builtin_amdgcn_mov_dpp(unsigned v, int control, int, int, bool) {
+  const unsigned l = emu::current;
+  if (control < 0 || (control > 0xff && control != 0x141)) __builtin_trap();
+  const unsigned from = control == 0x141 ? l / 8 * 8 + 7 - l % 8 : l / 4 * 4 + ((unsigned)control >> (2 * (l % 4)) & 3);
+  emu::slot[l] = v;
+  emu::yield();
+  const unsigned other = (unsigned)emu::slot[from];
+  emu::yield();
+  return other;
+}
