@@ -116,7 +116,7 @@ __device__ __forceinline__ void emit_index_field(const FormatDst& d, char* rec, 
     for (int e = d.vt; e < kMaxTiles; ++e) tail[e] = 0;
 }
 // The same for a whole lane 32*h + i at once, from the words of rows i, i+32, ...: one 8-byte store, where those
-// words are at hand (in LDS: compression gains 2 %; fetching them again, in the import, loses 10 %).
+// words are at hand, in LDS.
 __device__ __forceinline__ void emit_index(const FormatDst& d, char* rec, int i, int h, const uint32_t (&word)[kMaxTiles]) {
   uint32_t o[2] = {0, 0};
 #pragma unroll
@@ -384,74 +384,110 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
 
 // Canonical arrays from outside -> the workspace: checked, copied and packed in one pass (the handle
 // is only handed out if the check found nothing).  One thread per row and half metadata word = 4 groups: 16 bytes
-// of values, one 16-byte slot of the packed record.  A workgroup takes 2^wbits words of 128 >> wbits rows.  Where
-// there are packed records, 4 words x 32 rows: it reads rows of 128 bytes and completes the 128-byte lines of the
-// records.  Without them, 32 words x 4 rows: a row that starts inside a line then shares far fewer lines with
-// workgroups of other XCDs (4096 x 8190 at 1:2:7, us per call: 81 with 4 words, 60 with 32, three copies and a check 72).
+// of values, one 16-byte slot of the packed record.  TILES: 32-row tiles of a packed block row; a workgroup takes 4 words of all
+// of them, the loads of all rows in flight together: it reads rows of 128 bytes and completes the 128-byte lines of the
+// records, their index words by way of LDS (two bytes a row and tile: workgroups of one tile each wrote parts of the same lines
+// from several XCDs).  SPLIT: a workgroup takes one tile after all, where there are too few otherwise.  TILES = 0, no packed records: 2^wbits words of 128 >> wbits rows, 32 of 4 where there are as many; a row
+// that starts inside a line then shares far fewer lines with workgroups of other XCDs (4096 x 8190 at 1:2:7, us per call: 81 with 4 words,
+// 60 with 32, three copies and a check 72).
 // Checked is what the gather and the matrix instruction rely on -- column ids strictly increasing
 // and below M (once per block), the two m-indices of a nibble ordered idx0 < idx1, unused nibbles of
 // the last metadata word zero.
-// 8192 x 8192 at M = 8 (120 MB in and out): 28 us, 4.2 TB/s; three copies, the check and the packing by
-// themselves took 90 us.
+// 8192 x 8192, us per call of the binding (20 of them the launch and the wait), one tile a workgroup -> now: 64:2:8 (120 MB in and
+// out) 48.2 -> 46.0, 128:2:8 47.1 -> 44.7, 64:2:16 37.0 -> 34.0, 64:2:7 63.2 -> 59.4; three copies, the check and the packing by themselves
+// took 90 us at 64:2:8.
+template <int TILES, bool SPLIT>
 __global__ void __launch_bounds__(256) import_kernel(const u32_any* __restrict__ values, const u16_any* __restrict__ columns,
                                                      const u32_any* __restrict__ meta, int64_t R, int wbits, FormatDst d,
                                                      Legality legality) {
+  constexpr bool PACKED = TILES > 0, GATHER = PACKED && !SPLIT;   // GATHER: the index words go through LDS
+  constexpr int NT = PACKED ? TILES : 1;
+  __shared__ uint32_t words[GATHER ? 4 : 1][NT * kTileRows];
+  if constexpr (PACKED) wbits = 2;
   const int64_t wq = (d.W + (1 << wbits) - 1) >> wbits;
-  const int rows = 128 >> wbits;                   // of the workgroup
+  const int rows = PACKED ? NT * kTileRows : 128 >> wbits;   // of the workgroup
   const int64_t rblk = blockIdx.x / wq, wblk = blockIdx.x - rblk * wq;
+  const int64_t rb = SPLIT ? rblk / d.vt : rblk;   // packed block row
+  const int t0 = SPLIT ? (int)(rblk - rb * d.vt) : 0;
   const int u = threadIdx.x & ((2 << wbits) - 1), h = u & 1, i = threadIdx.x >> (wbits + 1);
-  const int64_t w = (wblk << wbits) + (u >> 1), r = rblk * rows + i;
-  if (w >= d.W || r >= R) return;
-  const int64_t cb0 = rblk * rows / d.V;           // of the workgroup's first row: a scalar division
-  const int v0 = (int)(rblk * rows - cb0 * d.V) + i;
-  const int down = v0 >= d.V ? v0 / d.V : 0;
-  const int64_t cb = cb0 + down;
-  const int v = v0 - down * d.V;
+  const int64_t w = (wblk << wbits) + (u >> 1), r0 = rblk * rows + i;
+  const bool in = w < d.W && r0 < R;               // (R is a multiple of a packed block's rows)
   const int64_t g = w * 8 + 4 * h;
-  const int ng = g >= d.G ? 0 : d.G - g < 4 ? (int)(d.G - g) : 4;         // groups of the half word that exist
-  const uint32_t word = meta[r * d.W + w];
-  uint32_t x[4] = {0, 0, 0, 0};
-  const u32_any* src = values + r * d.G + g;
-  uint32_t* dst = d.values + r * d.G + g;
-  if (ng == 4) {                                   // wide also where G is no multiple of 4 (rows start at any word)
-    const u32x4_any q = *reinterpret_cast<const u32x4_any*>(src);
-    x[0] = q.x; x[1] = q.y; x[2] = q.z; x[3] = q.w;
-    *reinterpret_cast<u32x4_word*>(dst) = q;
-  } else {
+  const int ng = !in || g >= d.G ? 0 : d.G - g < 4 ? (int)(d.G - g) : 4;  // groups of the half word that exist
+  uint32_t word[NT], x[NT][4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (e < ng) { x[e] = src[e]; dst[e] = x[e]; }
+  for (int t = 0; t < NT; ++t) {
+    const int64_t r = r0 + t * kTileRows;
+    word[t] = in ? (uint32_t)meta[r * d.W + w] : 0u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[t][e] = 0;
+    const u32_any* src = values + r * d.G + g;
+    if (ng == 4) {                                 // wide also where G is no multiple of 4 (rows start at any word)
+      const u32x4_any q = *reinterpret_cast<const u32x4_any*>(src);
+      x[t][0] = q.x; x[t][1] = q.y; x[t][2] = q.z; x[t][3] = q.w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (e < ng) x[t][e] = src[e];
+    }
   }
-  if (h == 0) d.meta[r * d.W + w] = word;
   bool bad = false;
+  const int64_t cb0 = rblk * rows / d.V;           // canonical block row of the workgroup's first row: a scalar division
+  const int first = (int)(rblk * rows - cb0 * d.V);
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const uint32_t nib = (word >> (16 * h + 4 * e)) & 0xfu;
-    bad = bad || (e < ng ? (nib & 3u) >= (nib >> 2) : nib != 0);
-  }
-  int64_t rb = 0;
-  int rr = 1;
-  if (d.arec != nullptr) {
-    packed_row(d, cb, v, rb, rr);
-    char* rec = d.arec + (rb * d.W + w) * ((int64_t)d.vt * kTileValBytes + kTailBytes);
-    *reinterpret_cast<uint4*>(rec + (rr / kTileRows) * kTileValBytes + (32 * h + rr % kTileRows) * 16) =
-        make_uint4(x[0], x[1], x[2], x[3]);
-    emit_index_field(d, rec, rr, h, word);
-  }
-  if (v == 0 || rr == 0) {
+  for (int t = 0; t < NT; ++t) {
+    if (!in) continue;
+    const int64_t r = r0 + t * kTileRows;
+    uint32_t* dst = d.values + r * d.G + g;
+    if (ng == 4) {
+      *reinterpret_cast<u32x4_word*>(dst) = u32x4_word{x[t][0], x[t][1], x[t][2], x[t][3]};
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (e < ng) dst[e] = x[t][e];
+    }
+    if (h == 0) d.meta[r * d.W + w] = word[t];
+#pragma unroll
     for (int e = 0; e < 4; ++e) {
-      ushort4 c = make_ushort4(0, 0, 0, 0);
-      if (e < ng) {
-        const u16_any* cp = columns + (cb * d.G + g + e) * kSelCols;
-        c = make_ushort4(cp[0], cp[1], cp[2], cp[3]);
-        bad = bad || !(c.x < c.y && c.y < c.z && c.z < c.w && c.w < d.M);
-        if (v == 0) emit_columns(d, cb, g + e, c);
+      const uint32_t nib = (word[t] >> (16 * h + 4 * e)) & 0xfu;
+      bad = bad || (e < ng ? (nib & 3u) >= (nib >> 2) : nib != 0);
+    }
+    const int rr = (t0 + t) * kTileRows + i;       // row of the packed block row
+    if constexpr (PACKED) {
+      char* rec = d.arec + (rb * d.W + w) * ((int64_t)d.vt * kTileValBytes + kTailBytes);
+      *reinterpret_cast<uint4*>(rec + (t0 + t) * kTileValBytes + (32 * h + i) * 16) = make_uint4(x[t][0], x[t][1], x[t][2], x[t][3]);
+      if (SPLIT) emit_index_field(d, rec, rr, h, word[t]);
+      else if (h == 0) words[u >> 1][rr] = word[t];
+    }
+    const int v0 = first + t * kTileRows + i, down = v0 >= d.V ? v0 / d.V : 0, v = v0 - down * d.V;
+    const int64_t cb = cb0 + down;
+    const bool ids = PACKED && rr == 0;
+    if (v == 0 || ids) {
+      for (int e = 0; e < 4; ++e) {
+        ushort4 c = make_ushort4(0, 0, 0, 0);
+        if (e < ng) {
+          const u16_any* cp = columns + (cb * d.G + g + e) * kSelCols;
+          c = make_ushort4(cp[0], cp[1], cp[2], cp[3]);
+          bad = bad || !(c.x < c.y && c.y < c.z && c.z < c.w && c.w < d.M);
+          if (v == 0) emit_columns(d, cb, g + e, c);
+        }
+        if (ids) emit_rowidx(d, rb, w, 4 * h + e, c);
       }
-      if (rr == 0) emit_rowidx(d, rb, w, 4 * h + e, c);
     }
   }
   const unsigned long long lanes = __ballot(bad);
   if (bad && (lanes & ((1ull << threadIdx.x % 64) - 1)) == 0) report(legality, 0);   // (which one it is nobody asks)
+  if constexpr (GATHER) {
+    __syncthreads();
+    const int k = threadIdx.x / 64, l = threadIdx.x % 64;
+    const int64_t wk = (wblk << wbits) + k;
+    if (wk < d.W) {
+      uint32_t tiles[kMaxTiles];
+#pragma unroll
+      for (int e = 0; e < kMaxTiles; ++e) tiles[e] = e < NT ? words[k][32 * e + l % 32] : 0u;
+      emit_index(d, d.arec + (rb * d.W + wk) * ((int64_t)d.vt * kTileValBytes + kTailBytes), l % 32, l / 32, tiles);
+    }
+  }
 }
 
 // Exact quotients of values below 2^31 by a divisor of at least 2: n / divisor = n * mul >> (31 + shift).
@@ -595,11 +631,16 @@ hipError_t launch_import(const uint16_t* values, const uint16_t* columns, const 
   const Legality legality{slot, found, reinterpret_cast<unsigned long long*>(h.ws + L.off_status)};
   if (slot < 0) hipLaunchKernelGGL(init_status_kernel, dim3(1), dim3(1), 0, st, legality.own);
   if (L.R > 0 && L.G > 0) {
-    // 32 rows x 4 words where there are packed records; otherwise longer pieces of fewer rows, as the rows are
+    // 4 words of a packed block row where there are packed records; otherwise longer pieces of fewer rows, as the rows are
     int wbits = 2;
     while (!L.packed && wbits < 5 && (1 << wbits) < L.W) ++wbits;
-    const int64_t words = (L.W + (1 << wbits) - 1) >> wbits, rows = 128 >> wbits;
-    hipLaunchKernelGGL(import_kernel, dim3((unsigned)(words * ((L.R + rows - 1) / rows))), dim3(256), 0, st,
+    const int64_t words = (L.W + (1 << wbits) - 1) >> wbits;
+    // fewer than three workgroups a unit: 8192 x 8192 at 128:2:64 (256 of them) 27.3 whole, 25.7 split; at 128:2:20 (832) 35.2 and 36.3
+    const bool split = L.vt > 1 && words * L.Rbp < 768;
+    const int64_t rows = !L.packed ? 128 >> wbits : split ? kTileRows : L.vt * kTileRows;
+    auto fn = L.vt == 0 ? import_kernel<0, false> : split ? import_kernel<1, true> : L.vt == 1 ? import_kernel<1, false>
+              : L.vt == 2 ? import_kernel<2, false> : L.vt == 3 ? import_kernel<3, false> : import_kernel<4, false>;
+    hipLaunchKernelGGL(fn, dim3((unsigned)(words * ((L.R + rows - 1) / rows))), dim3(256), 0, st,
                        reinterpret_cast<const u32_any*>(values), columns, meta, L.R, wbits, format_dst(h), legality);
   }
   return hipGetLastError();
