@@ -228,13 +228,20 @@ __global__ void __launch_bounds__(NP * GB * 64, 2) skinny_kernel(SkinnyParams p)
     for (int k = 0; k < PA; ++k)
       if (k < n) step(k, (k + PA) % (PA + 1));
   }
-  if (p.steps > whole && phase == whole % NP) {    // the last k-step, where G is no multiple of 8; two waves of one phase write
-    load_a(0, whole);                              // the same, to the window that neither has read since the last barrier
-    if constexpr (TOKENS) stage_end(whole);
-    else { load_rows(0); put_rows(); }
-    half16 b = operand(id[0][0], whole);
-    clear_absent(b, whole);
-    multiply(0, b);
+  if (p.steps > whole) {                           // the last k-step, where G is no multiple of 8: one phase's
+    const bool ours = phase == whole % NP;
+    if (ours) {
+      load_a(0, whole);
+      if constexpr (TOKENS) stage_end(whole);      // (to the window that nobody has read since the last barrier)
+      else { load_rows(0); put_rows(); }
+    }
+    // each wave of the phase has staged its share of the window
+    if constexpr (GB > 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (ours) {
+      half16 b = operand(id[0][0], whole);
+      clear_absent(b, whole);
+      multiply(0, b);
+    }
   }
 
   // ---- the partial sums of the waves, halved until four are left, then summed by one wave per tile

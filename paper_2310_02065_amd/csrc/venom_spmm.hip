@@ -134,6 +134,7 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
   static_assert(VT % NR == 0, "the tile rows divide evenly over the waves of a strip");
   static_assert(D == 1 || D == 2, "barriers between the hand-over of a stage and its return");
   constexpr bool EPI = MODE != 0;
+  constexpr int FENCE = MODE == 1 && NC * NR <= 4 ? 4 : 2;   // activations evaluated together
   static_assert(VT >= 1 && VT <= kMaxTiles, "32-row tiles per block row");
   constexpr int NP = kProducers;
   constexpr int CONS = NC * NR;                    // consumer waves
@@ -564,7 +565,7 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
               acc[tr][tc][v] = gelu_by_definition<OUT_F32>(acc[tr][tc][v]);
-              if ((v & 1) == 1) __builtin_amdgcn_sched_barrier(0);
+              if (v % FENCE == FENCE - 1) __builtin_amdgcn_sched_barrier(0);
             }
         } else if (p.act == VENOM_ACT_GELU_TANH) {
 #pragma unroll
@@ -572,7 +573,7 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
               acc[tr][tc][v] = gelu_tanh_form(acc[tr][tc][v]);
-              if ((v & 1) == 1) __builtin_amdgcn_sched_barrier(0);
+              if (v % FENCE == FENCE - 1) __builtin_amdgcn_sched_barrier(0);
             }
         }
       };
@@ -697,13 +698,29 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
           finish(tr);
 #pragma unroll
           for (int tc = 0; tc < CT; ++tc) {
-            const int c = tc * 32 + (ln & 31);
+            if constexpr (CONS <= 4) {
+              // two rows of this lane's column leave as two columns of one row, half as many LDS writes: the pair of rows is
+              // rounded into a word, and an even lane takes the first row of its own and its neighbour's, an odd lane the second
+              const int c = tc * 32 + (ln & 30);
+              const uint32_t pick = ln & 1 ? 0x07060302u : 0x01000504u;   // bytes: 0-3 the neighbour's, 4-7 its own
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              const int r = 8 * (v >> 2) + 4 * (ln >> 5) + (v & 3);
-              const int sw = ((c >> 3) ^ (SWZ * ((r >> 2) & 1)));
-              *reinterpret_cast<_Float16*>(stg + r * SROW + sw * 16 + (c & 7) * 2) =
-                  (_Float16)acc[tr][tc][v];        // one rounding, nearest-even
+              for (int v = 0; v < 16; v += 2) {
+                const int r = 8 * (v >> 2) + 4 * (ln >> 5) + (v & 3) + (ln & 1);
+                const int sw = ((c >> 3) ^ (SWZ * ((r >> 2) & 1)));
+                const half2 rows = {(_Float16)acc[tr][tc][v], (_Float16)acc[tr][tc][v + 1]};   // one rounding, nearest-even
+                const uint32_t own = __builtin_bit_cast(uint32_t, rows);
+                const uint32_t other = __builtin_amdgcn_mov_dpp(own, 0xb1, 0xf, 0xf, true);    // lanes 1 0 3 2
+                *reinterpret_cast<uint32_t*>(stg + r * SROW + sw * 16 + (c & 7) * 2) = __builtin_amdgcn_perm(own, other, pick);
+              }
+            } else {
+              const int c = tc * 32 + (ln & 31);
+#pragma unroll
+              for (int v = 0; v < 16; ++v) {
+                const int r = 8 * (v >> 2) + 4 * (ln >> 5) + (v & 3);
+                const int sw = ((c >> 3) ^ (SWZ * ((r >> 2) & 1)));
+                *reinterpret_cast<_Float16*>(stg + r * SROW + sw * 16 + (c & 7) * 2) =
+                    (_Float16)acc[tr][tc][v];      // one rounding, nearest-even
+              }
             }
           }
 #pragma unroll
