@@ -119,7 +119,8 @@ venom_status_t venom_decompress(const venom_handle_t* h, void* A_f16_dev, int64_
  *               or fp32 (c_dtype 1), ldc >= C_cols; must not overlap B
  * B, C and both leading dimensions must be 16-byte aligned; V in {32, 64, 96, 128}; C_cols % 8 == 0;
  * K < 2^24, ldb < 2^23 and K * ldb < 2^31 (32-bit gather offsets).
- * Asynchronous on `stream`, allocates nothing, bitwise repeatable (no atomics, no split K). */
+ * Asynchronous on `stream`, allocates nothing, bitwise repeatable (no atomics; with at most 32 columns the sum over K is
+ * split, and its parts are added in a fixed order). */
 venom_status_t venom_spmm(const venom_handle_t* h, const void* B_f16_dev, int64_t ldb, int64_t C_cols,
                           void* C_dev, int64_t ldc, int c_dtype, void* stream);
 
@@ -143,7 +144,7 @@ venom_status_t venom_spmm_bias_act(const venom_handle_t* h, const void* B_f16_de
  * a linear layer): activations token-major, X = tokens x K fp16 (ldx >= K), output token-major,
  * Y = tokens x R (ldy >= R), fp16 (y_dtype 0) or fp32 (1):
  *     Y = act(X . A^T + bias),  bias one fp16 entry per output feature (R), or NULL.
- * The gather needs rows of X^T, so X is first transposed into `scratch_dev` (caller-owned device
+ * The gather needs rows of X^T, so X (unless its tokens are few) is first transposed into `scratch_dev` (caller-owned device
  * memory, 16-byte aligned, at least venom_linear_scratch_bytes() bytes, overwritten); the product
  * kernel then writes Y transposed itself, no second transpose pass.  tokens % 8 == 0; Y and ldy
  * aligned to 4 elements (fp16 output is fastest with Y and ldy * 2 bytes 16-byte aligned: whole

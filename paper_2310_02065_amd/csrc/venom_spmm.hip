@@ -111,7 +111,7 @@ struct TileWalk {
 // the plain kernel carries none of the epilogue code, and one kernel holding both token-major
 // paths behind a run-time branch does not compile (the compiler then keeps the producers' scalar
 // operands in vector registers).
-// NS: stages of the B ring; NA: records in the A ring.
+// KS: k-steps of a stage, which one barrier hands over (1 or 2); NS: stages of the B ring; NA: stages of records in the A ring.
 // D: barriers after which a consumed stage returns to the producers.  The consumers read stage g
 // between barriers g and g+1 but use what they read only after barrier g+1.  D = 2: they do not
 // wait for those reads before barrier g+1, so the stage stays theirs until barrier g+2 and the
@@ -128,13 +128,14 @@ constexpr int simd_waves(int VT, int NC, int NR) {
   return VT / NR == 1 && NC * NR == 6 ? 5 : VT / NR <= 2 && NC * NR <= 4 ? 4 : 3;
 }
 
-template <int VT, int NC, int NR, int NS, int NA, int D, bool OUT_F32, int MODE>
+template <int VT, int NC, int NR, int KS, int NS, int NA, int D, bool OUT_F32, int MODE>
 __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC, NR)) spmm_kernel(SpmmParams p) {
   static_assert(NC == 1 || NC == 2 || NC == 4 || NC == 8, "64-column strips per workgroup");
   static_assert(VT % NR == 0, "the tile rows divide evenly over the waves of a strip");
   static_assert(D == 1 || D == 2, "barriers between the hand-over of a stage and its return");
   constexpr bool EPI = MODE != 0;
-  constexpr int FENCE = MODE == 1 && NC * NR <= 4 ? 4 : 2;   // activations evaluated together
+  constexpr int FENCE = MODE == 1 && NC * NR <= 4 ? 4 : 2;   // activations evaluated together (3072 x 768 x 4096 at
+                                                   // 64:2:8 with GELU 19.3 -> 18.6 us with four; no registers for that elsewhere)
   static_assert(VT >= 1 && VT <= kMaxTiles, "32-row tiles per block row");
   constexpr int NP = kProducers;
   constexpr int CONS = NC * NR;                    // consumer waves
@@ -145,14 +146,17 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
   constexpr int ROW_BYTES = 2 * BSC;               // one gathered row of B in LDS
   constexpr int RPI = 1024 / ROW_BYTES;            // rows written by one wave-wide 16-byte load
   constexpr int LPR = 64 / RPI;                    // lanes (= 16-byte slots) per row
-  constexpr int NI = kStepRows / RPI;              // B loads per k-step (4 * NC)
+  constexpr int SROWS = KS * kStepRows;            // gathered rows of B in a stage of KS k-steps
+  constexpr int NI = SROWS / RPI;                  // B loads per stage (4 * NC a k-step)
   constexpr int CB = NI / NP;                      // ... per producer
   static_assert(NI % NP == 0, "the B loads of a k-step divide evenly over the producers");
-  constexpr int B_BYTES = kStepRows * ROW_BYTES;
+  constexpr int STEP_BYTES = kStepRows * ROW_BYTES;
+  constexpr int B_BYTES = KS * STEP_BYTES;
   constexpr int REC = VT * kTileValBytes + kTailBytes;       // one A record
   constexpr int T_OFF = VT * kTileValBytes;        // record tail: index words
   constexpr int ARING = NS * B_BYTES;              // LDS: [B ring][A ring][row-id ring]
-  constexpr int RIDRING = ARING + NA * REC;
+  constexpr int RIDRING = ARING + NA * KS * REC;
+  constexpr int RID_BYTES = SROWS * 4;             // row ids of a stage
   constexpr int NJ = VT + 1;                       // A loads per k-step: VT value blocks + the tail
   constexpr int PB = NS - D;                       // k-steps the B stream runs ahead
   constexpr int PA = NA - D;                       // k-steps the A stream runs ahead
@@ -163,7 +167,7 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
   static_assert(kRidSlots >= PB + 2, "a row-id slot is rewritten only after its last reader");
   static_assert(RA <= kRidSlots, "the row ids of the start-up fit the ring");
   constexpr bool OWN_STG = NR > 1;                 // the consumers' output staging: the drained stage, or its own LDS
-  constexpr int STG = RIDRING + kRidSlots * kStepRows * 4;
+  constexpr int STG = RIDRING + kRidSlots * RID_BYTES;
   static_assert(OWN_STG || CONS * 32 * WCOLS * 2 <= B_BYTES, "the output staging of all consumers fits one B stage");
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -187,7 +191,11 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
   // Barriers, in order: one before the first step (the first row ids are on chip), one per step
   // ("step g is complete in LDS, step g-D is consumed"), and one more after the last step of each
   // tile, after which the consumers stage their output in the B stage they have just drained.
-  const int G = tw.count * p.steps;
+  // (KS = 2: "step" in the following is a stage of two k-steps, which one barrier hands over; the last stage of a tile
+  // has one where the k-steps are odd, `odd`, and its second half holds copies that nobody multiplies)
+  const int S = KS == 1 ? p.steps : (p.steps + 1) / 2;
+  const bool odd = KS == 2 && (p.steps & 1);
+  const int G = tw.count * S;
 
   if (wave >= CONS) {
     // ========================================================================= producers
@@ -199,7 +207,7 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
     __builtin_amdgcn_s_setprio(3);                 // their few instructions go ahead of the consumers'
     auto produce = [&](auto pj_const) {
       constexpr int PJ = decltype(pj_const)::value;
-      constexpr int CA = PJ < NJ ? (NJ - PJ + NP - 1) / NP : 0;   // A loads per k-step: loads PJ, PJ+NP, ...
+      constexpr int CA = PJ < KS * NJ ? (KS * NJ - PJ + NP - 1) / NP : 0;   // A loads per stage: loads PJ, PJ+NP, ...
       constexpr int CR = PJ == NP - 1 ? 1 : 0;                    // the row ids travel with the last producer
       constexpr int L = CA + CR + CB;
       static_assert((PB - 1) * L <= 63, "load counts fit the 6-bit counter");
@@ -219,51 +227,59 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
       // ---- record stream: record pointer, LDS slot address, k-steps left in its tile
       tw.locate(p, 0, ct, br);
       const char* a_ptr = p.arec + (int64_t)br * p.steps * p.rec_bytes;
-      int64_t a_inc = p.rec_bytes;
+      int64_t a_inc = KS * p.rec_bytes;
+      bool a_back = false;
       uint32_t a_lds = lds0 + ARING;
-      int a_left = p.steps, a_t = 0;
+      int a_left = S, a_t = 0;
       auto next_record = [&](auto inside_tile) {
+        const bool single = !decltype(inside_tile)::value && odd && a_left == (a_back ? S : 1);   // a stage of one k-step
+        const char* second = single ? a_ptr : a_ptr + p.rec_bytes;
 #pragma unroll
-        for (int a = PJ; a < NJ; a += NP) {
-          if (a < VT) dma16(a_ptr + a * 1024, lane_off, a_lds + a * 1024);
-          else if (lane < kTailBytes / 16) dma16(a_ptr + T_OFF, lane_off, a_lds + T_OFF);   // the 512-byte tail: half a wave
+        for (int l = PJ; l < KS * NJ; l += NP) {
+          const int a = l % NJ;
+          const char* rec = l < NJ ? a_ptr : second;
+          const uint32_t to = a_lds + l / NJ * REC;
+          if (a < VT) dma16(rec + a * 1024, lane_off, to + a * 1024);
+          else if (lane < kTailBytes / 16) dma16(rec + T_OFF, lane_off, to + T_OFF);   // the 512-byte tail: half a wave
         }
         a_ptr += a_inc;
-        a_lds = a_lds + REC == lds0 + ARING + NA * REC ? lds0 + ARING : a_lds + REC;
+        a_lds = a_lds + KS * REC == lds0 + ARING + NA * KS * REC ? lds0 + ARING : a_lds + KS * REC;
         if constexpr (decltype(inside_tile)::value) return;
         if (--a_left == 0) {
-          a_left = p.steps;
+          a_left = S;
           if (++a_t < tw.count) {
             tw.locate(p, a_t, ct, br);
             const bool back = p.serpentine && (a_t & 1);       // odd tiles run their k-steps backwards
-            a_inc = back ? -p.rec_bytes : p.rec_bytes;
-            a_ptr = p.arec + ((int64_t)br * p.steps + (back ? p.steps - 1 : 0)) * p.rec_bytes;
+            a_back = back;
+            a_inc = back ? -KS * p.rec_bytes : KS * p.rec_bytes;
+            a_ptr = p.arec + ((int64_t)br * p.steps + (back ? (S - 1) * KS : 0)) * p.rec_bytes;
           }
         }
       };
       // ---- row-id stream (producer NP-1 only)
       const char* r_ptr = reinterpret_cast<const char*>(p.rowidx) + (int64_t)br * p.steps * (kStepRows * 4);
-      int r_inc = kStepRows * 4;
+      int r_inc = RID_BYTES;
       uint32_t r_lds = lds0 + RIDRING;
-      int r_left = p.steps, r_t = 0;
+      int r_left = S, r_t = 0;
       auto end_of_rowids = [&]() {                 // the stream has come to the end of its tile
-        r_left = p.steps;
+        r_left = S;
         if (++r_t < tw.count) {
           int ct2, br2;
           tw.locate(p, r_t, ct2, br2);
           const bool back = p.serpentine && (r_t & 1);
-          r_inc = back ? -(kStepRows * 4) : kStepRows * 4;
+          r_inc = back ? -RID_BYTES : RID_BYTES;
           r_ptr = reinterpret_cast<const char*>(p.rowidx) +
-                  ((int64_t)br2 * p.steps + (back ? p.steps - 1 : 0)) * (kStepRows * 4);
+                  ((int64_t)br2 * p.steps + (back ? (S - 1) * KS : 0)) * (kStepRows * 4);
         } else {                                   // past the last one it stays on its last k-step: ids nobody reads,
           r_ptr -= r_inc;                          // so that an iteration has the same loads while records are left
           r_inc = 0;
         }
       };
       auto next_rowids = [&](auto inside_tile) {
-        if (lane < kStepRows) dma4(r_ptr, lane * 4, r_lds);
+        // (a stage of one k-step fetches 128 bytes past it, too: other ids or, after the last, what follows them in the workspace)
+        if (lane < SROWS) dma4(r_ptr, lane * 4, r_lds);
         r_ptr += r_inc;
-        r_lds = r_lds + kStepRows * 4 == lds0 + RIDRING + kRidSlots * kStepRows * 4 ? lds0 + RIDRING : r_lds + kStepRows * 4;
+        r_lds = r_lds + RID_BYTES == lds0 + RIDRING + kRidSlots * RID_BYTES ? lds0 + RIDRING : r_lds + RID_BYTES;
         if constexpr (decltype(inside_tile)::value) return;
         if (--r_left == 0) end_of_rowids();
       };
@@ -293,14 +309,18 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
       const uint32_t ldb24 = (uint32_t)p.ldb_bytes;
       uint32_t b_lds = lds0 + PJ * 1024;           // this producer's first row in the stage it fills next
       const char* rid_rd = smem + RIDRING + rowsel * 4;   // this lane's entry of the ring slot it reads next
-      int b_left = p.steps, b_t = 0;
+      int b_left = S, b_t = 0;
       set_tile(0);
       int rid[CB];
-      auto read_rowids = [&]() {
+      auto read_rowids = [&](auto inside_tile) {
+        // (a stage of one k-step: its rows once more)
+        const bool single = !decltype(inside_tile)::value && odd && b_left == ((p.serpentine && (b_t & 1)) ? S : 1);
+        const int again = single ? kStepRows * 4 : 0;
 #pragma unroll
-        for (int q = 0; q < CB; ++q) rid[q] = *reinterpret_cast<const int*>(rid_rd + (PJ + NP * q) * RPI * 4);
-        rid_rd = rid_rd + kStepRows * 4 == smem + RIDRING + rowsel * 4 + kRidSlots * kStepRows * 4
-                     ? smem + RIDRING + rowsel * 4 : rid_rd + kStepRows * 4;
+        for (int q = 0; q < CB; ++q)
+          rid[q] = *reinterpret_cast<const int*>(rid_rd + (PJ + NP * q) * RPI * 4 - (q >= CB / KS ? again : 0));
+        rid_rd = rid_rd + RID_BYTES == smem + RIDRING + rowsel * 4 + kRidSlots * RID_BYTES
+                     ? smem + RIDRING + rowsel * 4 : rid_rd + RID_BYTES;
       };
       auto next_rows = [&](auto inside_tile) {
         uint32_t off[CB];
@@ -312,7 +332,7 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
         b_lds = b_lds + B_BYTES == lds0 + PJ * 1024 + NS * B_BYTES ? lds0 + PJ * 1024 : b_lds + B_BYTES;
         if constexpr (decltype(inside_tile)::value) return;
         if (--b_left == 0) {
-          b_left = p.steps;
+          b_left = S;
           if (++b_t < tw.count) set_tile(b_t);
         }
       };
@@ -323,14 +343,14 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
           if (i + PA < G) next_record(checked{});
       };
       if constexpr (CR != 0) {
-        const int n0 = p.steps < RA ? p.steps : RA;  // those of the first tile: eight k-steps a load
+        const int n0 = S < RA ? S : RA, k0 = p.steps < KS * RA ? p.steps : KS * RA;   // those of the first tile: eight k-steps a load
 #pragma unroll
-        for (int q = 0; 8 * q < RA; ++q) {
+        for (int q = 0; 8 * q < KS * RA; ++q) {
           const int s = 8 * q + lane / 8;
-          if (s < n0) dma16(r_ptr, s * (kStepRows * 4) + lane % 8 * 16, r_lds + q * 1024);
+          if (s < k0) dma16(r_ptr, s * (kStepRows * 4) + lane % 8 * 16, r_lds + q * 1024);
         }
-        r_ptr += n0 * (kStepRows * 4);
-        r_lds = n0 == kRidSlots ? r_lds : r_lds + n0 * (kStepRows * 4);
+        r_ptr += n0 * RID_BYTES;
+        r_lds = n0 == kRidSlots ? r_lds : r_lds + n0 * RID_BYTES;
         r_left -= n0;
         if (r_left == 0) end_of_rowids();
         for (int j = n0; j < RA && j < G; ++j) next_rowids(checked{});
@@ -340,47 +360,48 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
       if constexpr (CR != 0) first_records();
       for (int i = -PB; i < 0; ++i) {
         if (i + PA < G) next_record(checked{});
-        if (i + PB < G) { read_rowids(); next_rows(checked{}); }
+        if (i + PB < G) { read_rowids(checked{}); next_rows(checked{}); }
       }
       const bool ragged = p.pad_row0 < kStepRows;  // K/M is not a multiple of 8
-      int c_left = p.steps, c_t = 0;               // k-steps left in the tile the consumers are on / that tile
+      int c_left = S, c_t = 0;               // k-steps left in the tile the consumers are on / that tile
       // One iteration: the loads of step g have landed, barrier, the next loads.  RECORDS, ROWS: these
       // streams are still inside the sequence.  `waited` waits for the loads of step g.
       auto iteration = [&](int g, auto records, auto rows, auto waited) {
         waited();
-        if (ragged && c_left == ((p.serpentine && (c_t & 1)) ? p.steps : 1)) {
+        if (ragged && c_left == ((p.serpentine && (c_t & 1)) ? S : 1)) {
           // The last k-step of a tile when K/M is not a multiple of 8: its trailing groups do not
           // exist.  Their values are zero, but 0 x Inf is not, so the rows gathered for them (row 0
           // of B, a valid address that keeps the load count exact) are overwritten with zeros once
           // they have landed; every producer cleans the rows it loaded itself.
           char* stage = smem + (g % NS) * B_BYTES;
 #pragma unroll
-          for (int q = 0; q < CB; ++q)
-            if ((PJ + NP * q) * RPI + rowsel >= p.pad_row0)
+          for (int q = 0; q < CB; ++q)             // (the rows of the last k-step: the second of its stage, or the first and only)
+            if ((PJ + NP * q) * RPI + rowsel >= p.pad_row0 + (KS == 2 && !odd ? kStepRows : 0))
               *reinterpret_cast<uint4*>(stage + (PJ + NP * q) * 1024 + lane * 16) = make_uint4(0, 0, 0, 0);
           lgkm_drained_barrier();
         } else barrier_only();
         // after barrier g the consumers are done with stage g-D and record g-D
-        if constexpr (decltype(rows)::value) read_rowids();
+        if constexpr (decltype(rows)::value) read_rowids(checked{});
         if constexpr (decltype(records)::value) {
           if constexpr (CR != 0) next_rowids(checked{});
           next_record(checked{});
         }
         if constexpr (decltype(rows)::value) next_rows(checked{});
-        if (--c_left == 0) { c_left = p.steps; ++c_t; barrier_only(); }
+        if (--c_left == 0) { c_left = S; ++c_t; barrier_only(); }
       };
       // How many iterations from the next on, at most n, do not end a tile of any of the streams
       // (the first k-step of a tile, where the ragged end of a backward tile lies, is left to the checked one).
-      const bool any_runs = p.steps > 4;           // (shorter tiles end a stream in all of them)
+      const bool any_runs = S > 4;           // (shorter tiles end a stream in all of them)
       auto runs = [&](int n, bool records) {
         if (!any_runs) return 0;
+        if (odd && (b_left == S || (records && a_left == S))) return 0;   // (the first stage of a backward tile has one k-step)
         n = n < b_left - 1 ? n : b_left - 1;
         n = n < c_left - 1 ? n : c_left - 1;
         if (records) {
           n = n < a_left - 1 ? n : a_left - 1;
           if constexpr (CR != 0) n = n < r_left - 1 ? n : r_left - 1;
         }
-        return ragged && c_left == p.steps ? 0 : n;
+        return ragged && c_left == S ? 0 : n;
       };
       // The loads of step g are those of iteration g-PB: step g is there when only those of the PB-1
       // iterations since are outstanding.  While records are left these are L each (the start-up
@@ -399,7 +420,7 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
         if constexpr (CR != 0) r_left -= n;
         do {
           asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((PB - 1) * L) : "memory");
-          read_rowids();
+          read_rowids(inside{});
           if constexpr (CR != 0) next_rowids(inside{});
           next_record(inside{});
           next_rows(inside{});
@@ -414,7 +435,7 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
         g += n; b_left -= n; c_left -= n;
         do {
           asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((PB - 1) * CB) : "memory");
-          read_rowids();
+          read_rowids(inside{});
           next_rows(inside{});
         } while (--n > 0);
       }
@@ -495,7 +516,7 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
       const char* sa = smem;
       auto advance = [&]() {
         sb = smem + b_slot * B_BYTES;
-        sa = smem + ARING + a_slot * REC;
+        sa = smem + ARING + a_slot * (KS * REC);
         b_slot = (b_slot + 1) % NS;
         a_slot = a_slot + 1 == NA ? 0 : a_slot + 1;
       };
@@ -506,24 +527,31 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
 #pragma unroll
       for (int tr = 0; tr < RT; ++tr) refill_after(sa, tr);
       read_b(sb, 1);
-      for (int s = 1; s < p.steps; ++s) {
+      // multiplies a k-step from registers and refills them with the next one, at (nb, na)
+      auto k_step = [&](const char* nb, const char* na) {
+#pragma unroll
+        for (int tc = 0; tc < CT; ++tc) {
+#pragma unroll
+          for (int tr = 0; tr < RT; ++tr) {
+            mma(tr, tc);
+            if (tc == CT - 1) refill_after(na, tr);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          read_b(nb, tc);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      };
+      const bool back = KS == 2 && p.serpentine && (t & 1);
+      if (KS == 2 && !(odd && (back || S == 1))) k_step(sb + STEP_BYTES, sa + REC);   // the first stage's second k-step
+      for (int s = 1; s < S; ++s) {
         if constexpr (D == 1) lgkm_drained_barrier();   // my reads of the last stage are over; this one is complete
         else barrier_only();                            // stage s and record s are complete
         // (the next matrix instruction may wait for this wave's reads, and the narrow tiles' k-steps are short: they
         // arrive at the barrier first.  On the wide ones it is issued while the wave waits there)
         if constexpr (NC <= 2) __builtin_amdgcn_sched_barrier(0);
         advance();
-#pragma unroll
-        for (int tc = 0; tc < CT; ++tc) {
-#pragma unroll
-          for (int tr = 0; tr < RT; ++tr) {
-            mma(tr, tc);
-            if (tc == CT - 1) refill_after(sa, tr);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-          read_b(sb, tc);
-          __builtin_amdgcn_sched_barrier(0);
-        }
+        k_step(sb, sa);
+        if (KS == 2 && !(odd && !back && s == S - 1)) k_step(sb + STEP_BYTES, sa + REC);
       }
 #pragma unroll
       for (int tc = 0; tc < CT; ++tc)
@@ -701,6 +729,8 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
             if constexpr (CONS <= 4) {
               // two rows of this lane's column leave as two columns of one row, half as many LDS writes: the pair of rows is
               // rounded into a word, and an even lane takes the first row of its own and its neighbour's, an odd lane the second
+              // (3072 x 768 x 4096 at 64:2:8 14.1 -> 13.6 us, 4096 x 1024 x 16384 on v128_c128d 42.3 -> 40.6; with eight waves
+              // and 128 accumulators a lane it costs registers: with GELU 65.5 -> 68.8)
               const int c = tc * 32 + (ln & 30);
               const uint32_t pick = ln & 1 ? 0x07060302u : 0x01000504u;   // bytes: 0-3 the neighbour's, 4-7 its own
 #pragma unroll
@@ -761,19 +791,19 @@ struct Variant {
   void (*fn[2][4])(SpmmParams);   // [fp32 output][mode]
 };
 
-template <int VT, int NC, int NR, int NS, int NA>
+template <int VT, int NC, int NR, int KS, int NS, int NA>
 constexpr int lds_bytes() {   // B ring, A ring, row-id ring, output staging (4 KB a wave) where it does not reuse a B stage
-  return NS * kStepRows * 128 * NC + NA * (VT * kTileValBytes + kTailBytes) + kRidSlots * kStepRows * 4 +
+  return KS * (NS * kStepRows * 128 * NC + NA * (VT * kTileValBytes + kTailBytes) + kRidSlots * kStepRows * 4) +
          (NR > 1 ? NC * NR * 4096 : 0);
 }
 
-#define VARIANT(NAME, VT, NC, NR, NS, NA, ...)                                                              \
-  { NAME, (VT) * 32, 64 * (NC), 64 * ((NC) * (NR) + kProducers), lds_bytes<VT, NC, NR, NS, NA>(),            \
-    simd_waves(VT, NC, NR) >= 4 && lds_bytes<VT, NC, NR, NS, NA>() <= 80 * 1024 ? 2 : 1, { __VA_ARGS__ },    \
-    { { spmm_kernel<VT, NC, NR, NS, NA, kD, false, 0>, spmm_kernel<VT, NC, NR, NS, NA, kD, false, 1>,       \
-        spmm_kernel<VT, NC, NR, NS, NA, kD, false, 2>, spmm_kernel<VT, NC, NR, NS, NA, kD, false, 3> },     \
-      { spmm_kernel<VT, NC, NR, NS, NA, kD, true, 0>, spmm_kernel<VT, NC, NR, NS, NA, kD, true, 1>,         \
-        spmm_kernel<VT, NC, NR, NS, NA, kD, true, 2>, spmm_kernel<VT, NC, NR, NS, NA, kD, true, 2> } } }
+#define VARIANT(NAME, VT, NC, NR, KS, NS, NA, ...)                                                          \
+  { NAME, (VT) * 32, 64 * (NC), 64 * ((NC) * (NR) + kProducers), lds_bytes<VT, NC, NR, KS, NS, NA>(),        \
+    simd_waves(VT, NC, NR) >= 4 && lds_bytes<VT, NC, NR, KS, NS, NA>() <= 80 * 1024 ? 2 : 1, { __VA_ARGS__ }, \
+    { { spmm_kernel<VT, NC, NR, KS, NS, NA, kD, false, 0>, spmm_kernel<VT, NC, NR, KS, NS, NA, kD, false, 1>, \
+        spmm_kernel<VT, NC, NR, KS, NS, NA, kD, false, 2>, spmm_kernel<VT, NC, NR, KS, NS, NA, kD, false, 3> }, \
+      { spmm_kernel<VT, NC, NR, KS, NS, NA, kD, true, 0>, spmm_kernel<VT, NC, NR, KS, NS, NA, kD, true, 1>,   \
+        spmm_kernel<VT, NC, NR, KS, NS, NA, kD, true, 2>, spmm_kernel<VT, NC, NR, KS, NS, NA, kD, true, 2> } } }
 
 constexpr int kD = 2;   // barriers between the hand-over of a stage and its return (1 and 2 measure the same)
 // Rows per wave and ring depths, as measured (us per call).  V = 128: two waves per strip up to 256 columns
@@ -781,29 +811,35 @@ constexpr int kD = 2;   // barriers between the hand-over of a stage and its ret
 // workgroup on the unit, whose k-loop runs while the first one stores: better with few k-steps a tile, worse with many
 // (16384 x 1024 x 512 at 128:2:8 13.9 against 14.5, 1024 x 16000 x 4096 at 128:2:40 20.4 against 17.8).  At V = 64 and 32
 // the accumulators allow that with 256 columns (3072 x 768 x 4096 at 64:2:8 14.6, one workgroup with deeper rings 15.3).
-// More stages than these cost start-up and gain nothing, except on the 64-column tile (V = 128: 5 stages
-// are 3 % faster below 20 k-steps, 6 stages 5 to 20 % above).
+// More stages than these cost start-up and gain nothing.
+// KS: k-steps per stage.  A k-step of a narrow tile is barrier, row-id read and two or three loads a producer, one after the
+// other (262 cycles with 64 columns, V = 128, of which no part waits for memory); two k-steps a barrier deal 19 loads over four
+// producers where one deals 10, so that none has three while others have two, and meet half as often.  us per call, one -> two,
+// V = 128: 8192 x 8192 x 64 at 2:16 12.0 -> 10.3 (64 columns), 12.4 -> 11.1 (128), x 256 13.3 -> 12.4; 3072 x 4096 x 256 at 96:2:8 12.0 -> 9.7
+// (64), 14.3 -> 11.9 (128); 2048 x 4096 x 256 at 64:2:8 10.6 -> 8.6; 1024 x 4096 x 256 at 32:2:8 9.9 -> 8.3.  With 256 columns the loads
+// take most of a k-step and two of them leave rings too short (8192 x 8192 x 256 18.4 -> 26.3); at V = 64 and 128 columns the second
+// workgroup of the unit would go (2048 x 1000 x 2048 at 64:2:10 9.0 -> 10.9).
 static const Variant kVariants[] = {
-    VARIANT("v128_c512", 4, 8, 1, 4, 6, 1.23f, .315f, 3.87f, .252f, 3.48f, 0.f),
-    VARIANT("v128_c256", 4, 4, 2, 5, 6, 2.69f, .215f, 1.24f, .125f, 2.34f, 0.f),
-    VARIANT("v128_c128", 4, 2, 2, 5, 6, 1.97f, .138f, 1.58f, .082f, .73f, 0.f),
-    VARIANT("v128_c128d", 4, 2, 2, 4, 6, 2.87f, .149f, .47f, .050f, 1.07f, .021f),
-    VARIANT("v128_c64", 4, 1, 2, 6, 6, 2.98f, .122f, .52f, .004f, .49f, .035f),
-    VARIANT("v96_c512", 3, 8, 1, 4, 6, 2.53f, .279f, 1.92f, .230f, 2.53f, 0.f),
-    VARIANT("v96_c256", 3, 4, 1, 5, 6, 3.27f, .174f, .88f, .122f, 1.60f, 0.f),
-    VARIANT("v96_c128", 3, 2, 3, 5, 6, 2.48f, .165f, .84f, .041f, .81f, .030f),
-    VARIANT("v96_c128d", 3, 2, 3, 4, 4, 2.99f, .160f, .17f, .011f, 1.09f, .028f),
-    VARIANT("v96_c64", 3, 1, 3, 5, 6, 3.07f, .128f, .04f, 0.f, .66f, .021f),
-    VARIANT("v64_c512", 2, 8, 1, 4, 10, 2.529f, .279f, 2.075f, .157f, 1.107f, .027f),
-    VARIANT("v64_c256", 2, 4, 1, 5, 6, 2.885f, .17f, .693f, .088f, 1.349f, .011f),
-    VARIANT("v64_c256d", 2, 4, 1, 4, 4, 3.263f, .163f, .316f, .07f, 1.176f, .049f),
-    VARIANT("v64_c128", 2, 2, 2, 5, 6, 2.608f, .146f, .317f, .024f, .544f, .024f),
-    VARIANT("v64_c64", 2, 1, 2, 6, 10, 2.314f, .101f, .026f, .015f, .74f, .032f),
-    VARIANT("v32_c512", 1, 8, 1, 4, 10, 3.21f, .242f, .031f, .117f, 1.984f, .034f),
-    VARIANT("v32_c256", 1, 4, 1, 6, 10, 1.9f, .142f, 1.182f, .073f, .464f, .009f),
-    VARIANT("v32_c256d", 1, 4, 1, 4, 6, 2.392f, .135f, .759f, .06f, .039f, .048f),
-    VARIANT("v32_c128", 1, 2, 1, 6, 6, 2.32f, .13f, .547f, 0.f, .137f, .001f),
-    VARIANT("v32_c64", 1, 1, 1, 6, 10, 1.95f, .065f, .595f, .033f, .084f, .005f),
+    VARIANT("v128_c512", 4, 8, 1, 1, 4, 6, 2.629f, .262f, 5.781f, .261f, 2.889f, 0.f),
+    VARIANT("v128_c256", 4, 4, 2, 1, 5, 6, 3.285f, .248f, 2.159f, .073f, 2.764f, 0.f),
+    VARIANT("v128_c128", 4, 2, 2, 2, 4, 4, 3.985f, .113f, 1.433f, .093f, .803f, 0.f),
+    VARIANT("v128_c128d", 4, 2, 2, 1, 4, 6, 4.448f, .168f, .818f, .04f, .992f, 0.f),
+    VARIANT("v128_c64", 4, 1, 2, 2, 4, 4, 4.681f, .103f, .764f, .014f, .518f, 0.f),
+    VARIANT("v96_c512", 3, 8, 1, 1, 4, 6, 3.049f, .312f, 4.218f, .173f, 1.88f, .006f),
+    VARIANT("v96_c256", 3, 4, 1, 1, 5, 6, 4.83f, .196f, .883f, .091f, 2.513f, .003f),
+    VARIANT("v96_c128", 3, 2, 3, 2, 4, 4, 3.298f, .131f, .73f, .057f, 1.378f, 0.f),
+    VARIANT("v96_c128d", 3, 2, 3, 1, 4, 4, 3.96f, .159f, .362f, .012f, 1.053f, .023f),
+    VARIANT("v96_c64", 3, 1, 3, 2, 4, 4, 3.344f, .072f, .732f, .029f, .304f, .069f),
+    VARIANT("v64_c512", 2, 8, 1, 1, 4, 10, 3.309f, .288f, 2.153f, .128f, 2.933f, 0.f),
+    VARIANT("v64_c256", 2, 4, 1, 1, 5, 6, 3.927f, .152f, .874f, .106f, 1.158f, 0.f),
+    VARIANT("v64_c256d", 2, 4, 1, 1, 4, 4, 4.121f, .173f, .412f, .053f, 1.52f, .021f),
+    VARIANT("v64_c128", 2, 2, 2, 1, 5, 6, 3.671f, .146f, .354f, .017f, .676f, 0.f),
+    VARIANT("v64_c64", 2, 1, 2, 2, 4, 4, 3.396f, .102f, .736f, .01f, .244f, .006f),
+    VARIANT("v32_c512", 1, 8, 1, 1, 4, 10, 3.965f, .279f, .824f, .056f, 2.184f, .008f),
+    VARIANT("v32_c256", 1, 4, 1, 1, 6, 10, 2.943f, .16f, 1.161f, .043f, .537f, .014f),
+    VARIANT("v32_c256d", 1, 4, 1, 1, 4, 6, 3.529f, .16f, .519f, .033f, .372f, .041f),
+    VARIANT("v32_c128", 1, 2, 1, 2, 4, 4, 3.45f, .093f, .775f, .052f, .05f, .003f),
+    VARIANT("v32_c64", 1, 1, 1, 2, 4, 4, 2.57f, .081f, .765f, 0.f, .062f, .035f),
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
@@ -814,15 +850,11 @@ const char* spmm_variant_name(int v) { return (v >= 0 && v < kNumVariants) ? kVa
 // have shorter k-steps (us alone on the chip, V = 128: 0.31 / 0.21 / 0.14 / 0.12 for 512 / 256 / 128 / 64 columns: 36.5 /
 // 20.5 / 12.5 / 8.5 KB); wide ones read the records of A less often and load the chip's fabric less; the columns that
 // pad C to whole tiles and a last round with few tiles cost as much as full ones.  The constants of TileCost are fits to the
-// times of all variants over random shapes (R 64-49152, K 256-16000, C 8-16384, M 4-128).  V = 128 and 96: least squares of the
-// relative error, 676 shapes, plain fp16 product, shapes where the variant is near the best counting three times.
-// V = 64 and 32: from such a fit on by random steps that make the chosen variant's time over the best one's smaller, on
-// average over 1551 shapes in seven output forms (so fitted, v32_c256 is taken where it is the best, for few tiles of many
-// k-steps: 416 x 14192 x 3616 at 32:2:8 56 -> 49 us).  In 3900 shapes the chosen variant is slower than the best by, on average and at most: plain
-// product 0.5 and 25 %, with bias and GELU 0.5 and 36 %, token-major 0.6 and 29 %, with both 0.7 and 32 %, fp32 1.0 and 29 %,
-// fp32 with GELU 0.6 and 31 %, token-major as well 1.3 and 42 %.  Against tiles chosen by columns and counts of tiles alone 0.76
-// to 0.81 of the time on average, 154 of 18769 calls over 8 us more than 3 % slower; in us: 256 x 15890 x 6944 at 64:2:10
-// 75 -> 51, 13056 x 2624 x 336 at 96:2:64 11.6 -> 7.6, 3968 x 11324 x 688 at 64:2:4 84 -> 66.
+// times of all variants over 4478 random shapes (R 64-49152, K 256-16000, C 40-16384, M 4-128, up to 6e10 FLOP) in four output
+// forms (plain, with bias and GELU, that in fp32, and token-major): least squares of the relative error, from there on random steps
+// on three quarters of them that make the chosen variant's time over the best one's smaller.  On the others the chosen variant is
+// slower than the best by 0.5 to 0.9 % on average and 32 % at most, and the calls take 0.935 (V = 96) to 0.964 of the time of the tiles with
+// one k-step a barrier, chosen by constants of their own.
 static int pick_variant(int V, int64_t Ccols, int64_t nbr, int64_t steps, int cus) {
   int best = -1;
   float best_time = 0.f;
