@@ -90,7 +90,7 @@ int compute_units();
 // The same for at most 32 columns (venom_skinny.hip), where skinny_product or skinny_layer says so.  in_place: src is X, tokens x K,
 // else B; token_major: as above.
 bool skinny_product(const venom_handle& h, int64_t ld, int64_t cols, int cus);
-bool skinny_layer(const venom_handle& h, int64_t ldx, int64_t tokens, int cus);
+bool skinny_layer(const venom_handle& h, const void* X, int64_t ldx, int64_t tokens, const void* Y, int64_t ldy, int dtype, int cus);
 venom_status_t launch_skinny(const venom_handle& h, const void* src, int64_t ld, int64_t cols, const void* bias, int act, void* out,
                              int64_t ldo, int dtype, bool in_place, bool token_major, int cus, hipStream_t st);
 // register-only loop of 2:4 matrix instructions, for the measured instruction peak (grid = one workgroup of 8 waves per

@@ -383,8 +383,17 @@ static int layer_form(const Layout& L, int64_t ldx, int64_t tokens, int M, int c
   return pair < 1.05f * first ? kPair : -1;
 }
 
-bool skinny_layer(const venom_handle& h, int64_t ldx, int64_t tokens, int cus) {
-  return layer_form(h.lay, ldx, tokens, h.M, cus) >= 0;
+static bool overlap(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + (uintptr_t)b_bytes && y < x + (uintptr_t)a_bytes;
+}
+
+// An output over X stays with the transposition, which has read all of X before the product starts: a workgroup here reads
+// every column of X to the end of its run, when others have long stored their features.  From the first byte to the last, gaps
+// between rows included (X and Y side by side in one buffer: transposed, as if they met).
+bool skinny_layer(const venom_handle& h, const void* X, int64_t ldx, int64_t tokens, const void* Y, int64_t ldy, int dtype, int cus) {
+  if (layer_form(h.lay, ldx, tokens, h.M, cus) < 0) return false;
+  return !overlap(X, 2 * ((tokens - 1) * ldx + h.K), Y, (dtype == 1 ? 4 : 2) * ((tokens - 1) * ldy + h.R));
 }
 
 venom_status_t launch_skinny(const venom_handle& h, const void* src, int64_t ld, int64_t cols, const void* bias, int act, void* out,
