@@ -337,10 +337,11 @@ static void (*skinny_of(int form, int xj, bool f32))(SkinnyParams) {
   return xj == 8 ? skinny_of<VT, kPair, 8>(f32) : skinny_of<VT, kPair, 16>(f32);
 }
 
-// Whether the kernel can serve: sizes, and 32-bit offsets into B or X
+// Whether the kernel can serve: sizes, 32-bit offsets into B or X, and a launch of fewer than 2^32 threads, 512 for each tile at most
+// (spmm_kernel's grid does not grow with the matrix)
 static bool skinny_can(const Layout& L, int64_t ld, int64_t cols, bool tokens) {
   if (!L.packed || L.R == 0 || L.steps == 0 || cols < 1 || cols > kSkinnyCols) return false;
-  if (L.K >= (int64_t)1 << 24 || L.Rbp * L.vt > (int64_t)1 << 30 || ld >= (int64_t)1 << 31) return false;
+  if (L.K >= (int64_t)1 << 24 || L.Rbp * L.vt >= (int64_t)1 << 23 || ld >= (int64_t)1 << 31) return false;
   return 2 * (tokens ? (cols - 1) * ld + L.K : (L.K - 1) * ld + cols) < (int64_t)1 << 32;
 }
 

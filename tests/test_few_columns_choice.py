@@ -20,3 +20,8 @@ def test_an_output_over_the_activations_is_not_written_while_they_are_read(R, K,
     assert in_place(X0 + x_bytes) and in_place(X0 - y_bytes)                       # end to end
     for y in (X0, X0 + x_bytes - 2, X0 - y_bytes + 2, X0 + x_bytes // 2, X0 - y_bytes // 2):
         assert not in_place(y), y - X0
+
+
+def test_more_rows_than_a_launch_has_threads_for_are_transposed_first():
+    # 2^31 rows, 2^24 packed block rows: pairs of them, 512 threads each, are 2^32
+    assert not layer_reads_in_place(host_handle(1 << 31, 36, 1 << 16, 4), X0, 36, 8, X0 << 8, 1 << 31)
