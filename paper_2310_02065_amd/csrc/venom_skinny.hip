@@ -102,12 +102,16 @@ __global__ void __launch_bounds__(NP * GB * 64, 2) skinny_kernel(SkinnyParams p)
       xlds[j] = in ? tok * pitch + c * 16 : p.cols * pitch;
     }
   } else xoff[0] = (lane & 3) * 8 < p.cols ? (lane & 3) * 16 : 0u;   // (columns past the last: any others, never stored)
+  // What a wave has put into LDS its other lanes read, as other types: nothing in the language keeps that order, so the compiler
+  // is told (the hardware runs a wave's LDS accesses in order).
+  auto lds_in_order = []() { asm volatile("" ::: "memory"); };
   auto load_x = [&](int s) {                       // a whole window
     const char* base = p.src + (int64_t)s * (16 * pieces);
 #pragma unroll
     for (int j = 0; j < XN; ++j) xr[j] = *reinterpret_cast<const u32x4_any*>(at(base, xoff[j]));
   };
   auto put_x = [&]() {
+    lds_in_order();                                // after the reads of the last k-step
 #pragma unroll
     for (int j = 0; j < XN; ++j) *reinterpret_cast<uint4*>(win + xlds[j]) = make_uint4(xr[j].x, xr[j].y, xr[j].z, xr[j].w);
   };
@@ -125,6 +129,7 @@ __global__ void __launch_bounds__(NP * GB * 64, 2) skinny_kernel(SkinnyParams p)
     for (int e = 0; e < 7; ++e)
       rest[e] = lane < p.cols && e < (n & 7) ? *reinterpret_cast<const u16_any*>(at(base, lane * p.ld_bytes + wide * 16 + 2 * e)) : 0;
     put_x();
+    lds_in_order();                                // zeros of other lanes lie where these go
     if (lane < p.cols)
 #pragma unroll
       for (int e = 0; e < 7; ++e)
@@ -137,6 +142,7 @@ __global__ void __launch_bounds__(NP * GB * 64, 2) skinny_kernel(SkinnyParams p)
     for (int j = 0; j < 2; ++j) xr[j] = *reinterpret_cast<const u32x4_any*>(at(p.src, (uint32_t)id[slot][TOKENS ? 0 : j] * p.ld_bytes + xoff[0]));
   };
   auto put_rows = [&]() {
+    lds_in_order();
 #pragma unroll
     for (int j = 0; j < 2; ++j) *reinterpret_cast<uint4*>(offs + j * 1024 + lane * 16) = make_uint4(xr[j].x, xr[j].y, xr[j].z, xr[j].w);
   };
@@ -150,6 +156,7 @@ __global__ void __launch_bounds__(NP * GB * 64, 2) skinny_kernel(SkinnyParams p)
     if constexpr (TOKENS) {
       const int c0 = row_id - s * 8 * p.M;         // (groups past the end have row 0: any column of the window)
       if (lane < kStepRows) *reinterpret_cast<uint32_t*>(offs + 4 * lane) = 2u * (c0 > 0 ? c0 : 0);
+      lds_in_order();
 #pragma unroll
       for (int cb = 0; cb < 4; ++cb) {
         const uint4 o = *reinterpret_cast<const uint4*>(offs + 16 * (4 * (cb >> 1) + (cb & 1) + 2 * h));
@@ -158,6 +165,7 @@ __global__ void __launch_bounds__(NP * GB * 64, 2) skinny_kernel(SkinnyParams p)
         for (int e = 0; e < 4; ++e) b[4 * cb + e] = *reinterpret_cast<const _Float16*>(win + (my_row + oe[e]));
       }
     } else {
+      lds_in_order();
       const int blk = lane >> 4, i = lane & 15;
 #pragma unroll
       for (int cb = 0; cb < 4; ++cb) {
