@@ -155,7 +155,7 @@ __host__ __device__ constexpr int bits_pitch(int wpw, int M) { return (wpw * M +
 //            the smallest unused positions, sorted -> nibble; values copied as bits; canonical and
 //            packed entries written together.  A thread keeps its group, so that only what depends on the row is
 //            left in the loop, and the nibble comes from a table of the 16 sets of kept positions.
-// NE: rows of phase 3 in flight per thread.  Bound by memory from M = 32 on: 49152 x 12288 (0.6 GB of mask, 1.2 GB of A -- the two
+// NE: rows of phase 3 in flight per thread (the rule: launch_compress).  Bound by memory from M = 32 on: 49152 x 12288 (0.6 GB of mask, 1.2 GB of A -- the two
 // kept values of 32 touch every 64-byte sector -- and 0.17 GB written) takes 0.39 ms, 5.0 TB/s; it was 0.40 ms with four rows in
 // flight, 0.45 ms, and another 0.08 ms to pack in a second pass, when phase 3 fetched the mask bytes again one by one.  For
 // smaller groups there are more entries than bytes to wait for, and eight rows in flight cost occupancy: 8192 x 8192 at 64:2:8,
@@ -668,7 +668,10 @@ hipError_t launch_compress(const uint16_t* A, int64_t lda, const uint8_t* mask, 
       constexpr int NE = decltype(ne)::value;
       return ub == 8 ? compress_kernel<8, false, NE> : bits_ok ? compress_kernel<16, true, NE> : compress_kernel<16, false, NE>;
     };
-    auto fn = h.M >= 32 ? of(std::integral_constant<int, 8>{}) : of(std::integral_constant<int, 2>{});
+    // A thread has V * wpw / 32 rows in phase 3, and rows that it does not have cost their instructions all the same: eight in flight
+    // where there are three or more.  With 2 / 8, us per call: 49152 x 12288 at 1:2:32 1690 / 2579 (wpw = 4), 8:2:32 351 / 410,
+    // 24:2:32 363 / 359, 32:2:32 409 / 392; 32768 x 768 at 64:2:32 36.3 / 40.8 (wpw = 1), 96:2:32 36.1 / 37.7, 128:2:32 36.6 / 37.8.
+    auto fn = h.M >= 32 && (int64_t)h.V * wpw >= 96 ? of(std::integral_constant<int, 8>{}) : of(std::integral_constant<int, 2>{});
     hipLaunchKernelGGL(fn, grid, dim3(256), lds, st, A, lda, mask, ldm, wpw, bits_ok, by(chunk / ub), by(last / ub), format_dst(h),
                        legality);
   }

@@ -97,6 +97,8 @@ def check_compress(L, R, K, V, M, ldm, offset):
     (64, 92, 32, 4, 96, 8),          # the same with 8-byte loads
     (64, 45, 32, 5, 45, 1), (64, 60, 32, 4, 61, 3),   # rows at every alignment, both load widths
     (8192, 45, 8192, 5, 45, 2),      # ... and a block too tall for bits on chip
+    (96, 9 * 32, 96, 32, 288, 0), (128, 9 * 33, 128, 33, 297, 1),   # eight rows in flight: three and four a thread
+    (64, 9 * 32, 64, 32, 288, 0), (6, 9 * 40, 2, 40, 360, 0),       # two, as threads have fewer
 ])
 def test_compress(library, R, K, V, M, ldm, offset):
     in_child(library, "check_compress", R, K, V, M, ldm, offset)
