@@ -442,6 +442,18 @@ static int64_t tile_pays_up_to(int cols, int general, bool general_wide) {
   return share < 3 ? 1300 : share < 4 ? 2600 : 12000;
 }
 
+// The mask bytes by way of LDS (PIECES) cost a second pass over the picks, which every call waits for: 2 us where a unit has one workgroup
+// or two.  They pay where the group's own stores are many and the rows of a workgroup short: 1010 shapes (M 65-500, V 1-256, 0.25 to 130
+// million entries), us per call without / with: 8192 x 8136 at 24:2:72 (9 stores) 90.5 / 94.4, 64:2:72 81 / 71; 32768 x
+// 1728 at 32:2:72 93 / 100; 8192 x 8100 at 8:2:100 (25) 1.03 times, 16:2:100 0.92, 8192 x 8125 at 8:2:65 (65, bytes) 1.04, 16:2:65 0.79;
+// small: 1024 x 1000 at 128:2:100 23.2 / 25.6.  Above 200 columns always: 0.74 to 1.00.  Chosen so 0.930 of the time without, at most 1.04
+// (with pieces for all groups above 64: 0.946 and 1.31).
+static bool pieces_pay(int64_t entries, int V, int M, int mask_word) {
+  if (mask_word == 16 || M <= 64) return false;
+  const int stores = M / mask_word < 48 ? M / mask_word : 48;   // of a row and group
+  return M > 200 || (V * stores >= 400 && entries >= (int64_t)8 << 20);
+}
+
 hipError_t launch_prune(const uint16_t* A, int64_t lda, int64_t R, int64_t K, int V, int M, uint8_t* mask, int64_t ldm,
                         unsigned long long* kept_mass, unsigned long long* total_mass, hipStream_t st) {
   const int64_t Rb = R / V, G = K / M;
@@ -460,7 +472,7 @@ hipError_t launch_prune(const uint16_t* A, int64_t lda, int64_t R, int64_t K, in
   const uintptr_t ma = reinterpret_cast<uintptr_t>(mask);
   const int mask_word = (M % 16 == 0 && ldm % 16 == 0 && ma % 16 == 0) ? 16 : (M % 8 == 0 && ldm % 8 == 0 && ma % 8 == 0) ? 8
                         : (M % 4 == 0 && ldm % 4 == 0 && ma % 4 == 0) ? 4 : 1;
-  if (tiled > 0 && mask_word < 16 && M > 64)
+  if (tiled > 0 && pieces_pay(R * K, V, M, mask_word))
     hipLaunchKernelGGL(prune_tile_kernel<true>, dim3((unsigned)chunks, (unsigned)Rb), dim3(256), (size_t)tile_lds(V, gpw * M), st,
                        A, lda, V, M, G, gpw, mask_word, mask, ldm, kept_mass, total_mass);
   else if (tiled > 0)

@@ -248,8 +248,10 @@ def check_prune(L, R, K, V, M, lda, offset):
     (4, 1100, 2, 100, 1104, 0),      # few rows: a tile of 1000 columns, and one group
     (32, 1304, 32, 8, 1304, 0), (64, 816, 64, 16, 817, 2),   # tiles of 512 and 256 columns, and a narrower last one
     (48, 1120, 48, 10, 1120, 0), (56, 560, 56, 7, 560, 0),   # 280 columns, and 168
-    (96, 500, 32, 100, 501, 2), (64, 455, 64, 65, 455, 0),   # mask pieces over two groups, the last of a row shorter
-    (288, 504, 32, 72, 504, 0), (32, 384, 32, 128, 384, 0),   # workgroups over XCDs, and some left
+    (96, 500, 32, 100, 501, 2), (64, 455, 64, 65, 455, 0),   # groups above 64 columns, a group's mask in words of 4 bytes and in bytes
+    (288, 504, 32, 72, 504, 0), (32, 384, 32, 128, 384, 0),   # ... of 8, and of 4 as the mask's rows are on no boundary
+    (96, 612, 32, 204, 613, 2), (24, 1250, 24, 250, 1250, 0),   # mask pieces over two groups, the last of a row shorter
+    (288, 408, 32, 204, 408, 0), (32, 1024, 32, 256, 1024, 0),   # ... workgroups over XCDs, and some left
     (640, 54, 640, 6, 55, 2),        # a tile of 24 columns
     (1024, 128, 1024, 64, 128, 0), (1024, 64, 1024, 64, 67, 6),   # too tall for a tile: the general kernel, wide loads and not
 ])

@@ -102,3 +102,17 @@ def test_argument_errors():
     assert L.venom_prune(None, 8, 8, 8, 4, 2, 4, None, 8, None, None, None) == binding.VENOM_ERR_INVALID_ARG
     assert L.venom_prune(None, 8, 8, 9, 4, 2, 4, None, 8, None, None, None) == binding.VENOM_ERR_SHAPE
     assert L.venom_prune(None, 8, 8, 8, 4, 3, 4, None, 8, None, None, None) == binding.VENOM_ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("R,K,V,M", [
+    (8192, 1100, 64, 100), (16384, 585, 16, 65), (8192, 1080, 128, 72),   # large groups of large matrices: mask pieces
+    (8192, 1100, 8, 100),                                                 # blocks too low for them
+])
+def test_large_matrices_are_pruned_as_their_halves(R, K, V, M):
+    # (a half is below the size from which a mask is written in pieces)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(M)
+    A = torch.randn(R, K, dtype=torch.float16, device=DEV, generator=gen)
+    whole = binding.venom_prune(A, V, 2, M)
+    halves = [binding.venom_prune(a, V, 2, M) for a in (A[:R // 2], A[R // 2:])]
+    assert R * K >= 8 << 20 and all(torch.equal(w, torch.cat(p)) for w, p in zip(whole, zip(*halves)))
