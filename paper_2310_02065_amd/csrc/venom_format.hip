@@ -742,12 +742,20 @@ hipError_t launch_decompress(const venom_handle& h, uint16_t* A, int64_t lda, hi
   const int64_t chunks = (L.K + 255) / 256;
   const bool aligned = reinterpret_cast<uintptr_t>(A) % 16 == 0 && lda % 8 == 0;
   auto fn = aligned ? decompress_of<true>(h.M) : decompress_of<false>(h.M);
+  // Six workgroups a unit (24 KB of LDS each) and not eight, where whole lines are streamed: more reads and stores in flight at once
+  // slow the memory down.  us per call with 8 / 6, cold (other records and output each time) and hot: 49152 x 12288 at 128:2:8 318 / 295 and
+  // 318 / 296 (before the table, at whose pace there were fewer: 299), 128:2:16 285 / 245 and 202 / 195, 128:2:20 354 / 338, 128:2:32
+  // 264 / 243, 24576 x 12288 at 128:2:10 179 / 173, 8192 x 8192 at 64:2:8 38.0 / 35.4 and 31.2 / 30.7.  Not above M = 64, where little is
+  // read (49152 x 12288 at 128:2:128 198 / 205), nor for merged stores (8192 x 8100 at 64:2:100 38 / 42), nor where all run in three or
+  // four rounds (4032 x 4096 at 96:2:16 11.4 / 12.5); M = 5 has six anyway.
+  const size_t tables = (size_t)(h.M % 8 == 0 ? 1 : h.M == 5 ? 3 : 2) * 8 * 1024;
+  const size_t lds = aligned && h.M <= 64 && L.R / kTileRows * chunks >= 24 * 256 ? 24 * 1024 - tables : 0;
   // a launch holds fewer than 2^32 threads, 256 per workgroup however few columns there are: tall narrow matrices
   // take several
   const int64_t tiles = L.R / kTileRows, most = kMaxBlocks / chunks;
   for (int64_t rt0 = 0; rt0 < tiles; rt0 += most) {
     const int64_t n = tiles - rt0 < most ? tiles - rt0 : most;
-    hipLaunchKernelGGL(fn, dim3((unsigned)(n * chunks)), dim3(256), 0, st, h.ws + L.off_arec,
+    hipLaunchKernelGGL(fn, dim3((unsigned)(n * chunks)), dim3(256), lds, st, h.ws + L.off_arec,
                        reinterpret_cast<const int32_t*>(h.ws + L.off_rowidx), L.K, h.M, make_divisor((uint32_t)h.M), L.steps,
                        L.vt, (int)chunks, rt0, A, lda);
     const hipError_t e = hipGetLastError();
