@@ -387,13 +387,13 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
 // of values, one 16-byte slot of the packed record.  TILES: 32-row tiles of a packed block row; a workgroup takes 4 words of all
 // of them, the loads of all rows in flight together: it reads rows of 128 bytes and completes the 128-byte lines of the
 // records, their index words by way of LDS (two bytes a row and tile: workgroups of one tile each wrote parts of the same lines
-// from several XCDs).  SPLIT: a workgroup takes one tile after all, where there are too few otherwise.  TILES = 0, no packed records: 2^wbits words of 128 >> wbits rows, 32 of 4 where there are as many; a row
-// that starts inside a line then shares far fewer lines with workgroups of other XCDs (4096 x 8190 at 1:2:7, us per call: 81 with 4 words,
-// 60 with 32, three copies and a check 72).
+// from several XCDs).  SPLIT: a workgroup takes one tile after all (the rule: launch_import).  TILES = 0, no packed records:
+// 2^wbits words of 128 >> wbits rows, 32 of 4 where there are as many; a row that starts inside a line then shares far fewer lines
+// with workgroups of other XCDs (4096 x 8190 at 1:2:7, us per call: 81 with 4 words, 60 with 32, three copies and a check 72).
 // Checked is what the gather and the matrix instruction rely on -- column ids strictly increasing
 // and below M (once per block), the two m-indices of a nibble ordered idx0 < idx1, unused nibbles of
 // the last metadata word zero.
-// 8192 x 8192, us per call of the binding (20 of them the launch and the wait), one tile a workgroup -> now: 64:2:8 (120 MB in and
+// 8192 x 8192, us per call of the binding (20 of them the launch and the wait), the same arrays again, one tile a workgroup -> all: 64:2:8 (120 MB in and
 // out) 48.2 -> 46.0, 128:2:8 47.1 -> 44.7, 64:2:16 37.0 -> 34.0, 64:2:7 63.2 -> 59.4; three copies, the check and the packing by themselves
 // took 90 us at 64:2:8.
 template <int TILES, bool SPLIT>
@@ -635,8 +635,14 @@ hipError_t launch_import(const uint16_t* values, const uint16_t* columns, const 
     int wbits = 2;
     while (!L.packed && wbits < 5 && (1 << wbits) < L.W) ++wbits;
     const int64_t words = (L.W + (1 << wbits) - 1) >> wbits;
-    // fewer than three workgroups a unit: 8192 x 8192 at 128:2:64 (256 of them) 27.3 whole, 25.7 split; at 128:2:20 (832) 35.2 and 36.3
-    const bool split = L.vt > 1 && words * L.Rbp < 768;
+    // One tile a workgroup where there are fewer than three workgroups for each of 256 units: 8192 x 8192 at 128:2:64 (256 of them)
+    // 27.3 whole, 25.7 split; at 128:2:20 (832) 35.2 and 36.3.  Also blocks of three and four tiles of 2^24 groups or more (64 MB of
+    // values), whose 96 or 128 rows at once the memory takes more slowly, with other arrays each time or the same: 8192 x 8192 at
+    // 128:2:4 85 whole, 79 split, 24576 x 12288 at 128:2:8 148 and 143, 49152 x 12288 at 128:2:16 153 and 147; below that the same arrays
+    // again are faster whole, others slower (8192 x 8192 at 128:2:8 44.4 and 47.1, 57 and 54), and two tiles are faster whole (49152 x 12288 at
+    // 64:2:8 282 and 299).  And packed blocks that are not the canonical ones (M = 4), where the rows of a thread lie in
+    // several of those: 8192 x 8192 at 32:2:4 97 and 83, 1:2:4 193 and 177.
+    const bool split = L.vt > 1 && (words * L.Rbp < 768 || (L.vt > 2 && L.R * L.G >= (int64_t)1 << 24) || h.V != L.vt * kTileRows);
     const int64_t rows = !L.packed ? 128 >> wbits : split ? kTileRows : L.vt * kTileRows;
     auto fn = L.vt == 0 ? import_kernel<0, false> : split ? import_kernel<1, true> : L.vt == 1 ? import_kernel<1, false>
               : L.vt == 2 ? import_kernel<2, false> : L.vt == 3 ? import_kernel<3, false> : import_kernel<4, false>;

@@ -1,4 +1,5 @@
-"""venom_import where a workgroup takes all tiles of a packed block row (768 workgroups or more) and where it takes one: the canonical
+"""venom_import where a workgroup takes all tiles of a packed block row (768 workgroups or more, fewer than 2^24 groups from three
+tiles on, packed blocks the same as the canonical ones) and where it takes one: the canonical
 arrays come back, the packed copies expand to the masked matrix, and a fault in the last row and group is refused."""
 import pytest
 
@@ -16,8 +17,10 @@ DEV = "cuda:0"
     (96 * 110, 7 * 220, 96, 7),      # three tiles, 770; the last words of a row are half a workgroup's
     (128 * 100, 16 * 250, 128, 16),  # four
     (128 * 3, 16 * 9, 128, 16),      # ... split
-    (256 * 50, 1000, 256, 4), (32 * 400, 1000, 32, 4),   # M = 4: packed blocks of 128 rows under blocks of 256 and of 32
-    (256 * 3, 1000, 256, 4), (32 * 12, 1000, 32, 4),     # ... split
+    (128 * 8192, 128, 128, 8), (128 * 8191, 128, 128, 8),   # 2^24 groups: split, and one block row less: whole
+    (128 * 100, 1000, 128, 4),       # M = 4: whole
+    (256 * 50, 1000, 256, 4), (32 * 400, 1000, 32, 4),   # ... split: packed blocks of 128 rows under blocks of 256 and of 32
+    (256 * 3, 1000, 256, 4), (32 * 12, 1000, 32, 4),
 ])
 def test_import_packs_whole_block_rows_and_tiles(R, K, V, M):
     gen = torch.Generator(device=DEV)
