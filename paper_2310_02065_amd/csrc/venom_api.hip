@@ -320,8 +320,9 @@ venom_status_t venom_linear(const venom_handle_t* h, const void* X_f16_dev, int6
   if (!scratch_dev || !aligned(scratch_dev, 16) || scratch_bytes < need) return VENOM_ERR_WORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int cus = venom::compute_units();
-  if (h->K > 0 && h->R > 0 && cus > 0 && venom::skinny_layer(*h, X_f16_dev, ldx, tokens, Y_dev, ldy, y_dtype, cus))
-    return venom::launch_skinny(*h, X_f16_dev, ldx, tokens, bias_f16_dev, activation, Y_dev, ldy, y_dtype, true, true, cus, st);
+  const int form = h->K > 0 && h->R > 0 && cus > 0 ? venom::skinny_layer(*h, X_f16_dev, ldx, tokens, Y_dev, ldy, y_dtype, cus) : -1;
+  if (form >= 0)
+    return venom::launch_skinny(*h, form, X_f16_dev, ldx, tokens, bias_f16_dev, activation, Y_dev, ldy, y_dtype, true, true, st);
   const int64_t ldbt = (tokens + 7) / 8 * 8;
   if (venom::launch_transpose_tokens(static_cast<const uint16_t*>(X_f16_dev), ldx, tokens, h->K,
                                      static_cast<uint16_t*>(scratch_dev), ldbt, tokens * h->R * (int64_t)esz, st) != hipSuccess)

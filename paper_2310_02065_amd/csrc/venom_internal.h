@@ -87,12 +87,14 @@ venom_status_t launch_spmm(const venom_handle& h, const void* B, int64_t ldb, in
                            void* C, int64_t ldc, int c_dtype, int tokens_major, int variant, hipStream_t st);
 // Compute units of the current device, 0 if they cannot be found out.
 int compute_units();
-// The same for at most 32 columns (venom_skinny.hip), where skinny_product or skinny_layer says so.  in_place: src is X, tokens x K,
-// else B; token_major: as above.
-bool skinny_product(const venom_handle& h, int64_t ld, int64_t cols, int cus);
-bool skinny_layer(const venom_handle& h, const void* X, int64_t ldx, int64_t tokens, const void* Y, int64_t ldy, int dtype, int cus);
-venom_status_t launch_skinny(const venom_handle& h, const void* src, int64_t ld, int64_t cols, const void* bias, int act, void* out,
-                             int64_t ldo, int dtype, bool in_place, bool token_major, int cus, hipStream_t st);
+// The same for at most 32 columns (venom_skinny.hip), where skinny_product or skinny_layer gives a form for it (else -1): a workgroup
+// takes a block row (products), one 32-row tile of it, or two block rows (layers that read X in place).
+enum SkinnyForm { kWhole, kSplit, kPair };
+int skinny_product(const venom_handle& h, int64_t ld, int64_t cols, int cus);
+int skinny_layer(const venom_handle& h, const void* X, int64_t ldx, int64_t tokens, const void* Y, int64_t ldy, int dtype, int cus);
+// in_place: src is X, tokens x K, else B; token_major: as above
+venom_status_t launch_skinny(const venom_handle& h, int form, const void* src, int64_t ld, int64_t cols, const void* bias, int act,
+                             void* out, int64_t ldo, int dtype, bool in_place, bool token_major, hipStream_t st);
 // register-only loop of 2:4 matrix instructions, for the measured instruction peak (grid = one workgroup of 8 waves per
 // compute unit x 2)
 hipError_t launch_smfmac_probe(int iters, float* sink, hipStream_t st);

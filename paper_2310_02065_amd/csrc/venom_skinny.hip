@@ -12,6 +12,7 @@
 // layer 16.8 -> 10; 96 x 13552 x 32 at 96:2:8 (one block row) 28 -> 9.9; 1024 x 1024 x 8 at 128:2:8 6.1 -> 4.8, as a layer 10.8 -> 6.4;
 // the layer of 49152 x 12288 with 16 tokens at 128:2:32 (85 MB of records) 22.6 -> 19.8.
 #include <atomic>
+#include <cmath>
 
 #include "venom_device.h"
 
@@ -329,7 +330,6 @@ __global__ void __launch_bounds__(NP * GB * 64, 2) skinny_kernel(SkinnyParams p)
 }
 
 // ---------------------------------------------------------------------------------------------
-enum SkinnyForm { kWhole, kSplit, kPair };   // a block row per workgroup, a tile of one, two block rows
 constexpr int kSkinnyPieces = 16;            // most pieces of X that a lane stages
 
 template <int VT, int FORM, int XJ>
@@ -357,37 +357,51 @@ static bool skinny_can(const Layout& L, int64_t ld, int64_t cols, bool tokens) {
 // 2896 x 8 at 64:2:16 4.6 both; 17664 x 6112 x 8 at 128:2:16 8.7 whole, 14.8 split (each tile gathers its rows of B again).
 static bool split_pays(int64_t tiles, int cus) { return tiles * 64 < 75 * (int64_t)cus; }
 
-bool skinny_product(const venom_handle& h, int64_t ld, int64_t cols, int cus) {
+// Many block rows of 128 keep spmm_kernel's units busy, whose loads bypass the registers: 49152 x 12288 x 16 at 128:2:32 16.8
+// there, 17.5 here; 24448 x 14320 x 32 at 128:2:20 15.9 and 16.6; up to 64 rows it is slower there, too (19648 x 4704 x 32 at
+// 64:2:32 7.6 and 5.8)
+static bool tile_serves(const Layout& L, int cus) { return L.vt == kMaxTiles && L.Rbp * 64 >= 50 * (int64_t)cus; }
+
+int skinny_product(const venom_handle& h, int64_t ld, int64_t cols, int cus) {
   const Layout& L = h.lay;
-  // many block rows of 128 keep spmm_kernel's units busy, whose loads bypass the registers: 49152 x 12288 x 16 at 128:2:32 16.8
-  // there, 17.5 here; 24448 x 14320 x 32 at 128:2:20 15.9 and 16.6; up to 64 rows it is slower there, too (19648 x 4704 x 32 at
-  // 64:2:32 7.6 and 5.8)
-  return skinny_can(L, ld, cols, false) && !(L.vt == kMaxTiles && L.Rbp * 64 >= 50 * (int64_t)cus);
+  if (!skinny_can(L, ld, cols, false) || tile_serves(L, cus)) return -1;
+  return split_pays(L.Rbp * L.vt, cus) ? kSplit : kWhole;
 }
 
+// Pieces of X that a lane loads per k-step (the needed ones or copies of the first): two instantiations.
+static int staged_pieces(int64_t tokens, int M) { return tokens * M <= 64 * 8 ? 8 : kSkinnyPieces; }
+static int layer_lds(int64_t tokens, int M) { return 8 * (128 + skinny_window((int)tokens, M)); }
+
 // A layer: X read in place, split or by pairs of block rows, or transposed and then a product.  The expected times are fits to
-// 240 shapes (R 64-49152, K 256-16000, 8-32 tokens, M 4-128; rms error 8 to 13 %): `load` workgroups per unit, `spw` k-steps per
-// wave, `pieces` of X per lane and k-step.  The choice is 1 % slower than the best of the four on average, 26 % at most, and
-// takes 0.78 of the time of transposition and 64-column tiles.  Reading in place counts 5 % less, as on an idle GPU a second
-// launch costs more than among others.
+// 8250 random shapes (R 64-49152, K 64-16000, 8-32 tokens, M 4-128; rms error 5 to 7 %): `load` workgroups per unit, `rounds` of
+// them, one at a time (pairs of single tiles with 8 staged pieces: two, if their LDS leaves room, `starts`), `spw` k-steps per wave.
+// On 2750 others the choice is 0.7 % slower than the best on average, and takes 0.74 of the time of transposition and 64-column tiles, 1.14 times
+// at most and more than 1.05 in one of 300.  (Fits to 240 shapes, with the needed pieces in the place of the loaded ones and no
+// rounds of pairs, took these also for many block rows of few k-steps: 35712 x 896 with 16 tokens at 32:2:64 10.8 -> 18.3 us, now
+// 7.3.)  Reading in place counts 5 % less, as on an idle GPU a second launch costs more than among others.
 static int layer_form(const Layout& L, int64_t ldx, int64_t tokens, int M, int cus) {
   if (!skinny_can(L, ldx, tokens, true) || tokens * M > 64 * kSkinnyPieces) return -1;
-  const float pieces = (float)(tokens * M) / 64.f, end = L.G % kStepGroups ? pieces : 0.f, steps = (float)L.steps;
-  const int64_t tiles = L.Rbp * L.vt;
+  const int64_t tiles = L.Rbp * L.vt, pairs = (L.Rbp + 1) / 2;
+  const float steps = (float)L.steps, vt = (float)L.vt, end = L.G % kStepGroups ? 1.f : 0.f;
+  const float staged = (float)staged_pieces(tokens, M), pieces = (float)(tokens * M) / 64.f;
   const float records = (float)(4.5e-6 * (double)L.R * (double)L.G) - 20.f, more = records > 0.f ? records : 0.f;   // MB over 20
   const float x_mb = (float)(2e-6 * (double)tokens * (double)L.K);
+  auto rounds_of = [&](int64_t wgs, int64_t resident) { return (float)((wgs + resident * cus - 1) / (resident * cus)); };
   struct Shape { float load, rounds, spw; };
   auto shape = [&](int64_t wgs, int waves) {
-    return Shape{(float)wgs / (float)cus, (float)((wgs + cus - 1) / cus), (float)((L.steps + waves - 1) / waves)};
+    return Shape{(float)wgs / (float)cus, rounds_of(wgs, 1), (float)((L.steps + waves - 1) / waves)};
   };
-  const Shape s = shape(tiles, 8), w = shape(L.Rbp, 4), p = shape((L.Rbp + 1) / 2, 4);
-  const float split = 4.656f + s.load * (.975f + .0057f * steps * pieces) + s.spw * (.0203f * pieces + .756f * s.rounds) +
-                      .0284f * end + .0048f * more;
-  const float pair = 5.247f + p.load * (.189f + .0214f * steps * (float)L.vt) + p.spw * (.322f + .03f * pieces + .324f * p.rounds) +
-                     .0597f * end + .0167f * more;
+  const Shape s = shape(tiles, 8), w = shape(L.Rbp, 4), p = shape(pairs, 4);
+  const float starts = rounds_of(pairs, L.vt == 1 && staged <= 8.f && layer_lds(tokens, M) <= 80 * 1024 ? 2 : 1);
+  const float split = 2.83f + s.rounds * (1.19f + .0455f * staged + s.spw * (.027f + .0727f * staged)) +
+                      s.load * steps * (.0114f + .0055f * pieces) + .196f * s.spw + .405f * end;
+  const float pair = 2.3f + starts * (2.57f + .0164f * staged + .1485f * p.spw) + p.rounds * p.spw * (.0435f * staged + .1167f * vt) +
+                     p.load * (.0086f * steps * pieces + .23f * vt) + .445f * end;
   const float first = split_pays(tiles, cus)
-      ? 7.012f + s.load * (.177f + .0177f * steps) + s.spw * (.059f + .249f * s.rounds) + .704f * x_mb + .061f * more
-      : 7.438f + w.load * (.053f + .0171f * steps * (float)L.vt) + w.spw * (.128f + .089f * w.rounds) + .659f * x_mb + .055f * more;
+      ? 6.2f + s.load * (.11f + .01f * steps) + s.spw * (.0793f + .2625f * s.rounds) + .36f * x_mb + .822f * sqrtf(x_mb) + .0448f * more + .388f * end
+      : tile_serves(L, cus)
+      ? 7.12f + 1.126f * w.rounds + w.load * .0287f * steps * vt + w.spw * (.0435f + .1577f * w.rounds) + .329f * sqrtf(x_mb) + .395f * end
+      : 5.88f + .345f * vt + w.load * .0289f * steps * vt + w.spw * (.0229f + .1187f * w.rounds) + 1.664f * x_mb + .013f * more + .4185f * end;
   if (split <= pair) return split < 1.05f * first ? kSplit : -1;
   return pair < 1.05f * first ? kPair : -1;
 }
@@ -400,14 +414,17 @@ static bool overlap(const void* a, int64_t a_bytes, const void* b, int64_t b_byt
 // An output over X stays with the transposition, which has read all of X before the product starts: a workgroup here reads
 // every column of X to the end of its run, when others have long stored their features.  From the first byte to the last, gaps
 // between rows included (X and Y side by side in one buffer: transposed, as if they met).
-bool skinny_layer(const venom_handle& h, const void* X, int64_t ldx, int64_t tokens, const void* Y, int64_t ldy, int dtype, int cus) {
-  if (layer_form(h.lay, ldx, tokens, h.M, cus) < 0) return false;
-  return !overlap(X, 2 * ((tokens - 1) * ldx + h.K), Y, (dtype == 1 ? 4 : 2) * ((tokens - 1) * ldy + h.R));
+int skinny_layer(const venom_handle& h, const void* X, int64_t ldx, int64_t tokens, const void* Y, int64_t ldy, int dtype, int cus) {
+  const int form = layer_form(h.lay, ldx, tokens, h.M, cus);
+  if (form < 0 || overlap(X, 2 * ((tokens - 1) * ldx + h.K), Y, (dtype == 1 ? 4 : 2) * ((tokens - 1) * ldy + h.R))) return -1;
+  return form;
 }
 
-venom_status_t launch_skinny(const venom_handle& h, const void* src, int64_t ld, int64_t cols, const void* bias, int act, void* out,
-                             int64_t ldo, int dtype, bool in_place, bool token_major, int cus, hipStream_t st) {
+venom_status_t launch_skinny(const venom_handle& h, int form, const void* src, int64_t ld, int64_t cols, const void* bias, int act,
+                             void* out, int64_t ldo, int dtype, bool in_place, bool token_major, hipStream_t st) {
   const Layout& L = h.lay;
+  if (!skinny_can(L, ld, cols, in_place) || (in_place && cols * h.M > 64 * kSkinnyPieces)) return VENOM_ERR_UNSUPPORTED;
+  if (form != kSplit && form != (in_place ? kPair : kWhole)) return VENOM_ERR_UNSUPPORTED;
   SkinnyParams p{};
   p.arec = h.ws + L.off_arec;
   p.rowidx = reinterpret_cast<const int32_t*>(h.ws + L.off_rowidx);
@@ -420,14 +437,12 @@ venom_status_t launch_skinny(const venom_handle& h, const void* src, int64_t ld,
   p.bias = static_cast<const _Float16*>(bias);
   p.act = act;
   p.token_major = token_major;
-  const int form = in_place ? layer_form(L, ld, cols, h.M, cus) : split_pays(L.Rbp * L.vt, cus) ? kSplit : kWhole;
-  if (form < 0) return VENOM_ERR_UNSUPPORTED;
-  const int xj = !in_place ? 0 : cols * h.M <= 64 * 8 ? 8 : kSkinnyPieces;
+  const int xj = in_place ? staged_pieces(cols, h.M) : 0;
   const bool f32 = dtype == 1;
   auto fn = L.vt == 1 ? skinny_of<1>(form, xj, f32) : L.vt == 2 ? skinny_of<2>(form, xj, f32)
             : L.vt == 3 ? skinny_of<3>(form, xj, f32) : skinny_of<4>(form, xj, f32);
   const int rt = form == kSplit ? 1 : L.vt, gb = form == kPair ? 2 : 1, waves = form == kWhole ? 4 : 8;
-  const int staged = waves * (in_place ? 128 + skinny_window(p.cols, p.M) : kStepRows * 64), sums = 4 * rt * gb * 4096;
+  const int staged = in_place ? layer_lds(cols, h.M) : waves * kStepRows * 64, sums = 4 * rt * gb * 4096;
   const int lds = staged > sums ? staged : sums;
   if (lds > 64 * 1024) {
     // opting in to more than 64 KB of dynamic LDS is a per-function attribute, set once per device, to the most that any call

@@ -916,8 +916,10 @@ venom_status_t launch_spmm(const venom_handle& h, const void* B, int64_t ldb, in
   // gather offsets are formed as row * ldb_bytes + column bytes in 32 bits with a 24-bit multiply
   if (h.K >= ((int64_t)1 << 24) || ldb * 2 >= ((int64_t)1 << 24) || h.K * ldb * 2 >= ((int64_t)1 << 32))
     return VENOM_ERR_UNSUPPORTED;
-  if (variant < 0 && skinny_product(h, ldb, Ccols, cus))
-    return launch_skinny(h, B, ldb, Ccols, bias, act, C, ldc, c_dtype, false, tokens_major != 0, cus, st);
+  if (variant < 0) {
+    const int form = skinny_product(h, ldb, Ccols, cus);
+    if (form >= 0) return launch_skinny(h, form, B, ldb, Ccols, bias, act, C, ldc, c_dtype, false, tokens_major != 0, st);
+  }
   if (variant < 0) variant = pick_variant(Vp, Ccols, L.Rbp, L.steps, cus);
   if (variant < 0 || variant >= kNumVariants || kVariants[variant].V != Vp) return VENOM_ERR_UNSUPPORTED;
   const Variant& var = kVariants[variant];

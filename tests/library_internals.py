@@ -30,7 +30,16 @@ def host_handle(R, K, V, M):
     return h
 
 
-def layer_reads_in_place(h, X, ldx, tokens, Y, ldy, dtype=0, units=256):
-    f = inner("_ZN5venom12skinny_layerERK12venom_handlePKvllS4_lii", c_bool, c_void_p, c_void_p, c_int64, c_int64, c_void_p, c_int64,
+# how a product of few columns, or a layer of few tokens that reads X in place, is dealt to workgroups
+NONE, WHOLE, SPLIT, PAIR = -1, 0, 1, 2
+
+
+def layer_form(h, X, ldx, tokens, Y, ldy, dtype=0, units=256):
+    f = inner("_ZN5venom12skinny_layerERK12venom_handlePKvllS4_lii", c_int, c_void_p, c_void_p, c_int64, c_int64, c_void_p, c_int64,
               c_int, c_int)
     return f(ctypes.byref(h), X, ldx, tokens, Y, ldy, dtype, units)
+
+
+def product_form(h, ldb, cols, units=256):
+    f = inner("_ZN5venom14skinny_productERK12venom_handlelli", c_int, c_void_p, c_int64, c_int64, c_int)
+    return f(ctypes.byref(h), ldb, cols, units)

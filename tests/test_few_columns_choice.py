@@ -1,27 +1,37 @@
-"""Which layers of few tokens are read in place: asked of the library on the host, no GPU needed."""
+"""How layers of few tokens are served: asked of the library on the host, no GPU needed."""
 import pytest
 
-from library_internals import host_handle, layer_reads_in_place
+from library_internals import NONE, PAIR, SPLIT, host_handle, layer_form
 
 X0 = 1 << 32
 
 
-@pytest.mark.parametrize("R,K,V,M", [(1024, 1024, 64, 16), (9664, 800, 64, 20)])   # single tiles; pairs of block rows
+@pytest.mark.parametrize("R,K,V,M,form", [(1024, 1024, 64, 16, SPLIT), (9664, 800, 64, 16, PAIR)])
 @pytest.mark.parametrize("tokens", [8, 16, 32])
 @pytest.mark.parametrize("dtype,size", [(0, 2), (1, 4)])
-def test_an_output_over_the_activations_is_not_written_while_they_are_read(R, K, V, M, tokens, dtype, size):
+def test_an_output_over_the_activations_is_not_written_while_they_are_read(R, K, V, M, form, tokens, dtype, size):
     h = host_handle(R, K, V, M)
     ldx, ldy = K + 6, R + 12
     x_bytes, y_bytes = 2 * ((tokens - 1) * ldx + K), size * ((tokens - 1) * ldy + R)
 
-    def in_place(y):
-        return layer_reads_in_place(h, X0, ldx, tokens, y, ldy, dtype)
+    def served(y):
+        return layer_form(h, X0, ldx, tokens, y, ldy, dtype)
 
-    assert in_place(X0 + x_bytes) and in_place(X0 - y_bytes)                       # end to end
+    assert served(X0 + x_bytes) == form and served(X0 - y_bytes) == form           # end to end: X is read in place
     for y in (X0, X0 + x_bytes - 2, X0 - y_bytes + 2, X0 + x_bytes // 2, X0 - y_bytes // 2):
-        assert not in_place(y), y - X0
+        assert served(y) == NONE, y - X0
 
 
 def test_more_rows_than_a_launch_has_threads_for_are_transposed_first():
     # 2^31 rows, 2^24 packed block rows: pairs of them, 512 threads each, are 2^32
-    assert not layer_reads_in_place(host_handle(1 << 31, 36, 1 << 16, 4), X0, 36, 8, X0 << 8, 1 << 31)
+    assert layer_form(host_handle(1 << 31, 36, 1 << 16, 4), X0, 36, 8, X0 << 8, 1 << 31) == NONE
+
+
+@pytest.mark.parametrize("R,K,V,M,tokens,form", [
+    (35712, 896, 32, 64, 16, NONE),      # 558 pairs, one at a time on a unit as their windows fill its LDS: 18 us, transposed first 7
+    (39488, 256, 32, 128, 8, NONE), (36160, 480, 64, 32, 24, NONE),
+    (49152, 12288, 128, 32, 16, PAIR),   # few tokens of a large layer: 21 us, transposed first 25
+    (1024, 1024, 128, 8, 8, SPLIT),
+])
+def test_many_block_rows_of_few_steps_are_transposed_first(R, K, V, M, tokens, form):
+    assert layer_form(host_handle(R, K, V, M), X0, K, tokens, X0 << 8, R) == form

@@ -35,7 +35,7 @@ def test_the_output_takes_the_input_s_place(R, V, M, T):
 
 
 @pytest.mark.parametrize("T", [8, 32, 40])
-@pytest.mark.parametrize("R,K,V,M", [(1024, 512, 64, 16), (9664, 800, 64, 20)])
+@pytest.mark.parametrize("R,K,V,M", [(1024, 512, 64, 16), (9664, 800, 64, 16)])
 def test_the_input_is_a_part_of_the_output(R, K, V, M, T):
     (A, mask), X, bias, (Ys, Ey) = problem(R, K, V, M, T)
     h = binding.venom_compress(A, mask, V, 2, M)
