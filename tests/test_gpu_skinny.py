@@ -1,6 +1,7 @@
-"""Products with at most 32 columns and layers with at most 32 tokens against the oracle, in each form of their kernel: single tiles,
-whole block rows, pairs of them (an odd number, too), X read in place or transposed first, one to four tiles per block row, fewer
-k-steps than waves, a last k-step with some of its groups, rows of X that end inside a 16-byte piece or start at any address."""
+"""Products with at most 32 columns and layers with at most 32 tokens against the oracle, in the form that is chosen for them (each form
+by itself, with longer reductions: tests/test_gpu_few_columns_forms.py): single tiles, whole block rows, pairs of them (an odd number,
+too), X read in place or transposed first, fewer k-steps than waves, a last k-step with some of its groups, rows of X that end
+inside a 16-byte piece or start at any address."""
 import numpy as np
 import pytest
 
@@ -22,16 +23,16 @@ def problem(R, K, C, V, M):
 @pytest.mark.parametrize("R,K,C,V,M", [
     (128, 16, 8, 128, 16),            # one group in all
     (96, 7 * 33, 24, 96, 7),          # odd rows, five k-steps, one group in the last; a wave has none
-    (64, 8 * 64, 32, 64, 8),          # eight k-steps, all whole; 16 pieces of X a lane would be too few, 4 are used
+    (64, 8 * 64, 32, 64, 8),          # eight k-steps, all whole: one for each wave
     (32, 10 * 77, 16, 32, 10),        # ten k-steps: two waves have a second one
-    (256, 32 * 100, 32, 128, 32),     # 1024 pieces: the most that are staged
-    (256, 32 * 24, 16, 128, 32),      # 512: the most of the smaller staging
+    (256, 32 * 100, 32, 128, 32),     # 1024 pieces of X, the most that can be staged; transposed first
+    (256, 32 * 24, 16, 128, 32),      # 512: the most of the smaller staging, 8 a lane
     (192, 100 * 12, 8, 64, 100), (192, 100 * 12, 16, 64, 100),   # 800; 1600: transposed first
     (10240 + 128, 4 * 50, 32, 128, 4),                # 81 block rows of 128, 324 tiles: by pairs, a half one at the end
     (9600 + 96, 10 * 30, 16, 96, 10),                 # 101 of 96, ragged
-    (9600 + 64, 20 * 40, 32, 64, 20),                 # 151 of 64: many pieces, transposed first; whole block rows
+    (9600 + 64, 20 * 40, 32, 64, 20),                 # 151 of 64, 640 pieces: transposed first, then whole block rows
     (9600 + 32, 16 * 9, 24, 32, 16),                  # 301 of 32
-    (26 * 1024, 7 * 20, 8, 128, 7),                   # 208 of 128: the product stays with the 64-column tile
+    (26 * 1024, 7 * 20, 8, 128, 7),                   # 208 of 128: the product stays with the 64-column tile, the layer goes by pairs
 ])
 def test_few_columns_match_oracle(R, K, C, V, M):
     h, (ov, oc, om), B, bias = problem(R, K, C, V, M)
