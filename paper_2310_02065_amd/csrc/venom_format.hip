@@ -155,8 +155,8 @@ __host__ __device__ constexpr int bits_pitch(int wpw, int M) { return (wpw * M +
 //            the smallest unused positions, sorted -> nibble; values copied as bits; canonical and
 //            packed entries written together.  A thread keeps its group, so that only what depends on the row is
 //            left in the loop, and the nibble comes from a table of the 16 sets of kept positions.
-// NE: rows of phase 3 in flight per thread (the rule: launch_compress).  Bound by memory from M = 32 on: 49152 x 12288 (0.6 GB of mask, 1.2 GB of A -- the two
-// kept values of 32 touch every 64-byte sector -- and 0.17 GB written) takes 0.39 ms, 5.0 TB/s; it was 0.40 ms with four rows in
+// NE: rows of phase 3 in flight per thread (the rule: launch_compress).  Bound by memory from M = 32 on: 49152 x 12288 (0.6 GB
+// of mask, 1.2 GB of A -- the two kept values of 32 touch every 64-byte sector -- and 0.17 GB written) takes 0.39 ms, 5.0 TB/s; it was 0.40 ms with four rows in
 // flight, 0.45 ms, and another 0.08 ms to pack in a second pass, when phase 3 fetched the mask bytes again one by one.  For
 // smaller groups there are more entries than bytes to wait for, and eight rows in flight cost occupancy: 8192 x 8192 at 64:2:8,
 // us per call with 2 / 4 / 8 rows 80.6 / 84.5 / 87.1.  Against an index computation for each entry: 128:2:4 135 -> 115, 64:2:8 83 -> 75,
@@ -393,8 +393,8 @@ __global__ void __launch_bounds__(256) compress_kernel(const uint16_t* __restric
 // Checked is what the gather and the matrix instruction rely on -- column ids strictly increasing
 // and below M (once per block), the two m-indices of a nibble ordered idx0 < idx1, unused nibbles of
 // the last metadata word zero.
-// 8192 x 8192, us per call of the binding (20 of them the launch and the wait), the same arrays again, one tile a workgroup -> all: 64:2:8 (120 MB in and
-// out) 48.2 -> 46.0, 128:2:8 47.1 -> 44.7, 64:2:16 37.0 -> 34.0, 64:2:7 63.2 -> 59.4; three copies, the check and the packing by themselves
+// 8192 x 8192, us per call of the binding (20 of them the launch and the wait), the same arrays again, one tile a workgroup ->
+// all: 64:2:8 (120 MB in and out) 48.2 -> 46.0, 128:2:8 47.1 -> 44.7, 64:2:16 37.0 -> 34.0, 64:2:7 63.2 -> 59.4; three copies, the check and the packing by themselves
 // took 90 us at 64:2:8.
 template <int TILES, bool SPLIT>
 __global__ void __launch_bounds__(256) import_kernel(const u32_any* __restrict__ values, const u16_any* __restrict__ columns,
@@ -510,8 +510,9 @@ __device__ __forceinline__ uint32_t divide(uint32_t n, Divisor d) { return __umu
 // the second starts a new half of the k-step.  STREAM: rows on 16-byte boundaries: stores past the caches, as nothing reads the
 // lines again here and streamed they leave at the rate of a linear fill.  Other rows have their stores merged to whole lines in
 // the L2, so neighbouring workgroups run on the same XCD.  Bound by the writes, below M = 16 by the number of loads.
-// us per call, positions compared in every row (some 40 instructions a row and group), one group at a time, all streamed -> now: 8192
-// x 8192 at 64:2:8 35 -> 31, at 64:2:16 31.8 -> 27.6, 49152 x 12288 at 128:2:32 207 -> 207 (6.2 TB/s); rows on no 16-byte boundary:
+// us per call (the same records and output again), positions compared in every row (some 40 instructions a row and group), one group at
+// a time, all streamed -> now: 8192 x 8192 at 64:2:8 35 -> 31, at 64:2:16 29 -> 25, 49152 x 12288 at 128:2:32 210 -> 200 (6.5 TB/s; with others
+// each time 274 -> 243); rows on no 16-byte boundary:
 // 8192 x 8100 at 64:2:100 47 -> 24 (streamed 41), 8192 x 8180 at 64:2:20 50 -> 32, 8192 x 8190 at 64:2:10 50 -> 34 and at 64:2:7 67 -> 49
 // (one group at a time 60).  The entries of a chunk staged in LDS by wide loads: 64:2:8 39, 64:2:7 65.
 template <int NG, bool ALL, bool PAIRS, bool STREAM>

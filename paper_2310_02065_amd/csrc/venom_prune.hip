@@ -443,7 +443,7 @@ static int64_t tile_pays_up_to(int cols, int general, bool general_wide) {
 }
 
 // The mask bytes by way of LDS (PIECES) cost a second pass over the picks, which every call waits for: 2 us where a unit has one workgroup
-// or two.  They pay where the group's own stores are many and the rows of a workgroup short: 1010 shapes (M 65-500, V 1-256, 0.25 to 130
+// or two.  They pay where the group's own stores are many and the rows of a workgroup short: 805 shapes (M 65-500, V 1-256, 0.25 to 130
 // million entries), us per call without / with: 8192 x 8136 at 24:2:72 (9 stores) 90.5 / 94.4, 64:2:72 81 / 71; 32768 x
 // 1728 at 32:2:72 93 / 100; 8192 x 8100 at 8:2:100 (25) 1.03 times, 16:2:100 0.92, 8192 x 8125 at 8:2:65 (65, bytes) 1.04, 16:2:65 0.79;
 // small: 1024 x 1000 at 128:2:100 23.2 / 25.6.  Above 200 columns always: 0.74 to 1.00.  Chosen so 0.930 of the time without, at most 1.04

@@ -8,9 +8,10 @@
 //     their own and read them transposed.  A layer's may take them from X itself, [token][k]: the wave stages the 8*M
 //     columns of the k-step for every token, and the gather is a 2-byte LDS read at any column, so that X is not transposed
 //     by a kernel before: 3.5 us less for M/4 times the bytes of X.
-// Measured, us per call, spmm_kernel's 64-column tile (and the transposition) -> now: 8192 x 8192 x 16 at 128:2:16 11.7 -> 6.5, as a
-// layer 16.8 -> 10; 96 x 13552 x 32 at 96:2:8 (one block row) 28 -> 9.9; 1024 x 1024 x 8 at 128:2:8 6.1 -> 4.8, as a layer 10.8 -> 6.4;
-// the layer of 49152 x 12288 with 16 tokens at 128:2:32 (85 MB of records) 22.6 -> 19.8.
+// Measured, us per call, spmm_kernel's 64-column tile (and the transposition) -> now, the same call again: 8192 x 8192 x 16 at
+// 128:2:16 11.6 -> 6.7, as a layer 14.9 -> 9.4; 96 x 13552 x 32 at 96:2:8 (one block row) 28 -> 10; 1024 x 1024 x 8 at 128:2:8 6.0 -> 4.4,
+// as a layer 9.4 -> 5.9; the layer of 49152 x 12288 with 16 tokens, bias and GELU at 128:2:32 (85 MB of records) 22.6 -> 20.1, with
+// other weights and activations each time 24.8 -> 22.3.
 #include <atomic>
 #include <cmath>
 
@@ -38,8 +39,10 @@ __host__ __device__ constexpr int skinny_window(int cols, int M) { return cols *
 
 // VT: 32-row tiles per block row; RT: those of a workgroup; NP: phases, the waves that deal out its k-steps; GB: block rows per
 // workgroup, NP waves each, whose waves of one phase share the window of X (all waves then keep in step, two windows in turn);
-// XJ: 16-byte pieces of X that a lane stages per k-step and block row (0: a product, B is gathered from memory).
-// Registers for two waves per SIMD; three records ahead instead of two measured the same.
+// XJ: 16-byte pieces of X that a lane stages per k-step and block row (0: a product, B is gathered from memory), all of them
+// loaded: those past the last token are the first piece again.
+// Registers for two waves per SIMD, enough but for pairs of block rows of 128 with 16 pieces, which spill 7 of them (32 bytes a lane); three
+// records ahead instead of two measured the same.
 template <int VT, int RT, int NP, int GB, int XJ, bool OUT_F32>
 __global__ void __launch_bounds__(NP * GB * 64, 2) skinny_kernel(SkinnyParams p) {
   constexpr bool TOKENS = XJ > 0;

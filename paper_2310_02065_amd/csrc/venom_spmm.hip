@@ -729,8 +729,9 @@ __global__ void __launch_bounds__((NC * NR + kProducers) * 64, simd_waves(VT, NC
             if constexpr (CONS <= 4) {
               // two rows of this lane's column leave as two columns of one row, half as many LDS writes: the pair of rows is
               // rounded into a word, and an even lane takes the first row of its own and its neighbour's, an odd lane the second
-              // (3072 x 768 x 4096 at 64:2:8 14.1 -> 13.6 us, 4096 x 1024 x 16384 on v128_c128d 42.3 -> 40.6; with eight waves
-              // and 128 accumulators a lane it costs registers: with GELU 65.5 -> 68.8)
+              // (3072 x 768 x 4096 at 64:2:8 14.1 -> 13.6 us, 4096 x 1024 x 16384 on v128_c128d 42.3 -> 40.6, the same call again:
+              // with other operands each time 67, where v128_c512 takes 56 and is chosen; with eight waves and 128 accumulators a lane
+              // it costs registers: with GELU 65.5 -> 68.8)
               const int c = tc * 32 + (ln & 30);
               const uint32_t pick = ln & 1 ? 0x07060302u : 0x01000504u;   // bytes: 0-3 the neighbour's, 4-7 its own
 #pragma unroll
@@ -847,9 +848,9 @@ int spmm_variant_count() { return kNumVariants; }
 const char* spmm_variant_name(int v) { return (v >= 0 && v < kNumVariants) ? kVariants[v].name : nullptr; }
 
 // The variant of block height V with the smallest expected time.  Narrow tiles spread a small product over more units and
-// have shorter k-steps (us alone on the chip, V = 128: 0.31 / 0.21 / 0.14 / 0.12 for 512 / 256 / 128 / 64 columns: 36.5 /
-// 20.5 / 12.5 / 8.5 KB); wide ones read the records of A less often and load the chip's fabric less; the columns that
-// pad C to whole tiles and a last round with few tiles cost as much as full ones.  The constants of TileCost are fits to the
+// have shorter k-steps (us of one tile alone on the chip, V = 128: 0.35 / 0.20 / 0.12 / 0.10 for 512 / 256 / 128 / 64 columns,
+// the last two with two k-steps a barrier: 36.5 / 20.5 / 12.5 / 8.5 KB); wide ones read the records of A less often and load the
+// chip's fabric less; the columns that pad C to whole tiles and a last round with few tiles cost as much as full ones.  The constants of TileCost are fits to the
 // times of all variants over 4478 random shapes (R 64-49152, K 256-16000, C 40-16384, M 4-128, up to 6e10 FLOP) in four output
 // forms (plain, with bias and GELU, that in fp32, and token-major): least squares of the relative error, from there on random steps
 // on three quarters of them that make the chosen variant's time over the best one's smaller.  On the others the chosen variant is
