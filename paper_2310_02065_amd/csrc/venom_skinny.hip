@@ -409,18 +409,25 @@ static int layer_form(const Layout& L, int64_t ldx, int64_t tokens, int M, int c
   return pair < 1.05f * first ? kPair : -1;
 }
 
-static bool overlap(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes) {
-  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
-  return x < y + (uintptr_t)b_bytes && y < x + (uintptr_t)a_bytes;
+struct Rows { const void* at; uintptr_t bytes, pitch; };   // of a row, and from one to the next
+
+// Whether two matrices of as many rows have bytes in common: from the first to the last, gaps between rows included, but for
+// matrices side by side in the rows of one buffer.
+static bool overlap(const Rows& a, const Rows& b, int64_t rows) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a.at), y = reinterpret_cast<uintptr_t>(b.at), gaps = (uintptr_t)(rows - 1);
+  if (x >= y + gaps * b.pitch + b.bytes || y >= x + gaps * a.pitch + a.bytes) return false;
+  if (a.pitch != b.pitch) return true;
+  const uintptr_t behind = y >= x ? (y - x) % a.pitch : (a.pitch - (x - y) % a.pitch) % a.pitch;   // where in a row of a one of b starts
+  return behind < a.bytes || behind + b.bytes > a.pitch;
 }
 
 // An output over X stays with the transposition, which has read all of X before the product starts: a workgroup here reads
-// every column of X to the end of its run, when others have long stored their features.  From the first byte to the last, gaps
-// between rows included (X and Y side by side in one buffer: transposed, as if they met).
+// every column of X to the end of its run, when others have long stored their features.
 int skinny_layer(const venom_handle& h, const void* X, int64_t ldx, int64_t tokens, const void* Y, int64_t ldy, int dtype, int cus) {
   const int form = layer_form(h.lay, ldx, tokens, h.M, cus);
-  if (form < 0 || overlap(X, 2 * ((tokens - 1) * ldx + h.K), Y, (dtype == 1 ? 4 : 2) * ((tokens - 1) * ldy + h.R))) return -1;
-  return form;
+  const uintptr_t size = dtype == 1 ? 4 : 2;
+  const Rows x{X, 2 * (uintptr_t)h.K, 2 * (uintptr_t)ldx}, y{Y, size * (uintptr_t)h.R, size * (uintptr_t)ldy};
+  return form < 0 || overlap(x, y, tokens) ? -1 : form;
 }
 
 venom_status_t launch_skinny(const venom_handle& h, int form, const void* src, int64_t ld, int64_t cols, const void* bias, int act,

@@ -22,6 +22,22 @@ def test_an_output_over_the_activations_is_not_written_while_they_are_read(R, K,
         assert served(y) == NONE, y - X0
 
 
+@pytest.mark.parametrize("dtype,size", [(0, 2), (1, 4)])
+def test_side_by_side_in_the_rows_of_one_buffer_they_do_not_meet(dtype, size):
+    R, K, tokens = 1024, 512, 16
+    h, pitch = host_handle(R, K, 64, 16), 2 * K + size * R + 64
+
+    def served(x, y):
+        return layer_form(h, x, pitch // 2, tokens, y, pitch // size, dtype)
+
+    for x, y in ((X0, X0 + 2 * K), (X0, X0 + 2 * K + 64), (X0 + size * R, X0), (X0 + size * R + 64, X0)):
+        for rows_apart in (-tokens, -3, 0, 1, tokens + 1):
+            assert served(x, y + rows_apart * pitch) == SPLIT
+    for x, y in ((X0, X0 + 2 * K - 2), (X0, X0 + 2 * K + 66), (X0 + size * R - 2, X0), (X0 + size * R + 66, X0)):
+        for rows_apart in (-3, 0, 1):
+            assert served(x, y + rows_apart * pitch) == NONE
+
+
 def test_more_rows_than_a_launch_has_threads_for_are_transposed_first():
     # 2^31 rows, 2^24 packed block rows: pairs of them, 512 threads each, are 2^32
     assert layer_form(host_handle(1 << 31, 36, 1 << 16, 4), X0, 36, 8, X0 << 8, 1 << 31) == NONE

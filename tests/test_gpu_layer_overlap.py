@@ -35,6 +35,20 @@ def test_the_output_takes_the_input_s_place(R, V, M, T):
 
 
 @pytest.mark.parametrize("T", [8, 32, 40])
+def test_input_and_output_share_the_rows_of_one_buffer(T):
+    R, K, V, M = 1024, 512, 64, 16
+    (A, mask), X, bias, (Ys, Ey) = problem(R, K, V, M, T)
+    h = binding.venom_compress(A, mask, V, 2, M)
+    for x_at, y_at in ((0, K), (R, 0)):
+        both = torch.full((T, K + R + 4), -7.0, dtype=torch.float16, device=DEV)
+        x, y = both[:, x_at:x_at + K], both[:, y_at:y_at + R]
+        x.copy_(X)
+        binding.venom_linear(h, x, bias=bias, activation="gelu", out=y)
+        ok, info = o.accept(y.double().cpu().numpy(), Ys, Ey)
+        assert ok and torch.equal(x, X) and bool((both[:, K + R:] == -7.0).all()), info
+
+
+@pytest.mark.parametrize("T", [8, 32, 40])
 @pytest.mark.parametrize("R,K,V,M", [(1024, 512, 64, 16), (9664, 800, 64, 16)])
 def test_the_input_is_a_part_of_the_output(R, K, V, M, T):
     (A, mask), X, bias, (Ys, Ey) = problem(R, K, V, M, T)
